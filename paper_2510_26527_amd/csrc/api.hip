@@ -269,6 +269,7 @@ struct ForwardPlan {
     bool half_copies;             // bf16, M > kStreamMaxRows or 4-bit projections: the producers also leave fp16 copies of the activations
     bool folded;                  // RMSNorm folded into the projections (bf16, packed weights, M <= kStreamMaxRows)
     bool fused_rope;              // the attention kernel reduces, rotates and appends q / k / v itself
+    bool gated;                   // bf16, M > kStreamMaxRows: the gate|up projection applies SwiGLU itself
 };
 
 ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit_rows, int len_bound, bool tree) {
@@ -296,6 +297,7 @@ ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit
                          : splits(M, d.d_ffn, d.d_model, n_o, 1);
     p.sk_head = Ml > 0 ? splits(Ml, d.d_model, d.vocab, n_v, 1) : 1;
     p.attn_splits = attn_pick_splits(d.dtype, batch, n_new, d.n_q_heads, d.n_kv_heads, d.d_head, len_bound, tree);
+    if (d.dtype == PSD_BF16 && M > kStreamMaxRows) p.gated = gemm_tiled_gates(M, d.d_model, n_gu);
     const size_t act = 4;                                    // activations are fp32 for both dtypes
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
@@ -310,7 +312,8 @@ ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit
     p.off_h16 = take(p.half_copies ? (size_t)M * d.d_ffn * 2 : 0);
     size_t part = 0;
     auto need = [&](int sk, int rows, int N) { const size_t b = (size_t)sk * rows * N * 4; if (b > part) part = b; };
-    need(p.sk_qkv, M, p.width_qkv); need(p.sk_o, M, d.d_model); need(p.sk_gu, M, 2 * d.d_ffn);
+    need(p.sk_qkv, M, p.width_qkv); need(p.sk_o, M, d.d_model);
+    if (!p.gated) need(p.sk_gu, M, 2 * d.d_ffn);
     need(p.sk_down, M, d.d_model);
     if (p.sk_head > 1 || p.folded) need(p.sk_head, Ml, d.vocab);  // else a single split writes the logits in place
     p.off_partial = take(part);
@@ -393,6 +396,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
 
     (void)hipGetLastError();
     auto norm_gain = [&](int l) { return l < d.n_layers ? m->layer(l, W_ATTN_NORM) : m->final_norm(); };
+    unsigned *tile_ctr = p.folded ? (unsigned *)(ws + p.off_tilectr) : nullptr;
     // ql, qj: layer and index of the first segment among the layer's 4-bit projections (q k v o gate up down), if any
     auto gemm = [&](const float *xin, int rows, int K, const void *w0, int n0, const void *w1, int n1,
                     const void *w2, int n2, int sk, float *dst, const void *wpack, int ql = -1, int qj = -1) {
@@ -404,6 +408,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         g.nseg = w2 ? 3 : (w1 ? 2 : 1);
         g.M = rows; g.K = K; g.N = n0 + n1 + n2; g.partial = dst; g.splitk = sk; g.reduced = nullptr;
         g.pack_tiles = gemm_pack_tiles(g.n, g.nseg);
+        if (p.gated && dst == nullptr) g.swiglu16 = h16;
         g.w4 = m->w4 && qj >= 0;
         for (int sgm = 0; sgm < g.nseg && g.w4; ++sgm) { g.w4_scale[sgm] = m->qscale(ql, qj + sgm); g.w4_zero[sgm] = m->qzero(ql, qj + sgm); }
         launch_gemm(d.dtype, g, st);
@@ -418,7 +423,6 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     RowScale rs{nullptr, 0, 1.0f / (float)d.d_model, d.rms_eps};
     if (p.folded) rs.sumsq = sumsq;
     const float *act = xn;     // what QKV / gate|up / lm_head read: rmsnorm(x) * gain, or x * gain when folded
-    unsigned *tile_ctr = p.folded ? (unsigned *)(ws + p.off_tilectr) : nullptr;
     auto resid_gemm = [&](const float *xin, int K, const void *w, int sk, const void *wpack, const void *next_gain,
                           bool by_units, int ql, int qj) {
         if (p.folded) {
@@ -467,9 +471,9 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         launch_attention(d.dtype, a, st);
 
         resid_gemm(attn, hd, m->layer(l, W_O), p.sk_o, m->pack(l, P_O), m->layer(l, W_FFN_NORM), false, l, 3);
-        gemm(act, M, d.d_model, m->layer(l, W_GATE), d.d_ffn, m->layer(l, W_UP), d.d_ffn, nullptr, 0, p.sk_gu, partial,
-             m->pack(l, P_GU), l, 4);
-        launch_reduce_swiglu(partial, p.sk_gu, rs, h, M, d.d_ffn, h16, st);
+        gemm(act, M, d.d_model, m->layer(l, W_GATE), d.d_ffn, m->layer(l, W_UP), d.d_ffn, nullptr, 0, p.sk_gu,
+             p.gated ? nullptr : partial, m->pack(l, P_GU), l, 4);
+        if (!p.gated) launch_reduce_swiglu(partial, p.sk_gu, rs, h, M, d.d_ffn, h16, st);
         resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), true, l, 6);
     }
     if (n_logit_rows > 0) {

@@ -22,8 +22,9 @@
 //                            integers against fp16-rounded activations, scale and zero point applied per group in
 //                            fp32; one partial slot per block and tile, or (O, down) the residual epilogue run by
 //                            the block that arrives last.
-//   gemm_f16_tiled_kernel    M > 16.  (128 or 256) x (128, 192, 256) x 64 LDS-staged tiles, 32x32x16 fp16 MFMA
-//                            (weights convert to fp16 exactly, activations are rounded to fp16).
+//   gemm_f16_tiled_kernel    M > 16.  (64, 128 or 256) x (128, 192, 256) x 64 LDS-staged tiles, 32x32x16 fp16 MFMA
+//                            (weights convert to fp16 exactly, activations are rounded to fp16); the gate|up projection
+//                            applies SwiGLU itself where its tiles alone fill the chip.
 // Activations are fp32 in memory in every case (the tiled kernel reads an fp16 copy its producers leave beside
 // them).  The M <= 16 bf16 kernels feed each activation to the matrix cores as a pair of bf16 values hi + lo (two
 // MFMAs against the same weight operand): with plain bf16 activations the logits of the 7B-shaped random-init
@@ -762,194 +763,242 @@ __device__ __forceinline__ u32x4 w4x8_to_f16x8(uint32_t raw, uint32_t sz) {
 }
 
 // ------------------------------------------------------------------------------ tiled (M > 16)
-// Block tile 128 or 256 rows of activations x 32*NB rows of W x 64 of K (NB = 4, 6, 8); wavefronts in a 2 x 2 or
-// 4 x 2 grid, each on 64 activation rows x 16*NB weight rows: 2 x NB/2 tiles of the 32x32x16 MFMA, so that per 16-wide K step
-// a wavefront reads 2 + NB/2 operands from LDS for NB MFMAs (with 1 x NB tiles per wavefront it would be 1 + NB
-// operands, and LDS reads, not the matrix cores, would set the pace).
+// Block tile 64 TA rows of activations x 32 TB WN rows of W x 64 of K; wavefronts in a 2 x WN grid, each on 32 TA x 32 TB
+// outputs, so that per 16-wide K step a wavefront reads TA + TB operands from LDS for TA TB MFMAs.
 // Both operands enter the matrix cores as fp16, one product each: the bf16 weights convert to fp16 exactly
 // (8 significant bits into 11; only magnitudes below 7.6e-6 fall under the fp16 grid and are rounded to it, by at
 // most 3e-8), the fp32 activations are rounded to fp16 (11 significant bits, the error of bf16 divided by 8),
 // which keeps the logits of the 7B-shaped models within 2e-2 of the fp64 result at half the MFMA issue of a
 // bf16 high + low pair.  Activations beyond +-65504 would overflow; none of the decoder's normalised or gated
 // activations come near.  Rows are padded to 72 elements (144 B): conflict-free 16-byte reads.  LDS is dynamic.
-// 128-row blocks run two per CU (one block's staging and barriers overlap the other's MFMAs); 256-row blocks run
-// one per CU with two sets of LDS tiles and two K tiles in flight in registers (what a CU keeps in flight bounds
-// its load rate, and one K tile is too little of it).
-// The tile width and the K split are chosen per projection by the host so that the number of blocks comes
-// close to a multiple of the resident block slots.
-constexpr int kBK = 64, kLdsStride = 72, kMaxNB = 8;
-constexpr int kTallRows = 160;                           // from this many rows on: 256-row blocks
-inline int tiled_block_rows(int M) { return M >= kTallRows ? 256 : 128; }
+//
+// What bounds it.  With many rows: instruction issue around the MFMAs (at 2048 x 8192 x 8192 the MFMAs and the barrier alone
+// run at 1.57 PFLOP/s, with the LDS reads and stores 1.31, with the global loads too 1.12; reading both operands from L2
+// only gains nothing).  So the K loop is one straight line without a branch: every load is a buffer load whose range says
+// what exists (rows past the end and K tiles past the last read nothing), the next tile goes into a second set of LDS
+// tiles spread over three of the four MFMA groups of the current one, its registers are refilled with the tile after
+// it at once, the operands of the next 16 K are read ahead of the MFMAs of the current ones, and there is one barrier
+// per tile.  Measured against the branchy loop before it (2001 rows, us): 12288 x 4096 243 -> 224, 22016 x 4096 451 ->
+// 364 (which also drops a SwiGLU launch of 46), 4096 x 8192 148 -> 127, 4096 x 4096 87 -> 70.
+// With few rows: streaming W; the blocks take equal ranges of all the product's K tiles, so none of the CUs idles in a last
+// round.  Measured (45 rows, us): 12288 x 4096 32.5 -> 25.9, 22016 x 4096 47.1 -> 42.3, 4096 x 4096 14.7 -> 10.4,
+// 32000 x 4096 78.8 -> 59.1 (4.4 TB/s).
+// Tried and not kept: tiles shared by several blocks added up by the last of them (256 x 256 fp32 through agent-scope
+// stores and loads: 140 us instead of 70 at 2001 x 4096 x 4096); an XCD-contiguous block order alone (no change: not
+// bound by L2 misses); four wavefronts of 128 x 128 (5 % slower than eight of 128 x 64: one wavefront per SIMD does not
+// cover its own load issue).
+constexpr int kBK = 64, kLdsStride = 72;
 
-// MW = wavefront rows of the block: 2 (128 activation rows, 256 threads, two blocks per CU) or 4 (256 rows, 512
-// threads, one block per CU: each weight tile then leaves L2 once for 256 rows instead of twice).
 // W4: the weights are 4-bit codes as the caller stores them (row-major, low nibble = even k) with a bf16 scale and
 // a zero point per row and group of 128 k.  A thread's 8 weights of a K tile are 4 bytes of codes; on the way into
 // LDS they become the fp16 numbers scale * (q - zero): (1024 + q) - (1024 + zero) is exact in fp16, the product
 // with the scale (itself exact in fp16 down to 6e-5) is rounded once, to 11 significant bits.
-template <int NB, int MW, bool W4 = false>
-__global__ __launch_bounds__(MW * 128, MW == 2 ? 2 : 1) void gemm_f16_tiled_kernel(GemmArgs g) {
-    constexpr int BM = 64 * MW, BN = 32 * NB, NH = NB / 2, NT = MW * 128;
+template <int TA, int TB, int WN, bool W4>
+__global__ __launch_bounds__(128 * WN, 1) void gemm_f16_tiled_kernel(GemmArgs g) {
+    constexpr int BM = 64 * TA, BN = 32 * TB * WN, NT = 128 * WN;
     constexpr int XCH = BM * 8 / NT;                        // 16-byte chunks of the fp16 X tile per thread (BM x 64)
     constexpr int WCH = BN * 8 / NT;                        // 16-byte chunks of the W tile per thread (BN x 64 bf16)
-    // MW == 4 has the CU to itself and LDS for two sets of tiles: the next K tile is stored into the other set in
-    // the middle of this tile's MFMAs (one barrier per K tile, no phase in which the matrix cores wait for the
-    // stores).  MW == 2 keeps one set: two blocks share the CU and overlap each other's barriers.
-    constexpr bool DB = MW == 4;
     constexpr int kSet = (BM + BN) * kLdsStride;            // elements of one set of tiles
     extern __shared__ __attribute__((aligned(16))) uint16_t lds_tiled[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 31, lg = lane >> 5;
-    const int wm = (wave >> 1) * 64, wn = (wave & 1) * (BN / 2);   // this wavefront's corner of the block tile
-    const int m_tiles = (g.M + BM - 1) / BM;
-    const int mt = blockIdx.x % m_tiles;                 // M tiles of one W tile are neighbours: W is re-read from L2
-    const TileRef t = find_tile(g, blockIdx.x / m_tiles, BN);
-    const int seg_rows = g.n[t.seg];
-    const uint16_t *W = (const uint16_t *)g.w[t.seg];
-    const int K = g.K;
-    const int nk = K / kBK;
-    const int k0 = (int)((long)blockIdx.y * nk / g.splitk), k1 = (int)((long)(blockIdx.y + 1) * nk / g.splitk);
-    const int m_base = mt * BM;
+    const int wm = (wave / WN) * (BM / 2), wn = (wave % WN) * (32 * TB);   // this wavefront's corner of the block tile
+    const int K = g.K, nk = K / kBK, m_tiles = (g.M + BM - 1) / BM;
+    const bool gated = g.swiglu16 != nullptr;
+    // Blocks that follow each other in the work order share weight tiles: they go to the same XCD (dispatch is round
+    // robin over the eight), whose L2 then serves the second reader.
+    const int P = gridDim.x, xcd = blockIdx.x % 8;
+    const int blk = xcd * (P / 8) + min(xcd, P % 8) + (int)blockIdx.x / 8;
+    const long U = (long)g.tiled_tiles * nk;
+    const int u0 = __builtin_amdgcn_readfirstlane((int)range_begin(blk, U, P));
+    const int u1 = __builtin_amdgcn_readfirstlane((int)range_begin(blk + 1, U, P));
 
-    // global -> register staging per K tile: XCH x 8 activations (fp16 copy if there is one, else fp32 rounded
-    // here) and WCH x 8 bf16 of W per thread
-    uint32_t xsrc[XCH], wsrc[WCH];                       // element offsets from the matrices' first elements
-    uint32_t wgrp[WCH];                                  // W4: index of the row's first group in scale / zero
-    int xoff[XCH], woff[WCH];
-#pragma unroll
-    for (int c = 0; c < XCH; ++c) {
-        const int chunk = tid + c * NT, row = chunk >> 3, col = (chunk & 7) * 8;
-        xsrc[c] = (uint32_t)(x_row(g, min(m_base + row, g.M - 1)) * K + col);
-        xoff[c] = row * kLdsStride + col;
-    }
-#pragma unroll
-    for (int c = 0; c < WCH; ++c) {
-        const int chunk = tid + c * NT, row = chunk >> 3, col = (chunk & 7) * 8;
-        wsrc[c] = (uint32_t)((size_t)min(t.row0 + row, seg_rows - 1) * K + col);
-        wgrp[c] = (uint32_t)(min(t.row0 + row, seg_rows - 1) * (K / kSkinnyStepK));
-        woff[c] = row * kLdsStride + col;
-    }
-    const uint8_t *Wq = (const uint8_t *)g.w[t.seg];
-    const uint16_t *Wscale = (const uint16_t *)g.w4_scale[t.seg];
-    const uint8_t *Wzero = (const uint8_t *)g.w4_zero[t.seg];
-    const bool have16 = g.x16 != nullptr;
-    // Register stages of the global -> LDS path.  What one CU keeps in flight bounds its load rate (bytes in flight /
-    // latency), and one K tile per block is too little of it: with two sets of LDS tiles the block also keeps two
-    // K tiles in flight in registers (stage = tile parity), except at the widest tile where the registers run out.
-    constexpr int NST = (DB && NB <= 6) ? 2 : 1;
+    // LDS byte addresses of this thread's chunks and operands: stores go to one set of tiles, reads to the other.  They are
+    // opaque to the compiler, which would otherwise keep one register per (set, chunk, K step) instead of a base and
+    // an immediate offset.
+    const int col = (tid & 7) * 8;
+    uint32_t st_x = (uint32_t)((tid >> 3) * kLdsStride + col) * 2, st_w = st_x + BM * kLdsStride * 2;
+    uint32_t rd_x = (uint32_t)(kSet + (wm + li) * kLdsStride + lg * 8) * 2;
+    uint32_t rd_w = (uint32_t)(kSet + (BM + wn + li) * kLdsStride + lg * 8) * 2;
+    asm volatile("" : "+v"(st_x), "+v"(st_w), "+v"(rd_x), "+v"(rd_w));
+    int flip = -kSet * 2;                                   // bytes from the set that is read to the other one
+    auto swap_sets = [&]() { rd_x += flip; rd_w += flip; flip = -flip; st_x += flip; st_w += flip; };
+    char *lds = (char *)lds_tiled;
+    constexpr int kChunkStep = NT / 8 * kLdsStride * 2;      // a thread's chunks are NT / 8 rows apart
     using WReg = std::conditional_t<W4, uint2v, u32x4>;   // what a thread holds of one 8-weight chunk
-    u32x4 xr[NST][XCH];
-    WReg wr[NST][WCH];
-    auto load_tiles = [&](auto stage, int kt) {
-        constexpr int st = decltype(stage)::value;
+    u32x4 xr[XCH];
+    WReg wr[WCH];
+
+    for (int u = u0; u < u1;) {
+        const int tile = __builtin_amdgcn_readfirstlane(u / nk), k0 = u - tile * nk, k1 = min(nk, k0 + u1 - u);
+        u += k1 - k0;
+        const int n_tile = __builtin_amdgcn_readfirstlane(tile / m_tiles), m_base = (tile - n_tile * m_tiles) * BM;
+        // tile row r of W: row r of the segment's tile, or, gated, 32 gate rows and 32 up rows in turn, so that a lane
+        // ends up with both factors of its outputs
+        TileRef t;
+        if (gated) t = TileRef{__builtin_amdgcn_readfirstlane(tid >> 8), n_tile * (BN / 2), 0};
+        else t = find_tile(g, n_tile, BN);
+        const int seg_rows = g.n[t.seg], w_rows = min(seg_rows - t.row0, gated ? BN / 2 : BN);
+        const int r_first = gated ? (tid >> 3) & 31 : tid >> 3, r_step = gated ? 32 : NT / 8;
+        const size_t x_first = x_row(g, m_base);
+        const char *xbase = (const char *)(g.x16 + x_first * K);
+        const char *wbase = (const char *)g.w[t.seg] + (size_t)t.row0 * K * (W4 ? 1 : 4) / 2;
+        const int ng = K / kSkinnyStepK;
+        const char *sbase = (const char *)g.w4_scale[t.seg] + (size_t)t.row0 * ng * 2;
+        const char *zbase = (const char *)g.w4_zero[t.seg] + (size_t)t.row0 * ng;
+        uint32_t xoff[XCH];
 #pragma unroll
         for (int c = 0; c < XCH; ++c) {
-            if (have16) xr[st][c] = *reinterpret_cast<const u32x4 *>(g.x16 + xsrc[c] + kt * kBK);
-            else xr[st][c] = f32x8_to_f16x8(load_f32x8(g.x + xsrc[c] + kt * kBK));
+            const int row = (tid + c * NT) >> 3;
+            xoff[c] = m_base + row < g.M ? (uint32_t)((x_row(g, m_base + row) - x_first) * K + col) * 2u : 0x80000000u;
         }
+        // chunks [C0, C1) of K tile kt: the X chunks first, then the W chunks.  Past the last K tile, and for rows past the
+        // end of a matrix, nothing is read.
+        auto load = [&](int kt, auto c0, auto c1) {
+            constexpr int C0 = decltype(c0)::value, C1 = decltype(c1)::value;
+            const bool live = kt < k1;
+            const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<char *>(xbase) + (size_t)kt * (kBK * 2), 0, live ? 0x7fffffff : 0, 0x00020000);
+            const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<char *>(wbase) + (size_t)kt * (W4 ? kBK / 2 : kBK * 2), 0,
+                live ? (w_rows * K - kt * kBK) * (W4 ? 1 : 4) / 2 : 0, 0x00020000);
 #pragma unroll
-        for (int c = 0; c < WCH; ++c) {
-            if constexpr (W4) {
-                // [0]: the 8 codes; [1]: fp16 scale (high half) and fp16 1024 + zero (low half) of the row's group
-                const uint32_t grp = wgrp[c] + (uint32_t)(kt * kBK / kSkinnyStepK);
-                const _Float16 sc = (_Float16)bf16_bits_to_f32(Wscale[grp]);
-                wr[st][c][0] = *reinterpret_cast<const uint32_t *>(Wq + (wsrc[c] + kt * kBK) / 2);
-                wr[st][c][1] = ((uint32_t)__builtin_bit_cast(uint16_t, sc) << 16) | 0x6400u | Wzero[grp];
-            } else {
-                wr[st][c] = *reinterpret_cast<const u32x4 *>(W + wsrc[c] + kt * kBK);
+            for (int c = C0; c < C1; ++c) {
+                if (c < XCH) xr[c] = __builtin_amdgcn_raw_buffer_load_b128(rx, xoff[c < XCH ? c : 0], 0, 0);
+                if (c >= XCH) {
+                    const int w = c >= XCH ? c - XCH : 0, row = r_first + w * r_step;
+                    if constexpr (W4) {
+                        const int grp = kt * kBK / kSkinnyStepK;
+                        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                            const_cast<char *>(sbase) + (size_t)grp * 2, 0, live ? (w_rows * ng - grp) * 2 : 0, 0x00020000);
+                        const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(
+                            const_cast<char *>(zbase) + grp, 0, live ? w_rows * ng - grp : 0, 0x00020000);
+                        wr[w][0] = __builtin_amdgcn_raw_buffer_load_b32(rw, (uint32_t)(row * K + col) / 2, 0, 0);
+                        const uint32_t sc = __builtin_amdgcn_raw_buffer_load_b16(rs, row * ng * 2, 0, 0);
+                        const uint32_t z = __builtin_amdgcn_raw_buffer_load_b8(rz, row * ng, 0, 0);
+                        wr[w][1] = (sc << 16) | (z & 0xffu);
+                    } else {
+                        wr[w] = __builtin_amdgcn_raw_buffer_load_b128(rw, (uint32_t)(row * K + col) * 2, 0, 0);
+                    }
+                }
             }
-        }
-    };
-    auto store_tiles = [&](auto stage, int set) {
-        constexpr int st = decltype(stage)::value;
-        uint16_t *Xs = lds_tiled + set * kSet, *Ws = Xs + BM * kLdsStride;     // activation tile, weight tile (fp16)
-#pragma unroll
-        for (int c = 0; c < XCH; ++c) *reinterpret_cast<u32x4 *>(&Xs[xoff[c]]) = xr[st][c];
-#pragma unroll
-        for (int c = 0; c < WCH; ++c) {
-            if constexpr (W4) *reinterpret_cast<u32x4 *>(&Ws[woff[c]]) = w4x8_to_f16x8(wr[st][c][0], wr[st][c][1]);
-            else *reinterpret_cast<u32x4 *>(&Ws[woff[c]]) = bf16x8_to_f16x8(wr[st][c]);
-        }
-    };
-    using S0 = std::integral_constant<int, 0>;
-    using S1 = std::integral_constant<int, NST - 1>;      // the second stage, or the only one
-
-    f32x16 acc[2][NH];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < NH; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-
-    auto multiply = [&](int set, int ks) {
-        const uint16_t *Xs = lds_tiled + set * kSet, *Ws = Xs + BM * kLdsStride;
-        f16x8 fa[2], fb[NH];
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-            fa[a] = *reinterpret_cast<const f16x8 *>(&Xs[(wm + a * 32 + li) * kLdsStride + ks * 16 + lg * 8]);
-#pragma unroll
-        for (int b = 0; b < NH; ++b)
-            fb[b] = *reinterpret_cast<const f16x8 *>(&Ws[(wn + b * 32 + li) * kLdsStride + ks * 16 + lg * 8]);
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < NH; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[a], fb[b], acc[a][b], 0, 0, 0);
-    };
-    if (k0 < k1) {
-        load_tiles(S0{}, k0);
-        store_tiles(S0{}, 0);
-        if constexpr (NST == 2) {
-            // tile t travels in stage (t - k0) & 1
-            if (k0 + 1 < k1) load_tiles(S1{}, k0 + 1);
-            if (k0 + 2 < k1) load_tiles(S0{}, k0 + 2);
-        } else if (DB && k0 + 1 < k1) {
-            load_tiles(S0{}, k0 + 1);
-        }
-    }
-    __syncthreads();
-    if constexpr (DB) {
-        // one K tile: half its MFMAs, the next tile from its registers into the other LDS set, the registers refilled
-        // with the tile NST ahead, the other half, one barrier (tile kt + 1 visible; this set free for tile kt + 2)
-        auto k_tile = [&](auto next_stage, int kt) {
-            const int set = (kt - k0) & 1;
-            multiply(set, 0);
-            multiply(set, 1);
-            if (kt + 1 < k1) store_tiles(next_stage, set ^ 1);
-            if (kt + 1 + NST < k1) load_tiles(next_stage, kt + 1 + NST);
-            multiply(set, 2);
-            multiply(set, 3);
-            __syncthreads();
         };
-        int kt = k0;
-        for (; kt + 1 < k1; kt += 2) {
-            k_tile(S1{}, kt);                                // tile kt + 1 has odd parity
-            k_tile(S0{}, kt + 1);
-        }
-        if (kt < k1) k_tile(S1{}, kt);
-    } else {
-        for (int kt = k0; kt < k1; ++kt) {
-            if (kt + 1 < k1) load_tiles(S0{}, kt + 1);       // in flight while this tile is multiplied
+        auto store = [&](auto c0, auto c1) {
+            constexpr int C0 = decltype(c0)::value, C1 = decltype(c1)::value;
 #pragma unroll
-            for (int ks = 0; ks < kBK / 16; ++ks) multiply(0, ks);
-            __syncthreads();
-            if (kt + 1 < k1) store_tiles(S0{}, 0);
-            __syncthreads();
-        }
-    }
-    // acc[a][b][v] = y[m_base + wm + a*32 + 8*(v/4) + 4*lg + v%4][row0 + wn + b*32 + li]
-#pragma unroll
-    for (int b = 0; b < NH; ++b) {
-        const int row = t.row0 + wn + b * 32 + li;
-        if (row >= seg_rows) continue;
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = m_base + wm + a * 32 + 8 * (v >> 2) + 4 * lg + (v & 3);
-                if (m < g.M) store_out(g, blockIdx.y, m, t.col0 + row, acc[a][b][v]);
+            for (int c = C0; c < C1; ++c) {
+                if (c < XCH) *reinterpret_cast<u32x4 *>(lds + st_x + c * kChunkStep) = xr[c < XCH ? c : 0];
+                if (c >= XCH) {
+                    const int w = c >= XCH ? c - XCH : 0;
+                    if constexpr (W4) {
+                        const _Float16 sc = (_Float16)__uint_as_float(wr[w][1] & 0xffff0000u);
+                        const uint32_t sz = ((uint32_t)__builtin_bit_cast(uint16_t, sc) << 16) | 0x6400u | (wr[w][1] & 0xffu);
+                        *reinterpret_cast<u32x4 *>(lds + st_w + w * kChunkStep) = w4x8_to_f16x8(wr[w][0], sz);
+                    } else {
+                        *reinterpret_cast<u32x4 *>(lds + st_w + w * kChunkStep) = bf16x8_to_f16x8(wr[w]);
+                    }
+                }
             }
+        };
+        f32x16 acc[TA][TB];
+#pragma unroll
+        for (int a = 0; a < TA; ++a)
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+        // operands of one 16-wide K step, two register sets: the reads of step ks + 1 are out while step ks is multiplied
+        f16x8 fa[2][TA], fb[2][TB];
+        auto read_frags = [&](auto buf, int ks) {
+            constexpr int q = decltype(buf)::value;
+#pragma unroll
+            for (int a = 0; a < TA; ++a) fa[q][a] = *reinterpret_cast<const f16x8 *>(lds + rd_x + (a * 32 * kLdsStride + ks * 16) * 2);
+#pragma unroll
+            for (int b = 0; b < TB; ++b) fb[q][b] = *reinterpret_cast<const f16x8 *>(lds + rd_w + (b * 32 * kLdsStride + ks * 16) * 2);
+        };
+        auto mma = [&](auto buf) {
+            constexpr int q = decltype(buf)::value;
+#pragma unroll
+            for (int a = 0; a < TA; ++a)
+#pragma unroll
+                for (int b = 0; b < TB; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[q][a], fb[q][b], acc[a][b], 0, 0, 0);
+        };
+        using F0 = std::integral_constant<int, 0>;
+        using F1 = std::integral_constant<int, 1>;
+        // the chunks in three groups, stored in the first three of a K tile's four regions
+        constexpr int kAll = XCH + WCH, kG1 = (kAll + 1) / 3, kG2 = (2 * kAll + 1) / 3;
+        constexpr std::integral_constant<int, 0> c_0{};
+        constexpr std::integral_constant<int, kG1> c_1{};
+        constexpr std::integral_constant<int, kG2> c_2{};
+        constexpr std::integral_constant<int, kAll> c_3{};
+        load(k0, c_0, c_3);
+        store(c_0, c_3);
+        load(k0 + 1, c_0, c_3);
+        swap_sets();
+        __syncthreads();
+        read_frags(F0{}, 0);
+        for (int kt = k0; kt < k1; ++kt) {
+            // (every access to the set that is read is done before the barrier, every store into the other set too)
+            read_frags(F1{}, 1);
+            store(c_0, c_1);
+            load(kt + 2, c_0, c_1);
+            mma(F0{});
+            __builtin_amdgcn_sched_barrier(0);
+            read_frags(F0{}, 2);
+            store(c_1, c_2);
+            load(kt + 2, c_1, c_2);
+            mma(F1{});
+            __builtin_amdgcn_sched_barrier(0);
+            read_frags(F1{}, 3);
+            store(c_2, c_3);
+            mma(F0{});
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+            swap_sets();
+            read_frags(F0{}, 0);
+            load(kt + 2, c_2, c_3);
+            mma(F1{});
+            __builtin_amdgcn_sched_barrier(0);
+        }
+
+        // acc[a][b][v] = y[m_base + wm + a*32 + 8*(v/4) + 4*lg + v%4][tile column wn + b*32 + li] over K tiles [k0, k1)
+        if (gated) {                                         // the host gives these tiles to one block each
+            if constexpr (TB == 2) {
+                const int c = n_tile * (BN / 2) + (wave % WN) * 32 + li;
+#pragma unroll
+                for (int a = 0; a < TA; ++a)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int m = m_base + wm + a * 32 + 8 * (v >> 2) + 4 * lg + (v & 3);
+                        const float gt = acc[a][0][v], h = gt / (1.0f + expf(-gt)) * acc[a][1][v];
+                        if (m < g.M) g.swiglu16[(size_t)m * seg_rows + c] = f32_to_f16_bits(h);
+                    }
+            }
+            continue;
+        }
+        const int slot = blk - __builtin_amdgcn_readfirstlane((int)range_owner((long)tile * nk, U, P));
+        const int zero_to = k1 == nk ? g.splitk : 0;         // the block that ends a tile clears the slots nobody writes
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            const int row = t.row0 + wn + b * 32 + li;
+            if (row >= seg_rows) continue;
+#pragma unroll
+            for (int a = 0; a < TA; ++a)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int m = m_base + wm + a * 32 + 8 * (v >> 2) + 4 * lg + (v & 3);
+                    if (m < g.M) store_out(g, slot, m, t.col0 + row, acc[a][b][v]);
+                }
+            for (int s = slot + 1; s < zero_to; ++s)
+#pragma unroll
+                for (int a = 0; a < TA; ++a)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int m = m_base + wm + a * 32 + 8 * (v >> 2) + 4 * lg + (v & 3);
+                        if (m < g.M) store_out(g, s, m, t.col0 + row, 0.f);
+                    }
+        }
     }
 }
 
@@ -961,28 +1010,45 @@ int tiles_of(const int *n, int nseg, int rows) {
 
 }  // namespace
 
-// Tile width (NB x 32 columns, NB = 4, 6, 8) and K split of the tiled kernel: the pair with the least estimated
-// time: rounds of 512 resident blocks x K tiles per block x the time of one K tile of two co-resident blocks,
-// which the LDS traffic sets (16 KB of activations and 4 NB KB of weights written, 4 (2 + NB/2) x 4 KB read, at
-// 128 B per clock, with a margin for what does not overlap), plus writing and re-reading one fp32 partial slot of
-// M x N per split at about 3 TB/s.
-static void tiled_choice(int M, int K, const int *n, int nseg, int *nb_out, int *sk_out) {
-    const int bm = tiled_block_rows(M), nk = K / kBK, m_tiles = (M + bm - 1) / bm;
-    const int slots = bm == 256 ? 256 : 512;          // resident blocks: one 512-thread or two 256-thread blocks per CU
+static int gemm_slots_of(int tiles, int units_per_tile, int grid);
+// The tile and the number of blocks of a tiled product.  Up to 128 rows it streams W: 256 columns, one block per CU but
+// at least eight K tiles each (45 rows x 4096 x 4096: 128 blocks 11.2 us and 16 slots less to add than 256 blocks, 11.6),
+// tiles shared wherever the ranges fall.  Above: 256 rows; the columns and the (even) K split with the least estimated
+// time: rounds of 256 blocks x K tiles x the measured time of one (us: 1.15, 1.65, 1.9 for 128, 192, 256 columns) plus 4
+// per round for filling and emptying the pipeline, plus a partial slot of M x N written and read at about 3 TB/s per
+// split.  gated: 128 gate and 128 up columns per tile, never split (the two factors meet in one lane).
+GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) {
+    GemmTiledPlan best{};
+    const int nk = K / kBK;
+    if (M <= 128 && !gated) {
+        best.ta = M <= 64 ? 1 : 2;
+        best.cols = 256;
+        best.tiles = tiles_of(n, nseg, 256);
+        const long U = (long)best.tiles * nk;
+        best.blocks = (int)(U / 8 < 1 ? 1 : (U / 8 < 256 ? U / 8 : 256));
+        best.slots = gemm_slots_of(best.tiles, nk, best.blocks);
+        return best;
+    }
+    const int m_tiles = (M + 255) / 256;
     long N = 0;
     for (int s = 0; s < nseg; ++s) N += n[s];
     const double slot_us = 2.0 * (double)M * (double)N * 4.0 / 3.0e6;
-    double best = 1e300;
-    *nb_out = 6; *sk_out = 1;
-    for (int nb = 4; nb <= kMaxNB; nb += 2)
-        for (int sk = 1; sk <= 16 && (sk == 1 || nk / sk >= 4); ++sk) {
-            const long blocks = (long)tiles_of(n, nseg, 32 * nb) * m_tiles * sk;
-            const long rounds = (blocks + slots - 1) / slots;
-            const double tile_clk = (48.0 + 12.0 * nb) * 8.0 * 1.3;     // per 128 rows
-            const double cost = rounds * (double)((nk + sk - 1) / sk) * 2.0 * tile_clk / 2400.0 + sk * slot_us;
-            if (cost < best) { best = cost; *nb_out = nb; *sk_out = sk; }
+    double least = 1e300;
+    best.ta = 4;
+    for (int cols = gated ? 256 : 128; cols <= 256; cols += 64) {
+        const int tiles = (gated ? n[0] / 128 : tiles_of(n, nseg, cols)) * m_tiles;
+        for (int c = 1; c <= (gated ? 1 : 16) && (c == 1 || nk / c >= 4); ++c) {
+            const long rounds = ((long)tiles * c + 255) / 256;
+            const double cost = rounds * ((nk + c - 1) / c * (cols == 256 ? 1.9 : (cols == 192 ? 1.65 : 1.15)) + 4.0) + c * slot_us;
+            if (cost < least) { least = cost; best.cols = cols; best.tiles = tiles; best.blocks = tiles * c; best.slots = c; }
         }
+    }
+    return best;
 }
+
+// from 128 tiles on (half the CUs busy) not splitting K costs less than a slot of gate and up written and read again
+// (256 x 37888 x 3584, 148 tiles: 95 us; separate, 84 + 11)
+bool gemm_tiled_gates(int M, int K, const int *n) { return M > 128 && gemm_tiled_plan(M, K, n, 2, true).tiles >= 128; }
 
 int gemm_stream_grid(int tiles, int K) {
     const long U = (long)tiles * (K / kSkinnyStepK);
@@ -1078,9 +1144,7 @@ int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg) {
         if (want > 16) want = 16;
         return want < 1 ? 1 : want;
     }
-    int nb, sk;
-    tiled_choice(M, K, n, nseg, &nb, &sk);
-    return sk;
+    return gemm_tiled_plan(M, K, n, nseg, false).slots;
 }
 
 void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
@@ -1122,36 +1186,27 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
         launch_kernel(gemm_bf16_skinny_kernel<1>, grid, 256, 0, stream, g);
     } else {
         ScopedProf sp(PSD_KIND_GEMM_TILED, stream);
-        int nb, sk;
-        tiled_choice(g.M, g.K, g.n, g.nseg, &nb, &sk);
-        if (sk != g.splitk) nb = 6;                       // the caller sized the partial slots for its own split
-        const int bm = tiled_block_rows(g.M);
-        dim3 grid(tiles_of(g.n, g.nseg, 32 * nb) * ((g.M + bm - 1) / bm), g.splitk);
-        auto go = [&](auto kernel) {
+        const GemmTiledPlan p = gemm_tiled_plan(g.M, g.K, g.n, g.nseg, g.swiglu16 != nullptr);
+        GemmArgs t = g;
+        t.tiled_tiles = p.tiles;
+        auto go = [&](auto kernel, int threads) {
             // opt in to more than 64 KB of dynamic LDS: a property of the function on the current device, set before
             // every launch (a cheap host call) so that no process-wide flag has to remember who set it where
-            const size_t lds = (size_t)(bm + 32 * nb) * kLdsStride * sizeof(uint16_t) * (bm == 256 ? 2 : 1);
+            const size_t lds = (size_t)(64 * p.ta + p.cols) * kLdsStride * sizeof(uint16_t) * 2;
             (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)lds);
-            launch_kernel(kernel, grid, bm * 2, lds, stream, g);
+            launch_kernel(kernel, p.blocks, threads, lds, stream, t);
         };
-        if (g.w4 && bm == 256) {
-            if (nb == 4) go(gemm_f16_tiled_kernel<4, 4, true>);
-            else if (nb == 6) go(gemm_f16_tiled_kernel<6, 4, true>);
-            else go(gemm_f16_tiled_kernel<8, 4, true>);
-        } else if (g.w4) {
-            if (nb == 4) go(gemm_f16_tiled_kernel<4, 2, true>);
-            else if (nb == 6) go(gemm_f16_tiled_kernel<6, 2, true>);
-            else go(gemm_f16_tiled_kernel<8, 2, true>);
-        } else if (bm == 256) {
-            if (nb == 4) go(gemm_f16_tiled_kernel<4, 4>);
-            else if (nb == 6) go(gemm_f16_tiled_kernel<6, 4>);
-            else go(gemm_f16_tiled_kernel<8, 4>);
-        } else {
-            if (nb == 4) go(gemm_f16_tiled_kernel<4, 2>);
-            else if (nb == 6) go(gemm_f16_tiled_kernel<6, 2>);
-            else go(gemm_f16_tiled_kernel<8, 2>);
-        }
+        auto pick = [&](auto w4) {
+            constexpr bool W4 = decltype(w4)::value;
+            if (p.ta == 1) go(gemm_f16_tiled_kernel<1, 2, 4, W4>, 512);
+            else if (p.ta == 2) go(gemm_f16_tiled_kernel<2, 2, 4, W4>, 512);
+            else if (p.cols == 128) go(gemm_f16_tiled_kernel<4, 1, 4, W4>, 512);
+            else if (p.cols == 192) go(gemm_f16_tiled_kernel<4, 3, 2, W4>, 256);
+            else go(gemm_f16_tiled_kernel<4, 2, 4, W4>, 512);
+        };
+        if (g.w4) pick(std::true_type{});
+        else pick(std::false_type{});
     }
     if (g.reduced) {
         const dim3 grid((unsigned)((g.N + 255) / 256), (unsigned)g.M);

@@ -77,9 +77,19 @@ struct GemmArgs {
     // launch_gemm_pack_w4; the projection writes `splitk` partial slots (gemm_w4_slots)
     bool w4;
     const void *w4_scale[3], *w4_zero[3];   // M > kStreamMaxRows: w[] are the codes [n][K/2], these the bf16 scales and uint8 zero points [n][K/128]
+    // -- M > kStreamMaxRows (the tiled kernel; see GemmTiledPlan) ---------------------------------------------------
+    int tiled_tiles;              // set by launch_gemm
+    uint16_t *swiglu16;           // segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
     RowScale scale;               // applied when writing `reduced` (row = the source row of m)
     int scale_rows;               //   rows per tile slab of scale.sumsq
 };
+struct GemmTiledPlan {
+    int ta, cols;                 // block tile: 64 ta rows x cols columns
+    int tiles, blocks;            // tiles of the product; blocks, each of which takes an equal range of all their K steps
+    int slots;                    // partial slots per output
+};
+GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated);
+bool gemm_tiled_gates(int M, int K, const int *n);                // whether the gate|up projection n = {f, f} applies SwiGLU itself
 int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg);
 // repacked weights for the M <= kStreamMaxRows path
 int gemm_pack_tiles(const int *n, int nseg);

@@ -152,6 +152,18 @@ def test_bf16_small_models(shape, n_new, ctx, pack):
     p.close()
 
 
+@pytest.mark.parametrize("rows", [17, 64, 65, 128, 129, 256, 257, 301])
+@pytest.mark.parametrize("w4", [False, True], ids=["bf16", "w4"])
+def test_tiled_projections_at_tile_edges(rows, w4):
+    """Row counts around the tile heights (64, 128, 256), output widths that no tile divides (384 + 2 x 128 columns of
+    QKV, 777 of the head), K of 3 and 128 K tiles (shared unevenly by the blocks), and from 129 rows on a gate|up
+    projection wide enough (2 x 16384) to apply SwiGLU itself.  Bar: the repository's 2e-2 for bf16 models."""
+    shape = synth.Shape(1, 384, 3, 1, 128, 8192 if rows > 256 or rows < 129 else 16384, 777, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 320, seed=70 + rows, std=0.05, w4=w4)
+    p.step(synth.make_tokens(shape.vocab, (1, rows), rows), what=f"{rows} rows")
+    p.close()
+
+
 def test_bf16_batch_ragged_lengths_truncate():
     shape = SMALL_GQA
     p = Pair(shape, torch.bfloat16, 4, 640, seed=21, ctx=512, lens=[512, 100, 333, 1], std=0.05, pack=True)
