@@ -270,34 +270,60 @@ struct ForwardPlan {
     bool folded;                  // RMSNorm folded into the projections (bf16, packed weights, M <= kStreamMaxRows)
     bool fused_rope;              // the attention kernel reduces, rotates and appends q / k / v itself
     bool gated;                   // bf16, M > kStreamMaxRows: the gate|up projection applies SwiGLU itself
+    size_t partial_bytes;         // of the layers' projections
 };
 
-ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit_rows, int len_bound, bool tree) {
+// partial slots of one projection (or head) over `rows` rows: what its kernel splits K into
+int proj_splits(const psd_model *mdl, int rows, int K, const int *n, int nseg, bool head) {
+    int N = 0;
+    for (int s = 0; s < nseg; ++s) N += n[s];
+    if (mdl->w4 && !head && rows <= kStreamMaxRows) return gemm_w4_slots(K, n, nseg, false);
+    if (mdl->packed && rows <= kStreamMaxRows) return gemm_packed_splits(rows, K, n, nseg);
+    return gemm_pick_splitk(mdl->d.dtype, rows, K, N, n, nseg);
+}
+
+// the part of the plan that depends on the number of rows alone
+ForwardPlan plan_projections(const psd_model *mdl, int M) {
     const psd_model_desc &d = mdl->d;
     ForwardPlan p{};
-    const int M = batch * n_new;
     p.M = M;
     const int hd = d.n_q_heads * d.d_head, kvd = d.n_kv_heads * d.d_head;
     p.width_qkv = hd + 2 * kvd;
-    const int n_qkv[3] = {hd, kvd, kvd}, n_o[1] = {d.d_model}, n_gu[2] = {d.d_ffn, d.d_ffn}, n_v[1] = {d.vocab};
-    const int Ml = batch * n_logit_rows;
+    const int n_qkv[3] = {hd, kvd, kvd}, n_o[1] = {d.d_model}, n_gu[2] = {d.d_ffn, d.d_ffn};
     p.folded = mdl->packed && d.dtype == PSD_BF16 && M <= kStreamMaxRows;
-    auto splits = [&](int rows, int K, int N, const int *n, int nseg) {
-        if (mdl->w4 && n != n_v && rows <= kStreamMaxRows) return gemm_w4_slots(K, n, nseg, false);
-        if (mdl->packed && rows <= kStreamMaxRows) return gemm_packed_splits(rows, K, n, nseg);
-        return gemm_pick_splitk(d.dtype, rows, K, N, n, nseg);
-    };
-    p.fused_rope = attn_fuses_rope(d.dtype, n_new, d.n_q_heads, d.n_kv_heads, d.d_head, tree);
-    p.sk_qkv = splits(M, d.d_model, p.width_qkv, n_qkv, 3);
+    p.sk_qkv = proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
     // folded: O runs on the column kernel (one owner per output), or, 4-bit, on partial slots with the arrival epilogue
-    p.sk_o = p.folded ? (mdl->w4 ? gemm_w4_slots(hd, n_o, 1, true) : 1) : splits(M, hd, d.d_model, n_o, 1);
-    p.sk_gu = splits(M, d.d_model, 2 * d.d_ffn, n_gu, 2);
+    p.sk_o = p.folded ? (mdl->w4 ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false);
+    p.gated = d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu);
+    p.sk_gu = p.gated ? 1 : proj_splits(mdl, M, d.d_model, n_gu, 2, false);
     // folded: the down projection runs on the unit kernel with the residual epilogue, its partials in slots
     p.sk_down = p.folded ? (mdl->w4 ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : gemm_resid_slots(gemm_pack_tiles(n_o, 1), d.d_ffn))
-                         : splits(M, d.d_ffn, d.d_model, n_o, 1);
-    p.sk_head = Ml > 0 ? splits(Ml, d.d_model, d.vocab, n_v, 1) : 1;
+                         : proj_splits(mdl, M, d.d_ffn, n_o, 1, false);
+    p.half_copies = d.dtype == PSD_BF16 && (M > kStreamMaxRows || (mdl->w4 && p.folded));
+    auto need = [&](int sk, int N) { const size_t b = (size_t)sk * M * N * 4; if (b > p.partial_bytes) p.partial_bytes = b; };
+    need(p.sk_qkv, p.width_qkv);
+    need(p.sk_o, d.d_model);
+    if (!p.gated) need(p.sk_gu, 2 * d.d_ffn);
+    need(p.sk_down, d.d_model);
+    return p;
+}
+
+// partial bytes of the head over Ml rows (0: a single split writes the logits in place), and its slots
+size_t head_partial_bytes(const psd_model *mdl, int Ml, bool folded, int *slots) {
+    const int n_v[1] = {mdl->d.vocab};
+    const int sk = Ml > 0 ? proj_splits(mdl, Ml, mdl->d.d_model, n_v, 1, true) : 1;
+    if (slots) *slots = sk;
+    return sk > 1 || folded ? (size_t)sk * Ml * mdl->d.vocab * 4 : 0;
+}
+
+// ... and the rest: attention splits, where everything lies in the workspace
+void plan_layout(const psd_model *mdl, int batch, int n_new, int len_bound, bool tree, size_t head_bytes, ForwardPlan *out) {
+    const psd_model_desc &d = mdl->d;
+    ForwardPlan &p = *out;
+    const int M = p.M, hd = d.n_q_heads * d.d_head;
+    const int n_o[1] = {d.d_model};
+    p.fused_rope = attn_fuses_rope(d.dtype, n_new, d.n_q_heads, d.n_kv_heads, d.d_head, tree);
     p.attn_splits = attn_pick_splits(d.dtype, batch, n_new, d.n_q_heads, d.n_kv_heads, d.d_head, len_bound, tree);
-    if (d.dtype == PSD_BF16 && M > kStreamMaxRows) p.gated = gemm_tiled_gates(M, d.d_model, n_gu);
     const size_t act = 4;                                    // activations are fp32 for both dtypes
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
@@ -306,17 +332,10 @@ ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit
     p.off_q = take((size_t)M * hd * act);
     p.off_attn = take((size_t)M * hd * act);
     p.off_h = take((size_t)M * d.d_ffn * act);
-    p.half_copies = d.dtype == PSD_BF16 && (M > kStreamMaxRows || (mdl->w4 && p.folded));
     p.off_xn16 = take(p.half_copies ? (size_t)M * d.d_model * 2 : 0);
     p.off_attn16 = take(p.half_copies ? (size_t)M * hd * 2 : 0);
     p.off_h16 = take(p.half_copies ? (size_t)M * d.d_ffn * 2 : 0);
-    size_t part = 0;
-    auto need = [&](int sk, int rows, int N) { const size_t b = (size_t)sk * rows * N * 4; if (b > part) part = b; };
-    need(p.sk_qkv, M, p.width_qkv); need(p.sk_o, M, d.d_model);
-    if (!p.gated) need(p.sk_gu, M, 2 * d.d_ffn);
-    need(p.sk_down, M, d.d_model);
-    if (p.sk_head > 1 || p.folded) need(p.sk_head, Ml, d.vocab);  // else a single split writes the logits in place
-    p.off_partial = take(part);
+    p.off_partial = take(p.partial_bytes > head_bytes ? p.partial_bytes : head_bytes);
     p.off_po = take(p.attn_splits > 1 ? (size_t)M * d.n_q_heads * p.attn_splits * d.d_head * 4 : 0);
     p.off_pml = take(p.attn_splits > 1 ? (size_t)M * d.n_q_heads * p.attn_splits * 2 * 4 : 0);
     p.off_sumsq = take(p.folded ? (size_t)(d.d_model / 16) * M * 4 : 0);
@@ -324,7 +343,35 @@ ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit
     p.off_tilectr = take(p.folded ? (size_t)gemm_pack_tiles(n_o, 1) * 4 : 0);
     p.off_tree = take(p.fused_rope ? (size_t)kTreeMaxNodes * 8 : 0);      // ancestor masks and depths of a tree pass
     p.total = off;
+}
+
+ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit_rows, int len_bound, bool tree) {
+    ForwardPlan p = plan_projections(mdl, batch * n_new);
+    plan_layout(mdl, batch, n_new, len_bound, tree, head_partial_bytes(mdl, batch * n_logit_rows, p.folded, &p.sk_head), &p);
     return p;
+}
+
+// the largest head_partial_bytes over every number of logit rows (0 .. n_new per sequence).  Up to kStreamMaxRows rows, and
+// from there to 128, the number of slots is one and the same, so the largest count has the most; above, it does not grow
+// with the rows as long as they fill the same number of 256-row tiles, so a run of them that starts at one slot is done.
+size_t worst_head_partial_bytes(const psd_model *mdl, int batch, int n_new, bool folded) {
+    size_t worst = 0;
+    const int M = batch * n_new;
+    auto at = [&](int Ml, int *slots) {
+        const size_t b = head_partial_bytes(mdl, Ml, folded, slots);
+        worst = b > worst ? b : worst;
+    };
+    for (int edge : {kStreamMaxRows, 128}) {
+        const int Ml = (M < edge ? M : edge) / batch * batch;
+        if (Ml > 0) at(Ml, nullptr);
+    }
+    for (int Ml = 129 > batch ? (128 + batch) / batch * batch : batch; Ml <= M;) {
+        int slots = 1;
+        at(Ml, &slots);
+        if (slots == 1) Ml = ((Ml + 255) / 256 * 256 + batch) / batch * batch;       // the first count past this tile row
+        else Ml += batch;
+    }
+    return worst;
 }
 
 bool forward_shape_ok(const psd_model *m, int batch, int n_new) {
@@ -343,13 +390,13 @@ size_t psd_model_workspace_bytes(const psd_model *m, int32_t batch, int32_t n_ne
     if (!m || max_len <= 0 || !forward_shape_ok(m, batch, n_new)) return 0;
     // split choices depend on the cache length bound, on how many rows get logits and on whether the rows are a
     // token tree: take the largest need over all of them
+    ForwardPlan p = plan_projections(m, batch * n_new);
+    const size_t head = worst_head_partial_bytes(m, batch, n_new, p.folded);
     size_t worst = 0;
-    for (int rows = 0; rows <= n_new; ++rows)
-        for (int tree = 0; tree < 2; ++tree) {
-            const size_t a = plan_forward(m, batch, n_new, rows, max_len, tree != 0).total;
-            const size_t b = plan_forward(m, batch, n_new, rows, n_new, tree != 0).total;
-            worst = a > worst ? a : worst;
-            worst = b > worst ? b : worst;
+    for (int tree = 0; tree < 2; ++tree)
+        for (int len : {max_len, n_new}) {
+            plan_layout(m, batch, n_new, len, tree != 0, head, &p);
+            worst = p.total > worst ? p.total : worst;
         }
     return worst;
 }
