@@ -123,6 +123,54 @@ def test_tree_accept_matches_oracle(rows, name, V, dtype, temperature):
     print("accepted path lengths: mean %.2f, excused %d" % (np.mean(lens), excused))
 
 
+@pytest.mark.parametrize("rows,name,V,temperature", [
+    (2, "star40", 4096, 1.0), (1, "star40", 4097, 0.5), (3, "binary7", 1, 1.0), (40, "full32", 12289, 0.8), (1, "binary7", 262145, 1.0)])
+def test_tree_accept_chunk_edges_and_many_refusals(rows, name, V, temperature):
+    """Vocabularies at the edges of a 4096-entry chunk, above 64 chunks and of one entry; forty children of one node whose
+    tokens the verifier dislikes, so that the walk passes the refusals that are summed ahead; statistics larger than a
+    scratch slot (40 x 32 nodes x 4 chunks).  Exact against the oracle on every call that is not a near tie."""
+    if name == "star40":
+        TREES[name] = [-1] + [0] * 40
+    parents, p, q, toks, u = _accept_case(rows, name, V, torch.float32, V + rows, temperature)
+    if name == "star40":
+        u[:, 1:-1] = 0.97 + 0.03 * u[:, 1:-1]               # nearly every child is refused
+    got = [x.cpu().numpy() for x in runtime.tree_accept(p.cuda(), q.cuda(), toks.cuda(), parents, u.cuda(), temperature)]
+    for r in range(rows):
+        path, tok, flags = otree.tree_accept(p[r].double().numpy(), q[r].double().numpy(), toks[r].numpy(), parents,
+                                             u[r].double().numpy(), temperature, return_flags=True)
+        if not (flags & 1 or got[3][r] & psd.PSD_FLAG_NEAR_TIE):
+            assert got[0][r] == len(path) and got[1][r, :len(path)].tolist() == path and got[2][r] == tok
+
+
+def test_tree_accept_overlapping_streams_and_capture():
+    """Calls that overlap on eight streams (more than there are scratch slots) and a captured call, replayed between eager
+    ones, give what the same calls give one after another."""
+    cases = [_accept_case(4, "binary7", 20000 + 37 * i, torch.float32, i, 1.0) for i in range(8)]
+    cases = [(c[0],) + tuple(t.cuda() for t in c[1:]) for c in cases]
+    call = lambda c, st=None: runtime.tree_accept(c[1], c[2], c[3], c[0], c[4], 1.0, st)
+    want = []
+    for c in cases:
+        want.append([x.clone() for x in call(c)])
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in cases]
+    got = []
+    for rep in range(6):
+        for c, st in zip(cases, streams):
+            with torch.cuda.stream(st):
+                got.append(call(c))
+    torch.cuda.synchronize()
+    for i, g in enumerate(got):
+        assert all(torch.equal(a, b) for a, b in zip(g, want[i % len(cases)])), i
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = call(cases[0])
+    for rep in range(3):
+        graph.replay()
+        call(cases[1])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want[0])), rep
+
+
 def test_tree_accept_chain_is_the_linear_call():
     """One child per node: the same accepted length and token as psd_spec_accept on the same inputs."""
     rows, gamma, V = 32, 6, 32000
