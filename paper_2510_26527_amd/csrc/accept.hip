@@ -7,7 +7,9 @@
 //      reductions, 8 x 16-byte loads in flight per lane.  The block whose chunk holds the
 //      draft token of its position also hands on that one logit, so the ratio test later
 //      needs no dependent load.
-//   2. accept_draw_kernel   several blocks per sequence.  Each re-derives the first rejection
+//   2. accept_draw_kernel   bound by a chain of dependent steps and by fp64 issue (two exponentials per entry of the one
+//      position): reductions and scans run on lane moves in registers, and the finishing block's chunk sums in one
+//      wavefront without a barrier.  Several blocks per sequence.  Each re-derives the first rejection
 //      n of its sequence from the statistics (ratio test against the supplied uniforms, scan
 //      over <= 64 flags) and accumulates, in fp64 and for the ONE position the draw needs, the
 //      softmax denominators and the residual mass of its chunk.  The block of a sequence that
@@ -29,8 +31,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kLoadsPerLane = 8;
 constexpr double kTieEps = 1e-5;
-constexpr int kMaxChunksE = 256;      // draw-pass chunks per logits row: one per thread of the block that finishes a sequence
-constexpr int kGroup = 8;             // consecutive entries a thread of the draw kernel takes at a time
+constexpr int kMaxChunksE = 128;      // draw-pass chunks per logits row: two per lane of the wavefront that finishes a sequence
+constexpr int kMaxGroup = 8;          // consecutive entries a thread of the draw kernel takes at a time (2 or 8)
 
 template <typename T>
 __device__ __forceinline__ const T *logits_row(const AcceptArgs &a, int b, bool is_q, int j) {
@@ -122,75 +124,90 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(AcceptArgs a) {
     if (tid == 0) a.stats[(size_t)vec * a.n_chunksA + c] = make_float2(m, ((ss[0] + ss[1]) + ss[2]) + ss[3]);
 }
 
-// (max raw logit, sum exp((l - max)/T)) of one logits row from its per-chunk statistics.  The chunk
-// sums are fp32 quantities; rescaling them with the fp32 exponential loses nothing.
-__device__ __forceinline__ void combine_stats(const AcceptArgs &a, int b, int r, float *M, double *Z) {
-    const float2 *st = a.stats + ((size_t)b * (a.n_p_rows + a.gamma) + r) * a.n_chunksA;
-    float m = -INFINITY;
-    for (int c = 0; c < a.n_chunksA; ++c) m = fmaxf(m, st[c].x);
-    double z = 0.0;
-    const float k2 = 1.4426950408889634f / a.temperature;
-    for (int c = 0; c < a.n_chunksA; ++c)
-        if (st[c].x > -INFINITY) z += (double)(st[c].y * __builtin_amdgcn_exp2f((st[c].x - m) * k2));
-    *M = m;
-    *Z = z;
-}
-
 // fp32 statistics of every position of one sequence, kept in LDS by the block that decides it
 struct SeqStats {
     float mp[65], mq[64];
     double zp[65], zq[64];
-    int bits[64];
     double exp2tab[64];           // kExp2Table, for exp_core
+    double inv_t;
+    int n, flags;
 };
 
-// Ratio tests of sequence b and the scan to the first rejection.  Called by a whole block;
-// every thread returns the same n and flags.
+// Ratio tests of sequence b and the scan to the first rejection.  Called by a whole block; every thread returns the same
+// n and flags.  The per-chunk statistics of a logits row (max raw logit, sum exp((l - max)/T)) are combined by eight lanes
+// per row, all rows at once; the chunk sums are fp32 quantities, so rescaling them with the fp32 exponential loses
+// nothing.  Then the first wavefront tests all positions, one per lane, and the first rejection is a bit scan.
 __device__ __forceinline__ void decide(const AcceptArgs &a, int b, SeqStats *ss, int *n_out, int *flags_out) {
-    const int j = threadIdx.x;
-    const double tabv = j < 64 ? kExp2Table[j] : 0.0;      // requested first, stored once the other loads are out
+    const int tid = threadIdx.x, lane = tid & 63, sub = tid & 7;
+    const double tabv = tid < 64 ? kExp2Table[tid] : 0.0;      // requested first, stored once the other loads are out
     double u = 0.0;
     float lpx = 0.f, lqx = 0.f;
-    float Mp = 0.f, Mq = 0.f;
-    double Zp = 1.0, Zq = 1.0;
-    if (j < a.n_p_rows) {
-        if (j < a.gamma) {                      // independent loads first
-            u = (double)a.u[(size_t)b * (a.gamma + 1) + j];
-            lpx = a.xlogit[((size_t)b * a.gamma + j) * 2];
-            lqx = a.xlogit[((size_t)b * a.gamma + j) * 2 + 1];
+    if (tid < a.gamma) {
+        u = (double)a.u[(size_t)b * (a.gamma + 1) + lane];
+        lpx = a.xlogit[((size_t)b * a.gamma + lane) * 2];
+        lqx = a.xlogit[((size_t)b * a.gamma + lane) * 2 + 1];
+    }
+    const float k2 = 1.4426950408889634f / a.temperature;
+    const int rows = a.n_p_rows + a.gamma, nA = a.n_chunksA;
+    for (int r0 = 0; r0 < rows; r0 += kThreads / 8) {          // the same number of rounds for the whole block
+        const int r = r0 + (tid >> 3);
+        const float2 *st = a.stats + ((size_t)b * rows + min(r, rows - 1)) * nA;
+        float m = -INFINITY;
+        double z = 0.0;
+        for (int c0 = 0; c0 < nA; c0 += 32) {                  // up to four chunks per lane in flight
+            float2 t[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t[i] = st[min(c0 + sub + 8 * i, nA - 1)];
+            float mm = m;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mm = c0 + sub + 8 * i < nA ? fmaxf(mm, t[i].x) : mm;
+            if (mm > m && m > -INFINITY) z *= (double)__builtin_amdgcn_exp2f((m - mm) * k2);
+            m = mm;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (c0 + sub + 8 * i < nA && t[i].x > -INFINITY) z += (double)(t[i].y * __builtin_amdgcn_exp2f((t[i].x - m) * k2));
         }
-        combine_stats(a, b, j, &Mp, &Zp);
-        ss->mp[j] = Mp;
-        ss->zp[j] = Zp;
-        if (j < a.gamma) {
-            combine_stats(a, b, a.n_p_rows + j, &Mq, &Zq);
-            ss->mq[j] = Mq;
-            ss->zq[j] = Zq;
+        float top = m;
+        top = fmaxf(top, __shfl_xor(top, 1, 64));
+        top = fmaxf(top, __shfl_xor(top, 2, 64));
+        top = fmaxf(top, __shfl_xor(top, 4, 64));
+        if (m > -INFINITY) z *= (double)__builtin_amdgcn_exp2f((m - top) * k2);
+        z += __shfl_xor(z, 1, 64);
+        z += __shfl_xor(z, 2, 64);
+        z += __shfl_xor(z, 4, 64);
+        if (sub == 0 && r < rows) {
+            if (r < a.n_p_rows) { ss->mp[r] = top; ss->zp[r] = z; }
+            else { ss->mq[r - a.n_p_rows] = top; ss->zq[r - a.n_p_rows] = z; }
         }
     }
-    if (j < 64) ss->exp2tab[j] = tabv;
+    if (tid < 64) ss->exp2tab[tid] = tabv;
     __syncthreads();
-    if (j < a.gamma && j < a.n_p_rows) {
-        double rho;
-        if (lqx == -INFINITY) {
-            rho = INFINITY;             // q[x] = 0: the token could not have been drafted; accept
-        } else {
-            rho = exp_any((((double)lpx - (double)Mp) - ((double)lqx - (double)Mq)) / (double)a.temperature, ss->exp2tab) * (Zq / Zp);
+    if (tid < 64) {
+        bool acc = true, tie = false;
+        if (lane < a.gamma) {
+            const float Mp = ss->mp[lane], Mq = ss->mq[lane];
+            double rho;
+            if (lqx == -INFINITY) {
+                rho = INFINITY;             // q[x] = 0: the token could not have been drafted; accept
+            } else {
+                rho = exp_any((((double)lpx - (double)Mp) - ((double)lqx - (double)Mq)) / (double)a.temperature, ss->exp2tab) *
+                      (ss->zq[lane] / ss->zp[lane]);
+            }
+            acc = u < fmin(1.0, rho);
+            tie = fabs(u - rho) < kTieEps;
         }
-        const int acc = u < fmin(1.0, rho) ? 1 : 0;
-        const int tie = fabs(u - rho) < kTieEps ? 2 : 0;
-        ss->bits[j] = acc | tie;
+        const unsigned long long refused = __ballot(!acc), ties = __ballot(tie);       // lanes from gamma on: neither
+        const int n = refused ? __ffsll(refused) - 1 : a.gamma;
+        const unsigned long long tested = n >= 63 ? ~0ull : (2ull << n) - 1;           // positions up to the first rejection
+        if (lane == 0) {
+            ss->n = n;
+            ss->flags = (ties & tested) ? PSD_FLAG_NEAR_TIE : 0;
+            ss->inv_t = 1.0 / (double)a.temperature;
+        }
     }
     __syncthreads();
-    int n = 0, flags = 0;
-    for (int k = 0; k < a.gamma; ++k) {
-        const int f = ss->bits[k];
-        if (f & 2) flags |= PSD_FLAG_NEAR_TIE;
-        if (!(f & 1)) break;
-        ++n;
-    }
-    *n_out = n;
-    *flags_out = flags;
+    *n_out = ss->n;
+    *flags_out = ss->flags;
 }
 
 // which position the draw reads: the rejected one (p and q) or the bonus row (p only)
@@ -228,20 +245,20 @@ struct DrawPos {
         tab = ss.exp2tab;
         prow = logits_row<T>(a, b, false, d.p_row);
         qrow = logits_row<T>(a, b, true, d.have_q ? n : 0);
-        inv_t = 1.0 / (double)a.temperature;
+        inv_t = ss.inv_t;
         mp = (double)Mp * inv_t;
         mq = (double)Mq * inv_t;
-        const float est = logf((float)(Zp32 / Zq32));
+        const float est = __logf((float)Zp32) - __logf((float)Zq32);
         delta = d.have_q && est == est ? (double)est : 0.0;       // any finite value will do
         have_q = d.have_q;
     }
-    // raw logits of the kGroup consecutive entries i0 .. i0 + kGroup - 1 (those at or past i_end: entry i0 again,
+    // raw logits of the G consecutive entries i0 .. i0 + G - 1 (those at or past i_end: entry i0 again,
     // q's are 0 when there is no q row).  VEC: rows are 16-byte aligned, i0 and V are multiples of the elements
-    // per 16-byte load, so whole vectors are inside the row
-    template <bool VEC>
-    __device__ __forceinline__ void load_group(int i0, int i_end, float (&lp)[kGroup], float (&lq)[kGroup]) const {
-        if constexpr (VEC) {
-            constexpr int EPL = (int)(16 / sizeof(T)), NV = kGroup / EPL;
+    // per 16-byte load, so whole vectors are inside the row (fewer than a vector's entries are loaded one by one)
+    template <bool VEC, int G>
+    __device__ __forceinline__ void load_group(int i0, int i_end, float (&lp)[G], float (&lq)[G]) const {
+        if constexpr (VEC && G % (int)(16 / sizeof(T)) == 0) {
+            constexpr int EPL = (int)(16 / sizeof(T)), NV = G / EPL;
             u32x4 rp[NV], rq[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
@@ -250,7 +267,7 @@ struct DrawPos {
                 rq[v] = have_q ? *reinterpret_cast<const u32x4 *>(qrow + i) : u32x4{0u, 0u, 0u, 0u};
             }
 #pragma unroll
-            for (int j = 0; j < kGroup; ++j) {
+            for (int j = 0; j < G; ++j) {
                 if constexpr (sizeof(T) == 2) {
                     const uint32_t wp = rp[j / EPL][(j % EPL) >> 1], wq = rq[j / EPL][(j % EPL) >> 1];
                     lp[j] = (j & 1) ? __uint_as_float(wp & 0xffff0000u) : __uint_as_float(wp << 16);
@@ -262,7 +279,7 @@ struct DrawPos {
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < kGroup; ++j) {
+            for (int j = 0; j < G; ++j) {
                 const int i = i0 + j < i_end ? i0 + j : i0;
                 lp[j] = load_elem(prow, i);
                 lq[j] = have_q ? load_elem(qrow, i) : 0.f;
@@ -280,50 +297,24 @@ struct DrawPos {
     }
 };
 
-// fixed-order block reductions of NV doubles per thread: butterfly inside each wavefront, then the four
-// wavefront results left to right
-template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double (*red)[kThreads / 64]) {
-    const int tid = threadIdx.x;
-    __syncthreads();                              // red may still be read from an earlier use
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        v[k] = wave_sum(v[k]);
-        if ((tid & 63) == 0) red[k][tid >> 6] = v[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = ((red[k][0] + red[k][1]) + red[k][2]) + red[k][3];
-}
-__device__ __forceinline__ double wave_min_d(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-__device__ __forceinline__ double wave_max_d(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
 // per (sequence, chunk): sum a, sum b, both over the entries with t_i > 0, the smallest positive t_i and the
 // largest non-positive t_i
 constexpr int kPartStride = 6;
 
 // Grid: rows x n_chunksE blocks.  Every block: first rejection of its sequence, fp64 sums of its chunk of
-// the draw position; the block that arrives last at the sequence's counter finishes the draw (thread k of
-// it owns chunk k: n_chunksE <= kThreads).
-template <typename T, bool VEC>
+// the draw position; the block that arrives last at the sequence's counter finishes the draw (lane k of its first
+// wavefront owns chunks 2k and 2k + 1: n_chunksE <= 128).
+template <typename T, bool VEC, int G>
 __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
+    constexpr int kWaves = kThreads / 64;
     __shared__ SeqStats s_seq;
-    __shared__ double s_red[6][kThreads / 64];
-    __shared__ double s_scan[kThreads / 64];
-
+    __shared__ double s_red[6][kWaves], s_scan[2][kWaves];
     __shared__ int s_redo[kMaxChunksE];           // chunks whose sign classification has to be redone
-    __shared__ int s_last, s_cstar, s_best, s_lastpos;
-    __shared__ double s_base;
+    __shared__ double s_again[kMaxChunksE];       // ... and their weight then
+    __shared__ int s_last, s_any, s_cstar, s_best, s_lastpos, s_fall;
+    __shared__ double s_base, s_target, s_inv[2];
     const int nE = a.n_chunksE;
-    const int b = blockIdx.x / nE, c = blockIdx.x % nE, tid = threadIdx.x;
+    const int b = blockIdx.x / nE, c = blockIdx.x % nE, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int n, flags;
     decide(a, b, &s_seq, &n, &flags);
     const DrawRows d = draw_rows(a, n);
@@ -333,20 +324,23 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
     }
     DrawPos<T> w;
     w.init(a, b, n, d, s_seq);
+    const auto add = [](double x, double y) { return x + y; };
+    const auto lower = [](double x, double y) { return fmin(x, y); };
+    const auto upper = [](double x, double y) { return fmax(x, y); };
 
     // ---- this block's chunk
     {
         const int e0 = c * a.chunkE, e1 = min(a.V, e0 + a.chunkE);
         double acc[4] = {0.0, 0.0, 0.0, 0.0};               // sum a, sum b, positive a, positive b
         double tpos = INFINITY, tneg = -INFINITY;
-        for (int i0 = e0 + tid * kGroup; i0 < e1; i0 += kGroup * kThreads) {
-            float lp[kGroup], lq[kGroup];
+        for (int i0 = e0 + tid * G; i0 < e1; i0 += G * kThreads) {
+            float lp[G], lq[G];
             w.template load_group<VEC>(i0, e1, lp, lq);
-            double ea[kGroup], eb[kGroup], t[kGroup];
+            double ea[G], eb[G], t[G];
 #pragma unroll
-            for (int j = 0; j < kGroup; ++j) w.eval(lp[j], lq[j], &ea[j], &eb[j], &t[j]);
+            for (int j = 0; j < G; ++j) w.eval(lp[j], lq[j], &ea[j], &eb[j], &t[j]);
 #pragma unroll
-            for (int j = 0; j < kGroup; ++j) {
+            for (int j = 0; j < G; ++j) {
                 if (i0 + j < e1) {
                     acc[0] += ea[j];
                     acc[1] += eb[j];
@@ -357,14 +351,14 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
         }
         // one value per wavefront into LDS, thread 0 folds the four in wavefront order
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] = wave_sum(acc[k]);
-        tpos = wave_min_d(tpos);
-        tneg = wave_max_d(tneg);
-        if ((tid & 63) == 0) {
+        for (int k = 0; k < 4; ++k) acc[k] = wave_scan_d(acc[k], 0.0, add);
+        tpos = wave_scan_d(tpos, INFINITY, lower);
+        tneg = wave_scan_d(tneg, -INFINITY, upper);
+        if (lane == 63) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) s_red[k][tid >> 6] = acc[k];
-            s_red[4][tid >> 6] = tpos;
-            s_red[5][tid >> 6] = tneg;
+            for (int k = 0; k < 4; ++k) s_red[k][wave] = acc[k];
+            s_red[4][wave] = tpos;
+            s_red[5][wave] = tneg;
         }
         __syncthreads();
         if (tid == 0) {
@@ -387,97 +381,118 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
         if (!s_last) return;
     }
 
-    // ---- the last block of the sequence: thread k takes chunk k's results (one round of loads)
-    double pk[kPartStride] = {0.0, 0.0, 0.0, 0.0, INFINITY, -INFINITY};
-    if (tid < nE) {
-        const double *src = a.part + ((size_t)b * nE + tid) * kPartStride;
-#pragma unroll
-        for (int k = 0; k < kPartStride; ++k) pk[k] = __hip_atomic_load(src + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    // ---- the last block of the sequence: its first wavefront takes all chunks' results, two per lane (one round of loads)
     const double u = (double)a.u[(size_t)b * (a.gamma + 1) + a.gamma];
-    double zz[2] = {pk[0], pk[1]};
-    block_sum<2>(zz, s_red);
-    const double inv_zp = 1.0 / zz[0], inv_zq = d.have_q ? 1.0 / zz[1] : 0.0;
-    double wk = pk[2] * inv_zp - pk[3] * inv_zq;                 // weight of chunk tid
-    if (d.have_q) {
+    double pk[2][kPartStride];
+    if (wave == 0) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = 2 * lane + h;
+            const double *src = a.part + ((size_t)b * nE + min(k, nE - 1)) * kPartStride;
+#pragma unroll
+            for (int e = 0; e < kPartStride; ++e) {
+                const double v = __hip_atomic_load(src + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                pk[h][e] = k < nE ? v : (e < 4 ? 0.0 : (e == 4 ? (double)INFINITY : -(double)INFINITY));
+            }
+        }
+        const double zp = wave_total_d(pk[0][0] + pk[1][0]), zq = wave_total_d(pk[0][1] + pk[1][1]);
         // chunks with a t_i between 0 and eps (or too close to tell): every entry's sign again, from the fp64 weights
-        const double eps = log(zz[0] / zz[1]) - w.delta;
-        const double lo = fmin(0.0, eps) - kSignTol, hi = fmax(0.0, eps) + kSignTol;
-        const bool redo = tid < nE && (!(eps == eps) || pk[5] >= lo || pk[4] <= hi);
-        if (tid < nE) s_redo[tid] = redo ? 1 : 0;
-        __syncthreads();
+        bool redo[2] = {false, false};
+        if (d.have_q) {
+            const double eps = log(zp / zq) - w.delta;
+            const double lo = fmin(0.0, eps) - kSignTol, hi = fmax(0.0, eps) + kSignTol;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                redo[h] = 2 * lane + h < nE && (!(eps == eps) || pk[h][5] >= lo || pk[h][4] <= hi);
+                s_redo[2 * lane + h] = redo[h] ? 1 : 0;
+            }
+        }
+        const bool any = __ballot(redo[0] || redo[1]) != 0;
+        if (lane == 0) {
+            s_inv[0] = 1.0 / zp;
+            s_inv[1] = d.have_q ? 1.0 / zq : 0.0;
+            s_any = any ? 1 : 0;
+            s_best = 0x7fffffff;
+            s_lastpos = -1;
+        }
+    }
+    __syncthreads();
+    const double inv_zp = s_inv[0], inv_zq = s_inv[1];
+    if (s_any) {                                                 // the same for the whole block
         for (int k = 0; k < nE; ++k) {
-            if (!s_redo[k]) continue;                            // the same for the whole block
+            if (!s_redo[k]) continue;
             const int f0 = k * a.chunkE, f1 = min(a.V, f0 + a.chunkE);
-            double pw[2] = {0.0, 0.0};
-            for (int i0 = f0 + tid * kGroup; i0 < f1; i0 += kGroup * kThreads) {
-                float lp[kGroup], lq[kGroup];
+            double pa = 0.0, pb = 0.0;
+            for (int i0 = f0 + tid * G; i0 < f1; i0 += G * kThreads) {
+                float lp[G], lq[G];
                 w.template load_group<VEC>(i0, f1, lp, lq);
 #pragma unroll
-                for (int j = 0; j < kGroup; ++j) {
+                for (int j = 0; j < G; ++j) {
                     double ea, eb, t;
                     w.eval(lp[j], lq[j], &ea, &eb, &t);
-                    if (i0 + j < f1 && ea * inv_zp - eb * inv_zq > 0.0) { pw[0] += ea; pw[1] += eb; }
+                    if (i0 + j < f1 && ea * inv_zp - eb * inv_zq > 0.0) { pa += ea; pb += eb; }
                 }
             }
-            block_sum<2>(pw, s_red);
-            if (tid == k) wk = pw[0] * inv_zp - pw[1] * inv_zq;
+            pa = wave_total_d(pa);
+            pb = wave_total_d(pb);
+            __syncthreads();                                     // s_red: earlier readers are done
+            if (lane == 0) { s_red[0][wave] = pa; s_red[1][wave] = pb; }
+            __syncthreads();
+            if (tid == 0)
+                s_again[k] = (((s_red[0][0] + s_red[0][1]) + s_red[0][2]) + s_red[0][3]) * inv_zp -
+                             (((s_red[1][0] + s_red[1][1]) + s_red[1][2]) + s_red[1][3]) * inv_zq;
         }
+        __syncthreads();
     }
-    double ms[1] = {wk};
-    block_sum<1>(ms, s_red);
-    double mass = ms[0];
-    const bool fall_back_to_p = d.have_q && !(mass > 0.0);
-    if (fall_back_to_p) {                         // residual mass 0: draw from p itself
-        mass = 1.0;                               // sum of a_i / Zp
-        wk = pk[0] * inv_zp;
-    }
-    // first chunk whose inclusive prefix exceeds t
-    const double t = u * mass;
-    {
-        double incl = wk;
+    if (wave == 0) {
+        double wk[2];
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double up = __shfl_up(incl, o, 64);
-            if ((tid & 63) >= o) incl += up;
+        for (int h = 0; h < 2; ++h) {
+            const int k = 2 * lane + h;
+            wk[h] = pk[h][2] * inv_zp - pk[h][3] * inv_zq;
+            if (s_any && k < nE && s_redo[k]) wk[h] = s_again[k];
         }
-        if (tid == 0) { s_best = 0x7fffffff; s_lastpos = -1; s_cstar = 0x7fffffff; }
-        __syncthreads();                          // s_scan: earlier readers are done
-        if ((tid & 63) == 63) s_scan[tid >> 6] = incl;
-        __syncthreads();
-        double base = 0.0;
-        for (int wvi = 0; wvi < (tid >> 6); ++wvi) base += s_scan[wvi];
-        base += incl - wk;                        // weight in front of chunk tid
-        const bool mine = tid < nE && base + wk > t;
-        if (mine) atomicMin(&s_cstar, tid);
-        if (tid < nE && wk > 0.0) atomicMax(&s_lastpos, tid);
-        __syncthreads();
-        const int cstar = s_cstar;
-        if (cstar == 0x7fffffff) {                // rounding left no crossing: last chunk with weight
-            if (tid == 0) { s_cstar = max(s_lastpos, 0); s_base = -INFINITY; }
-        } else if (tid == cstar) {
-            s_base = base;
+        double incl = wave_prefix_sum_d(wk[0] + wk[1]), mass = lane_value_d(incl, 63);
+        const bool fall = d.have_q && !(mass > 0.0);             // residual mass 0: draw from p itself
+        if (fall) {
+            wk[0] = pk[0][0] * inv_zp;
+            wk[1] = pk[1][0] * inv_zp;
+            incl = wave_prefix_sum_d(wk[0] + wk[1]);
+            mass = 1.0;                                          // sum of a_i / Zp
         }
-        __syncthreads();
-        if (tid == 0) s_lastpos = -1;
+        // first chunk whose inclusive prefix exceeds t
+        const double t = u * mass, base1 = incl - wk[1], base0 = base1 - wk[0];
+        const bool over0 = 2 * lane < nE && base0 + wk[0] > t, over1 = 2 * lane + 1 < nE && base1 + wk[1] > t;
+        const unsigned long long over = __ballot(over0 || over1), held = __ballot(wk[0] > 0.0 || wk[1] > 0.0);
+        const bool crossing = over != 0;
+        // rounding left no crossing: last chunk with weight, whose walk then only looks for its last entry with weight
+        const int pick = crossing ? __ffsll(over) - 1 : (held ? 63 - __clzll(held) : 0);
+        if (lane == pick) {
+            const bool second = crossing ? !over0 : wk[1] > 0.0;
+            s_cstar = 2 * lane + (second ? 1 : 0);
+            s_base = crossing ? (second ? base1 : base0) : -(double)INFINITY;
+            s_target = t;
+            s_fall = fall ? 1 : 0;
+        }
     }
     __syncthreads();
     const int cs = s_cstar;
-    const bool no_crossing = s_base == -INFINITY;  // then the walk only looks for the last entry with weight
+    const bool no_crossing = s_base == -INFINITY, fall_back_to_p = s_fall != 0;
+    const double t = s_target;
     const int f0 = cs * a.chunkE, f1 = min(a.V, f0 + a.chunkE);
-    // walk the chunk in tiles of 256 x kGroup entries, kGroup consecutive entries per thread, carrying the prefix
+    // walk the chunk in tiles of 256 x G entries, G consecutive entries per thread, carrying the prefix
     double before = no_crossing ? 0.0 : s_base;    // weight in front of the current tile
-    int found = 0x7fffffff, lastpos = -1;
-    for (int t0 = f0; t0 < f1; t0 += kThreads * kGroup) {
-        const int g0 = t0 + tid * kGroup;
+    int found = 0x7fffffff, lastpos = -1, turn = 0;
+    for (int t0 = f0; t0 < f1; t0 += kThreads * G, turn ^= 1) {
+        const int g0 = t0 + tid * G;
         const bool active = g0 < f1;              // idle threads re-read the chunk's first group and count nothing
-        const int i0 = active ? g0 : f0, i1 = active ? min(f1, g0 + kGroup) : f0;
-        double wv[kGroup];
+        const int i0 = active ? g0 : f0, i1 = active ? min(f1, g0 + G) : f0;
+        double wv[G];
         double local = 0.0;
-        float lp[kGroup], lq[kGroup];
+        float lp[G], lq[G];
         w.template load_group<VEC>(i0, active ? i1 : f1, lp, lq);
 #pragma unroll
-        for (int j = 0; j < kGroup; ++j) {
+        for (int j = 0; j < G; ++j) {
             double ea, eb, tt;
             w.eval(lp[j], lq[j], &ea, &eb, &tt);
             const double r = ea * inv_zp - eb * inv_zq;
@@ -486,27 +501,21 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
             local += wv[j];
         }
         // exclusive prefix of `local` over threads, in thread order
-        double incl = local;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double up = __shfl_up(incl, o, 64);
-            if ((tid & 63) >= o) incl += up;
-        }
-        __syncthreads();                          // s_scan: the previous tile's readers are done
-        if ((tid & 63) == 63) s_scan[tid >> 6] = incl;
+        const double incl = wave_prefix_sum_d(local);
+        if (lane == 63) s_scan[turn][wave] = incl;  // two sets: the previous tile's may still be read
         __syncthreads();
         double run = before;
-        for (int wvi = 0; wvi < (tid >> 6); ++wvi) run += s_scan[wvi];
+        for (int wvi = 0; wvi < wave; ++wvi) run += s_scan[turn][wvi];
         run += incl - local;
 #pragma unroll
-        for (int j = 0; j < kGroup; ++j) {
+        for (int j = 0; j < G; ++j) {
             if (i0 + j < i1) {
                 if (wv[j] > 0.0) lastpos = i0 + j;
                 run += wv[j];
                 if (!no_crossing && run > t && found == 0x7fffffff) found = i0 + j;
             }
         }
-        before += ((s_scan[0] + s_scan[1]) + s_scan[2]) + s_scan[3];
+        before += ((s_scan[turn][0] + s_scan[turn][1]) + s_scan[turn][2]) + s_scan[turn][3];
     }
     if (found != 0x7fffffff) atomicMin(&s_best, found);
     if (lastpos >= 0) atomicMax(&s_lastpos, lastpos);
@@ -523,23 +532,6 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 }  // namespace
-
-void accept_plan(int rows, int gamma, int n_p_rows, int V, int dtype, bool vec, AcceptArgs *a) {
-    a->rows = rows; a->gamma = gamma; a->n_p_rows = n_p_rows; a->V = V; a->dtype = dtype;
-    const int epl = !vec ? 1 : (dtype == PSD_BF16 ? 8 : 4);
-    const int cap = kThreads * kLoadsPerLane * epl;            // elements one block can hold
-    const int nA = (V + cap - 1) / cap;
-    a->chunkA = round_up((V + nA - 1) / nA, epl);
-    a->n_chunksA = (V + a->chunkA - 1) / a->chunkA;
-    // draw pass: about 512 blocks in all.  Every block repeats the decision of its sequence, so more and smaller
-    // chunks cost more than they spread (64 sequences x 32 000 entries: 4 chunks per sequence 30.7 us, 8 28.0, 16 29.9,
-    // 32 41.7, 63 64.0)
-    long want = ((long)V * (rows > 0 ? rows : 1) + 511) / 512;
-    int ce = round_up((int)(want < 512 ? 512 : (want > 8192 ? 8192 : want)), 256);
-    if ((V + ce - 1) / ce > kMaxChunksE) ce = round_up((V + kMaxChunksE - 1) / kMaxChunksE, 256);
-    a->chunkE = ce;
-    a->n_chunksE = (V + ce - 1) / ce;
-}
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -559,6 +551,49 @@ static WsLayout ws_layout(const AcceptArgs &a) {
 }
 
 size_t accept_workspace_bytes(const AcceptArgs &a) { return ws_layout(a).total; }
+
+// Draw pass chunking.  Every block repeats its sequence's decision and one of them finishes the draw from the chunk sums, so
+// chunks of 4096 entries (a thread takes eight consecutive ones twice), or of 512 (two per thread, once) where that leaves
+// no more than 512 blocks.  From 2048 blocks on, chunks of up to 8192.  That coarser division needs the least
+// workspace: it is also taken where the finer one would not fit the built-in scratch buffer.  Measured (us, draw kernel;
+// the kernel before this one with about 512 blocks in all: 64 sequences x 32 000 entries 25.5, 16 x 152 064 43.0, 1 x
+// 32 000 21.2): chunks of 4096 by eights 22.2 / 30.6, of 2048 by eights 23.9 / 34.6, by fours 24.1 / 33.2, by twos 26.7 /
+// 37.2; one sequence, 512 by twos 11.7.
+static void accept_draw_chunks(AcceptArgs *a, bool coarse) {
+    const long rows = a->rows > 0 ? a->rows : 1;
+    const int V = a->V;
+    a->groupE = kMaxGroup;
+    int ce = 4096;
+    if (V <= 512 * kMaxChunksE && rows * ((V + 511) / 512) <= 512) {
+        a->groupE = 2;
+        ce = 512;
+    } else if (rows * ((V + ce - 1) / ce) > 2048) {
+        coarse = true;
+    }
+    if (coarse) {
+        const long want = ((long)V * rows + 511) / 512;
+        a->groupE = kMaxGroup;
+        ce = round_up((int)(want < 512 ? 512 : (want > 8192 ? 8192 : want)), 256);
+    }
+    if ((V + ce - 1) / ce > kMaxChunksE) ce = round_up((V + kMaxChunksE - 1) / kMaxChunksE, 256);
+    a->chunkE = ce;
+    a->n_chunksE = (V + ce - 1) / ce;
+}
+
+void accept_plan(int rows, int gamma, int n_p_rows, int V, int dtype, bool vec, AcceptArgs *a) {
+    a->rows = rows; a->gamma = gamma; a->n_p_rows = n_p_rows; a->V = V; a->dtype = dtype;
+    // the division of the draw is that of the plan that needs the most workspace (unaligned rows), whatever these rows are
+    const int nU = (V + kThreads * kLoadsPerLane - 1) / (kThreads * kLoadsPerLane);
+    a->chunkA = (V + nU - 1) / nU;
+    a->n_chunksA = (V + a->chunkA - 1) / a->chunkA;
+    accept_draw_chunks(a, false);
+    if (accept_workspace_bytes(*a) > PSD_STATIC_SCRATCH_BYTES) accept_draw_chunks(a, true);
+    const int epl = !vec ? 1 : (dtype == PSD_BF16 ? 8 : 4);
+    const int cap = kThreads * kLoadsPerLane * epl;            // elements one block can hold
+    const int nA = (V + cap - 1) / cap;
+    a->chunkA = round_up((V + nA - 1) / nA, epl);
+    a->n_chunksA = (V + a->chunkA - 1) / a->chunkA;
+}
 
 void accept_bind_workspace(AcceptArgs *a, void *ws, int32_t *out_flags) {
     const WsLayout l = ws_layout(*a);
@@ -581,8 +616,9 @@ static void launch_accept_t(const AcceptArgs &a, bool vec_ok, hipStream_t stream
     }
     dim3 gridE((unsigned)a.rows * a.n_chunksE);
     ScopedProf sp(PSD_KIND_ACCEPT_DRAW, stream);
-    if (vec_ok) launch_kernel(accept_draw_kernel<T, true>, gridE, kThreads, 0, stream, a);
-    else launch_kernel(accept_draw_kernel<T, false>, gridE, kThreads, 0, stream, a);
+    auto go = [&](auto kernel) { launch_kernel(kernel, gridE, kThreads, 0, stream, a); };
+    if (a.groupE == 2) { if (vec_ok) go(accept_draw_kernel<T, true, 2>); else go(accept_draw_kernel<T, false, 2>); }
+    else { if (vec_ok) go(accept_draw_kernel<T, true, kMaxGroup>); else go(accept_draw_kernel<T, false, kMaxGroup>); }
 }
 
 void launch_accept(const AcceptArgs &a, bool vec_ok, hipStream_t stream) {

@@ -88,4 +88,32 @@ __device__ __forceinline__ T wave_sum(T v) {
     return v;
 }
 
+// fp64 wavefront reductions on the vector ALU's own lane moves (about a tenth of the latency of a trip through the LDS
+// crossbar per step).  Inclusive prefix over the lanes in a fixed order: rows of 16 first, then across rows; lanes that a
+// move does not reach get `none`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_move(double v, double none) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, v), o = __builtin_bit_cast(uint64_t, none);
+    const uint32_t lo = __builtin_amdgcn_update_dpp((int)(uint32_t)o, (int)(uint32_t)x, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(o >> 32), (int)(uint32_t)(x >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <typename F>
+__device__ __forceinline__ double wave_scan_d(double v, double none, F op) {
+    v = op(v, lane_move<0x111, 0xf>(v, none));             // row_shr:1, 2, 4, 8
+    v = op(v, lane_move<0x112, 0xf>(v, none));
+    v = op(v, lane_move<0x114, 0xf>(v, none));
+    v = op(v, lane_move<0x118, 0xf>(v, none));
+    v = op(v, lane_move<0x142, 0xa>(v, none));             // row_bcast:15 into rows 1 and 3
+    v = op(v, lane_move<0x143, 0xc>(v, none));             // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ __forceinline__ double lane_value_d(double v, int lane) {        // the same lane for the whole wavefront
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)x, lane), hi = __builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_prefix_sum_d(double v) { return wave_scan_d(v, 0.0, [](double a, double b) { return a + b; }); }
+__device__ __forceinline__ double wave_total_d(double v) { return lane_value_d(wave_prefix_sum_d(v), 63); }
+
 }  // namespace psd

@@ -18,6 +18,7 @@ struct AcceptArgs {
     float temperature;
     int chunkA, n_chunksA;        // statistics pass: elements per block, blocks per logits row
     int chunkE, n_chunksE;        // draw pass chunking
+    int groupE;                   // consecutive entries per thread of it
     float2 *stats;                // [rows][n_p_rows+gamma][n_chunksA] (max raw logit, sum exp)
     float *xlogit;                // [rows][gamma][2] the draft token's logit under p and under q
     double *part;                 // [rows][n_chunksE][6] fp64 chunk sums of the draw position (accept.hip)

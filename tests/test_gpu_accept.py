@@ -61,6 +61,15 @@ def test_small_shapes(rows, gamma, V, dtype, bonus):
     assert np.all(tok[n < gamma] >= 0)
 
 
+@pytest.mark.parametrize("rows,gamma,V,dtype", [
+    (1, 3, 512, torch.float32), (1, 3, 65536, torch.bfloat16), (1, 3, 65537, torch.float32), (60, 2, 4097, torch.float32),
+    (130, 1, 4096, torch.bfloat16), (1, 2, 524289, torch.float32), (2, 5, 152065, torch.bfloat16)])
+def test_draw_chunk_edges(rows, gamma, V, dtype):
+    """The draw's division of the vocabulary: 512-entry chunks up to 128 of them, 4096-entry chunks at both sides of one,
+    more than 128 chunks (larger ones), and more per-chunk statistics than eight lanes take in one round."""
+    _compare(synth.make_accept_inputs(rows, gamma, V, seed=V + rows, n_p_rows=gamma + 1, dtype=dtype))
+
+
 def test_workload2_full_size():
     """64 rows x gamma 8 x vocab 32000 bf16, the isolated acceptance workload, with and
     without the bonus row; mean accepted length lands near the 3.37 expected at alpha ~ 0.80."""
