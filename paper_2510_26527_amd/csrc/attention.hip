@@ -72,7 +72,6 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(AttnArgs a, float scale
     }
 }
 
-constexpr int kKeysPerWaveIter = 64;
 constexpr int kKeysPerBlockIter = 256;
 
 // Sum over the S split-K slots (sstride floats apart) of NI pairs (src[it][0], src[it][second]) per thread.  The
@@ -118,8 +117,8 @@ __device__ __forceinline__ void sum_pairs_n(int ni, const float *const *src, siz
 // Every block does that for its own query rows; the blocks of the last split also build the step's new keys and
 // values (<= 32 rows), keep them in LDS as one more 32-key tile, and the one with query chunk 0 appends them to
 // the cache.  Cache reads then stop at the old length, so no block reads what another one is writing.
-template <int DH, int QT, bool FUSED>
-__global__ __launch_bounds__(256) void attn_mfma_kernel(AttnArgs a, float scale_log2, int range) {
+template <int DH, int QT, bool FUSED, int NSUB = 2>
+__global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnArgs a, float scale_log2, int range) {
     constexpr int KS = DH / 32;      // MFMA k-steps of S^T = K Q^T
     constexpr int DT = DH / 16;      // 16-row d tiles of O^T
     constexpr int HALF = DH / 2;
@@ -149,11 +148,11 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(AttnArgs a, float scale_
     __shared__ float s_scale[32];
     // the first 64-key tile of this wavefront is requested before anything else: its trip to HBM overlaps the
     // operand build below
-    bf16x8 ka[2][2][KS];
-    bf16x8 va[2][DT];
+    bf16x8 ka[NSUB][2][KS];
+    bf16x8 va[NSUB][DT];
     auto load_tile = [&](int kt) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
+        for (int sub = 0; sub < NSUB; ++sub) {
             // a half that starts at or beyond kb1 is fully masked; clamp its address into the tile's first half
             const int kb = (kt + sub * 32 < kb1) ? kt + sub * 32 : kt;
             // K rows of the two 16-key score tiles: row i of tile t is key kb + 8*(i/4) + 4*t + i%4
@@ -175,8 +174,8 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(AttnArgs a, float scale_
     // The wavefront's first K / V^T tile is requested ahead of the loop, so that it streams in while the operands are
     // built; but behind the loads the build waits for (returns are in order, and all blocks' tiles together are the
     // kernel's whole traffic: requested first, they would hold the build up for the time the cache takes to arrive).
-    constexpr bool HOIST = QT == 1;            // two query tiles leave no registers to hold a tile across the build
-    const int kt_first = kb0 + wave * kKeysPerWaveIter;
+    constexpr bool HOIST = QT == 1 && NSUB == 2; // two query tiles, or two blocks per CU, leave no registers to hold a tile across the build
+    const int kt_first = kb0 + wave * (32 * NSUB);
     auto hoisted_tile = [&]() {
         if (HOIST && kt_first < kb1) load_tile(kt_first);
     };
@@ -452,10 +451,10 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(AttnArgs a, float scale_
                 o[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[dt], pl[qt], o[qt][dt], 0, 0, 0);
     };
 
-    for (int kt = kt_first; kt < kb1; kt += kKeysPerBlockIter) {
+    for (int kt = kt_first; kt < kb1; kt += 128 * NSUB) {
         if (!HOIST || kt != kt_first) load_tile(kt); // every K and V^T load of the tile before its first MFMA
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
+        for (int sub = 0; sub < NSUB; ++sub) {
             const int kb = kt + sub * 32;
             if (kb >= kb1) break;
             consume(std::false_type{}, kb, n_keys, ka[sub], va[sub]);
@@ -847,6 +846,19 @@ bool attn_fuses_rope(int dtype, int R, int h_q, int h_kv, int d_h, bool tree) {
     return dtype == PSD_BF16 && (d_h == 64 || d_h == 128) && R <= 32 && !use_wide((h_q / h_kv) * R, tree);
 }
 
+// The direct kernel comes in two builds: one block per CU whose wavefronts hold a 64-key tile across the operand build, or
+// two blocks per CU with 32-key tiles, which overlap each other's build, loads and merge.  The second pays once 256-key
+// splits make more blocks than there are CUs (a block then walks several tiles, one trip to memory each).  Measured per
+// layer with the combine (us, first / second): LLaMA2-7B shape, five ragged sequences of up to 1024 keys x 9 rows 39.9 /
+// 30.1, one sequence of 4000 keys x 8 rows 30.5 / 28.7, of 1024 keys 18.9 / 23.0; LLaMA3-8B shape, eight sequences of 2000
+// keys x 2 rows 32.8 / 27.4.  In the second, holding a tile across the build (29.2) or keeping the next one in flight
+// (34.9) costs more in spilled registers than it hides (26.0 without the combine).
+static bool direct_pairs(int dtype, int B, int R, int h_q, int h_kv, int d_h, int len_bound, bool tree) {
+    const int NQ = (h_q / h_kv) * R, cached = len_bound - R > 1 ? len_bound - R : 1;
+    return attn_fuses_rope(dtype, R, h_q, h_kv, d_h, tree) && q_tiles(NQ) == 1 &&
+           (long)B * h_kv * ((cached + kKeysPerBlockIter - 1) / kKeysPerBlockIter + 1) > 256;
+}
+
 int attn_pick_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int len_bound, bool tree) {
     if (dtype != PSD_BF16) return 1;
     const int NQ = (h_q / h_kv) * R;
@@ -866,9 +878,15 @@ int attn_pick_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int le
         // of 128 keys 17.9; 9 splits 24.5 (every block repeats the operand build, and only one block is resident
         // per CU, so a 257th block waits for a whole block's lifetime).
         const int cached = len_bound - R > 1 ? len_bound - R : 1;
-        int old_splits = (cached + kKeysPerBlockIter - 1) / kKeysPerBlockIter;
+        const bool pairs = direct_pairs(dtype, B, R, h_q, h_kv, d_h, len_bound, tree);
+        const int step = pairs ? 128 : 256;
+        if (pairs) by_grid = 512 / (B * h_kv * chunks);
+        int old_splits = (cached + step - 1) / step;
         if (old_splits > by_grid - 1) old_splits = by_grid - 1;
-        return old_splits < 1 ? 1 : old_splits + 1;
+        if (old_splits < 1) return 1;
+        if (!pairs) return old_splits + 1;
+        const int range = ((cached + old_splits - 1) / old_splits + step - 1) / step * step;   // whole steps per block
+        return (cached + range - 1) / range + 1;
     }
     const int by_len = (len_bound + kKeysPerBlockIter - 1) / kKeysPerBlockIter;
     int s = by_len < by_grid ? by_len : by_grid;
@@ -883,12 +901,14 @@ static void launch_mfma(const AttnArgs &a, hipStream_t stream) {
     const bool wide = use_wide(NQ, a.tree_anc != nullptr);
     // keys per split; the kernel that builds its own operands reads only the keys already in the cache and leaves its
     // last split (if it has several) to the step's own rows
+    const bool pairs = direct_pairs(PSD_BF16, a.B, a.R, a.h_q, a.h_kv, DH, a.len_bound, a.tree_anc != nullptr);
     int range = (a.len_bound + a.splits - 1) / a.splits;
     if (!wide && a.qkv_partial && a.splits > 1) {
         const int cached = a.len_bound - a.R > 1 ? a.len_bound - a.R : 1;
         range = (cached + a.splits - 2) / (a.splits - 1);
+        if (pairs) range = (range + 127) / 128 * 128;
     }
-    range = (range + kKeysPerWaveIter - 1) / kKeysPerWaveIter * kKeysPerWaveIter;
+    range = (range + 63) / 64 * 64;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
     if (wide) {
         const int rows = wide_rows(NQ);
@@ -918,7 +938,8 @@ static void launch_mfma(const AttnArgs &a, hipStream_t stream) {
     {
     ScopedProf sp(PSD_KIND_ATTN, stream);
     if (a.qkv_partial) {
-        if (QT == 1) launch_kernel(attn_mfma_kernel<DH, 1, true>, grid, 256, 0, stream, a, scale_log2, range);
+        if (pairs) launch_kernel(attn_mfma_kernel<DH, 1, true, 1>, grid, 256, 0, stream, a, scale_log2, range);
+        else if (QT == 1) launch_kernel(attn_mfma_kernel<DH, 1, true>, grid, 256, 0, stream, a, scale_log2, range);
         else launch_kernel(attn_mfma_kernel<DH, 2, true>, grid, 256, 0, stream, a, scale_log2, range);
     } else {
         if (QT == 1) launch_kernel(attn_mfma_kernel<DH, 1, false>, grid, 256, 0, stream, a, scale_log2, range);

@@ -164,6 +164,19 @@ def test_tiled_projections_at_tile_edges(rows, w4):
     p.close()
 
 
+@pytest.mark.parametrize("d_head,batch,ctx,rows", [(128, 40, 300, 3), (64, 40, 300, 10), (128, 24, 700, 1), (64, 130, 70, 2)])
+def test_attention_of_many_sequences(d_head, batch, ctx, rows):
+    """More 256-key splits than CUs: the build of the direct attention kernel that runs two blocks per CU on 32-key
+    tiles, with ragged lengths (from one key on), several splits and, at 130 x 4 heads, a single one."""
+    shape = synth.Shape(1, 256, 4, 4, d_head, 256, 600, 1.0e4)
+    lens = [1 + (ctx - 1) * ((7 * b) % batch) // batch for b in range(batch - 1)] + [ctx]
+    p = Pair(shape, torch.bfloat16, batch, (ctx + 2 * rows + 63) // 64 * 64, seed=batch, ctx=ctx, lens=lens, std=0.05)
+    toks = synth.make_tokens(shape.vocab, (batch, 2 * rows), 5)
+    p.step(toks[:, :rows], what="first step")
+    p.step(toks[:, rows:], what="second step")
+    p.close()
+
+
 def test_bf16_batch_ragged_lengths_truncate():
     shape = SMALL_GQA
     p = Pair(shape, torch.bfloat16, 4, 640, seed=21, ctx=512, lens=[512, 100, 333, 1], std=0.05, pack=True)
