@@ -339,7 +339,7 @@ void plan_layout(const psd_model *mdl, int batch, int n_new, int len_bound, bool
     p.off_po = take(p.attn_splits > 1 ? (size_t)M * d.n_q_heads * p.attn_splits * d.d_head * 4 : 0);
     p.off_pml = take(p.attn_splits > 1 ? (size_t)M * d.n_q_heads * p.attn_splits * 2 * 4 : 0);
     p.off_sumsq = take(p.folded ? (size_t)(d.d_model / 16) * M * 4 : 0);
-    p.off_rope = take(p.fused_rope ? (size_t)M * (d.d_head / 2) * sizeof(float2) : 0);
+    p.off_rope = take(d.dtype == PSD_BF16 ? (size_t)M * (d.d_head / 2) * sizeof(float2) : 0);
     p.off_tilectr = take(p.folded ? (size_t)gemm_pack_tiles(n_o, 1) * 4 : 0);
     p.off_tree = take(p.fused_rope ? (size_t)kTreeMaxNodes * 8 : 0);      // ancestor masks and depths of a tree pass
     p.total = off;
@@ -488,7 +488,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         }
     };
     RopeTable rt{};
-    if (p.fused_rope) rt = RopeTable{(float2 *)(ws + p.off_rope), kv->lens, n_new, d.d_head, d.rope_theta, nullptr};
+    if (d.dtype == PSD_BF16) rt = RopeTable{(float2 *)(ws + p.off_rope), kv->lens, n_new, d.d_head, d.rope_theta, nullptr};
     const uint32_t *tree_anc = nullptr;
     if (tree) {
         // a token tree: positions by depth, visibility by ancestry (both only exist in the fused attention build)
@@ -508,7 +508,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         char *kl = (char *)kv->k + (size_t)l * kv_layer, *vl = (char *)kv->v + (size_t)l * kv_layer;
         if (!p.fused_rope)
             launch_reduce_rope_append(d.dtype, partial, p.sk_qkv, rs, q, kl, vl, kv->lens, B, n_new, d.n_q_heads,
-                                      d.n_kv_heads, d.d_head, kv->max_len, d.rope_theta, st);
+                                      d.n_kv_heads, d.d_head, kv->max_len, d.rope_theta, rt.cs, st);
         AttnArgs a{};
         if (p.fused_rope) { a.qkv_partial = partial; a.qkv_splits = p.sk_qkv; a.rs = rs; a.rope_cs = rt.cs; a.tree_anc = tree_anc; }
         a.q = q; a.k = kl; a.v = vl; a.lens = kv->lens; a.out = attn; a.out16 = attn16;

@@ -186,10 +186,10 @@ void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, floa
                        float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, ZeroFill zf,
                        hipStream_t stream);
 // qkv = sum over splits of partial [S][M][(h_q+2h_kv) d_h] -> rotated q (fp32), rotated k and v appended
-// to the cache (model dtype)
+// to the cache (model dtype); cs_table: RopeTable::cs of these rows, NULL: the angles are evaluated again
 void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale rs, float *q_out, void *k_cache,
                                void *v_cache, const int32_t *lens, int B, int R, int h_q, int h_kv, int d_h,
-                               int max_len, float theta, hipStream_t stream);
+                               int max_len, float theta, const float2 *cs_table, hipStream_t stream);
 // x += sum over splits of partial [S][M][d]; xn = rmsnorm(x) * gain (xn16, if given: the same rounded to fp16)
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
                                  int M, int d, float eps, uint16_t *xn16, hipStream_t stream);
