@@ -471,7 +471,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     if (p.folded) rs.sumsq = sumsq;
     const float *act = xn;     // what QKV / gate|up / lm_head read: rmsnorm(x) * gain, or x * gain when folded
     auto resid_gemm = [&](const float *xin, int K, const void *w, int sk, const void *wpack, const void *next_gain,
-                          bool by_units, int ql, int qj) {
+                          bool by_units, int ql, int qj, bool last = false) {
         if (p.folded) {
             GemmArgs g{};
             g.wpack = wpack; g.x = xin; g.x_rows_per_group = M; g.w[0] = w; g.n[0] = d.d_model; g.nseg = 1;
@@ -484,7 +484,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
             rs.tiles = slots ? g.pack_tiles : col_tiles;
         } else {
             gemm(xin, M, K, w, d.d_model, nullptr, 0, nullptr, 0, sk, partial, wpack, ql, qj);
-            launch_reduce_residual_norm(d.dtype, partial, sk, x, next_gain, xn, M, d.d_model, d.rms_eps, xn16, st);
+            launch_reduce_residual_norm(d.dtype, partial, sk, x, next_gain, p.half_copies && !last ? nullptr : xn, M, d.d_model, d.rms_eps, xn16, st);
         }
     };
     RopeTable rt{};
@@ -511,7 +511,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
                                       d.n_kv_heads, d.d_head, kv->max_len, d.rope_theta, rt.cs, st);
         AttnArgs a{};
         if (p.fused_rope) { a.qkv_partial = partial; a.qkv_splits = p.sk_qkv; a.rs = rs; a.rope_cs = rt.cs; a.tree_anc = tree_anc; }
-        a.q = q; a.k = kl; a.v = vl; a.lens = kv->lens; a.out = attn; a.out16 = attn16;
+        a.q = q; a.k = kl; a.v = vl; a.lens = kv->lens; a.out = p.half_copies ? nullptr : attn; a.out16 = attn16;   // the O projection reads one of the two
         a.B = B; a.R = n_new; a.h_q = d.n_q_heads; a.h_kv = d.n_kv_heads; a.d_h = d.d_head; a.max_len = kv->max_len;
         a.len_bound = len_bound; a.part_o = (float *)(ws + p.off_po); a.part_ml = (float *)(ws + p.off_pml);
         a.splits = p.attn_splits;
@@ -520,8 +520,8 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         resid_gemm(attn, hd, m->layer(l, W_O), p.sk_o, m->pack(l, P_O), m->layer(l, W_FFN_NORM), false, l, 3);
         gemm(act, M, d.d_model, m->layer(l, W_GATE), d.d_ffn, m->layer(l, W_UP), d.d_ffn, nullptr, 0, p.sk_gu,
              p.gated ? nullptr : partial, m->pack(l, P_GU), l, 4);
-        if (!p.gated) launch_reduce_swiglu(partial, p.sk_gu, rs, h, M, d.d_ffn, h16, st);
-        resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), true, l, 6);
+        if (!p.gated) launch_reduce_swiglu(partial, p.sk_gu, rs, p.half_copies ? nullptr : h, M, d.d_ffn, h16, st);
+        resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), true, l, 6, l + 1 == d.n_layers);
     }
     if (n_logit_rows > 0) {
         // lm_head on the last n_logit_rows rows of every sequence (unfolded: xn already holds the final norm)

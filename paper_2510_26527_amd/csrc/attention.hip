@@ -552,7 +552,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
         for (int sl = 0; sl < NSLAB; ++sl) acc += sm_o[sl][qc][d] * s_f[sl][qc];
         if (a.splits == 1) {
             const float L = s_L[qc];
-            a.out[row * DH + d] = acc / L;
+            if (a.out) a.out[row * DH + d] = acc / L;
             if (a.out16) a.out16[row * DH + d] = f32_to_f16_bits(acc / L);
         } else {
             a.part_o[(row * a.splits + split) * DH + d] = acc;
@@ -791,7 +791,7 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_wide_kernel(AttnArgs a, flo
             for (int dt = 0; dt < DT; ++dt)
             {
                 const f32x4 r = o[qt][dt] * inv;
-                *reinterpret_cast<f32x4 *>(a.out + out_row[qt] * DH + dt * 16 + 4 * g) = r;
+                if (a.out) *reinterpret_cast<f32x4 *>(a.out + out_row[qt] * DH + dt * 16 + 4 * g) = r;
                 if (a.out16)
                     *reinterpret_cast<uint2 *>(a.out16 + out_row[qt] * DH + dt * 16 + 4 * g) =
                         make_uint2(f32_to_f16_bits(r[0]) | ((uint32_t)f32_to_f16_bits(r[1]) << 16),
@@ -824,7 +824,7 @@ __global__ void attn_combine_kernel(AttnArgs a) {
         L += ml[2 * s + 1] * f;
         acc += a.part_o[(row * a.splits + s) * DH + d] * f;
     }
-    a.out[row * DH + d] = acc / L;
+    if (a.out) a.out[row * DH + d] = acc / L;
     if (a.out16) a.out16[row * DH + d] = f32_to_f16_bits(acc / L);
 }
 

@@ -116,8 +116,8 @@ struct AttnArgs {
     const void *k;                // this layer's K cache [B][h_kv][max_len][d_h]
     const void *v;                // this layer's V cache [B][h_kv][d_h][max_len]
     const int32_t *lens;          // [B] valid positions BEFORE this forward
-    float *out;                   // [B][R][h_q*d_h] fp32
-    uint16_t *out16;              // optional copy of `out` rounded to fp16 (the operand of the tiled O projection)
+    float *out;                   // [B][R][h_q*d_h] fp32; NULL where only the next one is read
+    uint16_t *out16;              // optional: the same rounded to fp16 (the operand of the tiled and the 4-bit O projection)
     int B, R, h_q, h_kv, d_h, max_len;
     int len_bound;                // host upper bound of lens[b] + R
     float *part_o;                // split scratch [B][h_q][R][splits][d_h]
@@ -190,10 +190,10 @@ void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, floa
 void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale rs, float *q_out, void *k_cache,
                                void *v_cache, const int32_t *lens, int B, int R, int h_q, int h_kv, int d_h,
                                int max_len, float theta, const float2 *cs_table, hipStream_t stream);
-// x += sum over splits of partial [S][M][d]; xn = rmsnorm(x) * gain (xn16, if given: the same rounded to fp16)
+// x += sum over splits of partial [S][M][d]; xn = rmsnorm(x) * gain (xn16, if given: the same rounded to fp16, and xn may be NULL)
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
                                  int M, int d, float eps, uint16_t *xn16, hipStream_t stream);
-// h = silu(g) * u with [g | u] = sum over splits of partial [S][M][2f]
+// h (may be NULL beside h16) = silu(g) * u with [g | u] = sum over splits of partial [S][M][2f]
 void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, hipStream_t stream);
 void launch_advance_lens(int32_t *lens, int B, int delta, int max_len, hipStream_t stream);
 void launch_truncate(int32_t *lens, const int32_t *base, const int32_t *keep, int offset, int cap, int B,

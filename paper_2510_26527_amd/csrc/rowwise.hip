@@ -10,15 +10,18 @@
 namespace psd {
 namespace {
 
-constexpr int kRowThreads = 256;
-constexpr int kMaxV4 = 8;              // float4 per thread kept in registers: rows up to 8192 wide
+constexpr int kMaxRowV4 = 2048;        // float4 per row kept in registers: rows up to 8192 wide
 
-// fixed-order block sum: butterfly inside each wavefront, then the four totals left to right
+// fixed-order block sum: butterfly inside each wavefront, then the wavefronts' totals left to right
+template <int NT = 256>
 __device__ __forceinline__ float block_sum4(float v, float *red) {
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    return ((red[0] + red[1]) + red[2]) + red[3];
+    float t = red[0];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) t += red[w];
+    return t;
 }
 
 __device__ __forceinline__ f32x4 load_gain4(const float *g, int i4) { return reinterpret_cast<const f32x4 *>(g)[i4]; }
@@ -32,14 +35,17 @@ __device__ __forceinline__ f32x4 load_row4(const uint16_t *row, int i4) { return
 
 // One block per row: x (+)= source, then xn = x * rsqrt(mean(x^2) + eps) * gain.  The source is either
 // an embedding row (EMBED) or the split-K partial sums of the projection that feeds the residual
-// stream, added in split order.  All loads of a row are issued before the first use.
-template <typename TW, bool EMBED>
+// stream, added in split order.  All loads of a row are issued before the first use.  xn NULL: only the fp16 copy is read.
+// A row is one block, so few rows leave most CUs idle and the block's own loads in flight set the time: 1024 threads
+// then hold a whole row of a split at once (45 rows x 4096, 8 splits: 9.6 us with 256 threads, 5.2; 256 rows x 3584: 10.1, 7.0).
+template <typename TW, bool EMBED, int kRowThreads>
 __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *embed, const int32_t *tokens, int vocab,
                                                                     const float *partial, int S, size_t split_stride,
                                                                     float *x, const TW *gain, float *xn, float *sumsq_out,
                                                                     int d, float eps, RopeTable rt, uint16_t *xn16,
                                                                     ZeroFill zf) {
-    __shared__ float red[4];
+    constexpr int kMaxV4 = kMaxRowV4 / kRowThreads;
+    __shared__ float red[kRowThreads / 64];
     const int m = blockIdx.x, tid = threadIdx.x, n4 = d >> 2;
     if constexpr (EMBED) {
         // counters that later kernels of this forward pass expect at zero
@@ -111,7 +117,7 @@ __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *em
             ss += a[0] * a[0] + a[1] * a[1] + a[2] * a[2] + a[3] * a[3];
         }
     }
-    const float tot = block_sum4(ss, red);
+    const float tot = block_sum4<kRowThreads>(ss, red);
     float scale = 1.0f / sqrtf(tot / (float)d + eps);
     if (sumsq_out) {                       // the norm scale is applied by the consumer of the next projection
         if (tid == 0) sumsq_out[m] = tot;
@@ -123,7 +129,7 @@ __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *em
         const int i4 = tid + j * kRowThreads;
         if (i4 < n4) {
             const f32x4 r = v[j] * scale * load_gain4(gain, i4);
-            orow[i4] = r;
+            if (xn) orow[i4] = r;
             if (xn16)              // the same row rounded to fp16: the operand of the tiled projections
                 reinterpret_cast<uint2 *>(xn16 + (size_t)m * d)[i4] =
                     make_uint2(f32_to_f16_bits(r[0]) | ((uint32_t)f32_to_f16_bits(r[1]) << 16),
@@ -279,7 +285,7 @@ __global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float *partial
     f32x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
-    reinterpret_cast<f32x4 *>(h + (size_t)m * f)[j4] = o;
+    if (h) reinterpret_cast<f32x4 *>(h + (size_t)m * f)[j4] = o;
     if (h16)
         reinterpret_cast<uint2 *>(h16 + (size_t)m * f)[j4] =
             make_uint2(f32_to_f16_bits(o[0]) | ((uint32_t)f32_to_f16_bits(o[1]) << 16),
@@ -308,22 +314,25 @@ void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, floa
                        hipStream_t stream) {
     ScopedProf sp(PSD_KIND_EMBED, stream);
     if (dtype == PSD_BF16)
-        launch_kernel(residual_norm_kernel<uint16_t, true>, M, kRowThreads, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0,
+        launch_kernel(residual_norm_kernel<uint16_t, true, 256>, M, 256, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0,
                                                                            x, (const uint16_t *)gain, xn, sumsq_out, d, eps, rt, xn16, zf);
     else
-        launch_kernel(residual_norm_kernel<float, true>, M, kRowThreads, 0, stream, (const float *)embed, tokens, vocab, nullptr, 0, 0, x,
+        launch_kernel(residual_norm_kernel<float, true, 256>, M, 256, 0, stream, (const float *)embed, tokens, vocab, nullptr, 0, 0, x,
                                                                         (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, zf);
 }
 
+constexpr int kWideRowMax = 256;       // rows up to which a norm block has 1024 threads
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
                                  int M, int d, float eps, uint16_t *xn16, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_RMSNORM, stream);
     const size_t stride = (size_t)M * d;
     if (dtype == PSD_BF16)
-        launch_kernel(residual_norm_kernel<uint16_t, false>, M, kRowThreads, 0, stream, nullptr, nullptr, 0, partial, S, stride, x,
-                                                                            (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{});
+        (M <= kWideRowMax ? launch_kernel(residual_norm_kernel<uint16_t, false, 1024>, M, 1024, 0, stream, nullptr, nullptr, 0, partial, S,
+                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{})
+                          : launch_kernel(residual_norm_kernel<uint16_t, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S,
+                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}));
     else
-        launch_kernel(residual_norm_kernel<float, false>, M, kRowThreads, 0, stream, nullptr, nullptr, 0, partial, S, stride, x,
+        launch_kernel(residual_norm_kernel<float, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S, stride, x,
                                                                          (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{});
 }
 
