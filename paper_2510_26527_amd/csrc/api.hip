@@ -317,13 +317,15 @@ size_t head_partial_bytes(const psd_model *mdl, int Ml, bool folded, int *slots)
 }
 
 // ... and the rest: attention splits, where everything lies in the workspace
-void plan_layout(const psd_model *mdl, int batch, int n_new, int len_bound, bool tree, size_t head_bytes, ForwardPlan *out) {
+void plan_layout(const psd_model *mdl, int batch, int n_new, int len_bound, bool tree, size_t head_bytes, ForwardPlan *out,
+                 bool any_len = false) {
     const psd_model_desc &d = mdl->d;
     ForwardPlan &p = *out;
     const int M = p.M, hd = d.n_q_heads * d.d_head;
     const int n_o[1] = {d.d_model};
     p.fused_rope = attn_fuses_rope(d.dtype, n_new, d.n_q_heads, d.n_kv_heads, d.d_head, tree);
-    p.attn_splits = attn_pick_splits(d.dtype, batch, n_new, d.n_q_heads, d.n_kv_heads, d.d_head, len_bound, tree);
+    p.attn_splits = (any_len ? attn_max_splits : attn_pick_splits)(d.dtype, batch, n_new, d.n_q_heads, d.n_kv_heads, d.d_head,
+                                                                   len_bound, tree);
     const size_t act = 4;                                    // activations are fp32 for both dtypes
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
@@ -341,7 +343,7 @@ void plan_layout(const psd_model *mdl, int batch, int n_new, int len_bound, bool
     p.off_sumsq = take(p.folded ? (size_t)(d.d_model / 16) * M * 4 : 0);
     p.off_rope = take(d.dtype == PSD_BF16 ? (size_t)M * (d.d_head / 2) * sizeof(float2) : 0);
     p.off_tilectr = take(p.folded ? (size_t)gemm_pack_tiles(n_o, 1) * 4 : 0);
-    p.off_tree = take(p.fused_rope ? (size_t)kTreeMaxNodes * 8 : 0);      // ancestor masks and depths of a tree pass
+    p.off_tree = take(p.fused_rope ? (size_t)kTreeMaxNodes * 4 : 0);      // ancestor masks of a tree pass
     p.total = off;
 }
 
@@ -351,8 +353,8 @@ ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit
     return p;
 }
 
-// the largest head_partial_bytes over every number of logit rows (0 .. n_new per sequence).  Up to kStreamMaxRows rows, and
-// from there to 128, the number of slots is one and the same, so the largest count has the most; above, it does not grow
+// the largest head_partial_bytes over every number of logit rows (0 .. n_new per sequence).  Below kPairRows
+// rows, from there to kStreamMaxRows and from there to 128, the slots are one and the same, so the largest count has the most; above, it does not grow
 // with the rows as long as they fill the same number of 256-row tiles, so a run of them that starts at one slot is done.
 size_t worst_head_partial_bytes(const psd_model *mdl, int batch, int n_new, bool folded) {
     size_t worst = 0;
@@ -361,7 +363,7 @@ size_t worst_head_partial_bytes(const psd_model *mdl, int batch, int n_new, bool
         const size_t b = head_partial_bytes(mdl, Ml, folded, slots);
         worst = b > worst ? b : worst;
     };
-    for (int edge : {kStreamMaxRows, 128}) {
+    for (int edge : {kPairRows - 1, kStreamMaxRows, 128}) {
         const int Ml = (M < edge ? M : edge) / batch * batch;
         if (Ml > 0) at(Ml, nullptr);
     }
@@ -393,11 +395,10 @@ size_t psd_model_workspace_bytes(const psd_model *m, int32_t batch, int32_t n_ne
     ForwardPlan p = plan_projections(m, batch * n_new);
     const size_t head = worst_head_partial_bytes(m, batch, n_new, p.folded);
     size_t worst = 0;
-    for (int tree = 0; tree < 2; ++tree)
-        for (int len : {max_len, n_new}) {
-            plan_layout(m, batch, n_new, len, tree != 0, head, &p);
-            worst = p.total > worst ? p.total : worst;
-        }
+    for (int tree = 0; tree < 2; ++tree) {
+        plan_layout(m, batch, n_new, max_len, tree != 0, head, &p, true);
+        worst = p.total > worst ? p.total : worst;
+    }
     return worst;
 }
 
@@ -488,19 +489,16 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         }
     };
     RopeTable rt{};
-    if (d.dtype == PSD_BF16) rt = RopeTable{(float2 *)(ws + p.off_rope), kv->lens, n_new, d.d_head, d.rope_theta, nullptr};
+    if (d.dtype == PSD_BF16) rt = RopeTable{(float2 *)(ws + p.off_rope), kv->lens, n_new, d.d_head, d.rope_theta};
     const uint32_t *tree_anc = nullptr;
     if (tree) {
         // a token tree: positions by depth, visibility by ancestry (both only exist in the fused attention build)
         if (!p.fused_rope) return PSD_ERR_UNIMPLEMENTED;
-        uint32_t *anc = (uint32_t *)(ws + p.off_tree);
-        int32_t *depth = (int32_t *)(anc + kTreeMaxNodes);
-        launch_tree_setup(*tree, anc, depth, st);
-        rt.depth = depth;
-        tree_anc = anc;
+        tree_anc = (const uint32_t *)(ws + p.off_tree);      // written by the embedding kernel
     }
     launch_embed_norm(d.dtype, m->embed(), tokens_dev, x, norm_gain(0), xn, p.folded ? sumsq : nullptr, M, d.d_model,
-                      d.vocab, d.rms_eps, rt, xn16, ZeroFill{tile_ctr, p.folded ? gemm_pack_tiles(n_o_fw, 1) : 0}, st);
+                      d.vocab, d.rms_eps, rt, xn16, ZeroFill{tile_ctr, p.folded ? gemm_pack_tiles(n_o_fw, 1) : 0},
+                      tree, tree ? (uint32_t *)(ws + p.off_tree) : nullptr, st);
     rs.tiles = 1;
     for (int l = 0; l < d.n_layers; ++l) {
         gemm(act, M, d.d_model, m->layer(l, W_Q), hd, m->layer(l, W_K), kvd, m->layer(l, W_V), kvd, p.sk_qkv, partial,
@@ -523,6 +521,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         if (!p.gated) launch_reduce_swiglu(partial, p.sk_gu, rs, p.half_copies ? nullptr : h, M, d.d_ffn, h16, st);
         resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), true, l, 6, l + 1 == d.n_layers);
     }
+    bool advanced = false;                                   // the head's reduction, the last kernel of its kind of pass, does it
     if (n_logit_rows > 0) {
         // lm_head on the last n_logit_rows rows of every sequence (unfolded: xn already holds the final norm)
         GemmArgs hg{};
@@ -536,9 +535,11 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         hg.partial = two_step ? partial : logits_out_dev;
         hg.reduced = two_step ? logits_out_dev : nullptr;
         if (p.folded) { hg.scale = rs; hg.scale_rows = M; }
+        if (hg.reduced) { hg.lens = kv->lens; hg.lens_n = B; hg.lens_add = n_new; hg.lens_max = kv->max_len; }
         launch_gemm(d.dtype, hg, st);
+        advanced = hg.reduced != nullptr;
     }
-    launch_advance_lens(kv->lens, B, n_new, kv->max_len, st);
+    if (!advanced) launch_advance_lens(kv->lens, B, n_new, kv->max_len, st);
     const psd_status s = check_launch();
     if (s == PSD_OK) kv->len_ub += n_new;
     return s;

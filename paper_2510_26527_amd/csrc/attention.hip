@@ -893,6 +893,18 @@ int attn_pick_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int le
     return s < 1 ? 1 : s;
 }
 
+// the most splits any cache length up to len_bound gets (the two-blocks-per-CU build takes fewer, longer ones at some lengths)
+int attn_max_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int len_bound, bool tree) {
+    const int at = attn_pick_splits(dtype, B, R, h_q, h_kv, d_h, len_bound, tree);
+    if (!direct_pairs(dtype, B, R, h_q, h_kv, d_h, len_bound, tree)) return at;
+    const int cached = len_bound - R > 1 ? len_bound - R : 1;
+    int most = (cached + 127) / 128;                                  // (direct_pairs: one query tile, so one chunk)
+    if (most > 512 / (B * h_kv) - 1) most = 512 / (B * h_kv) - 1;
+    const int one = 256 / (B * h_kv);                                // at the longest lengths of the other build
+    most = most + 1 > one ? most + 1 : one;
+    return most > at ? most : at;
+}
+
 template <int DH>
 static void launch_mfma(const AttnArgs &a, hipStream_t stream) {
     const int NQ = (a.h_q / a.h_kv) * a.R;

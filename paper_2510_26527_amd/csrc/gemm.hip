@@ -113,6 +113,8 @@ __device__ __forceinline__ void store_out(const GemmArgs &g, int ks, int m, int 
 __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(GemmArgs g) {
     __shared__ float red[4];
     const int m = blockIdx.y;
+    if (m == 0 && blockIdx.x == 0)
+        for (int b = threadIdx.x; b < g.lens_n; b += 256) g.lens[b] = min(g.lens[b] + g.lens_add, g.lens_max);
     float sc = 1.0f;
     if (g.scale.sumsq) {
         const size_t src = x_row(g, m);
@@ -272,8 +274,6 @@ __host__ __device__ __forceinline__ long range_begin(long b, long U, long P) { r
 // the block whose range holds unit u
 __host__ __device__ __forceinline__ long range_owner(long u, long U, long P) { return ((u + 1) * P - 1) / U; }
 
-constexpr int kUnitRing = 2;                       // units in flight per wavefront (its 4 KB of each)
-
 // The residual epilogue of one 64-column output tile that several blocks contributed partial sums to.  The calling
 // thread holds, for column `col` of the tile (the 64 lanes of its wavefront = the tile's 64 columns), this block's
 // sums of rows row0, row0 + rstep, ...: it publishes them in partial slot `slot` with agent-scope stores, waits for
@@ -333,19 +333,19 @@ __device__ __forceinline__ void resid_tile_finish(const GemmArgs &g, int tile, i
 // A block of a unit kernel is done with a tile (the tile's last unit, or the end of the block's range): red[q][row][token]
 // holds the sums of its four wavefronts.  They are added in wavefront order and the block writes ONE partial, slot =
 // its index among the blocks that share the tile (the block that finishes the tile zeroes the slots nobody writes),
-// or, RESID, hands them to the arrival epilogue above.  upt = units per tile, U = units of the GEMM, P = blocks.
+// or, RESID, hands them to the arrival epilogue above.  The tile's units are [first, first + upt) of the U that P blocks share.
 template <bool RESID>
-__device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (&red)[4][kSkinnyRows][17], int tile, int upt,
-                                                long U, long P, bool tile_end, int *s_last) {
+__device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (&red)[4][kSkinnyRows][17], int tile, long first,
+                                                int upt, long U, long P, bool tile_end, int *s_last) {
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const TileRef t = find_tile(g, tile, kSkinnyRows);
-    const long first_owner = range_owner((long)tile * upt, U, P);
+    const long first_owner = range_owner(first, U, P);
     const int slot = (int)(blockIdx.x - first_owner);
     const int row = t.row0 + lane;                                  // lane = row of the tile
     const bool row_ok = row < g.n[t.seg];
     const size_t col = (size_t)t.col0 + row;
     if constexpr (RESID) {
-        const int n_contrib = (int)(range_owner((long)tile * upt + upt - 1, U, P) - first_owner) + 1;
+        const int n_contrib = (int)(range_owner(first + upt - 1, U, P) - first_owner) + 1;
         float mine[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -383,76 +383,131 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
 // slots in slot order (so the sum does not depend on who that was) and runs the column kernel's epilogue on the
 // tile's 64 columns: residual add, gain-scaled copy, sum of squares per row into sumsq_out[tile][m].  It leaves the
 // counter at zero for the next launch.  No block waits for another.
-template <bool RESID>
+//
+// PAIR: the unit is two 16 KB units, the same K step of two neighbouring tiles.  The activations of a K step are then read
+// from L2 and split once for 128 weight rows instead of 64; at 16 rows they weigh half as much as the weights of 64.
+template <bool RESID, bool PAIR>
 __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
-    constexpr int R = kUnitRing;
+    constexpr int H = PAIR ? 2 : 1;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int i = lane & 15, gq = lane >> 4;
     const int K = g.K, ns = K / kSkinnyStepK;
-    const long U = (long)g.pack_tiles * ns, P = gridDim.x;
+    const long U = (long)((g.pack_tiles + H - 1) / H) * ns, P = gridDim.x;
     const int u0 = (int)range_begin(blockIdx.x, U, P), u1 = (int)range_begin(blockIdx.x + 1, U, P);
     if (u0 >= u1) return;
     const int n_my = u1 - u0;
+    const int tile0 = u0 / ns * H;                         // the block's first tile
+    // the buffer starts at that tile (or, alone, at the block's first unit and ends with its last)
+    const size_t w_first = PAIR ? (size_t)tile0 * ns : (size_t)u0;
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-        (char *)const_cast<void *>(g.wpack) + (size_t)u0 * kUnitBytes, 0, n_my * kUnitBytes, 0x00020000);
+        (char *)const_cast<void *>(g.wpack) + w_first * kUnitBytes, 0, PAIR ? 0x7fffffff : n_my * kUnitBytes, 0x00020000);
     // activations: offsets from the first row's source row; a row past M points past the buffer and reads zeros
     const size_t row_first = x_row(g, 0);
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(g.x) + row_first * K, 0, 0x7ffffff0, 0x00020000);
     const unsigned kq = (unsigned)((q >> 1) * 64 + gq * 16 + (q & 1) * 8) * 4u;
     const unsigned xbase = i < g.M ? (unsigned)((x_row(g, i) - row_first) * K * 4) + kq : 0x80000000u;
+    const unsigned lane_off = q * 4096u + lane * 16u;
 
-    u32x4 A[R][4], X[R][2];
-    int step_issue = u0 % ns;
-    auto issue = [&](int j, int n) {                       // n = index of the unit inside the block's range
-        const unsigned woff = (unsigned)n * kUnitBytes + q * 4096u + lane * 16u;
+    u32x4 A[2][4], X[PAIR ? 1 : 2][2];
+    auto load_w = [&](u32x4 (&a)[4], unsigned off) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) A[j][s] = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + s * 1024, 0, 2);   // 2: streaming
-        const unsigned xoff = n < n_my ? xbase + (unsigned)step_issue * (kSkinnyStepK * 4) : 0x80000000u;
-        X[j][0] = __builtin_amdgcn_raw_buffer_load_b128(rx, xoff, 0, 0);
-        X[j][1] = __builtin_amdgcn_raw_buffer_load_b128(rx, xoff + 16, 0, 0);
-        step_issue = step_issue + 1 == ns ? 0 : step_issue + 1;
+        for (int s = 0; s < 4; ++s) a[s] = __builtin_amdgcn_raw_buffer_load_b128(rw, off + s * 1024, 0, 2);   // 2: streaming
     };
-    f32x4 acc[4];
+    auto load_x = [&](u32x4 (&x)[2], unsigned off) {
+        x[0] = __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0);
+        x[1] = __builtin_amdgcn_raw_buffer_load_b128(rx, off + 16, 0, 0);
+    };
+    f32x4 acc[4 * H];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < 4 * H; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 bh, bl;
+    auto split_x = [&](const u32x4 (&x)[2]) {
+        f32x8 xv;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { xv[e] = __uint_as_float(x[0][e]); xv[4 + e] = __uint_as_float(x[1][e]); }
+        split_bf16(xv, &bh, &bl);
+    };
+    // hi parts over all accumulators, then lo parts: no back-to-back MFMAs on one accumulator
+    auto multiply = [&](const u32x4 (&a)[4], int at) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            acc[at + s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[s]), bh, acc[at + s], 0, 0, 0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            acc[at + s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[s]), bl, acc[at + s], 0, 0, 0);
+    };
     __shared__ float red[4][kSkinnyRows][17];
     __shared__ int s_last;
+    // acc[s][v] = y[token i][row s*16 + 4*gq + v of the tile] over this wavefront's K quarter
+    auto flush = [&](int tile, long first, bool tile_end) {
 #pragma unroll
-    for (int j = 0; j < R; ++j) issue(j, j);
-    int step_use = u0 % ns, tile = u0 / ns;
-    for (int base = 0; base < n_my; base += R) {
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int n = base + j;
-            f32x8 xv;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { xv[e] = __uint_as_float(X[j][0][e]); xv[4 + e] = __uint_as_float(X[j][1][e]); }
-            bf16x8 bh, bl;
-            split_bf16(xv, &bh, &bl);
-            // hi parts over all accumulators, then lo parts: no back-to-back MFMAs on one accumulator
+        for (int h = 0; h < H; ++h) {
+            if (PAIR && tile + h >= g.pack_tiles) break;                    // the same for all four wavefronts
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-                acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[j][s]), bh, acc[s], 0, 0, 0);
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[j][s]), bl, acc[s], 0, 0, 0);
-            issue(j, n + R);
+                for (int v = 0; v < 4; ++v) red[q][s * 16 + 4 * gq + v][i] = acc[h * 4 + s][v];
+            __syncthreads();
+            unit_tile_flush<RESID>(g, red, tile + h, first, ns, U, P, tile_end, &s_last);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int s = 0; s < 4 * H; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    int step_use = u0 % ns, tile = tile0;
+    long first = (long)(u0 / ns) * ns;                     // first unit of the tile (or pair)
+    if constexpr (PAIR) {
+        // stage h = tile h of the pair; unit n + 1 of a stage is requested when unit n of it has been multiplied
+        int step_issue = step_use;
+        unsigned at = lane_off + (unsigned)step_issue * kUnitBytes;          // first tile of the unit to request
+        int tile_issue = tile0;
+        const unsigned tile_bytes = (unsigned)ns * kUnitBytes;
+        auto w_off = [&](int n, int h) { return n < n_my && tile_issue + h < g.pack_tiles ? at + h * tile_bytes : 0x80000000u; };
+        auto x_off = [&](int n) { return n < n_my ? xbase + (unsigned)step_issue * (kSkinnyStepK * 4) : 0x80000000u; };
+        auto next = [&]() {
+            if (++step_issue == ns) { step_issue = 0; tile_issue += 2; at += tile_bytes; }       // past the second tile
+            at += kUnitBytes;
+        };
+        load_w(A[0], w_off(0, 0));
+        load_x(X[0], x_off(0));
+        load_w(A[1], w_off(0, 1));
+        next();
+        for (int n = 0; n < n_my; ++n) {
+            split_x(X[0]);
+            multiply(A[0], 0);
+            load_w(A[0], w_off(n + 1, 0));
+            load_x(X[0], x_off(n + 1));
+            multiply(A[1], 4);
+            load_w(A[1], w_off(n + 1, 1));
+            next();
             const bool tile_end = step_use + 1 == ns;
             step_use = tile_end ? 0 : step_use + 1;
-            if (n < n_my && (tile_end || n + 1 == n_my)) {                  // the same for all four wavefronts
-                // acc[s][v] = y[token i][row s*16 + 4*gq + v of the tile] over this wavefront's K quarter
+            if (tile_end || n + 1 == n_my) flush(tile, first, tile_end);
+            if (tile_end) { tile += 2; first += ns; }
+        }
+    } else {
+        constexpr int R = 2;                               // units in flight per wavefront (its 4 KB of each)
+        int step_issue = step_use;
+        auto issue = [&](int j, int n) {                   // n = index of the unit inside the block's range
+            load_w(A[j], (unsigned)n * kUnitBytes + lane_off);
+            load_x(X[j], n < n_my ? xbase + (unsigned)step_issue * (kSkinnyStepK * 4) : 0x80000000u);
+            step_issue = step_issue + 1 == ns ? 0 : step_issue + 1;
+        };
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
+        for (int j = 0; j < R; ++j) issue(j, j);
+        for (int base = 0; base < n_my; base += R) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) red[q][s * 16 + 4 * gq + v][i] = acc[s][v];
-                __syncthreads();
-                unit_tile_flush<RESID>(g, red, tile, ns, U, P, tile_end, &s_last);
-                __syncthreads();
-#pragma unroll
-                for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < R; ++j) {
+                const int n = base + j;
+                split_x(X[j]);
+                multiply(A[j], 0);
+                issue(j, n + R);
+                const bool tile_end = step_use + 1 == ns;
+                step_use = tile_end ? 0 : step_use + 1;
+                if (n < n_my && (tile_end || n + 1 == n_my)) flush(tile, first, tile_end);   // the same for all four wavefronts
+                if (tile_end) { ++tile; first += ns; }
             }
-            if (tile_end) ++tile;
         }
     }
 }
@@ -734,7 +789,7 @@ __global__ __launch_bounds__(256) void gemm_w4_unit_kernel(GemmArgs g) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) red[q][s * 16 + i][4 * gq + v] = acc[s][v];
                 __syncthreads();
-                unit_tile_flush<RESID>(g, red, tile, nq, U, P, tile_end, &s_last);
+                unit_tile_flush<RESID>(g, red, tile, (long)tile * nq, nq, U, P, tile_end, &s_last);
                 __syncthreads();
 #pragma unroll
                 for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1050,23 +1105,25 @@ GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) 
 // (256 x 37888 x 3584, 148 tiles: 95 us; separate, 84 + 11)
 bool gemm_tiled_gates(int M, int K, const int *n) { return M > 128 && gemm_tiled_plan(M, K, n, 2, true).tiles >= 128; }
 
-int gemm_stream_grid(int tiles, int K) {
-    const long U = (long)tiles * (K / kSkinnyStepK);
+static int gemm_stream_units(int M, int tiles) { return M >= kPairRows ? (tiles + 1) / 2 : tiles; }
+static int gemm_stream_grid(int M, int tiles, int K) {
+    const long U = (long)gemm_stream_units(M, tiles) * (K / kSkinnyStepK);
     return (int)(U < kStreamBlocks ? (U < 1 ? 1 : U) : kStreamBlocks);
 }
 
 // grid of the unit kernel with the residual epilogue: one block per CU, so that few blocks share a tile (the last of
 // them to arrive adds their partials).  Measured on the 7B down projection, O and down averaged: 256 blocks 16.2 us,
 // 384 blocks 18.5 us, 512 blocks 17.8 us, 128 blocks slower still.
-int gemm_resid_grid(int tiles, int K) {
+static int gemm_resid_grid(int tiles, int K) {
     const long U = (long)tiles * (K / kSkinnyStepK);
     return (int)(U < kStreamBlocks / 2 ? (U < 1 ? 1 : U) : kStreamBlocks / 2);
 }
 
 // largest number of blocks that share one tile, i.e. partial slots per output element
-static int gemm_slots_of(int tiles, int units_per_tile, int grid);
 int gemm_resid_slots(int tiles, int K) { return gemm_slots_of(tiles, K / kSkinnyStepK, gemm_resid_grid(tiles, K)); }
-int gemm_stream_slots(int tiles, int K) { return gemm_slots_of(tiles, K / kSkinnyStepK, gemm_stream_grid(tiles, K)); }
+static int gemm_stream_slots(int M, int tiles, int K) {
+    return gemm_slots_of(gemm_stream_units(M, tiles), K / kSkinnyStepK, gemm_stream_grid(M, tiles, K));
+}
 static int gemm_slots_of(int tiles, int units_per_tile, int grid) {
     const long ns = units_per_tile, U = (long)tiles * ns, P = grid;
     long worst = 1;
@@ -1127,8 +1184,7 @@ int gemm_w4_slots(int K, const int *n, int nseg, bool resid) {
 }
 
 int gemm_packed_splits(int M, int K, const int *n, int nseg) {
-    (void)M;
-    return gemm_stream_slots(tiles_of(n, nseg, kSkinnyRows), K);
+    return gemm_stream_slots(M, tiles_of(n, nseg, kSkinnyRows), K);
 }
 
 int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg) {
@@ -1166,7 +1222,7 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
     }
     if (g.M <= kStreamMaxRows && g.wpack && g.x_resid && g.tile_counter) {
         ScopedProf sp(PSD_KIND_GEMM_COLUMN, stream);
-        launch_kernel(gemm_bf16_unit_kernel<true>, gemm_resid_grid(g.pack_tiles, g.K), 256, 0, stream, g);
+        launch_kernel(gemm_bf16_unit_kernel<true, false>, gemm_resid_grid(g.pack_tiles, g.K), 256, 0, stream, g);
         return;
     }
     if (g.M <= kStreamMaxRows && g.wpack && g.x_resid) {
@@ -1179,7 +1235,9 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
     const bool x_near = (long)(x_row(g, g.M - 1) - x_row(g, 0) + 1) * g.K * 4 < 0x7fff0000L;
     if (g.M <= kStreamMaxRows && g.wpack && x_near) {
         ScopedProf sp(PSD_KIND_GEMM_SKINNY, stream);
-        launch_kernel(gemm_bf16_unit_kernel<false>, gemm_stream_grid(g.pack_tiles, g.K), 256, 0, stream, g);
+        const int grid = gemm_stream_grid(g.M, g.pack_tiles, g.K);
+        if (g.M >= kPairRows) launch_kernel(gemm_bf16_unit_kernel<false, true>, grid, 256, 0, stream, g);
+        else launch_kernel(gemm_bf16_unit_kernel<false, false>, grid, 256, 0, stream, g);
     } else if (g.M <= kStreamMaxRows) {
         ScopedProf sp(PSD_KIND_GEMM_SLOT, stream);
         dim3 grid(tiles_of(g.n, g.nseg, kSkinnyRows), g.splitk);

@@ -39,6 +39,11 @@ void launch_accept_greedy(const AcceptArgs &a, bool vec_ok, hipStream_t stream);
 // LDS-tiled kernel wins (measured on two LLaMA2-7B-shaped layers: 0.28 ms at 16 rows; at 32 rows 0.43 ms
 // streaming against 0.38 ms tiled, at 64 rows 0.66 against 0.38).
 constexpr int kStreamMaxRows = 16;
+// From this many rows on the unit kernel takes tiles in pairs.  Measured (us a launch, QKV, gate|up and head of the 7B shape
+// averaged, pairs / single): 4 rows 29.1 / 28.4, 9 rows 29.7 / 29.1, 12 rows 29.8 / 30.0, 15 rows 30.9 / 32.3, 16 rows
+// 30.5 / 32.6; below, the larger unit's uneven ranges and longer flush cost what it saves.  The residual projections stay
+// single (15 rows 28.2 / 19.9: twice the blocks meet at every arrival).
+constexpr int kPairRows = 13;
 // y[m][n] = sum_k x[m][k] * W[n][k]; W is up to three row-major [n_i][K] matrices whose
 // outputs are concatenated along n (QKV, gate|up).
 // r_m from per-tile sums of squares: rsqrt(sum_t sumsq[t * M + m] * inv_d + eps); sumsq NULL: 1
@@ -83,6 +88,8 @@ struct GemmArgs {
     uint16_t *swiglu16;           // segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
     RowScale scale;               // applied when writing `reduced` (row = the source row of m)
     int scale_rows;               //   rows per tile slab of scale.sumsq
+    int32_t *lens;                // non-NULL: the kernel that writes `reduced` also moves these lens_n lengths on by lens_add
+    int lens_n, lens_add, lens_max;
 };
 struct GemmTiledPlan {
     int ta, cols;                 // block tile: 64 ta rows x cols columns
@@ -97,9 +104,6 @@ int gemm_pack_tiles(const int *n, int nseg);
 size_t gemm_pack_bytes(const int *n, int nseg, int K);
 int gemm_w4_slots(int K, const int *n, int nseg, bool resid);  // partial slots of a 4-bit projection (resid: the arrival epilogue's grid)
 int gemm_packed_splits(int M, int K, const int *n, int nseg);   // partial slots (the splitk to use) with packed weights
-int gemm_stream_grid(int tiles, int K);
-int gemm_stream_slots(int tiles, int K);
-int gemm_resid_grid(int tiles, int K);
 int gemm_resid_slots(int tiles, int K);                          // partial slots of a projection run with tile_counter
 // strip_major: the layout of the column kernel (the O projection)
 void launch_gemm_pack(const void *const *w, const int *n, int nseg, int K, void *dst, bool strip_major, hipStream_t stream);
@@ -137,6 +141,7 @@ struct AttnArgs {
 };
 // whether launch_attention builds its operands itself for this shape (then no rotation / append kernel runs before it)
 bool attn_fuses_rope(int dtype, int R, int h_q, int h_kv, int d_h, bool tree);
+int attn_max_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int len_bound, bool tree);
 int attn_pick_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int len_bound, bool tree);
 void launch_attention(int dtype, const AttnArgs &a, hipStream_t stream);
 
@@ -148,7 +153,6 @@ struct TreeShape {
     int32_t depth[kTreeMaxNodes];
     int n;
 };
-void launch_tree_setup(const TreeShape &ts, uint32_t *anc, int32_t *depth, hipStream_t stream);
 struct TreeAcceptArgs {
     const void *p, *q;            // [rows][n_nodes][vocab] logits (strides in elements per sequence), q unused when greedy
     int64_t p_stride, q_stride;
@@ -175,16 +179,16 @@ struct RopeTable {
     const int32_t *lens;
     int R, d_h;
     float theta;
-    const int32_t *depth;         // token tree: row r sits at position lens[b] + depth[r]; NULL: lens[b] + r
 };
 struct ZeroFill {
     unsigned *words;              // n 32-bit words set to zero by the first kernel of a forward pass (NULL / 0: none)
     int n;
 };
+// tree (or NULL): row r sits at position lens[b] + depth[r], and tree_anc receives the ancestor masks
 // x = embed[token]; then xn = rmsnorm(x) * gain, or (sumsq_out non-NULL) xn = x * gain and sumsq_out[m] = sum_k x[m][k]^2
 void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, float *x, const void *gain, float *xn,
                        float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, ZeroFill zf,
-                       hipStream_t stream);
+                       const TreeShape *tree, uint32_t *tree_anc, hipStream_t stream);
 // qkv = sum over splits of partial [S][M][(h_q+2h_kv) d_h] -> rotated q (fp32), rotated k and v appended
 // to the cache (model dtype); cs_table: RopeTable::cs of these rows, NULL: the angles are evaluated again
 void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale rs, float *q_out, void *k_cache,

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *em
                                                                     const float *partial, int S, size_t split_stride,
                                                                     float *x, const TW *gain, float *xn, float *sumsq_out,
                                                                     int d, float eps, RopeTable rt, uint16_t *xn16,
-                                                                    ZeroFill zf) {
+                                                                    ZeroFill zf, TreeShape tree, uint32_t *tree_anc) {
     constexpr int kMaxV4 = kMaxRowV4 / kRowThreads;
     __shared__ float red[kRowThreads / 64];
     const int m = blockIdx.x, tid = threadIdx.x, n4 = d >> 2;
@@ -51,10 +51,11 @@ __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *em
         // counters that later kernels of this forward pass expect at zero
         if (m == 0)
             for (int j = tid; j < zf.n; j += kRowThreads) zf.words[j] = 0u;
+        if (m < tree.n && tid == 0) tree_anc[m] = tree.anc[m];                  // m: the same for the block
         // (cos, sin) of this row's position at every rotation frequency, once per forward pass for all layers;
         // the angle position * theta^(-2i/d_h) is evaluated in fp64
         if (rt.cs && tid < rt.d_h / 2) {
-            const int pos = rt.lens[m / rt.R] + (rt.depth ? rt.depth[m % rt.R] : m % rt.R);
+            const int pos = rt.lens[m / rt.R] + (tree.n ? tree.depth[m % rt.R] : m % rt.R);
             const double inv_freq = exp2(-2.0 * (double)tid / (double)rt.d_h * log2((double)rt.theta));
             double sn, cs;
             sincos((double)pos * inv_freq, &sn, &cs);
@@ -311,14 +312,15 @@ __global__ void truncate_to_kernel(int32_t *lens, int new_len, int B) {
 
 void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, float *x, const void *gain, float *xn,
                        float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, ZeroFill zf,
-                       hipStream_t stream) {
+                       const TreeShape *tree, uint32_t *tree_anc, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_EMBED, stream);
+    const TreeShape ts = tree ? *tree : TreeShape{};
     if (dtype == PSD_BF16)
         launch_kernel(residual_norm_kernel<uint16_t, true, 256>, M, 256, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0,
-                                                                           x, (const uint16_t *)gain, xn, sumsq_out, d, eps, rt, xn16, zf);
+                                                                           x, (const uint16_t *)gain, xn, sumsq_out, d, eps, rt, xn16, zf, ts, tree_anc);
     else
         launch_kernel(residual_norm_kernel<float, true, 256>, M, 256, 0, stream, (const float *)embed, tokens, vocab, nullptr, 0, 0, x,
-                                                                        (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, zf);
+                                                                        (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, zf, ts, tree_anc);
 }
 
 constexpr int kWideRowMax = 256;       // rows up to which a norm block has 1024 threads
@@ -328,12 +330,12 @@ void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *
     const size_t stride = (size_t)M * d;
     if (dtype == PSD_BF16)
         (M <= kWideRowMax ? launch_kernel(residual_norm_kernel<uint16_t, false, 1024>, M, 1024, 0, stream, nullptr, nullptr, 0, partial, S,
-                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{})
+                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr)
                           : launch_kernel(residual_norm_kernel<uint16_t, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S,
-                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}));
+                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr));
     else
         launch_kernel(residual_norm_kernel<float, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S, stride, x,
-                                                                         (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{});
+                                                                         (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr);
 }
 
 void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale rs, float *q_out, void *k_cache,

@@ -3,8 +3,6 @@
 // sampling for sibling tokens drawn independently from the drafter's distribution at their parent, which leaves the
 // verifier's distribution unchanged (Abstract; Sec. 3.1).
 //
-//   tree_setup_kernel        the tree's shape (ancestor bit masks, depths) from kernel arguments into device memory,
-//                            where the embedding and attention kernels of a tree forward pass read it;
 //   tree_stats / mass / draw_kernel  the walk from the root: at a node the children are tried in index order against the
 //                            running residual of the verifier's distribution, the first accepted child is descended
 //                            into, and where none is accepted one token is drawn from what is left; every pass over
@@ -30,17 +28,6 @@ namespace {
 
 constexpr int kTreeThreads = 1024;
 constexpr int kTreeWaves = kTreeThreads / 64;
-
-__global__ void tree_setup_kernel(TreeShape ts, uint32_t *anc, int32_t *depth) {
-    const int t = threadIdx.x;
-    // static indices into the kernel arguments, selected per lane
-#pragma unroll
-    for (int j = 0; j < kTreeMaxNodes; ++j)
-        if (t == j && j < ts.n) {
-            anc[j] = ts.anc[j];
-            depth[j] = ts.depth[j];
-        }
-}
 
 // block-wide sum in a fixed order: butterfly inside each wavefront, wavefronts added in order; every thread gets it
 __device__ __forceinline__ double block_sum_d(double v, double *s_w) {
@@ -674,11 +661,6 @@ __global__ __launch_bounds__(128) void kv_compact_tree_kernel(T *k, T *v, int32_
 }
 
 }  // namespace
-
-void launch_tree_setup(const TreeShape &ts, uint32_t *anc, int32_t *depth, hipStream_t stream) {
-    ScopedProf sp(PSD_KIND_LENS, stream);
-    launch_kernel(tree_setup_kernel, 1, 64, 0, stream, ts, anc, depth);
-}
 
 template <typename T>
 static void launch_tree_accept_t(const TreeAcceptArgs &a, hipStream_t stream) {

@@ -177,6 +177,17 @@ def test_attention_of_many_sequences(d_head, batch, ctx, rows):
     p.close()
 
 
+def test_workspace_covers_every_cache_length():
+    """16 sequences x 4 KV heads: a 900-key step takes more, shorter key splits than one at the end of its 1408-key cache;
+    the workspace that the cache's size asks for has to serve it."""
+    shape = synth.Shape(1, 256, 4, 4, 64, 256, 600, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 16, 1408, seed=3, ctx=896, std=0.05)
+    need = psd.psd_model_workspace_bytes(p.model.handle, 16, 3, 1408)
+    assert need > 0
+    p.step(synth.make_tokens(shape.vocab, (16, 3), 5), what="896 keys")
+    p.close()
+
+
 def test_bf16_batch_ragged_lengths_truncate():
     shape = SMALL_GQA
     p = Pair(shape, torch.bfloat16, 4, 640, seed=21, ctx=512, lens=[512, 100, 333, 1], std=0.05, pack=True)
