@@ -837,7 +837,11 @@ __device__ __forceinline__ u32x4 w4x8_to_f16x8(uint32_t raw, uint32_t sz) {
 // 364 (which also drops a SwiGLU launch of 46), 4096 x 8192 148 -> 127, 4096 x 4096 87 -> 70.
 // With few rows: streaming W; the blocks take equal ranges of all the product's K tiles, so none of the CUs idles in a last
 // round.  Measured (45 rows, us): 12288 x 4096 32.5 -> 25.9, 22016 x 4096 47.1 -> 42.3, 4096 x 4096 14.7 -> 10.4,
-// 32000 x 4096 78.8 -> 59.1 (4.4 TB/s).
+// 32000 x 4096 78.8 -> 59.1 (4.4 TB/s).  Up to 64 rows two blocks of 128 columns share a CU, so that one's loads cover the
+// other's barriers and its write-out (one block of 256: 26.8 / 26.1, 41.9 / 41.0, 10.3 / 9.8, 4096 x 8192 16.5 / 15.9; two
+// layers and a head of the 7B shape 384 -> 374); at 65 to 128 rows that gains nothing (128 x 12288 x 4096 35.5 / 37.3).
+// Neither does a second K tile in registers (26.5), nor asking for both halves of a 256-byte row piece together (28.5),
+// nor reading the weights from the packed copy in contiguous 8 KB pieces (27.3).
 // Tried and not kept: tiles shared by several blocks added up by the last of them (256 x 256 fp32 through agent-scope
 // stores and loads: 140 us instead of 70 at 2001 x 4096 x 4096); an XCD-contiguous block order alone (no change: not
 // bound by L2 misses); four wavefronts of 128 x 128 (5 % slower than eight of 128 x 64: one wavefront per SIMD does not
@@ -849,7 +853,7 @@ constexpr int kBK = 64, kLdsStride = 72;
 // LDS they become the fp16 numbers scale * (q - zero): (1024 + q) - (1024 + zero) is exact in fp16, the product
 // with the scale (itself exact in fp16 down to 6e-5) is rounded once, to 11 significant bits.
 template <int TA, int TB, int WN, bool W4>
-__global__ __launch_bounds__(128 * WN, 1) void gemm_f16_tiled_kernel(GemmArgs g) {
+__global__ __launch_bounds__(128 * WN, TA == 1 ? 4 : 1) void gemm_f16_tiled_kernel(GemmArgs g) {
     constexpr int BM = 64 * TA, BN = 32 * TB * WN, NT = 128 * WN;
     constexpr int XCH = BM * 8 / NT;                        // 16-byte chunks of the fp16 X tile per thread (BM x 64)
     constexpr int WCH = BN * 8 / NT;                        // 16-byte chunks of the W tile per thread (BN x 64 bf16)
@@ -1066,9 +1070,9 @@ int tiles_of(const int *n, int nseg, int rows) {
 }  // namespace
 
 static int gemm_slots_of(int tiles, int units_per_tile, int grid);
-// The tile and the number of blocks of a tiled product.  Up to 128 rows it streams W: 256 columns, one block per CU but
-// at least eight K tiles each (45 rows x 4096 x 4096: 128 blocks 11.2 us and 16 slots less to add than 256 blocks, 11.6),
-// tiles shared wherever the ranges fall.  Above: 256 rows; the columns and the (even) K split with the least estimated
+// The tile and the number of blocks of a tiled product.  Up to 128 rows it streams W: two blocks of 128 columns per CU up to
+// 64 rows, one of 256 above, but at least eight K tiles each (45 rows x 4096 x 4096 in tiles of 256: 128 blocks 11.2 us and
+// 16 slots less to add than 256 blocks, 11.6), tiles shared wherever the ranges fall.  Above: 256 rows; the columns and the (even) K split with the least estimated
 // time: rounds of 256 blocks x K tiles x the measured time of one (us: 1.15, 1.65, 1.9 for 128, 192, 256 columns) plus 4
 // per round for filling and emptying the pipeline, plus a partial slot of M x N written and read at about 3 TB/s per
 // split.  gated: 128 gate and 128 up columns per tile, never split (the two factors meet in one lane).
@@ -1077,10 +1081,11 @@ GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) 
     const int nk = K / kBK;
     if (M <= 128 && !gated) {
         best.ta = M <= 64 ? 1 : 2;
-        best.cols = 256;
-        best.tiles = tiles_of(n, nseg, 256);
+        best.cols = best.ta == 1 ? 128 : 256;
+        best.tiles = tiles_of(n, nseg, best.cols);
+        const long cap = best.ta == 1 ? 512 : 256;
         const long U = (long)best.tiles * nk;
-        best.blocks = (int)(U / 8 < 1 ? 1 : (U / 8 < 256 ? U / 8 : 256));
+        best.blocks = (int)(U / 8 < 1 ? 1 : (U / 8 < cap ? U / 8 : cap));
         best.slots = gemm_slots_of(best.tiles, nk, best.blocks);
         return best;
     }
@@ -1257,7 +1262,7 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
         };
         auto pick = [&](auto w4) {
             constexpr bool W4 = decltype(w4)::value;
-            if (p.ta == 1) go(gemm_f16_tiled_kernel<1, 2, 4, W4>, 512);
+            if (p.ta == 1) go(gemm_f16_tiled_kernel<1, 1, 4, W4>, 512);
             else if (p.ta == 2) go(gemm_f16_tiled_kernel<2, 2, 4, W4>, 512);
             else if (p.cols == 128) go(gemm_f16_tiled_kernel<4, 1, 4, W4>, 512);
             else if (p.cols == 192) go(gemm_f16_tiled_kernel<4, 3, 2, W4>, 256);
