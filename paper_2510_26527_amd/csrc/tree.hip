@@ -662,9 +662,18 @@ __global__ __launch_bounds__(128) void kv_compact_tree_kernel(T *k, T *v, int32_
 
 }  // namespace
 
+// This call's number, never 0.  One count for all element types: the number says which slot a call takes and whether a
+// slot is its own, and calls of both types share the slots.
+static uint32_t tree_call_number() {
+    static std::atomic<uint32_t> tree_calls{0};
+    uint32_t id;
+    do id = tree_calls.fetch_add(1, std::memory_order_relaxed) + 1;
+    while (id == 0);
+    return id;
+}
+
 template <typename T>
 static void launch_tree_accept_t(const TreeAcceptArgs &a, hipStream_t stream) {
-    static std::atomic<uint32_t> calls{0};
     TreeShare sh{};
     sh.n_chunks = (a.vocab + kTreeChunk - 1) / kTreeChunk;
     size_t st, ms, pt;
@@ -676,8 +685,7 @@ static void launch_tree_accept_t(const TreeAcceptArgs &a, hipStream_t stream) {
         launch_kernel(tree_accept_alone_kernel<T>, a.rows, kTreeThreads, 0, stream, a);
         return;
     }
-    do sh.id = calls.fetch_add(1, std::memory_order_relaxed) + 1;
-    while (sh.id == 0);
+    sh.id = tree_call_number();
     const bool greedy = a.temperature == 0.f;
     launch_kernel(tree_claim_kernel, 1, 64, 0, stream, a, sh);
     launch_kernel(tree_stats_kernel<T>, (unsigned)(a.rows * a.n_nodes * sh.n_chunks), kStatThreads, 0, stream, a, sh);

@@ -3,6 +3,7 @@ include/psd.h declares, and rejects bad arguments on the host before any launch.
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -29,6 +30,14 @@ def test_exports_every_declared_symbol(lib):
     for n in names:
         assert hasattr(lib, n), n
     assert set(names) == set(psd._SIGNATURES), "binding and header disagree"
+
+
+def test_tree_acceptance_numbers_its_calls_once_for_all_types(lib):
+    """fp32 and bf16 calls share the scratch slots and own one by their call number: the library may hold one counter of
+    calls, not one per element type (two calls of the same number would both take the slot for theirs)."""
+    out = subprocess.run(["nm", "-C", psd.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    data = [m.group(1) for m in re.finditer(r"^[0-9a-f]+ [bBdDu] (.*tree.*calls?\S*)$", out, re.M)]
+    assert len(data) == 1, data
 
 
 def _desc(**kw):

@@ -171,6 +171,31 @@ def test_tree_accept_overlapping_streams_and_capture():
         assert all(torch.equal(a, b) for a, b in zip(out, want[0])), rep
 
 
+def test_tree_accept_overlapping_calls_of_both_types():
+    """fp32 and bf16 calls, of different batches, trees and vocabularies and a greedy one among them, in turn on two and
+    on five streams: a call must never take the scratch another one is using for its own."""
+    kinds = [(4, "binary7", 20000, torch.float32, 1.0), (6, "comb16", 30011, torch.bfloat16, 1.0),
+             (3, "wide_then_deep8", 40960, torch.float32, 0.8), (9, "binary7", 24001, torch.bfloat16, 1.0),
+             (2, "comb16", 70000, torch.bfloat16, 0.0), (4, "full32", 16385, torch.float32, 1.0)]
+    cases = [_accept_case(*k[:4], i, k[4]) + (k[4],) for i, k in enumerate(kinds)]
+    cases = [(c[0],) + tuple(t.cuda() for t in c[1:5]) + (c[5],) for c in cases]
+    call = lambda c: runtime.tree_accept(c[1], c[2], c[3], c[0], c[4], c[5])
+    want = []
+    for c in cases:
+        want.append([x.clone() for x in call(c)])
+        torch.cuda.synchronize()
+    for n_streams in (2, 5):
+        streams, got = [torch.cuda.Stream() for _ in range(n_streams)], []
+        for rep in range(8):
+            for i, c in enumerate(cases):
+                with torch.cuda.stream(streams[(rep + i) % n_streams]):
+                    got.append(call(c))
+        torch.cuda.synchronize()
+        for i, g in enumerate(got):
+            assert all(torch.equal(a, b) for a, b in zip(g, want[i % len(cases)])), (n_streams, i)
+
+
+
 def test_tree_accept_chain_is_the_linear_call():
     """One child per node: the same accepted length and token as psd_spec_accept on the same inputs."""
     rows, gamma, V = 32, 6, 32000
