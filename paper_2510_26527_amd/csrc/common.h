@@ -91,6 +91,8 @@ __device__ __forceinline__ T wave_sum(T v) {
 // fp64 wavefront reductions on the vector ALU's own lane moves (about a tenth of the latency of a trip through the LDS
 // crossbar per step).  Inclusive prefix over the lanes in a fixed order: rows of 16 first, then across rows; lanes that a
 // move does not reach get `none`.
+template <int N>
+struct Int { static constexpr int value = N; };
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double lane_move(double v, double none) {
     const uint64_t x = __builtin_bit_cast(uint64_t, v), o = __builtin_bit_cast(uint64_t, none);
@@ -112,6 +114,20 @@ __device__ __forceinline__ double lane_value_d(double v, int lane) {        // t
     const uint64_t x = __builtin_bit_cast(uint64_t, v);
     const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)x, lane), hi = __builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// the largest value of the wavefront (NaN counts for nothing)
+__device__ __forceinline__ float wave_top_f(float v) {
+    auto step = [&](auto ctrl, auto rows) {
+        v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(-INFINITY), __float_as_int(v), decltype(ctrl)::value,
+                                                                decltype(rows)::value, 0xf, false)));
+    };
+    step(Int<0x111>{}, Int<0xf>{});                        // row_shr:1, 2, 4, 8, then row_bcast:15 and :31
+    step(Int<0x112>{}, Int<0xf>{});
+    step(Int<0x114>{}, Int<0xf>{});
+    step(Int<0x118>{}, Int<0xf>{});
+    step(Int<0x142>{}, Int<0xa>{});
+    step(Int<0x143>{}, Int<0xc>{});
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 __device__ __forceinline__ double wave_prefix_sum_d(double v) { return wave_scan_d(v, 0.0, [](double a, double b) { return a + b; }); }
 __device__ __forceinline__ double wave_total_d(double v) { return lane_value_d(wave_prefix_sum_d(v), 63); }

@@ -40,177 +40,106 @@ __device__ __forceinline__ double block_sum_d(double v, double *s_w) {
     for (int w = 0; w < kTreeWaves; ++w) t += s_w[w];
     return t;
 }
-__device__ __forceinline__ float block_max_f(float v, float *s_w) {
-    v = wave_max(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float t = s_w[0];
-#pragma unroll
-    for (int w = 1; w < kTreeWaves; ++w) t = fmaxf(t, s_w[w]);
-    return t;
-}
 
-// The whole walk by one block, which needs no memory to share: calls whose statistics do not fit a scratch slot (below),
-// or that find theirs taken.
+// The vocabulary is cut into chunks of kTreeChunk entries and these into pieces of kPiece, one wavefront's work: lane l has
+// the entries l, l + 64, ... of a piece.  Every sum over a row adds in the same order whoever takes it: over a lane's
+// entries, over the lanes, over the pieces of a chunk, over the chunks (one a lane).  So a call's result does not depend
+// on which of the two ways of walking the tree it gets.
+constexpr int kTreeChunk = 4096, kPiece = 256, kPieces = kTreeChunk / kPiece, kPerLane = kPiece / 64;
+constexpr int kTreeMaxChunks = 64;                // per row: one per lane
+constexpr int kMassPasses = 3;                    // refusals at one node whose masses are added piece by piece (all of them at a
+                                                  //   node of up to four children: the last refusal needs none)
+static_assert(kPieces == 16, "a chunk's pieces are joined by 16 lanes");
+
+struct TreeStat { double zp, zq; float mp, mq; };                  // sums of exp((l - max) / T), maxima
+
+// this lane's entries of the piece that begins at `first` (-infinity past the end of the row)
 template <typename T>
-__device__ void walk_alone(const TreeAcceptArgs &a, int row) {
-    __shared__ double s_wd[kTreeWaves];
-    __shared__ float s_wf[kTreeWaves];
-    __shared__ int s_par[kTreeMaxAcceptNodes];
-    __shared__ int s_pick, s_lastpos;
-    __shared__ unsigned long long s_best;
-    __shared__ double s_exp2[64];                           // kExp2Table, for exp_nonpos
-    const int tid = threadIdx.x, n = a.n_nodes, V = a.vocab;
-    for (int j = tid; j < n; j += kTreeThreads) s_par[j] = a.parents[j];
-    if (tid < 64) s_exp2[tid] = kExp2Table[tid];
-    __syncthreads();
-    const T *P = (const T *)a.p + (size_t)row * a.p_stride;
-    const T *Q = (const T *)a.q + (size_t)row * a.q_stride;
-    const int32_t *tok = a.tokens + (size_t)row * n;
-    const float *u = a.uniforms ? a.uniforms + (size_t)row * (n + 1) : nullptr;
-    const bool greedy = a.temperature == 0.f;
-    const double Tm = (double)a.temperature, inv_t = 1.0 / Tm;
-    // exp(logit / T - max / T): the scaled logit minus the row's scaled maximum is never positive
-    auto ex = [&](float logit, double m) { return exp_nonpos(fma((double)logit, inv_t, -m), s_exp2); };
-    int32_t *path = a.out_path + (size_t)row * n;
-    int node = 0, plen = 0, flags = 0;
-
-    while (true) {                                          // every descent moves to a larger node index: at most n rounds
-        const T *lp = P + (size_t)node * V;
-        const T *lq = Q + (size_t)node * V;
-        if (greedy) {
-            // the verifier's most likely token, lowest index among equals
-            unsigned long long best = 0ull;                 // (order-preserving bits of the logit) << 32 | ~index
-            for (int i = tid; i < V; i += kTreeThreads) {
-                const float x = load_elem(lp, (size_t)i);
-                uint32_t b = __float_as_uint(x);
-                b = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-                const unsigned long long key = ((unsigned long long)b << 32) | (uint32_t)(~(uint32_t)i);
-                best = key > best ? key : best;
-            }
-            best = wave_max(best);
-            if (tid == 0) s_best = 0ull;
-            __syncthreads();
-            if ((tid & 63) == 0) atomicMax(&s_best, best);
-            __syncthreads();
-            const int top = (int)(~(uint32_t)(s_best & 0xffffffffull));
-            int next = -1;
-            for (int c = node + 1; c < n && next < 0; ++c)
-                if (s_par[c] == node && tok[c] == top) next = c;
-            __syncthreads();                                // s_best is reset by the next round
-            if (next < 0) {
-                if (tid == 0) { a.out_path_len[row] = plen; a.out_token[row] = top; if (a.out_flags) a.out_flags[row] = 0; }
-                return;
-            }
-            if (tid == 0) path[plen] = next;
-            ++plen;
-            node = next;
-            continue;
-        }
-
-        // ---- softmax statistics of the two rows at this node: s_i = logit_i / T, max, sum of exp(s_i - max)
-        float mpf = -INFINITY, mqf = -INFINITY;
-        for (int i = tid; i < V; i += kTreeThreads) {
-            mpf = fmaxf(mpf, load_elem(lp, (size_t)i));
-            mqf = fmaxf(mqf, load_elem(lq, (size_t)i));
-        }
-        const double mp = (double)block_max_f(mpf, s_wf) * inv_t, mq = (double)block_max_f(mqf, s_wf) * inv_t;
-        double zp = 0.0, zq = 0.0;
-        for (int i = tid; i < V; i += kTreeThreads) {
-            zp += ex(load_elem(lp, (size_t)i), mp);
-            zq += ex(load_elem(lq, (size_t)i), mq);
-        }
-        const double Zp = block_sum_d(zp, s_wd), Zq = block_sum_d(zq, s_wd);
-        const double inv_zp = 1.0 / Zp, inv_zq = 1.0 / Zq;       // one division per row, not one per entry
-        double c = 0.0, mass = 1.0;                         // the residual here is max(0, p - c q) / mass
-
-        int next = -1;
-        for (int ch = node + 1; ch < n; ++ch) {
-            if (s_par[ch] != node) continue;
-            int x = tok[ch];
-            x = min(max(x, 0), V - 1);
-            const double px = ex(load_elem(lp, (size_t)x), mp) * inv_zp;
-            const double qx = ex(load_elem(lq, (size_t)x), mq) * inv_zq;
-            const double rx = fmax(px - c * qx, 0.0);
-            const double ratio = qx == 0.0 ? INFINITY : rx / (mass * qx);
-            const double thr = fmin(1.0, ratio), uu = (double)u[ch];
-            if (fabs(uu - thr) < 1e-5) flags |= PSD_FLAG_NEAR_TIE;
-            if (uu < thr) { next = ch; break; }
-            // refused: take the drafter's share out of what is left
-            const double c2 = c + mass;
-            double m2 = 0.0;
-            for (int i = tid; i < V; i += kTreeThreads) {
-                const double pi = ex(load_elem(lp, (size_t)i), mp) * inv_zp;
-                const double qi = ex(load_elem(lq, (size_t)i), mq) * inv_zq;
-                m2 += fmax(pi - c2 * qi, 0.0);
-            }
-            m2 = block_sum_d(m2, s_wd);
-            if (m2 > 0.0) { c = c2; mass = m2; }            // mass 0: the residual equalled q, where no refusal can happen
-        }
-        if (next >= 0) {
-            if (tid == 0) path[plen] = next;
-            ++plen;
-            node = next;
-            continue;
-        }
-
-        // ---- no child accepted: one draw from max(0, p - c q) by inverse CDF in index order.  Thread t owns the
-        // contiguous entries [t * per, (t + 1) * per); prefix sums over threads in a fixed order.
-        const int per = (V + kTreeThreads - 1) / kTreeThreads;
-        const int i0 = min(tid * per, V), i1 = min(i0 + per, V);
-        double w = 0.0;
-        int lastpos = -1;
-        for (int i = i0; i < i1; ++i) {
-            const double pi = ex(load_elem(lp, (size_t)i), mp) * inv_zp;
-            const double qi = ex(load_elem(lq, (size_t)i), mq) * inv_zq;
-            const double r = fmax(pi - c * qi, 0.0);
-            if (r > 0.0) lastpos = i;
-            w += r;
-        }
-        // inclusive prefix inside the wavefront, then the wavefronts before it
-        double incl = w;
+__device__ __forceinline__ void load_piece(const T *row, int first, int V, float (&x)[kPerLane]) {
+    const T *at = row + first;
+    const int lane = threadIdx.x & 63, left = __builtin_amdgcn_readfirstlane(V - first);
+    if (left >= kPiece) {
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double up = __shfl_up(incl, o, 64);
-            if ((tid & 63) >= o) incl += up;
-        }
-        __syncthreads();
-        if ((tid & 63) == 63) s_wd[tid >> 6] = incl;
-        if (tid == 0) { s_pick = kTreeThreads; s_lastpos = -1; }
-        __syncthreads();
-        double before = 0.0, total = 0.0;
+        for (int i = 0; i < kPerLane; ++i) x[i] = load_elem(at, (size_t)(lane + i * 64));
+    } else {
 #pragma unroll
-        for (int wv = 0; wv < kTreeWaves; ++wv) {
-            if (wv < (tid >> 6)) before += s_wd[wv];
-            total += s_wd[wv];
-        }
-        const double target = (double)u[n] * total;
-        if (w > 0.0 && before + incl > target) atomicMin(&s_pick, tid);
-        if (lastpos >= 0) atomicMax(&s_lastpos, lastpos);
-        __syncthreads();
-        if (tid == s_pick) {
-            double cum = before + incl - w;
-            int token = lastpos;                            // rounding left no crossing inside: the last positive entry
-            for (int i = i0; i < i1; ++i) {
-                const double pi = ex(load_elem(lp, (size_t)i), mp) * inv_zp;
-                const double qi = ex(load_elem(lq, (size_t)i), mq) * inv_zq;
-                cum += fmax(pi - c * qi, 0.0);
-                if (cum > target) { token = i; break; }
-            }
-            a.out_token[row] = token;
-        }
-        if (tid == 0) {
-            if (s_pick == kTreeThreads) a.out_token[row] = s_lastpos;      // no crossing at all: last positive entry
-            a.out_path_len[row] = plen;
-            if (a.out_flags) a.out_flags[row] = flags;
-        }
-        return;
+        for (int i = 0; i < kPerLane; ++i) x[i] = lane + i * 64 < left ? load_elem(at, (size_t)(lane + i * 64)) : -INFINITY;
     }
 }
+// a lane's share of a piece's denominators, against maxima taken over the whole wavefront
+__device__ __forceinline__ TreeStat piece_stat(const float (&p)[kPerLane], const float (&q)[kPerLane], double inv_t, const double *exp2tab) {
+    TreeStat t{0.0, 0.0, p[0], q[0]};
+#pragma unroll
+    for (int i = 1; i < kPerLane; ++i) { t.mp = fmaxf(t.mp, p[i]); t.mq = fmaxf(t.mq, q[i]); }
+    t.mp = wave_top_f(t.mp);
+    t.mq = wave_top_f(t.mq);
+    const double dp = (double)t.mp * inv_t, dq = (double)t.mq * inv_t;
+#pragma unroll
+    for (int i = 0; i < kPerLane; ++i) {
+        t.zp += exp_nonpos(fma((double)p[i], inv_t, -dp), exp2tab);
+        t.zq += exp_nonpos(fma((double)q[i], inv_t, -dq), exp2tab);
+    }
+    return t;
+}
+// z against the maximum m, now against `top`; a piece or chunk of -infinities contributes nothing
+__device__ __forceinline__ double against(double z, float m, float top, double inv_t, const double *exp2tab) {
+    return m > -INFINITY ? z * exp_nonpos(fma((double)m, inv_t, -(double)top * inv_t), exp2tab) : 0.0;
+}
+// over the 16 lanes that hold a chunk's pieces
+__device__ __forceinline__ double join_pieces(double v) {
+#pragma unroll
+    for (int o = kPieces / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+__device__ __forceinline__ TreeStat join_pieces(const TreeStat &t, double inv_t, const double *exp2tab) {
+    float mp = t.mp, mq = t.mq;
+#pragma unroll
+    for (int o = kPieces / 2; o > 0; o >>= 1) {
+        mp = fmaxf(mp, __shfl_xor(mp, o, 64));
+        mq = fmaxf(mq, __shfl_xor(mq, o, 64));
+    }
+    return TreeStat{join_pieces(against(t.zp, t.mp, mp, inv_t, exp2tab)), join_pieces(against(t.zq, t.mq, mq, inv_t, exp2tab)), mp, mq};
+}
 
-template <typename T>
-__global__ __launch_bounds__(kTreeThreads) void tree_accept_alone_kernel(TreeAcceptArgs a) { walk_alone<T>(a, blockIdx.x); }
+struct NodeStat { double mp, mq, inv_zp, inv_zq; };                // scaled maxima, reciprocals of the denominators
+// one wavefront, lane = chunk
+__device__ __forceinline__ NodeStat node_stat(const TreeStat *st, int chunks, double inv_t, const double *exp2tab) {
+    const int lane = threadIdx.x & 63;
+    TreeStat t = st[min(lane, chunks - 1)];
+    if (lane >= chunks) t.mp = t.mq = -INFINITY;
+    const float mp = wave_top_f(t.mp), mq = wave_top_f(t.mq);
+    NodeStat s;
+    s.mp = (double)mp * inv_t;
+    s.mq = (double)mq * inv_t;
+    s.inv_zp = 1.0 / wave_total_d(against(t.zp, t.mp, mp, inv_t, exp2tab));
+    s.inv_zq = 1.0 / wave_total_d(against(t.zq, t.mq, mq, inv_t, exp2tab));
+    return s;
+}
+// weight of one entry in the residual max(0, p - c q)
+__device__ __forceinline__ double residual(const NodeStat &s, float lp, float lq, double c, double inv_t, const double *exp2tab) {
+    const double pi = exp_nonpos(fma((double)lp, inv_t, -s.mp), exp2tab) * s.inv_zp;
+    const double qi = exp_nonpos(fma((double)lq, inv_t, -s.mq), exp2tab) * s.inv_zq;
+    return fmax(fma(-c, qi, pi), 0.0);
+}
+// a lane's share of a piece's residual mass
+__device__ __forceinline__ double piece_mass(const NodeStat &s, const float (&p)[kPerLane], const float (&q)[kPerLane], double c,
+                                             double inv_t, const double *exp2tab) {
+    double m = 0.0;
+#pragma unroll
+    for (int i = 0; i < kPerLane; ++i) m += residual(s, p[i], q[i], c, inv_t, exp2tab);
+    return m;
+}
+// (c, mass) of the residual max(0, p - c q) / mass, taken one refusal further: mass 0 means that the residual equalled q,
+// where no refusal can happen
+__device__ __forceinline__ void refuse(double m, double *c, double *mass) {
+    if (m > 0.0) { *c += *mass; *mass = m; }
+}
+// (order-preserving bits of the logit) << 32 | ~index: the largest is the likeliest token, the lowest index among equals
+__device__ __forceinline__ unsigned long long argmax_key(float x, int i) {
+    uint32_t b = __float_as_uint(x);
+    b = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+    return ((unsigned long long)b << 32) | (uint32_t)(~(uint32_t)i);
+}
 
 // ---- the same walk spread over the chip.  What a node's decisions need is taken for all nodes at once, chunk by chunk:
 // tree_stats_kernel (softmax statistics, or the argmax when greedy) and, for nodes with more than j children,
@@ -227,13 +156,9 @@ __global__ __launch_bounds__(kTreeThreads) void tree_accept_alone_kernel(TreeAcc
 // device by the same test in every later block.  Nothing waits.  The last block of the last kernel frees the slot.
 // (Claimed by the 480 blocks of the statistics kernel themselves, the same-address atomics took 13 us.)  Calls under graph capture, vocabularies above 262 144 entries and calls whose
 // statistics exceed a slot (64 sequences x 8 nodes x 32 000 entries need 205 KB) run walk_alone from the start.
-constexpr int kTreeChunk = 4096;                  // entries of one chunk
-constexpr int kTreeMaxChunks = 64;                // per row: one per lane
-constexpr int kMassPasses = 3;                    // further refusals at one node are summed by walk-time passes
 constexpr int kTreeSlots = 4;
 constexpr size_t kTreeSlotBytes = 512 << 10;
 struct TreeSlotHead { uint32_t owner, done, pad[62]; };
-struct TreeStat { double zp, zq; float mp, mq; };                  // sums of exp((l - chunk max) / T), chunk maxima
 __device__ __align__(256) unsigned char g_tree_slots[kTreeSlots * kTreeSlotBytes];
 
 struct TreeShare {
@@ -278,15 +203,17 @@ __global__ void tree_claim_kernel(TreeAcceptArgs a, TreeShare sh) {
         for (int i = threadIdx.x; i < a.rows; i += 64) sv.count[i] = 0u;
 }
 
-constexpr int kStatThreads = 256, kPerThread = kTreeChunk / kStatThreads;
+// Measured (us a call, 256 / 512 / 1024 threads; in the same order of sums): 4 sequences x 15 nodes x 32 000 entries about
+// 41 / 40 / 38, 64 x 7 x 32 000 in bf16 136 / 119 / 130, 8 x 15 x 128 256 101 / 98 / 106.
+constexpr int kStatThreads = 512, kStatWaves = kStatThreads / 64, kWavePieces = kPieces / kStatWaves;
 
+// Grid: rows x nodes x chunks; a wavefront takes kWavePieces pieces of its chunk.
 template <typename T>
 __global__ __launch_bounds__(kStatThreads) void tree_stats_kernel(TreeAcceptArgs a, TreeShare sh) {
     __shared__ double s_exp2[64];
-    __shared__ double s_z[2][kStatThreads / 64];
-    __shared__ float s_m[2][kStatThreads / 64];
-    __shared__ unsigned long long s_k[kStatThreads / 64];
-    const int tid = threadIdx.x, wave = tid >> 6, V = a.vocab;
+    __shared__ TreeStat s_piece[kPieces];
+    __shared__ unsigned long long s_k[kStatWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V = a.vocab;
     const SlotView sv = slot_of(a, sh);
     if (!slot_is_mine(sv, sh)) return;
     if (tid < 64) s_exp2[tid] = kExp2Table[tid];
@@ -294,124 +221,84 @@ __global__ __launch_bounds__(kStatThreads) void tree_stats_kernel(TreeAcceptArgs
     const bool greedy = a.temperature == 0.f;
     const T *lp = (const T *)a.p + (size_t)row * a.p_stride + (size_t)node * V;
     const T *lq = (const T *)a.q + (size_t)row * a.q_stride + (size_t)node * V;
-    const int e0 = c * kTreeChunk + tid;
-    float p[kPerThread], q[kPerThread];
+    const int first = c * kTreeChunk + wave * kWavePieces * kPiece;
+    float p[kWavePieces][kPerLane], q[kWavePieces][kPerLane];
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-        const int e = e0 + i * kStatThreads;
-        p[i] = e < V ? load_elem(lp, (size_t)e) : -INFINITY;
-        q[i] = e < V && !greedy ? load_elem(lq, (size_t)e) : -INFINITY;
+    for (int k = 0; k < kWavePieces; ++k) {
+        load_piece(lp, first + k * kPiece, V, p[k]);
+        load_piece(lq, first + k * kPiece, greedy ? 0 : V, q[k]);
     }
     __syncthreads();
     if (greedy) {
-        unsigned long long best = 0ull;                        // (order-preserving bits of the logit) << 32 | ~index
+        unsigned long long best = 0ull;
 #pragma unroll
-        for (int i = 0; i < kPerThread; ++i) {
-            const int e = e0 + i * kStatThreads;
-            uint32_t b = __float_as_uint(p[i]);
-            b = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-            const unsigned long long key = ((unsigned long long)b << 32) | (uint32_t)(~(uint32_t)e);
-            if (e < V && key > best) best = key;
-        }
+        for (int k = 0; k < kWavePieces; ++k)
+#pragma unroll
+            for (int i = 0; i < kPerLane; ++i) {
+                const int e = first + k * kPiece + lane + i * 64;
+                const unsigned long long key = argmax_key(p[k][i], e);
+                if (e < V && key > best) best = key;
+            }
         best = wave_max(best);
-        if ((tid & 63) == 0) s_k[wave] = best;
+        if (lane == 0) s_k[wave] = best;
         __syncthreads();
         if (tid == 0) {
-            for (int w = 1; w < kStatThreads / 64; ++w) best = s_k[w] > best ? s_k[w] : best;
+            for (int w = 1; w < kStatWaves; ++w) best = s_k[w] > best ? s_k[w] : best;
             *reinterpret_cast<unsigned long long *>(&sv.stat[(size_t)rn * sh.n_chunks + c]) = best;
         }
         return;
     }
-    float mp = -INFINITY, mq = -INFINITY;
+    const double inv_t = 1.0 / (double)a.temperature;
+    TreeStat t[kWavePieces];
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) { mp = fmaxf(mp, p[i]); mq = fmaxf(mq, q[i]); }
-    mp = wave_max(mp);
-    mq = wave_max(mq);
-    if ((tid & 63) == 0) { s_m[0][wave] = mp; s_m[1][wave] = mq; }
-    __syncthreads();
-    mp = fmaxf(fmaxf(s_m[0][0], s_m[0][1]), fmaxf(s_m[0][2], s_m[0][3]));
-    mq = fmaxf(fmaxf(s_m[1][0], s_m[1][1]), fmaxf(s_m[1][2], s_m[1][3]));
-    const double inv_t = 1.0 / (double)a.temperature, dp = (double)mp * inv_t, dq = (double)mq * inv_t;
-    double zp = 0.0, zq = 0.0;
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-        zp += exp_nonpos(fma((double)p[i], inv_t, -dp), s_exp2);
-        zq += exp_nonpos(fma((double)q[i], inv_t, -dq), s_exp2);
+    for (int k = 0; k < kWavePieces; ++k) {
+        t[k] = piece_stat(p[k], q[k], inv_t, s_exp2);
+        t[k].zp = wave_total_d(t[k].zp);
+        t[k].zq = wave_total_d(t[k].zq);
     }
-    zp = wave_sum(zp);
-    zq = wave_sum(zq);
-    if ((tid & 63) == 0) { s_z[0][wave] = zp; s_z[1][wave] = zq; }
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < kWavePieces; ++k) s_piece[wave * kWavePieces + k] = t[k];
     __syncthreads();
-    if (tid == 0)
-        sv.stat[(size_t)rn * sh.n_chunks + c] = TreeStat{((s_z[0][0] + s_z[0][1]) + s_z[0][2]) + s_z[0][3],
-                                                         ((s_z[1][0] + s_z[1][1]) + s_z[1][2]) + s_z[1][3], mp, mq};
-}
-
-struct NodeStat { double mp, mq, inv_zp, inv_zq; };                // scaled maxima, reciprocals of the denominators
-// one wavefront, lane = chunk
-__device__ __forceinline__ NodeStat node_stat(const TreeStat *st, int chunks, double inv_t, const double *exp2tab) {
-    const int lane = threadIdx.x & 63;
-    const TreeStat t = st[min(lane, chunks - 1)];
-    const float mp = wave_max(t.mp), mq = wave_max(t.mq);
-    NodeStat s;
-    s.mp = (double)mp * inv_t;
-    s.mq = (double)mq * inv_t;
-    // a chunk of -infinities contributes nothing
-    const bool in = lane < chunks;
-    const double zp = in && t.mp > -INFINITY ? t.zp * exp_nonpos(fma((double)t.mp, inv_t, -s.mp), exp2tab) : 0.0;
-    const double zq = in && t.mq > -INFINITY ? t.zq * exp_nonpos(fma((double)t.mq, inv_t, -s.mq), exp2tab) : 0.0;
-    s.inv_zp = 1.0 / wave_sum(zp);
-    s.inv_zq = 1.0 / wave_sum(zq);
-    return s;
-}
-// (c, mass) of the residual max(0, p - c q) / mass, taken one refusal further: mass 0 means that the residual equalled q,
-// where no refusal can happen
-__device__ __forceinline__ void refuse(double m, double *c, double *mass) {
-    if (m > 0.0) { *c += *mass; *mass = m; }
+    if (wave != 0) return;
+    const TreeStat all = join_pieces(s_piece[lane % kPieces], inv_t, s_exp2);
+    if (lane == 0) sv.stat[(size_t)rn * sh.n_chunks + c] = all;
 }
 
 // M_{j+1} = sum max(0, p - c q) of one chunk of one node, c after j refusals and the next
 template <typename T>
 __global__ __launch_bounds__(kStatThreads) void tree_mass_kernel(TreeAcceptArgs a, TreeShare sh, int j) {
     __shared__ double s_exp2[64];
-    __shared__ double s_w[kStatThreads / 64];
-    const int tid = threadIdx.x, wave = tid >> 6, V = a.vocab;
+    __shared__ double s_piece[kPieces];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V = a.vocab;
     const SlotView sv = slot_of(a, sh);
     if (!slot_is_mine(sv, sh)) return;
     if (tid < 64) s_exp2[tid] = kExp2Table[tid];
     const int ch = sh.n_chunks, c = blockIdx.x % ch, rn = blockIdx.x / ch, row = rn / sh.n_inner[j];
     const int node = sh.inner[j][rn % sh.n_inner[j]];
-    const T *lp = (const T *)a.p + (size_t)row * a.p_stride + (size_t)node * V;
-    const T *lq = (const T *)a.q + (size_t)row * a.q_stride + (size_t)node * V;
-    const int e0 = c * kTreeChunk + tid;
-    float p[kPerThread], q[kPerThread];
+    const int first = c * kTreeChunk + wave * kWavePieces * kPiece;
+    float p[kWavePieces][kPerLane], q[kWavePieces][kPerLane];
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-        const int e = e0 + i * kStatThreads;
-        p[i] = e < V ? load_elem(lp, (size_t)e) : -INFINITY;
-        q[i] = e < V ? load_elem(lq, (size_t)e) : -INFINITY;
+    for (int k = 0; k < kWavePieces; ++k) {
+        load_piece((const T *)a.p + (size_t)row * a.p_stride + (size_t)node * V, first + k * kPiece, V, p[k]);
+        load_piece((const T *)a.q + (size_t)row * a.q_stride + (size_t)node * V, first + k * kPiece, V, q[k]);
     }
     __syncthreads();
     const double inv_t = 1.0 / (double)a.temperature;
     const size_t at = ((size_t)row * a.n_nodes + node) * ch, pass = (size_t)a.rows * a.n_nodes * ch;
     const NodeStat s = node_stat(sv.stat + at, ch, inv_t, s_exp2);
     double cc = 0.0, mass = 1.0;
-    for (int t = 0; t < j; ++t) {
-        const int lane = tid & 63;
-        refuse(wave_sum(lane < ch ? sv.mass[t * pass + at + lane] : 0.0), &cc, &mass);
-    }
-    cc += mass;
-    double m = 0.0;
+    for (int t = 0; t < j; ++t) refuse(wave_total_d(lane < ch ? sv.mass[t * pass + at + lane] : 0.0), &cc, &mass);
+    double m[kWavePieces];
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-        const double pi = exp_nonpos(fma((double)p[i], inv_t, -s.mp), s_exp2) * s.inv_zp;
-        const double qi = exp_nonpos(fma((double)q[i], inv_t, -s.mq), s_exp2) * s.inv_zq;
-        m += fmax(pi - cc * qi, 0.0);
-    }
-    m = wave_sum(m);
-    if ((tid & 63) == 0) s_w[wave] = m;
+    for (int k = 0; k < kWavePieces; ++k) m[k] = wave_total_d(piece_mass(s, p[k], q[k], cc + mass, inv_t, s_exp2));
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < kWavePieces; ++k) s_piece[wave * kWavePieces + k] = m[k];
     __syncthreads();
-    if (tid == 0) sv.mass[j * pass + at + c] = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
+    if (wave != 0) return;
+    const double all = join_pieces(s_piece[lane % kPieces]);
+    if (lane == 0) sv.mass[j * pass + at + c] = all;
 }
 
 // this call's last access to the slot: whoever counts last hands it back
@@ -425,21 +312,84 @@ __device__ __forceinline__ void slot_leave(const SlotView &s, unsigned blocks) {
     __hip_atomic_store(&s.head->owner, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Grid: rows x chunks (greedy: rows).  kTreeThreads threads, each on kTreeChunk / kTreeThreads consecutive entries.
+// Greedy matching of one sequence by one block.
 template <typename T>
-__device__ void shared_walk(const TreeAcceptArgs &a, const TreeShare &sh, const SlotView &sv, int row, int chunk, int chunks) {
+__device__ void walk_alone_greedy(const TreeAcceptArgs &a, int row) {
+    __shared__ int s_par[kTreeMaxAcceptNodes];
+    __shared__ unsigned long long s_best;
+    const int tid = threadIdx.x, n = a.n_nodes, V = a.vocab;
+    for (int j = tid; j < n; j += kTreeThreads) s_par[j] = a.parents[j];
+    __syncthreads();
+    const T *P = (const T *)a.p + (size_t)row * a.p_stride;
+    const int32_t *tok = a.tokens + (size_t)row * n;
+    int32_t *path = a.out_path + (size_t)row * n;
+    int node = 0, plen = 0;
+    while (true) {                                          // every descent moves to a larger node index: at most n rounds
+        const T *lp = P + (size_t)node * V;
+        unsigned long long best = 0ull;
+        for (int i = tid; i < V; i += kTreeThreads) {
+            const unsigned long long key = argmax_key(load_elem(lp, (size_t)i), i);
+            best = key > best ? key : best;
+        }
+        best = wave_max(best);
+        if (tid == 0) s_best = 0ull;
+        __syncthreads();
+        if ((tid & 63) == 0) atomicMax(&s_best, best);
+        __syncthreads();
+        const int top = (int)(~(uint32_t)(s_best & 0xffffffffull));
+        int next = -1;
+        for (int c = node + 1; c < n && next < 0; ++c)
+            if (s_par[c] == node && tok[c] == top) next = c;
+        __syncthreads();                                    // s_best is reset by the next round
+        if (next < 0) {
+            if (tid == 0) { a.out_path_len[row] = plen; a.out_token[row] = top; if (a.out_flags) a.out_flags[row] = 0; }
+            return;
+        }
+        if (tid == 0) path[plen] = next;
+        ++plen;
+        node = next;
+    }
+}
+
+// Greedy matching of one sequence on the argmax of every chunk of every node.
+__device__ void walk_shared_greedy(const TreeAcceptArgs &a, const SlotView &sv, int row, int chunks) {
+    __shared__ int s_top[kTreeMaxAcceptNodes];
+    const int tid = threadIdx.x, lane = tid & 63, n = a.n_nodes;
+    const int32_t *tok = a.tokens + (size_t)row * n;
+    for (int v = tid >> 6; v < n; v += kTreeWaves) {
+        const TreeStat *st = sv.stat + ((size_t)row * n + v) * chunks + min(lane, chunks - 1);
+        const unsigned long long best = wave_max(*reinterpret_cast<const unsigned long long *>(st));
+        if (lane == 0) s_top[v] = (int)(~(uint32_t)(best & 0xffffffffull));
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    int node = 0, plen = 0;
+    for (int c = 1; c < n; ++c)                               // a node's children follow it, so one sweep walks the path
+        if (a.parents[c] == node && tok[c] == s_top[node]) { a.out_path[(size_t)row * n + plen++] = c; node = c; }
+    a.out_path_len[row] = plen;
+    a.out_token[row] = s_top[node];
+    if (a.out_flags) a.out_flags[row] = 0;
+}
+
+// The walk of one sequence.  ALONE: by one block, which takes the statistics of the nodes it visits itself and needs no
+// memory to share (more than kTreeMaxChunks chunks: longer ones, of `sub` times kTreeChunk entries).  Otherwise by
+// `chunks` blocks on what the kernels above left in the slot: block `chunk` sums the draw's weights over its chunk, and
+// the one that counts itself in last finds the token.
+template <typename T, bool ALONE>
+__device__ void walk(const TreeAcceptArgs &a, const SlotView &sv, int row, int chunk, int chunks, int sub) {
     constexpr int E = kTreeChunk / kTreeThreads;
     __shared__ double s_wd[kTreeWaves], s_exp2[64];
-    __shared__ NodeStat s_node[kTreeMaxAcceptNodes];
-    __shared__ double s_mass[kMassPasses][kTreeMaxAcceptNodes], s_px[kTreeMaxAcceptNodes], s_qx[kTreeMaxAcceptNodes];
+    __shared__ NodeStat s_node[ALONE ? 1 : kTreeMaxAcceptNodes];
+    __shared__ double s_mass[ALONE ? 1 : kMassPasses][kTreeMaxAcceptNodes], s_px[kTreeMaxAcceptNodes], s_qx[kTreeMaxAcceptNodes];
     __shared__ float s_u[kTreeMaxAcceptNodes + 1];
-    __shared__ int s_par[kTreeMaxAcceptNodes], s_tok[kTreeMaxAcceptNodes], s_top[kTreeMaxAcceptNodes], s_kids[kTreeMaxAcceptNodes];
+    __shared__ int s_par[kTreeMaxAcceptNodes], s_tok[kTreeMaxAcceptNodes], s_kids[kTreeMaxAcceptNodes];
     __shared__ int s_pick, s_lastpos, s_chunk, s_last;
-    __shared__ double s_c, s_base;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = a.n_nodes, V = a.vocab;
+    __shared__ double s_target, s_base;
+    __shared__ TreeStat s_piece[ALONE ? kTreeMaxChunks * kPieces : 1], s_chunk_stat[ALONE ? kTreeMaxChunks : 1];
+    __shared__ double s_part[ALONE ? kTreeMaxChunks : 1][kPieces + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = a.n_nodes, V = a.vocab, length = sub * kTreeChunk;
     const T *P = (const T *)a.p + (size_t)row * a.p_stride;
     const T *Q = (const T *)a.q + (size_t)row * a.q_stride;
-    const bool greedy = a.temperature == 0.f;
     const double inv_t = 1.0 / (double)a.temperature;
     int32_t *path = a.out_path + (size_t)row * n;
     if (tid < 64) s_exp2[tid] = kExp2Table[tid];
@@ -448,69 +398,125 @@ __device__ void shared_walk(const TreeAcceptArgs &a, const TreeShare &sh, const 
         s_tok[tid] = a.tokens[(size_t)row * n + tid];
         s_kids[tid] = 0;
     }
-    if (!greedy && tid <= n) s_u[tid] = a.uniforms[(size_t)row * (n + 1) + tid];
+    if (tid <= n) s_u[tid] = a.uniforms[(size_t)row * (n + 1) + tid];
     __syncthreads();
     if (tid > 0 && tid < n) atomicAdd(&s_kids[s_par[tid]], 1);
-    const size_t row_at = (size_t)row * n * chunks;
-    if (greedy) {
+    __syncthreads();
+    NodeStat here;                                              // alone: of the node the walk is at
+    auto stat_of = [&](int v) {
+        if constexpr (ALONE) return here;
+        else return s_node[v];
+    };
+    // the probabilities at its parent of the token that node v carries
+    auto probe = [&](int v) {
+        const NodeStat s = stat_of(s_par[v]);
+        const size_t at = (size_t)s_par[v] * V + min(max(s_tok[v], 0), V - 1);
+        s_px[v] = exp_nonpos(fma((double)load_elem(P, at), inv_t, -s.mp), s_exp2) * s.inv_zp;
+        s_qx[v] = exp_nonpos(fma((double)load_elem(Q, at), inv_t, -s.mq), s_exp2) * s.inv_zq;
+    };
+    if constexpr (!ALONE) {
+        // every node's statistics and masses, then every child's probabilities, all at once
+        const size_t row_at = (size_t)row * n * chunks;
         for (int v = wave; v < n; v += kTreeWaves) {
-            const unsigned long long k = *reinterpret_cast<const unsigned long long *>(&sv.stat[row_at + (size_t)v * chunks + min(lane, chunks - 1)]);
-            const unsigned long long best = wave_max(k);
-            if (lane == 0) s_top[v] = (int)(~(uint32_t)(best & 0xffffffffull));
+            const NodeStat s = node_stat(sv.stat + row_at + (size_t)v * chunks, chunks, inv_t, s_exp2);
+            double m[kMassPasses];
+#pragma unroll
+            for (int j = 0; j < kMassPasses; ++j) {
+                const bool there = s_kids[v] > j + 1 && lane < chunks;
+                m[j] = wave_total_d(there ? sv.mass[((size_t)j * a.rows * n + (size_t)row * n + v) * chunks + lane] : 0.0);
+            }
+            if (lane == 0) {
+                s_node[v] = s;
+#pragma unroll
+                for (int j = 0; j < kMassPasses; ++j) s_mass[j][v] = m[j];
+            }
         }
         __syncthreads();
-        if (tid == 0) {
-            int node = 0, plen = 0;
-            for (int c = 1; c < n; ++c)                       // a node's children follow it, so one sweep walks the path
-                if (s_par[c] == node && s_tok[c] == s_top[node]) { path[plen++] = c; node = c; }
-            a.out_path_len[row] = plen;
-            a.out_token[row] = s_top[node];
-            if (a.out_flags) a.out_flags[row] = 0;
-        }
-        return;
+        if (tid > 0 && tid < n) probe(tid);
+        __syncthreads();
     }
-    // every node's statistics and masses, then every child's probabilities at its parent, all at once
-    __syncthreads();
-    for (int v = wave; v < n; v += kTreeWaves) {
-        const NodeStat s = node_stat(sv.stat + row_at + (size_t)v * chunks, chunks, inv_t, s_exp2);
-        double m[kMassPasses];
-#pragma unroll
-        for (int j = 0; j < kMassPasses; ++j) {
-            const bool there = s_kids[v] > j + 1 && lane < chunks;
-            m[j] = wave_sum(there ? sv.mass[((size_t)j * a.rows * n + (size_t)row * n + v) * chunks + lane] : 0.0);
+    // alone: statistics of a node, then its children's probabilities
+    auto visit = [&](int v) {
+        const T *lp = P + (size_t)v * V, *lq = Q + (size_t)v * V;
+        for (int c = 0; c < chunks; ++c) {
+            TreeStat all{0.0, 0.0, -INFINITY, -INFINITY};
+            for (int k = 0; k < sub; ++k) {
+                const int first = c * length + k * kTreeChunk + wave * kPiece;
+                if (first >= V) break;                          // the same for the wavefront
+                float p[kPerLane], q[kPerLane];
+                load_piece(lp, first, V, p);
+                load_piece(lq, first, V, q);
+                const TreeStat t = piece_stat(p, q, inv_t, s_exp2);
+                if (k == 0) {
+                    all = t;
+                } else {
+                    const float mp = fmaxf(all.mp, t.mp), mq = fmaxf(all.mq, t.mq);
+                    all.zp = against(all.zp, all.mp, mp, inv_t, s_exp2) + against(t.zp, t.mp, mp, inv_t, s_exp2);
+                    all.zq = against(all.zq, all.mq, mq, inv_t, s_exp2) + against(t.zq, t.mq, mq, inv_t, s_exp2);
+                    all.mp = mp;
+                    all.mq = mq;
+                }
+            }
+            all.zp = wave_total_d(all.zp);
+            all.zq = wave_total_d(all.zq);
+            if (lane == 0) s_piece[c * kPieces + wave] = all;
         }
-        if (lane == 0) {
-            s_node[v] = s;
-#pragma unroll
-            for (int j = 0; j < kMassPasses; ++j) s_mass[j][v] = m[j];
+        __syncthreads();
+        if (wave * 64 < chunks * kPieces) {                     // one piece a lane
+            const TreeStat t = join_pieces(s_piece[min(tid, chunks * kPieces - 1)], inv_t, s_exp2);
+            if (tid % kPieces == 0 && tid < chunks * kPieces) s_chunk_stat[tid / kPieces] = t;
         }
-    }
-    __syncthreads();
-    if (tid > 0 && tid < n) {
-        const NodeStat s = s_node[s_par[tid]];
-        const int x = min(max(s_tok[tid], 0), V - 1);
-        const size_t at = (size_t)s_par[tid] * V + x;
-        s_px[tid] = exp_nonpos(fma((double)load_elem(P, at), inv_t, -s.mp), s_exp2) * s.inv_zp;
-        s_qx[tid] = exp_nonpos(fma((double)load_elem(Q, at), inv_t, -s.mq), s_exp2) * s.inv_zq;
-    }
-    __syncthreads();
-    // the walk (every thread alike): at a node the children are tried in index order
-    auto entry = [&](const NodeStat &s, const T *lp, const T *lq, int e, double c) {
-        const double pi = exp_nonpos(fma((double)load_elem(lp, (size_t)e), inv_t, -s.mp), s_exp2) * s.inv_zp;
-        const double qi = exp_nonpos(fma((double)load_elem(lq, (size_t)e), inv_t, -s.mq), s_exp2) * s.inv_zq;
-        return fmax(pi - c * qi, 0.0);
+        __syncthreads();
+        here = node_stat(s_chunk_stat, chunks, inv_t, s_exp2);
+        if (tid > v && tid < n && s_par[tid] == v) probe(tid);
+        __syncthreads();
     };
-    auto mass_of_row = [&](int node, double c) {                // a pass by this block: past the precomputed refusals
+    // alone: the sums over the chunks of what f(chunk) gives each lane, chunk l in lane l
+    auto by_chunks = [&](auto f) {
+        for (int c = 0; c < chunks; ++c) {
+            const double m = wave_total_d(f(c));
+            if (lane == 0) s_part[c][wave] = m;
+        }
+        __syncthreads();
+        double v[kPieces];                                      // added in join_pieces' order
+#pragma unroll
+        for (int k = 0; k < kPieces; ++k) v[k] = s_part[min(lane, chunks - 1)][k];
+#pragma unroll
+        for (int o = kPieces / 2; o > 0; o >>= 1)
+#pragma unroll
+            for (int k = 0; k < o; ++k) v[k] += v[k + o];
+        __syncthreads();                                        // s_part: read before the next pass writes it
+        return lane < chunks ? v[0] : 0.0;
+    };
+    auto mass_by_chunks = [&](int v, double c) {
+        const T *lp = P + (size_t)v * V, *lq = Q + (size_t)v * V;
+        const NodeStat s = stat_of(v);
+        return wave_total_d(by_chunks([&](int ch) {
+            double m = 0.0;
+            for (int first = ch * length + wave * kPiece; first < min(ch * length + length, V); first += kTreeChunk) {
+                float p[kPerLane], q[kPerLane];
+                load_piece(lp, first, V, p);
+                load_piece(lq, first, V, q);
+                m += piece_mass(s, p, q, c, inv_t, s_exp2);
+            }
+            return m;
+        }));
+    };
+    auto mass_of_row = [&](int v, double c) {                   // past the first kMassPasses refusals
+        const NodeStat s = stat_of(v);
         double m = 0.0;
-        for (int e = tid; e < V; e += kTreeThreads) m += entry(s_node[node], P + (size_t)node * V, Q + (size_t)node * V, e, c);
+        for (int e = tid; e < V; e += kTreeThreads)
+            m += residual(s, load_elem(P, (size_t)v * V + e), load_elem(Q, (size_t)v * V + e), c, inv_t, s_exp2);
         return block_sum_d(m, s_wd);
     };
+    // the walk (every thread alike): at a node the children are tried in index order
     const bool writer = chunk == 0 && tid == 0;
     int node = 0, plen = 0, flags = 0;
     double c = 0.0, mass = 1.0, c_before = 0.0;
-    while (true) {
+    while (true) {                                              // every descent moves to a larger node index: at most n rounds
+        if constexpr (ALONE) visit(node);
         int next = -1, tried = 0;
-        c = 0.0; mass = 1.0; c_before = 0.0;
+        c = 0.0; mass = 1.0; c_before = 0.0;                    // the residual here is max(0, p - c q) / mass
         for (int k = node + 1; k < n; ++k) {
             if (s_par[k] != node) continue;
             ++tried;
@@ -520,32 +526,55 @@ __device__ void shared_walk(const TreeAcceptArgs &a, const TreeShare &sh, const 
             if (fabs(uu - thr) < 1e-5) flags |= PSD_FLAG_NEAR_TIE;
             if (uu < thr) { next = k; break; }
             c_before = c;
-            if (tried == s_kids[node]) c += mass;             // the draw's own sums say whether anything is left
-            else refuse(tried <= kMassPasses ? s_mass[tried - 1][node] : mass_of_row(node, c + mass), &c, &mass);
+            if (tried == s_kids[node]) { c += mass; continue; } // the draw's own sums say whether anything is left
+            double m;
+            if (tried > kMassPasses) m = mass_of_row(node, c + mass);
+            else if constexpr (ALONE) m = mass_by_chunks(node, c + mass);
+            else m = s_mass[tried - 1][node];
+            refuse(m, &c, &mass);
         }
         if (next < 0) break;
         if (writer) path[plen] = next;
         ++plen;
         node = next;
     }
-    // one draw from max(0, p - c q): this block's chunk
-    const NodeStat s = s_node[node];
+    // one draw from max(0, p - c q) by inverse CDF in index order: first the weight of every chunk
+    const NodeStat s = stat_of(node);
     const T *lp = P + (size_t)node * V, *lq = Q + (size_t)node * V;
-    const int i0 = min(chunk * kTreeChunk + tid * E, V), i1 = min(i0 + E, V);
-    double w = 0.0;
+    auto entry = [&](int e, double at_c) {
+        return residual(s, load_elem(lp, (size_t)e), load_elem(lq, (size_t)e), at_c, inv_t, s_exp2);
+    };
+    auto my_share = [&](int ch) {                               // of chunk ch: E consecutive entries of every kTreeChunk
+        double w = 0.0;
+        for (int t0 = ch * length; t0 < min(ch * length + length, V); t0 += kTreeChunk) {
+            const int i0 = min(t0 + tid * E, V), i1 = min(i0 + E, V);
 #pragma unroll
-    for (int k = 0; k < E; ++k)
-        if (i0 + k < i1) w += entry(s, lp, lq, i0 + k, c);
-    w = block_sum_d(w, s_wd);
-    if (tid == 0) {
-        __hip_atomic_store(sv.part + (size_t)row * chunks + chunk, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        s_last = __hip_atomic_fetch_add(sv.count + row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)chunks - 1u;
+            for (int k = 0; k < E; ++k)
+                if (i0 + k < i1) w += entry(i0 + k, c);
+        }
+        return w;
+    };
+    double mine = 0.0;                                          // first wavefront: the weight of chunk `lane`
+    if constexpr (ALONE) {
+        mine = by_chunks(my_share);
+    } else {
+        const double part = wave_total_d(my_share(chunk));
+        if (lane == 0) s_wd[wave] = part;
+        __syncthreads();
+        if (wave == 0) {
+            const double w = join_pieces(s_wd[lane % kPieces]);
+            if (lane == 0) {
+                __hip_atomic_store(sv.part + (size_t)row * chunks + chunk, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                s_last = __hip_atomic_fetch_add(sv.count + row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)chunks - 1u;
+            }
+        }
+        __syncthreads();
+        if (!s_last) return;
+        if (wave == 0 && lane < chunks)
+            mine = __hip_atomic_load(sv.part + (size_t)row * chunks + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
-    if (!s_last) return;
     if (wave == 0) {
-        const double mine = lane < chunks ? __hip_atomic_load(sv.part + (size_t)row * chunks + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
         double incl = mine;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -559,31 +588,31 @@ __device__ void shared_walk(const TreeAcceptArgs &a, const TreeShare &sh, const 
         if (lane == (pick < 0 ? 0 : pick)) {
             s_chunk = pick;
             s_base = incl - mine;
-            s_c = target;
+            s_target = target;
         }
     }
     if (tid == 0) { s_pick = kTreeThreads; s_lastpos = -1; }
     __syncthreads();
-    int first = s_chunk * kTreeChunk, last = min(first + kTreeChunk, V);
-    double base = s_base, target = s_c;
+    int first = s_chunk * length, last = min(first + length, V);
+    double base = s_base, target = s_target;
     if (s_chunk < 0 && c != c_before) {
         // the last refusal left a mass of exactly 0 (the residual equalled q): the draw is from what was there before it
         c = c_before;
         target = (double)s_u[n] * mass_of_row(node, c);
     }
-    if (s_chunk < 0) { first = 0; last = V; base = 0.0; }       // all of the row, a chunk at a time
+    if (s_chunk < 0) { first = 0; last = V; base = 0.0; }       // all of the row
     __syncthreads();
     for (int t0 = first; t0 < last; t0 += kTreeChunk) {
         const int j0 = min(t0 + tid * E, last), j1 = min(j0 + E, last);
-        double wv[E], mine = 0.0;
+        double wv[E], sum = 0.0;
         int lastpos = -1;
 #pragma unroll
         for (int k = 0; k < E; ++k) {
-            wv[k] = j0 + k < j1 ? entry(s, lp, lq, j0 + k, c) : 0.0;
+            wv[k] = j0 + k < j1 ? entry(j0 + k, c) : 0.0;
             if (wv[k] > 0.0) lastpos = j0 + k;
-            mine += wv[k];
+            sum += wv[k];
         }
-        double incl = mine;
+        double incl = sum;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const double up = __shfl_up(incl, o, 64);
@@ -598,12 +627,12 @@ __device__ void shared_walk(const TreeAcceptArgs &a, const TreeShare &sh, const 
             if (v < wave) before += s_wd[v];
             total += s_wd[v];
         }
-        if (mine > 0.0 && before + incl > target) atomicMin(&s_pick, tid);
+        if (sum > 0.0 && before + incl > target) atomicMin(&s_pick, tid);
         if (lastpos >= 0) atomicMax(&s_lastpos, lastpos);
         __syncthreads();
         if (s_pick < kTreeThreads) {
             if (tid == s_pick) {
-                double cum = before + incl - mine;
+                double cum = before + incl - sum;
                 int token = lastpos;                            // rounding left no crossing inside: the last positive entry
                 bool found = false;
 #pragma unroll
@@ -625,14 +654,29 @@ __device__ void shared_walk(const TreeAcceptArgs &a, const TreeShare &sh, const 
 }
 
 template <typename T>
+__device__ __forceinline__ void walk_alone(const TreeAcceptArgs &a, int row) {
+    if (a.temperature == 0.f) return walk_alone_greedy<T>(a, row);
+    const int tiles = (a.vocab + kTreeChunk - 1) / kTreeChunk, sub = (tiles + kTreeMaxChunks - 1) / kTreeMaxChunks;
+    walk<T, true>(a, SlotView{}, row, 0, (tiles + sub - 1) / sub, sub);
+}
+template <typename T>
+__global__ __launch_bounds__(kTreeThreads) void tree_accept_alone_kernel(TreeAcceptArgs a) { walk_alone<T>(a, blockIdx.x); }
+
+// Grid: rows x chunks (greedy: rows).
+template <typename T>
 __global__ __launch_bounds__(kTreeThreads) void tree_draw_kernel(TreeAcceptArgs a, TreeShare sh) {
     const SlotView sv = slot_of(a, sh);
     const bool mine = slot_is_mine(sv, sh);                 // only this call's blocks can end that, after all have counted
-    const int chunks = sh.n_chunks, per_row = a.temperature == 0.f ? 1 : chunks;
+    const bool greedy = a.temperature == 0.f;
+    const int per_row = greedy ? 1 : sh.n_chunks;
     const int chunk = blockIdx.x % per_row, row = blockIdx.x / per_row;
-    if (mine) shared_walk<T>(a, sh, sv, row, chunk, chunks);
-    else if (chunk == 0) walk_alone<T>(a, row);
-    if (mine) slot_leave(sv, gridDim.x);
+    if (!mine) {
+        if (chunk == 0) walk_alone<T>(a, row);
+        return;
+    }
+    if (greedy) walk_shared_greedy(a, sv, row, sh.n_chunks);
+    else walk<T, false>(a, sv, row, chunk, sh.n_chunks, 1);
+    slot_leave(sv, gridDim.x);
 }
 
 // One block per (layer, sequence, KV head).  Thread t moves element t of the d_h-long K row and of the V^T column of

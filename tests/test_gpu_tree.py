@@ -171,6 +171,33 @@ def test_tree_accept_overlapping_streams_and_capture():
         assert all(torch.equal(a, b) for a, b in zip(out, want[0])), rep
 
 
+@pytest.mark.parametrize("name,V,dtype", [("root", 12000, torch.float32), ("star6", 60000, torch.float32),
+                                          ("chain5", 33333, torch.bfloat16), ("star6", 4100, torch.float32)])
+def test_tree_accept_adds_in_one_order(name, V, dtype):
+    """Logits of two values each and uniforms at multiples of 1/16, so that the draw's crossing is an exact tie that the
+    rounding of the sums decides: a captured call (one block per sequence) and an eager one (spread over the chip) have to
+    add in the same order to give the same token.  Every child is refused; one of six, past the refusals summed ahead."""
+    TREES["root"], TREES["star6"] = [-1], [-1] + [0] * 6
+    parents, rows = TREES[name], 16
+    n = len(parents)
+    p = torch.zeros((rows, n, V), dtype=dtype, device="cuda")
+    q = torch.zeros_like(p)
+    p[..., ::3] = 0.75
+    q[..., ::2] = 0.25
+    toks = torch.ones((rows, n), dtype=torch.int32, device="cuda")
+    u = torch.full((rows, n + 1), 1.0 - 2.0 ** -24, device="cuda")
+    u[:, n] = torch.arange(rows, device="cuda") / rows
+    eager = [x.clone() for x in runtime.tree_accept(p, q, toks, parents, u, 1.0)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = runtime.tree_accept(p, q, toks, parents, u, 1.0)
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, eager))
+
+
 def test_tree_accept_overlapping_calls_of_both_types():
     """fp32 and bf16 calls, of different batches, trees and vocabularies and a greedy one among them, in turn on two and
     on five streams: a call must never take the scratch another one is using for its own."""
