@@ -252,10 +252,12 @@ psd_status psd_kv_truncate_to(psd_kv *kv, int32_t new_len, void *hip_stream);
  *   tokens_dev device int32[rows][n_nodes] (entry 0 unused); uniforms device fp32[rows][n_nodes + 1] (entry 0 unused).
  *   Outputs (device): out_path_len[rows]; out_path[rows][n_nodes]: the accepted nodes root first, root excluded
  *   (entries past the length are not written); out_token[rows]; out_flags[rows] or NULL (PSD_FLAG_NEAR_TIE as in
- *   psd_spec_accept).  Everything that decides a token runs in fp64.  Limits: n_nodes <= 64.  Needs no workspace:
- *   the statistics of all nodes go through one of four 512 KB slots built into the library, which calls take and hand
- *   back on the device; calls that overlap on other streams are safe, one that finds its slot taken (or is captured into
- *   a graph, or too large for a slot) runs on one block per sequence, several passes over two logits rows per node.
+ *   psd_spec_accept).  Everything that decides a token runs in fp64.  Limits: n_nodes <= 64.  Needs no workspace: where
+ *   it pays, a call spreads over the chip and the statistics of all nodes go through one of four 512 KB slots built into
+ *   the library, the one its number (counted over all calls) selects, which it takes and hands back on the device.  Calls
+ *   that overlap on other streams are safe: one that finds its slot taken (or is greedy, small, captured into a graph or
+ *   too large for a slot) runs on one block per sequence, several passes over two logits rows per node.  Either way adds
+ *   in the same order, so the results are the same.
  *
  * psd_kv_compact_tree: after the acceptance, for every sequence b with base = base_lens_dev[b] (the length before the
  *   tree pass): the K/V rows of the accepted nodes move to slots base + 1 .. base + path_len[b] (the root stays at

@@ -6,7 +6,8 @@
 //   tree_stats / mass / draw_kernel  the walk from the root: at a node the children are tried in index order against the
 //                            running residual of the verifier's distribution, the first accepted child is descended
 //                            into, and where none is accepted one token is drawn from what is left; every pass over
-//                            the vocabulary is spread over the chip (tree_accept_alone_kernel: by one block per sequence);
+//                            the vocabulary is spread over the chip;
+//   tree_accept_alone_kernel the same by one block per sequence: greedy matching, small calls, captured ones;
 //   kv_compact_tree_kernel   after acceptance: the accepted nodes' K/V rows move to consecutive cache positions.
 //
 // The residual after j refusals at one node needs no vector: with p, q the two distributions at the node,
@@ -142,20 +143,20 @@ __device__ __forceinline__ unsigned long long argmax_key(float x, int i) {
 }
 
 // ---- the same walk spread over the chip.  What a node's decisions need is taken for all nodes at once, chunk by chunk:
-// tree_stats_kernel (softmax statistics, or the argmax when greedy) and, for nodes with more than j children,
-// tree_mass_kernel j (the residual mass M_j after j refusals, j = 1 .. kMassPasses); then every block of
-// tree_draw_kernel walks the tree on those numbers, sums the weights of its chunk of the row the draw reads, and the
-// block of a sequence that arrives last finds the token.  Bound by fp64 arithmetic (2 exponentials per entry and pass):
-// one block needs about 15 us per pass of 32 000 entries and makes ten of them.  Four sequences x 15 nodes x 32 000
-// entries (fp32 logits): 128 us with a block per sequence, 44 us this way
-// (2 + 9 + 10 + 24 for claim, statistics, one mass pass and the draw).
+// tree_stats_kernel (softmax statistics) and, for nodes with more than j children, tree_mass_kernel j (the residual mass M_j
+// after j refusals, j = 1 .. kMassPasses); then every block of tree_draw_kernel walks the tree on those numbers, sums the
+// weights of its chunk of the row the draw reads, and the block of a sequence that arrives last finds the token.  Bound by
+// fp64 arithmetic (2 exponentials per entry and pass: one block needs about 15 us per pass of 32 000 entries) and by the
+// launches.  Four sequences x 15 nodes x 32 000 entries (fp32 logits): 127 us with a block per sequence, 41 us this way;
+// which way a call goes: spread_pays.
 //
 // The statistics travel through a slot of a static array, so that the call needs no workspace.  Calls on different
 // streams may overlap: a call has a number of its own (the host counts them) and tree_claim_kernel takes the slot that
 // number selects, by compare-and-swap, if it is free.  A call that did not get it falls back to walk_alone, decided on the
 // device by the same test in every later block.  Nothing waits.  The last block of the last kernel frees the slot.
-// (Claimed by the 480 blocks of the statistics kernel themselves, the same-address atomics took 13 us.)  Calls under graph capture, vocabularies above 262 144 entries and calls whose
-// statistics exceed a slot (64 sequences x 8 nodes x 32 000 entries need 205 KB) run walk_alone from the start.
+// (Claimed by the 480 blocks of the statistics kernel themselves, the same-address atomics took 13 us.)  Calls under graph
+// capture, vocabularies above 262 144 entries and calls whose statistics exceed a slot (64 sequences x 8 nodes x 32 000
+// entries need 213 KB, 24 bytes and kMassPasses times 8 a chunk and node) run walk_alone from the start.
 constexpr int kTreeSlots = 4;
 constexpr size_t kTreeSlotBytes = 512 << 10;
 struct TreeSlotHead { uint32_t owner, done, pad[62]; };
@@ -212,13 +213,11 @@ template <typename T>
 __global__ __launch_bounds__(kStatThreads) void tree_stats_kernel(TreeAcceptArgs a, TreeShare sh) {
     __shared__ double s_exp2[64];
     __shared__ TreeStat s_piece[kPieces];
-    __shared__ unsigned long long s_k[kStatWaves];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V = a.vocab;
     const SlotView sv = slot_of(a, sh);
     if (!slot_is_mine(sv, sh)) return;
     if (tid < 64) s_exp2[tid] = kExp2Table[tid];
     const int c = blockIdx.x % sh.n_chunks, rn = blockIdx.x / sh.n_chunks, node = rn % a.n_nodes, row = rn / a.n_nodes;
-    const bool greedy = a.temperature == 0.f;
     const T *lp = (const T *)a.p + (size_t)row * a.p_stride + (size_t)node * V;
     const T *lq = (const T *)a.q + (size_t)row * a.q_stride + (size_t)node * V;
     const int first = c * kTreeChunk + wave * kWavePieces * kPiece;
@@ -226,28 +225,9 @@ __global__ __launch_bounds__(kStatThreads) void tree_stats_kernel(TreeAcceptArgs
 #pragma unroll
     for (int k = 0; k < kWavePieces; ++k) {
         load_piece(lp, first + k * kPiece, V, p[k]);
-        load_piece(lq, first + k * kPiece, greedy ? 0 : V, q[k]);
+        load_piece(lq, first + k * kPiece, V, q[k]);
     }
     __syncthreads();
-    if (greedy) {
-        unsigned long long best = 0ull;
-#pragma unroll
-        for (int k = 0; k < kWavePieces; ++k)
-#pragma unroll
-            for (int i = 0; i < kPerLane; ++i) {
-                const int e = first + k * kPiece + lane + i * 64;
-                const unsigned long long key = argmax_key(p[k][i], e);
-                if (e < V && key > best) best = key;
-            }
-        best = wave_max(best);
-        if (lane == 0) s_k[wave] = best;
-        __syncthreads();
-        if (tid == 0) {
-            for (int w = 1; w < kStatWaves; ++w) best = s_k[w] > best ? s_k[w] : best;
-            *reinterpret_cast<unsigned long long *>(&sv.stat[(size_t)rn * sh.n_chunks + c]) = best;
-        }
-        return;
-    }
     const double inv_t = 1.0 / (double)a.temperature;
     TreeStat t[kWavePieces];
 #pragma unroll
@@ -351,26 +331,6 @@ __device__ void walk_alone_greedy(const TreeAcceptArgs &a, int row) {
     }
 }
 
-// Greedy matching of one sequence on the argmax of every chunk of every node.
-__device__ void walk_shared_greedy(const TreeAcceptArgs &a, const SlotView &sv, int row, int chunks) {
-    __shared__ int s_top[kTreeMaxAcceptNodes];
-    const int tid = threadIdx.x, lane = tid & 63, n = a.n_nodes;
-    const int32_t *tok = a.tokens + (size_t)row * n;
-    for (int v = tid >> 6; v < n; v += kTreeWaves) {
-        const TreeStat *st = sv.stat + ((size_t)row * n + v) * chunks + min(lane, chunks - 1);
-        const unsigned long long best = wave_max(*reinterpret_cast<const unsigned long long *>(st));
-        if (lane == 0) s_top[v] = (int)(~(uint32_t)(best & 0xffffffffull));
-    }
-    __syncthreads();
-    if (tid != 0) return;
-    int node = 0, plen = 0;
-    for (int c = 1; c < n; ++c)                               // a node's children follow it, so one sweep walks the path
-        if (a.parents[c] == node && tok[c] == s_top[node]) { a.out_path[(size_t)row * n + plen++] = c; node = c; }
-    a.out_path_len[row] = plen;
-    a.out_token[row] = s_top[node];
-    if (a.out_flags) a.out_flags[row] = 0;
-}
-
 // The walk of one sequence.  ALONE: by one block, which takes the statistics of the nodes it visits itself and needs no
 // memory to share (more than kTreeMaxChunks chunks: longer ones, of `sub` times kTreeChunk entries).  Otherwise by
 // `chunks` blocks on what the kernels above left in the slot: block `chunk` sums the draw's weights over its chunk, and
@@ -467,7 +427,12 @@ __device__ void walk(const TreeAcceptArgs &a, const SlotView &sv, int row, int c
             if (tid % kPieces == 0 && tid < chunks * kPieces) s_chunk_stat[tid / kPieces] = t;
         }
         __syncthreads();
-        here = node_stat(s_chunk_stat, chunks, inv_t, s_exp2);
+        if (wave == 0) {
+            const NodeStat t = node_stat(s_chunk_stat, chunks, inv_t, s_exp2);
+            if (lane == 0) s_node[0] = t;
+        }
+        __syncthreads();
+        here = s_node[0];
         if (tid > v && tid < n && s_par[tid] == v) probe(tid);
         __syncthreads();
     };
@@ -662,21 +627,18 @@ __device__ __forceinline__ void walk_alone(const TreeAcceptArgs &a, int row) {
 template <typename T>
 __global__ __launch_bounds__(kTreeThreads) void tree_accept_alone_kernel(TreeAcceptArgs a) { walk_alone<T>(a, blockIdx.x); }
 
-// Grid: rows x chunks (greedy: rows).
+// Grid: rows x chunks.
 template <typename T>
 __global__ __launch_bounds__(kTreeThreads) void tree_draw_kernel(TreeAcceptArgs a, TreeShare sh) {
     const SlotView sv = slot_of(a, sh);
     const bool mine = slot_is_mine(sv, sh);                 // only this call's blocks can end that, after all have counted
-    const bool greedy = a.temperature == 0.f;
-    const int per_row = greedy ? 1 : sh.n_chunks;
-    const int chunk = blockIdx.x % per_row, row = blockIdx.x / per_row;
-    if (!mine) {
-        if (chunk == 0) walk_alone<T>(a, row);
-        return;
+    const int chunk = blockIdx.x % sh.n_chunks, row = blockIdx.x / sh.n_chunks;
+    if (mine) {
+        walk<T, false>(a, sv, row, chunk, sh.n_chunks, 1);
+        slot_leave(sv, gridDim.x);
+    } else if (chunk == 0) {
+        walk_alone<T>(a, row);
     }
-    if (greedy) walk_shared_greedy(a, sv, row, sh.n_chunks);
-    else walk<T, false>(a, sv, row, chunk, sh.n_chunks, 1);
-    slot_leave(sv, gridDim.x);
 }
 
 // One block per (layer, sequence, KV head).  Thread t moves element t of the d_h-long K row and of the V^T column of
@@ -716,31 +678,55 @@ static uint32_t tree_call_number() {
     return id;
 }
 
+// Whether spreading a call over the chip is the faster way.  Both times are estimates (us) fitted to calls of 1 to 128
+// sequences, 1 to 41 nodes and 512 to 128 256 entries.  Spread: the launches; 9 a mass pass; 12 a round of the draw's blocks
+// (one per CU); 2.4 per million entries that the statistics and mass passes read, those of every node whether the walk
+// gets there or not.  One block per sequence: 0.5 per thousand entries and pass; about 1.2 passes a level of the tree, and
+// more the more sequences there are, since the longest walk counts.  Measured, spread / one block: 1 x 15 x 4096 34.9 / 33.8,
+// 1 x 15 x 10 000 35.7 / 53.8, 1 x 31 x 10 000 (four children) 55.6 / 56.5, 4 x 15 x 32 000 40.8 / 127, 64 x 7 x 32 000 102 /
+// 123, 64 x 15 x 32 000 161 / 147, 128 x 7 x 32 000 182 / 123, 32 x 7 x 128 256 176 / 363.
+static bool spread_pays(const TreeAcceptArgs &a, const TreeShare &sh) {
+    double entries = (double)a.rows * a.n_nodes, passes = 0.0, rows_pow = 0.0;
+    for (int j = 0; j < kMassPasses && sh.n_inner[j] > 0; ++j) { entries += (double)a.rows * sh.n_inner[j]; ++passes; }
+    int depth[kTreeMaxAcceptNodes] = {}, deepest = 0;
+    for (int i = 1; i < a.n_nodes; ++i) {
+        depth[i] = depth[a.parents[i]] + 1;
+        deepest = depth[i] > deepest ? depth[i] : deepest;
+    }
+    for (int r = 1; r < a.rows; r *= 2) ++rows_pow;
+    const double rounds = (double)(((long)a.rows * sh.n_chunks + 255) / 256);
+    const double spread = 17.0 + 9.0 * passes + 12.0 * rounds + 2.4e-6 * entries * a.vocab;
+    const double alone = 17.0 + 0.5e-3 * a.vocab * (2.0 + 1.2 * deepest + 0.4 * rows_pow);
+    return spread < alone;
+}
+
 template <typename T>
 static void launch_tree_accept_t(const TreeAcceptArgs &a, hipStream_t stream) {
+    auto alone = [&]() { launch_kernel(tree_accept_alone_kernel<T>, a.rows, kTreeThreads, 0, stream, a); };
+    // greedy: one launch that reads each visited node once is faster at every size measured but the largest (a path of
+    // two nodes, 128 256 entries: 21 us, spread 22; 32 sequences of them 42 / 33)
+    if (a.temperature == 0.f) return alone();
     TreeShare sh{};
     sh.n_chunks = (a.vocab + kTreeChunk - 1) / kTreeChunk;
     size_t st, ms, pt;
+    if (sh.n_chunks > kTreeMaxChunks || slot_layout(a.rows, a.n_nodes, sh.n_chunks, &st, &ms, &pt) > kTreeSlotBytes) return alone();
+    int kids[kTreeMaxAcceptNodes] = {};
+    for (int i = 1; i < a.n_nodes; ++i) ++kids[a.parents[i]];
+    for (int j = 0; j < kMassPasses; ++j)
+        for (int i = 0; i < a.n_nodes; ++i)
+            if (kids[i] > j + 1) sh.inner[j][sh.n_inner[j]++] = (uint8_t)i;
+    if (!spread_pays(a, sh)) return alone();
     // a captured call would keep its number in every copy of its graph, and two copies may run at once
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     const bool captured = hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
     (void)hipGetLastError();
-    if (captured || sh.n_chunks > kTreeMaxChunks || slot_layout(a.rows, a.n_nodes, sh.n_chunks, &st, &ms, &pt) > kTreeSlotBytes) {
-        launch_kernel(tree_accept_alone_kernel<T>, a.rows, kTreeThreads, 0, stream, a);
-        return;
-    }
+    if (captured) return alone();
     sh.id = tree_call_number();
-    const bool greedy = a.temperature == 0.f;
     launch_kernel(tree_claim_kernel, 1, 64, 0, stream, a, sh);
     launch_kernel(tree_stats_kernel<T>, (unsigned)(a.rows * a.n_nodes * sh.n_chunks), kStatThreads, 0, stream, a, sh);
-    int kids[kTreeMaxAcceptNodes] = {};
-    for (int i = 1; i < a.n_nodes; ++i) ++kids[a.parents[i]];
-    for (int j = 0; j < kMassPasses && !greedy; ++j)
-        for (int i = 0; i < a.n_nodes; ++i)
-            if (kids[i] > j + 1) sh.inner[j][sh.n_inner[j]++] = (uint8_t)i;
     for (int j = 0; j < kMassPasses && sh.n_inner[j] > 0; ++j)
         launch_kernel(tree_mass_kernel<T>, (unsigned)(a.rows * sh.n_inner[j] * sh.n_chunks), kStatThreads, 0, stream, a, sh, j);
-    launch_kernel(tree_draw_kernel<T>, (unsigned)(a.rows * (greedy ? 1 : sh.n_chunks)), kTreeThreads, 0, stream, a, sh);
+    launch_kernel(tree_draw_kernel<T>, (unsigned)(a.rows * sh.n_chunks), kTreeThreads, 0, stream, a, sh);
 }
 
 void launch_tree_accept(int dtype, const TreeAcceptArgs &a, hipStream_t stream) {

@@ -198,6 +198,36 @@ def test_tree_accept_adds_in_one_order(name, V, dtype):
         assert all(torch.equal(a, b) for a, b in zip(out, eager))
 
 
+@pytest.mark.parametrize("rows,n,reach,V,dtype,temperature", [
+    (1, 12, 1, 12289, torch.float32, 1.0), (5, 23, 3, 32001, torch.bfloat16, 0.7), (2, 41, 40, 60001, torch.float32, 1.0),
+    (16, 9, 2, 16384, torch.bfloat16, 2.0), (1, 64, 5, 262144, torch.bfloat16, 1.0), (33, 6, 2, 20479, torch.float32, 1.0)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_tree_accept_spread_equals_one_block(rows, n, reach, V, dtype, temperature, masked):
+    """Calls that are spread over the chip against the same calls captured (one block per sequence): odd vocabularies,
+    chains, wide and deep trees, most children refused, rows with -infinity entries.  Equal to the bit."""
+    rng = np.random.default_rng(V + n)
+    parents = [-1] + [int(rng.integers(max(0, i - reach), i)) for i in range(1, n)]
+    g = torch.Generator(device="cuda").manual_seed(V)
+    p = torch.randn((rows, n, V), device="cuda", generator=g) * 2
+    q = p + 0.7 * torch.randn((rows, n, V), device="cuda", generator=g)
+    if masked:
+        p[..., ::3] = -float("inf")
+        q[..., 1::5] = -float("inf")
+    p, q = p.to(dtype), q.to(dtype)
+    toks = torch.randint(0, V, (rows, n), device="cuda", dtype=torch.int32, generator=g)
+    u = torch.rand((rows, n + 1), device="cuda", generator=g)
+    u[:, 1:n] = 0.6 + 0.4 * u[:, 1:n]
+    eager = [x.clone() for x in runtime.tree_accept(p, q, toks, parents, u, temperature)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = runtime.tree_accept(p, q, toks, parents, u, temperature)
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, eager))
+
+
 def test_tree_accept_overlapping_calls_of_both_types():
     """fp32 and bf16 calls, of different batches, trees and vocabularies and a greedy one among them, in turn on two and
     on five streams: a call must never take the scratch another one is using for its own."""
