@@ -2,6 +2,8 @@
 // embedding + KV append, SwiGLU, and the KV-length bookkeeping (the rollback of Sec. 3.3).
 // All are bandwidth-trivial next to the weight streaming of the GEMMs; they exist so that no
 // step of the forward pass leaves the GPU.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "prof.h"
@@ -208,22 +210,43 @@ __global__ __launch_bounds__(64) void reduce_rope_append_kernel(const float *par
     }
 }
 
-// The same for many rows of a bf16 model without a row scale (kAppendRows rows of one sequence per value block).  Bound by
-// the bytes: the first blocks take one row and 2048 / d_head query and key heads each, four rotation pairs per thread; the
-// others take the values of one head through LDS, so that the transposed cache is written along the positions.  The
-// kernel above (one wavefront per row and head) evaluated every sine and cosine again per head and wrote each value into a
-// line of its own: 2001 rows x (32 + 32 + 32) heads 106 us, here 40; 256 rows x (28 + 4 + 4) heads in 16 sequences 10.8, here 8.1.
-constexpr int kAppendRows = 64;
+// The same for a bf16 model without a row scale (more than 16 rows in all, or no packed weights).  Bound by the bytes with
+// many rows, by the trips to the partial sums with few: the first blocks take one row and 2048 / d_head query and key heads
+// each, four rotation pairs per thread; the others take kAppendRows rows of the values of one head through LDS, so that the
+// transposed cache is written along the positions; four splits of every sum are in flight.  The kernel above (one wavefront
+// per row and head, each value into a line of its own) and the present one, us: one sequence of the LLaMA3-8B shape (8 KV
+// heads) 20 rows 5.2 / 4.1, 64 rows 5.5 / 4.8, 256 rows 10.2 / 7.2; of the 7B shape 64 rows 7.9 / 5.9, 1800 rows 103 / 29;
+// 16 x 16 rows of the Qwen2-7B shape 9.8 / 6.1.  64 rows a value block and one split in flight left too few loads under
+// way: 20 rows 11.0, 64 rows 23.9, 16 x 16 rows 8.3; 8 and 32 rows a block with four in flight: 64 rows 4.5 and 6.9, 1800
+// rows 31.6 and 29.3.
+constexpr int kAppendRows = 16;
 __global__ __launch_bounds__(256) void reduce_rope_append_tiled_kernel(const float *partial, int S, size_t split_stride,
                                                                        float *q_out, uint16_t *k_cache, uint16_t *v_cache,
                                                                        const int32_t *lens, int B, int R, int h_q, int h_kv,
                                                                        int d_h, int max_len, const float2 *cs_table, int qk_blocks) {
     __shared__ float tile[kAppendRows][129];
     const int half = d_h / 2, width = (h_q + 2 * h_kv) * d_h, tid = threadIdx.x;
-    auto sum4 = [&](size_t at) {
-        f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int sp = 0; sp < S; ++sp) v += *reinterpret_cast<const f32x4 *>(partial + sp * split_stride + at);
-        return v;
+    // sums of N groups of four columns, four splits of each in flight, added in split order
+    auto sums = [&](auto &v, const size_t (&at)[std::extent<std::remove_reference_t<decltype(v)>>::value]) {
+        constexpr int N = std::extent<std::remove_reference_t<decltype(v)>>::value;
+        auto get = [&](int sp, int k) { return *reinterpret_cast<const f32x4 *>(partial + sp * split_stride + at[k]); };
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+        int sp = 0;
+        for (; sp + 4 <= S; sp += 4) {
+            f32x4 t[4][N];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int k = 0; k < N; ++k) t[u][k] = get(sp + u, k);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int k = 0; k < N; ++k) v[k] += t[u][k];
+        }
+        for (; sp < S; ++sp)
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] += get(sp, k);
     };
     if ((int)blockIdx.x < qk_blocks) {
         const int per = 1024 / half, groups = (h_q + h_kv + per - 1) / per;                       // heads per block
@@ -231,7 +254,9 @@ __global__ __launch_bounds__(256) void reduce_rope_append_tiled_kernel(const flo
         const int head = (blockIdx.x % groups) * per + tid * 4 / half, i = tid * 4 % half;
         if (head >= h_q + h_kv || pos >= max_len) return;           // capacity was checked on the host; never write outside
         const size_t at = (size_t)m * width + (size_t)head * d_h + i;
-        const f32x4 x1 = sum4(at), x2 = sum4(at + half);
+        f32x4 x[2];
+        sums(x, {at, at + half});
+        const f32x4 x1 = x[0], x2 = x[1];
         const f32x4 t0 = reinterpret_cast<const f32x4 *>(cs_table + (size_t)m * half + i)[0];
         const f32x4 t1 = reinterpret_cast<const f32x4 *>(cs_table + (size_t)m * half + i)[1];
         const f32x4 c = f32x4{t0[0], t0[2], t1[0], t1[2]}, s = f32x4{t0[1], t0[3], t1[1], t1[3]};
@@ -249,11 +274,23 @@ __global__ __launch_bounds__(256) void reduce_rope_append_tiled_kernel(const flo
     }
     const int vb = blockIdx.x - qk_blocks, h = vb % h_kv, tiles = (R + kAppendRows - 1) / kAppendRows;
     const int b = vb / h_kv / tiles, r0 = vb / h_kv % tiles * kAppendRows, rows = min(kAppendRows, R - r0);
-    for (int e = tid; e < rows * (d_h / 4); e += 256) {
-        const int r = e / (d_h / 4), d = e % (d_h / 4) * 4;
-        const f32x4 v = sum4((size_t)(b * R + r0 + r) * width + (size_t)(h_q + h_kv + h) * d_h + d);
+    const int n4 = rows * (d_h / 4);
+    for (int e0 = tid; e0 < n4; e0 += 512) {
+        size_t at[2];
+        f32x4 v[2];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) tile[r][d + j] = v[j];
+        for (int k = 0; k < 2; ++k) {
+            const int e = min(e0 + k * 256, n4 - 1);
+            at[k] = (size_t)(b * R + r0 + e / (d_h / 4)) * width + (size_t)(h_q + h_kv + h) * d_h + e % (d_h / 4) * 4;
+        }
+        sums(v, {at[0], at[1]});
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (e0 + k * 256 < n4) {
+                const int r = (e0 + k * 256) / (d_h / 4), d = (e0 + k * 256) % (d_h / 4) * 4;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) tile[r][d + j] = v[k][j];
+            }
     }
     __syncthreads();
     const int r = tid & (kAppendRows - 1), pos = lens[b] + r0 + r;
@@ -346,7 +383,8 @@ void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale 
     const dim3 grid(B * R, h_q + 2 * h_kv);
     if (dtype == PSD_BF16 && !rs.sumsq && cs_table) {
         const int per = 1024 / (d_h / 2);                                   // query and key heads per block
-        const int qk = B * R * ((h_q + h_kv + per - 1) / per), vb = B * ((R + kAppendRows - 1) / kAppendRows) * h_kv;
+        const int qk = B * R * ((h_q + h_kv + per - 1) / per);
+        const int vb = B * ((R + kAppendRows - 1) / kAppendRows) * h_kv;
         launch_kernel(reduce_rope_append_tiled_kernel, qk + vb, 256, 0, stream, partial, S, stride, q_out, (uint16_t *)k_cache,
                       (uint16_t *)v_cache, lens, B, R, h_q, h_kv, d_h, max_len, cs_table, qk);
         return;

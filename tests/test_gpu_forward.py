@@ -164,6 +164,20 @@ def test_tiled_projections_at_tile_edges(rows, w4):
     p.close()
 
 
+@pytest.mark.parametrize("d_head,batch,rows", [(128, 2, 15), (64, 3, 16), (128, 3, 17), (64, 2, 33), (128, 1, 65)])
+def test_rotation_and_append_at_tile_edges(d_head, batch, rows):
+    """Steps of more than 10 query rows per KV head, which the rotation kernel prepares: row counts around its 16-row
+    value tiles, several sequences at ragged positions, 3 + 1 query and key heads (a part of one block's), split counts
+    that are no multiple of the four in flight; a second step reads what the first appended."""
+    shape = synth.Shape(1, 384, 384 // d_head, 1, d_head, 640, 500, 1.0e4)
+    lens = [130 - 9 * b for b in range(batch)]
+    p = Pair(shape, torch.bfloat16, batch, 320, seed=rows, ctx=130, lens=lens, std=0.05)
+    toks = synth.make_tokens(shape.vocab, (batch, rows + 12), rows)
+    p.step(toks[:, :rows], what="first step")
+    p.step(toks[:, rows:], what="second step")
+    p.close()
+
+
 @pytest.mark.parametrize("d_head,batch,ctx,rows", [(128, 40, 300, 3), (64, 40, 300, 10), (128, 24, 700, 1), (64, 130, 70, 2)])
 def test_attention_of_many_sequences(d_head, batch, ctx, rows):
     """More 256-key splits than CUs: the build of the direct attention kernel that runs two blocks per CU on 32-key
