@@ -835,8 +835,7 @@ __device__ __forceinline__ u32x4 w4x8_to_f16x8(uint32_t raw, uint32_t sz) {
 // it at once, the operands of the next 16 K are read ahead of the MFMAs of the current ones, and there is one barrier
 // per tile.  Measured against the branchy loop before it (2001 rows, us): 12288 x 4096 243 -> 224, 22016 x 4096 451 ->
 // 364 (which also drops a SwiGLU launch of 46), 4096 x 8192 148 -> 127, 4096 x 4096 87 -> 70.
-// With few rows: streaming W; the blocks take equal ranges of all the product's K tiles, so none of the CUs idles in a last
-// round.  Measured (45 rows, us): 12288 x 4096 32.5 -> 25.9, 22016 x 4096 47.1 -> 42.3, 4096 x 4096 14.7 -> 10.4,
+// With few rows: streaming W; the blocks take equal ranges of all the product's K tiles, so none of the CUs idles in a last round.  Measured (45 rows, us): 12288 x 4096 32.5 -> 25.9, 22016 x 4096 47.1 -> 42.3, 4096 x 4096 14.7 -> 10.4,
 // 32000 x 4096 78.8 -> 59.1 (4.4 TB/s).  Up to 64 rows two blocks of 128 columns share a CU, so that one's loads cover the
 // other's barriers and its write-out (one block of 256: 26.8 / 26.1, 41.9 / 41.0, 10.3 / 9.8, 4096 x 8192 16.5 / 15.9; two
 // layers and a head of the 7B shape 384 -> 374); at 65 to 128 rows that gains nothing (128 x 12288 x 4096 35.5 / 37.3).
@@ -1072,17 +1071,23 @@ int tiles_of(const int *n, int nseg, int rows) {
 static int gemm_slots_of(int tiles, int units_per_tile, int grid);
 // The tile and the number of blocks of a tiled product.  Up to 128 rows it streams W: two blocks of 128 columns per CU up to
 // 64 rows, one of 256 above, but at least eight K tiles each (45 rows x 4096 x 4096 in tiles of 256: 128 blocks 11.2 us and
-// 16 slots less to add than 256 blocks, 11.6), tiles shared wherever the ranges fall.  Above: 256 rows; the columns and the (even) K split with the least estimated
+// 16 slots less to add than 256 blocks, 11.6), tiles shared wherever the ranges fall.  An exception, us of a two-layer pass'
+// tiled launches and their reductions, without / with:
+//   - 65 to 128 rows of a product with fewer than 1600 K tiles of 256 columns, which would leave CUs idle, take 64-row tiles
+//     of 128 columns and read W twice (d_model 256, 100 rows: 176 / 114; 768: 217 / 145; LLaMA3-8B shape, whose QKV and O
+//     are of this kind, 540 / 527; a head of 32000 x 1024, 2000 K tiles, is 6 us slower this way).
+// Above: 256 rows; the columns and the (even) K split with the least estimated
 // time: rounds of 256 blocks x K tiles x the measured time of one (us: 1.15, 1.65, 1.9 for 128, 192, 256 columns) plus 4
 // per round for filling and emptying the pipeline, plus a partial slot of M x N written and read at about 3 TB/s per
 // split.  gated: 128 gate and 128 up columns per tile, never split (the two factors meet in one lane).
+constexpr long kTallKTiles = 1600;
 GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) {
     GemmTiledPlan best{};
     const int nk = K / kBK;
     if (M <= 128 && !gated) {
-        best.ta = M <= 64 ? 1 : 2;
+        best.ta = M <= 64 || (long)tiles_of(n, nseg, 256) * nk < kTallKTiles ? 1 : 2;
         best.cols = best.ta == 1 ? 128 : 256;
-        best.tiles = tiles_of(n, nseg, best.cols);
+        best.tiles = tiles_of(n, nseg, best.cols) * (M <= 64 * best.ta ? 1 : 2);
         const long cap = best.ta == 1 ? 512 : 256;
         const long U = (long)best.tiles * nk;
         best.blocks = (int)(U / 8 < 1 ? 1 : (U / 8 < cap ? U / 8 : cap));

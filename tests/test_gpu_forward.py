@@ -164,6 +164,15 @@ def test_tiled_projections_at_tile_edges(rows, w4):
     p.close()
 
 
+@pytest.mark.parametrize("rows,d,ffn,vocab", [(65, 256, 640, 500), (128, 384, 1024, 777), (127, 2560, 2560, 900)])
+def test_tiled_projections_of_small_products_and_wide_heads(rows, d, ffn, vocab):
+    """65 to 128 rows on 64-row tiles (few K tiles) next to products on 128-row tiles (2560 x 7680: 2560 of them)."""
+    shape = synth.Shape(1, d, d // 64, d // 64, 64, ffn, vocab, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 192, seed=rows, std=0.05)
+    p.step(synth.make_tokens(vocab, (1, rows), rows), what=f"{rows} rows")
+    p.close()
+
+
 @pytest.mark.parametrize("d_head,batch,rows", [(128, 2, 15), (64, 3, 16), (128, 3, 17), (64, 2, 33), (128, 1, 65)])
 def test_rotation_and_append_at_tile_edges(d_head, batch, rows):
     """Steps of more than 10 query rows per KV head, which the rotation kernel prepares: row counts around its 16-row
