@@ -354,9 +354,9 @@ ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit
 }
 
 // the largest head_partial_bytes over every number of logit rows (0 .. n_new per sequence).  Below kPairRows
-// rows, from there to kStreamMaxRows, from there to 64 and from there to 128, the slots are one and the same, so the
-// largest count has the most; above, it does not grow with the rows as long as they fill the same number of 256-row tiles,
-// so a run of them that starts at one slot is done.
+// rows, from there to kStreamMaxRows, from there to 64 and from there to 128, on either side of kWholeTilesFrom, the slots
+// are one and the same, so the largest count has the most; above, it does not grow with the rows as long as they fill the
+// same number of 256-row tiles, so a run of them that starts at one slot is done.
 size_t worst_head_partial_bytes(const psd_model *mdl, int batch, int n_new, bool folded) {
     size_t worst = 0;
     const int M = batch * n_new;
@@ -364,7 +364,7 @@ size_t worst_head_partial_bytes(const psd_model *mdl, int batch, int n_new, bool
         const size_t b = head_partial_bytes(mdl, Ml, folded, slots);
         worst = b > worst ? b : worst;
     };
-    for (int edge : {kPairRows - 1, kStreamMaxRows, 64, 128}) {
+    for (int edge : {kPairRows - 1, kStreamMaxRows, (kWholeTilesFrom - 1) / mdl->d.d_model, 64, 128}) {
         const int Ml = (M < edge ? M : edge) / batch * batch;
         if (Ml > 0) at(Ml, nullptr);
     }

@@ -835,7 +835,8 @@ __device__ __forceinline__ u32x4 w4x8_to_f16x8(uint32_t raw, uint32_t sz) {
 // it at once, the operands of the next 16 K are read ahead of the MFMAs of the current ones, and there is one barrier
 // per tile.  Measured against the branchy loop before it (2001 rows, us): 12288 x 4096 243 -> 224, 22016 x 4096 451 ->
 // 364 (which also drops a SwiGLU launch of 46), 4096 x 8192 148 -> 127, 4096 x 4096 87 -> 70.
-// With few rows: streaming W; the blocks take equal ranges of all the product's K tiles, so none of the CUs idles in a last round.  Measured (45 rows, us): 12288 x 4096 32.5 -> 25.9, 22016 x 4096 47.1 -> 42.3, 4096 x 4096 14.7 -> 10.4,
+// With few rows: streaming W; the blocks take equal ranges of all the product's K tiles (unless there are tiles enough to
+// give each block whole ones), so none of the CUs idles in a last round.  Measured (45 rows, us): 12288 x 4096 32.5 -> 25.9, 22016 x 4096 47.1 -> 42.3, 4096 x 4096 14.7 -> 10.4,
 // 32000 x 4096 78.8 -> 59.1 (4.4 TB/s).  Up to 64 rows two blocks of 128 columns share a CU, so that one's loads cover the
 // other's barriers and its write-out (one block of 256: 26.8 / 26.1, 41.9 / 41.0, 10.3 / 9.8, 4096 x 8192 16.5 / 15.9; two
 // layers and a head of the 7B shape 384 -> 374); at 65 to 128 rows that gains nothing (128 x 12288 x 4096 35.5 / 37.3).
@@ -1071,8 +1072,12 @@ int tiles_of(const int *n, int nseg, int rows) {
 static int gemm_slots_of(int tiles, int units_per_tile, int grid);
 // The tile and the number of blocks of a tiled product.  Up to 128 rows it streams W: two blocks of 128 columns per CU up to
 // 64 rows, one of 256 above, but at least eight K tiles each (45 rows x 4096 x 4096 in tiles of 256: 128 blocks 11.2 us and
-// 16 slots less to add than 256 blocks, 11.6), tiles shared wherever the ranges fall.  An exception, us of a two-layer pass'
+// 16 slots less to add than 256 blocks, 11.6), tiles shared wherever the ranges fall.  Two exceptions, us of a two-layer pass'
 // tiled launches and their reductions, without / with:
+//   - tiles enough for every resident block are given out whole: a second slot of a wide head costs more to write and add
+//     than an uneven last round (LLaMA3-8B shape, head of 128 256: 40 rows 483 / 449, 128 rows 637 / 564; Qwen2-7B shape,
+//     152 064: 64 rows 571 / 520, 128 rows 703 / 630), except for so few rows of so short tiles that the slot is the
+//     smaller loss (K = 2048: 17 rows 241 / 246, 20 rows 248 / 243);
 //   - 65 to 128 rows of a product with fewer than 1600 K tiles of 256 columns, which would leave CUs idle, take 64-row tiles
 //     of 128 columns and read W twice (d_model 256, 100 rows: 176 / 114; 768: 217 / 145; LLaMA3-8B shape, whose QKV and O
 //     are of this kind, 540 / 527; a head of 32000 x 1024, 2000 K tiles, is 6 us slower this way).
@@ -1089,6 +1094,11 @@ GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) 
         best.cols = best.ta == 1 ? 128 : 256;
         best.tiles = tiles_of(n, nseg, best.cols) * (M <= 64 * best.ta ? 1 : 2);
         const long cap = best.ta == 1 ? 512 : 256;
+        if (best.tiles >= cap && (long)M * K >= kWholeTilesFrom) {
+            best.blocks = best.tiles;
+            best.slots = 1;
+            return best;
+        }
         const long U = (long)best.tiles * nk;
         best.blocks = (int)(U / 8 < 1 ? 1 : (U / 8 < cap ? U / 8 : cap));
         best.slots = gemm_slots_of(best.tiles, nk, best.blocks);
