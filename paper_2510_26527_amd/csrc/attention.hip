@@ -885,6 +885,11 @@ int attn_pick_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int le
         if (old_splits > by_grid - 1) old_splits = by_grid - 1;
         if (old_splits < 1) return 1;
         if (!pairs) return old_splits + 1;
+        // One split of the cache: the step's own rows ride on it, since a split for them alone would leave half of the resident
+        // blocks idle and need a combine.  Two splits / one (us a layer): 7B shape, 8 sequences x 8 rows, 60 keys 21.6 /
+        // 16.4, 1024 keys 50.3 / 40.6, 4000 keys 160 / 113; 6 x 3 rows, 2000 keys 79.9 / 56.1; LLaMA3-8B shape, 32 x 1
+        // row, 2000 keys 86.3 / 62.9 (the build with one block per CU: 20.0, 47.6, 127; 61.7; 69.6).
+        if (old_splits == 1) return 1;
         const int range = ((cached + old_splits - 1) / old_splits + step - 1) / step * step;   // whole steps per block
         return (cached + range - 1) / range + 1;
     }
@@ -901,7 +906,8 @@ int attn_max_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int len
     int most = (cached + 127) / 128;                                  // (direct_pairs: one query tile, so one chunk)
     if (most > 512 / (B * h_kv) - 1) most = 512 / (B * h_kv) - 1;
     const int one = 256 / (B * h_kv);                                // at the longest lengths of the other build
-    most = most + 1 > one ? most + 1 : one;
+    most = most > 1 ? most + 1 : 1;
+    most = most > one ? most : one;
     return most > at ? most : at;
 }
 

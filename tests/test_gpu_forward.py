@@ -202,6 +202,19 @@ def test_attention_of_many_sequences(d_head, batch, ctx, rows):
     p.close()
 
 
+@pytest.mark.parametrize("d_head,batch,ctx,rows", [(64, 50, 700, 2), (128, 64, 330, 3), (128, 40, 100, 3), (64, 43, 129, 1)])
+def test_attention_of_one_split_per_head(d_head, batch, ctx, rows):
+    """Two blocks per CU and one split of the cache, the step's own rows riding on it: 172 to 256 heads at any length, 160
+    heads with at most 128 keys (129 keys and 172 heads: one; the second step is past 128 keys)."""
+    shape = synth.Shape(1, 256, 4, 4, d_head, 256, 600, 1.0e4)
+    lens = [1 + (ctx - 1) * ((7 * b) % batch) // batch for b in range(batch - 1)] + [ctx]
+    p = Pair(shape, torch.bfloat16, batch, (ctx + 2 * rows + 63) // 64 * 64, seed=batch, ctx=ctx, lens=lens, std=0.05)
+    toks = synth.make_tokens(shape.vocab, (batch, 2 * rows), 5)
+    p.step(toks[:, :rows], what="first step")
+    p.step(toks[:, rows:], what="second step")
+    p.close()
+
+
 def test_workspace_covers_every_cache_length():
     """16 sequences x 4 KV heads: a 900-key step takes more, shorter key splits than one at the end of its 1408-key cache;
     the workspace that the cache's size asks for has to serve it."""
