@@ -552,22 +552,30 @@ static WsLayout ws_layout(const AcceptArgs &a) {
 
 size_t accept_workspace_bytes(const AcceptArgs &a) { return ws_layout(a).total; }
 
-// Draw pass chunking.  Every block repeats its sequence's decision and one of them finishes the draw from the chunk sums, so
-// chunks of 4096 entries (a thread takes eight consecutive ones twice), or of 512 (two per thread, once) where that leaves
-// no more than 512 blocks.  From 2048 blocks on, chunks of up to 8192.  That coarser division needs the least
-// workspace: it is also taken where the finer one would not fit the built-in scratch buffer.  Measured (us, draw kernel;
-// the kernel before this one with about 512 blocks in all: 64 sequences x 32 000 entries 25.5, 16 x 152 064 43.0, 1 x
-// 32 000 21.2): chunks of 4096 by eights 22.2 / 30.6, of 2048 by eights 23.9 / 34.6, by fours 24.1 / 33.2, by twos 26.7 /
-// 37.2; one sequence, 512 by twos 11.7.
-static void accept_draw_chunks(AcceptArgs *a, bool coarse) {
+// Draw pass chunking.  Every block repeats its sequence's decision (about 10 us of dependent steps) and one of them finishes
+// the draw from the chunk sums; three blocks fit a CU, and the fewer of them share it the faster each.  So: chunks of 512
+// entries (two per thread, once) while that makes at most 256 blocks; of 2048 (eight per thread, once) up to 512 blocks; of
+// 4096 (twice); and of 8192 for 96 sequences and more of aligned rows once chunks of 4096 no longer fit in one round of the
+// chip, or from 2048 blocks on.  Measured (us, draw kernel, fp32; chunks of 512 / 2048 / 4096 / 8192): 1 sequence x 32 000 entries 11.7 /
+// 13.5 / 16.7 / 22.3, 4 x 32 000 13.7 / 13.4 / 16.9 / 22.7, 9 x 32 000 17.7 / 14.3 / 16.8 / 22.6, 1 x 128 256 (chunks of 1024
+// at least: 128 a row) 13.7 / 12.6 / 16.3 / 22.3, 4 x 152 064 19.4 / 16.7 / 17.5 / 23.0, 32 x 32 000 34.7 / 17.5 / 18.0 / 24.7,
+// 96 x 10 000 23.8 / 16.0 / 19.9 / 24.2, 64 x 32 000 45 / 25.9 / 21.7 / 26.1, 128 x 32 000 68 / 42.5 / 37.5 / 34.7, 192 x
+// 32 000 91 / 60 / 47.7 / 39.5, 32 x 152 064 66 / 48 / 37.5 / 41.7; unaligned rows, 128 x 32 001 70 / 50 / 44.6 / 47.9.  The last form needs the least workspace: it is
+// also taken where the finer one would not fit the built-in scratch buffer.
+static void accept_draw_chunks(AcceptArgs *a, bool vec, bool coarse) {
     const long rows = a->rows > 0 ? a->rows : 1;
     const int V = a->V;
+    auto blocks = [&](int ce) { return rows * ((V + ce - 1) / ce); };
     a->groupE = kMaxGroup;
     int ce = 4096;
-    if (V <= 512 * kMaxChunksE && rows * ((V + 511) / 512) <= 512) {
+    if (V <= 512 * kMaxChunksE && blocks(512) <= 256) {
         a->groupE = 2;
         ce = 512;
-    } else if (rows * ((V + ce - 1) / ce) > 2048) {
+    } else if (blocks(2048) <= 512) {
+        ce = 2048;
+    } else if (vec && rows >= 96 && blocks(4096) >= 1024) {
+        ce = 8192;
+    } else if (blocks(4096) > 2048) {
         coarse = true;
     }
     if (coarse) {
@@ -582,12 +590,13 @@ static void accept_draw_chunks(AcceptArgs *a, bool coarse) {
 
 void accept_plan(int rows, int gamma, int n_p_rows, int V, int dtype, bool vec, AcceptArgs *a) {
     a->rows = rows; a->gamma = gamma; a->n_p_rows = n_p_rows; a->V = V; a->dtype = dtype;
-    // the division of the draw is that of the plan that needs the most workspace (unaligned rows), whatever these rows are
+    // whether the finer division of the draw is taken rests on the plan that needs the most workspace (unaligned rows),
+    // whatever these rows are: a workspace sized for that plan serves every other
     const int nU = (V + kThreads * kLoadsPerLane - 1) / (kThreads * kLoadsPerLane);
     a->chunkA = (V + nU - 1) / nU;
     a->n_chunksA = (V + a->chunkA - 1) / a->chunkA;
-    accept_draw_chunks(a, false);
-    if (accept_workspace_bytes(*a) > PSD_STATIC_SCRATCH_BYTES) accept_draw_chunks(a, true);
+    accept_draw_chunks(a, false, false);
+    accept_draw_chunks(a, vec, accept_workspace_bytes(*a) > PSD_STATIC_SCRATCH_BYTES);
     const int epl = !vec ? 1 : (dtype == PSD_BF16 ? 8 : 4);
     const int cap = kThreads * kLoadsPerLane * epl;            // elements one block can hold
     const int nA = (V + cap - 1) / cap;

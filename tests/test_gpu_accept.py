@@ -70,6 +70,16 @@ def test_draw_chunk_edges(rows, gamma, V, dtype):
     _compare(synth.make_accept_inputs(rows, gamma, V, seed=V + rows, n_p_rows=gamma + 1, dtype=dtype))
 
 
+@pytest.mark.parametrize("rows,gamma,V,dtype", [
+    (8, 2, 16384, torch.float32), (8, 2, 16385, torch.bfloat16), (1, 3, 128256, torch.bfloat16), (2, 1, 262145, torch.float32),
+    (128, 2, 8193, torch.float32), (103, 1, 10001, torch.float32), (96, 1, 40968, torch.bfloat16), (95, 1, 40968, torch.bfloat16), (96, 1, 40961, torch.float32)])
+def test_draw_chunk_sizes(rows, gamma, V, dtype):
+    """Both sides of each line of the division: 256 blocks of 512 entries, 512 blocks of 2048 (more than 128 of them a row,
+    too), 96 sequences of more than 1024 chunks of 4096, aligned and not."""
+    _compare(synth.make_accept_inputs(rows, gamma, V, seed=V + rows, n_p_rows=gamma + 1, dtype=dtype))
+
+
+
 def test_workload2_full_size():
     """64 rows x gamma 8 x vocab 32000 bf16, the isolated acceptance workload, with and
     without the bonus row; mean accepted length lands near the 3.37 expected at alpha ~ 0.80."""
