@@ -135,8 +135,8 @@ struct SeqStats {
 
 // Ratio tests of sequence b and the scan to the first rejection.  Called by a whole block; every thread returns the same
 // n and flags.  The per-chunk statistics of a logits row (max raw logit, sum exp((l - max)/T)) are combined by eight lanes
-// per row, all rows at once; the chunk sums are fp32 quantities, so rescaling them with the fp32 exponential loses
-// nothing.  Then the first wavefront tests all positions, one per lane, and the first rejection is a bit scan.
+// per row, all rows at once: first the row's maximum, then every chunk's sum against it, so that a sum (an fp32 quantity)
+// meets one fp32 exponential on its way; the sums add in fp64.  Then the first wavefront tests all positions, one per lane, and the first rejection is a bit scan.
 __device__ __forceinline__ void decide(const AcceptArgs &a, int b, SeqStats *ss, int *n_out, int *flags_out) {
     const int tid = threadIdx.x, lane = tid & 63, sub = tid & 7;
     const double tabv = tid < 64 ? kExp2Table[tid] : 0.0;      // requested first, stored once the other loads are out
@@ -152,26 +152,27 @@ __device__ __forceinline__ void decide(const AcceptArgs &a, int b, SeqStats *ss,
     for (int r0 = 0; r0 < rows; r0 += kThreads / 8) {          // the same number of rounds for the whole block
         const int r = r0 + (tid >> 3);
         const float2 *st = a.stats + ((size_t)b * rows + min(r, rows - 1)) * nA;
-        float m = -INFINITY;
-        double z = 0.0;
-        for (int c0 = 0; c0 < nA; c0 += 32) {                  // up to four chunks per lane in flight
-            float2 t[4];
+        float2 t[4];                                           // up to four chunks per lane in flight
+        auto load = [&](int c0) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) t[i] = st[min(c0 + sub + 8 * i, nA - 1)];
-            float mm = m;
+        };
+        float top = -INFINITY;
+        for (int c0 = 0; c0 < nA; c0 += 32) {
+            load(c0);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) mm = c0 + sub + 8 * i < nA ? fmaxf(mm, t[i].x) : mm;
-            if (mm > m && m > -INFINITY) z *= (double)__builtin_amdgcn_exp2f((m - mm) * k2);
-            m = mm;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (c0 + sub + 8 * i < nA && t[i].x > -INFINITY) z += (double)(t[i].y * __builtin_amdgcn_exp2f((t[i].x - m) * k2));
+            for (int i = 0; i < 4; ++i) top = fmaxf(top, t[i].x);      // past the end: the last chunk again
         }
-        float top = m;
         top = fmaxf(top, __shfl_xor(top, 1, 64));
         top = fmaxf(top, __shfl_xor(top, 2, 64));
         top = fmaxf(top, __shfl_xor(top, 4, 64));
-        if (m > -INFINITY) z *= (double)__builtin_amdgcn_exp2f((m - top) * k2);
+        double z = 0.0;
+        for (int c0 = 0; c0 < nA; c0 += 32) {
+            if (nA > 32) load(c0);                             // else they are still there
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (c0 + sub + 8 * i < nA && t[i].x > -INFINITY) z += (double)(t[i].y * __builtin_amdgcn_exp2f((t[i].x - top) * k2));
+        }
         z += __shfl_xor(z, 1, 64);
         z += __shfl_xor(z, 2, 64);
         z += __shfl_xor(z, 4, 64);
