@@ -146,8 +146,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
     uint16_t (*s_k)[DH + 8] = reinterpret_cast<uint16_t (*)[DH + 8]>(lds_raw + (size_t)QT * 16 * (DH + 4) * 4);
     uint16_t (*s_vt)[40] = reinterpret_cast<uint16_t (*)[40]>(lds_raw + (size_t)QT * 16 * (DH + 4) * 4 + 32 * (DH + 8) * 2);
     __shared__ float s_scale[32];
-    // the first 64-key tile of this wavefront is requested before anything else: its trip to HBM overlaps the
-    // operand build below
+    // K and V^T operands of this wavefront's tile of 32 NSUB keys
     bf16x8 ka[NSUB][2][KS];
     bf16x8 va[NSUB][DT];
     auto load_tile = [&](int kt) {
@@ -171,8 +170,8 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
                 va[sub][dt] = *reinterpret_cast<const bf16x8 *>(Vt + (size_t)(dt * 16 + i) * max_len + kb + 8 * g);
         }
     };
-    // The wavefront's first K / V^T tile is requested ahead of the loop, so that it streams in while the operands are
-    // built; but behind the loads the build waits for (returns are in order, and all blocks' tiles together are the
+    // Where the registers hold it, the wavefront's first K / V^T tile is requested ahead of the loop, so that it streams in
+    // while the operands are built; but behind the loads the build waits for (returns are in order, and all blocks' tiles together are the
     // kernel's whole traffic: requested first, they would hold the build up for the time the cache takes to arrive).
     constexpr bool HOIST = QT == 1 && NSUB == 2; // two query tiles, or two blocks per CU, leave no registers to hold a tile across the build
     const int kt_first = kb0 + wave * (32 * NSUB);

@@ -370,12 +370,13 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
 // Block b streams the contiguous units [range_begin(b), range_begin(b + 1)); wavefront q multiplies the q-th 4 KB of
 // every unit (K offsets (q>>1)*64 + (q&1)*8 + 16 gq of the unit's 128), so the four wavefronts of a block read 16 KB
 // in one piece and the blocks of the grid adjacent ranges: the access pattern of a plain streaming read.  Weights
-// and the matching 8 activations per lane travel through a ring of kUnitRing register stages filled by buffer
-// loads: the block's range is the buffer, so the loads issued past its end return zeros without touching memory,
-// every wavefront runs the same straight-line loop, and a stage's data is waited for with the later stages still
-// in flight.  At the end of a tile (or of the range) the four K quarters are added through LDS in wavefront order
-// and the block writes ONE partial: slot = its index among the blocks that share the tile; the block that
-// finishes a tile zeroes the slots nobody writes.
+// and the matching 8 activations per lane travel through two register stages filled by buffer loads that return zeros
+// without touching memory where there is nothing to load, so that every wavefront runs the same straight-line loop, and a
+// stage's data is waited for with the other stage still in flight.  (Single: the block's range is the buffer and ends the
+// weight loads.  PAIR: a load past the range, or of a second tile that is not there, gets an offset beyond any buffer; the
+// buffer itself ends with the packed matrix.)  At the end of a tile (or of the range) the four K quarters are added
+// through LDS in wavefront order and the block writes ONE partial: slot = its index among the blocks that share the tile;
+// the block that finishes a tile zeroes the slots nobody writes.
 //
 // RESID (the projections that write the residual stream, when a block per 16 columns would be the slower choice):
 // every output element still gets one owner, found at run time.  A block publishes its partial with agent-scope
@@ -397,10 +398,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
     if (u0 >= u1) return;
     const int n_my = u1 - u0;
     const int tile0 = u0 / ns * H;                         // the block's first tile
-    // the buffer starts at that tile (or, alone, at the block's first unit and ends with its last)
-    const size_t w_first = PAIR ? (size_t)tile0 * ns : (size_t)u0;
+    // the buffer: from that tile to the end of the packed matrix, or, single, the block's units
+    const size_t w_first = PAIR ? (size_t)tile0 * ns : (size_t)u0, w_left = ((size_t)g.pack_tiles * ns - w_first) * kUnitBytes;
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-        (char *)const_cast<void *>(g.wpack) + w_first * kUnitBytes, 0, PAIR ? 0x7fffffff : n_my * kUnitBytes, 0x00020000);
+        (char *)const_cast<void *>(g.wpack) + w_first * kUnitBytes, 0,
+        PAIR ? (int)(w_left < 0x7fffffff ? w_left : 0x7fffffff) : n_my * kUnitBytes, 0x00020000);
     // activations: offsets from the first row's source row; a row past M points past the buffer and reads zeros
     const size_t row_first = x_row(g, 0);
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
