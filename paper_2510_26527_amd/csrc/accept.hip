@@ -7,8 +7,8 @@
 //      reductions, 8 x 16-byte loads in flight per lane.  The block whose chunk holds the
 //      draft token of its position also hands on that one logit, so the ratio test later
 //      needs no dependent load.
-//   2. accept_draw_kernel   bound by a chain of dependent steps and by fp64 issue (two exponentials per entry of the one
-//      position): reductions and scans run on lane moves in registers, and the finishing block's chunk sums in one
+//   2. accept_draw_kernel   bound by a chain of dependent steps (its fp64 instructions, two exponentials per entry of the
+//      one position, fill about a fifth of its time): reductions and scans run on lane moves in registers, and the finishing block's chunk sums in one
 //      wavefront without a barrier.  Several blocks per sequence.  Each re-derives the first rejection
 //      n of its sequence from the statistics (ratio test against the supplied uniforms, scan
 //      over <= 64 flags) and accumulates, in fp64 and for the ONE position the draw needs, the
