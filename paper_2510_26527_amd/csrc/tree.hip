@@ -524,6 +524,7 @@ __device__ void walk(const TreeAcceptArgs &a, const SlotView &sv, int row, int c
         mine = by_chunks(my_share);
     } else {
         const double part = wave_total_d(my_share(chunk));
+        __syncthreads();                                        // s_wd: a refusal's pass may still be read
         if (lane == 0) s_wd[wave] = part;
         __syncthreads();
         if (wave == 0) {
