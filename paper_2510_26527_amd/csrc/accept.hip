@@ -8,10 +8,10 @@
 //      draft token of its position also hands on that one logit, so the ratio test later
 //      needs no dependent load.
 //   2. accept_draw_kernel   bound by a chain of dependent steps (its fp64 instructions, two exponentials per entry of the
-//      one position, fill about a fifth of its time): reductions and scans run on lane moves in registers, and the finishing block's chunk sums in one
-//      wavefront without a barrier.  Several blocks per sequence.  Each re-derives the first rejection
-//      n of its sequence from the statistics (ratio test against the supplied uniforms, scan
-//      over <= 64 flags) and accumulates, in fp64 and for the ONE position the draw needs, the
+//      one position, fill about a fifth of its time): reductions and scans run on lane moves in registers, and the finishing
+//      block's chunk sums in one wavefront without a barrier.  Several blocks per sequence.  Each re-derives the first
+//      rejection n of its sequence from the statistics (ratio test against the supplied uniforms, scan over <= 64
+//      flags) and accumulates, in fp64 and for the ONE position the draw needs, the
 //      softmax denominators and the residual mass of its chunk.  The block of a sequence that
 //      finishes last (one counter per sequence; partial sums travel as agent-scope atomic
 //      stores / loads, so no cache write-back fence is needed and nothing ever waits) sums the
