@@ -354,18 +354,19 @@ ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit
 }
 
 // the largest head_partial_bytes over every number of logit rows (0 .. n_new per sequence).  Below kPairRows
-// rows, from there to kStreamMaxRows, from there to 64 and from there to 128, on either side of kWholeTilesFrom, the slots
-// are one and the same, so the largest count has the most; above, it does not grow with the rows as long as they fill the
-// same number of 256-row tiles, so a run of them that starts at one slot is done.
+// rows, from there to kStreamMaxRows, from there to 64 and from there to 128, the slots are one and the same among the counts
+// that share tiles between blocks, so the largest of those has the most (a count with whole tiles has none); above, it does not
+// grow with the rows as long as they fill the same number of 256-row tiles, so a run of them that starts at one slot is done.
 size_t worst_head_partial_bytes(const psd_model *mdl, int batch, int n_new, bool folded) {
     size_t worst = 0;
-    const int M = batch * n_new;
+    const int M = batch * n_new, n_v[1] = {mdl->d.vocab};
     auto at = [&](int Ml, int *slots) {
         const size_t b = head_partial_bytes(mdl, Ml, folded, slots);
         worst = b > worst ? b : worst;
     };
-    for (int edge : {kPairRows - 1, kStreamMaxRows, (kWholeTilesFrom - 1) / mdl->d.d_model, 64, 128}) {
-        const int Ml = (M < edge ? M : edge) / batch * batch;
+    for (int edge : {kPairRows - 1, kStreamMaxRows, 64, 128}) {
+        int Ml = (M < edge ? M : edge) / batch * batch;
+        while (mdl->d.dtype == PSD_BF16 && Ml > (edge == 128 ? 64 : kStreamMaxRows) && gemm_tiles_whole(Ml, mdl->d.d_model, n_v, 1)) Ml -= batch;
         if (Ml > 0) at(Ml, nullptr);
     }
     for (int Ml = 129 > batch ? (128 + batch) / batch * batch : batch; Ml <= M;) {

@@ -837,8 +837,8 @@ __device__ __forceinline__ u32x4 w4x8_to_f16x8(uint32_t raw, uint32_t sz) {
 // it at once, the operands of the next 16 K are read ahead of the MFMAs of the current ones, and there is one barrier
 // per tile.  Measured against the branchy loop before it (2001 rows, us): 12288 x 4096 243 -> 224, 22016 x 4096 451 ->
 // 364 (which also drops a SwiGLU launch of 46), 4096 x 8192 148 -> 127, 4096 x 4096 87 -> 70.
-// With few rows: streaming W; the blocks take equal ranges of all the product's K tiles (unless there are tiles enough to
-// give each block whole ones), so none of the CUs idles in a last round.  Measured (45 rows, us): 12288 x 4096 32.5 -> 25.9, 22016 x 4096 47.1 -> 42.3, 4096 x 4096 14.7 -> 10.4,
+// With few rows: streaming W; the blocks take equal ranges of all the product's K tiles (unless the product is so wide that whole
+// tiles are the better choice), so none of the CUs idles in a last round.  Measured (45 rows, us): 12288 x 4096 32.5 -> 25.9, 22016 x 4096 47.1 -> 42.3, 4096 x 4096 14.7 -> 10.4,
 // 32000 x 4096 78.8 -> 59.1 (4.4 TB/s).  Up to 64 rows two blocks of 128 columns share a CU, so that one's loads cover the
 // other's barriers and its write-out (one block of 256: 26.8 / 26.1, 41.9 / 41.0, 10.3 / 9.8, 4096 x 8192 16.5 / 15.9; two
 // layers and a head of the 7B shape 384 -> 374); at 65 to 128 rows that gains nothing (128 x 12288 x 4096 35.5 / 37.3).
@@ -1072,14 +1072,30 @@ int tiles_of(const int *n, int nseg, int rows) {
 }  // namespace
 
 static int gemm_slots_of(int tiles, int units_per_tile, int grid);
+constexpr long kTallKTiles = 1600;
+static int few_row_tile(int M, int K, const int *n, int nseg) {         // 64-row halves of the block tile of up to 128 rows
+    return M <= 64 || (long)tiles_of(n, nseg, 256) * (K / kBK) < kTallKTiles ? 1 : 2;
+}
+// Whether a product of up to 128 rows leaves its tiles whole.  Sharing them fills the last round of blocks but gives most
+// outputs a second partial slot, to be written, read and added.  Both losses are estimates (us) fitted to heads of 65 700 to
+// 256 000 columns at K = 2048 and 4096: an idle share of the last round costs what its K tiles take, half of that from the
+// third round on, where the blocks have drifted apart; a second slot costs more the more rows there are.  Tiled launch and
+// reduction, shared / whole, K = 4096: 64 rows x 65 700 columns 196 / 242, x 100 352 258 / 252, x 256 000 555 / 471; 18 x
+// 151 936 288 / 307; 128 x 73 448 266 / 284, x 100 352 321 / 283, x 256 000 668 / 495; K = 2048: 32 x 140 000 175 / 190,
+// 64 x 110 000 170 / 158, 128 x 65 700 174 / 157.
+bool gemm_tiles_whole(int M, int K, const int *n, int nseg) {
+    const int ta = few_row_tile(M, K, n, nseg), nk = K / kBK, tiles = tiles_of(n, nseg, 128 * ta) * (M <= 64 * ta ? 1 : 2);
+    const int cap = 512 / ta, idle = (cap - tiles % cap) % cap;
+    if (tiles < cap) return false;
+    const double tail = (double)idle / cap * nk * (ta == 1 ? 1.6 : 1.9) * (tiles < 2 * cap ? 1.0 : 0.5);
+    const double slot = ta == 1 ? (0.6 * M + 14.0) * (0.25 + 0.75 * nk / 64.0) : (0.3 * M + 52.0) * (0.36 + 0.64 * nk / 64.0);
+    return tail < slot;
+}
 // The tile and the number of blocks of a tiled product.  Up to 128 rows it streams W: two blocks of 128 columns per CU up to
 // 64 rows, one of 256 above, but at least eight K tiles each (45 rows x 4096 x 4096 in tiles of 256: 128 blocks 11.2 us and
 // 16 slots less to add than 256 blocks, 11.6), tiles shared wherever the ranges fall.  Two exceptions, us of a two-layer pass'
 // tiled launches and their reductions, without / with:
-//   - tiles enough for every resident block are given out whole: a second slot of a wide head costs more to write and add
-//     than an uneven last round (LLaMA3-8B shape, head of 128 256: 40 rows 483 / 449, 128 rows 637 / 564; Qwen2-7B shape,
-//     152 064: 64 rows 571 / 520, 128 rows 703 / 630), except for so few rows of so short tiles that the slot is the
-//     smaller loss (K = 2048: 17 rows 241 / 246, 20 rows 248 / 243);
+//   - the tiles of a wide head may be given out whole (gemm_tiles_whole);
 //   - 65 to 128 rows of a product with fewer than 1600 K tiles of 256 columns, which would leave CUs idle, take 64-row tiles
 //     of 128 columns and read W twice (d_model 256, 100 rows: 176 / 114; 768: 217 / 145; LLaMA3-8B shape, whose QKV and O
 //     are of this kind, 540 / 527; a head of 32000 x 1024, 2000 K tiles, is 6 us slower this way).
@@ -1087,16 +1103,15 @@ static int gemm_slots_of(int tiles, int units_per_tile, int grid);
 // time: rounds of 256 blocks x K tiles x the measured time of one (us: 1.15, 1.65, 1.9 for 128, 192, 256 columns) plus 4
 // per round for filling and emptying the pipeline, plus a partial slot of M x N written and read at about 3 TB/s per
 // split.  gated: 128 gate and 128 up columns per tile, never split (the two factors meet in one lane).
-constexpr long kTallKTiles = 1600;
 GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) {
     GemmTiledPlan best{};
     const int nk = K / kBK;
     if (M <= 128 && !gated) {
-        best.ta = M <= 64 || (long)tiles_of(n, nseg, 256) * nk < kTallKTiles ? 1 : 2;
+        best.ta = few_row_tile(M, K, n, nseg);
         best.cols = best.ta == 1 ? 128 : 256;
         best.tiles = tiles_of(n, nseg, best.cols) * (M <= 64 * best.ta ? 1 : 2);
         const long cap = best.ta == 1 ? 512 : 256;
-        if (best.tiles >= cap && (long)M * K >= kWholeTilesFrom) {
+        if (gemm_tiles_whole(M, K, n, nseg)) {
             best.blocks = best.tiles;
             best.slots = 1;
             return best;

@@ -96,7 +96,7 @@ struct GemmTiledPlan {
     int tiles, blocks;            // tiles of the product; blocks, each of which takes an equal range of all their K steps
     int slots;                    // partial slots per output
 };
-constexpr int kWholeTilesFrom = 20 * 2048;         // rows x K from which the tiles of a wide product of up to 128 rows stay whole
+bool gemm_tiles_whole(int M, int K, const int *n, int nseg);     // up to 128 rows: no tile shared; once true for M rows, for more (to 64, to 128) too
 GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated);
 bool gemm_tiled_gates(int M, int K, const int *n);                // whether the gate|up projection n = {f, f} applies SwiGLU itself
 int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg);

@@ -165,10 +165,11 @@ def test_tiled_projections_at_tile_edges(rows, w4):
 
 
 @pytest.mark.parametrize("rows,d,ffn,vocab", [(65, 256, 640, 500), (128, 384, 1024, 777), (127, 2560, 2560, 900),
-                                               (40, 128, 256, 65537), (64, 256, 256, 65600), (100, 256, 384, 65700)])
+                                               (40, 128, 256, 65537), (64, 256, 256, 65600), (100, 256, 384, 65700),
+                                               (20, 512, 512, 65700), (64, 512, 512, 65700)])
 def test_tiled_projections_of_small_products_and_wide_heads(rows, d, ffn, vocab):
     """65 to 128 rows on 64-row tiles (few K tiles) next to products on 128-row tiles (2560 x 7680: 2560 of them), and heads
-    of 512 column tiles and more, which are given out whole, the last one a part."""
+    of 512 column tiles and more, given out whole, the last one a part, or (20 rows of d_model 512) shared."""
     shape = synth.Shape(1, d, d // 64, d // 64, 64, ffn, vocab, 1.0e4)
     p = Pair(shape, torch.bfloat16, 1, 192, seed=rows, std=0.05)
     p.step(synth.make_tokens(vocab, (1, rows), rows), what=f"{rows} rows")
