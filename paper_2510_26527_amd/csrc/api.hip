@@ -215,7 +215,7 @@ psd_status psd_model_pack(psd_model *m, void *packed_mem, size_t packed_bytes, v
         const int n_gu[2] = {d.d_ffn, d.d_ffn};
         launch_gemm_pack(gu, n_gu, 2, d.d_model, base + off[4 * l + P_GU], false, st);
         const void *dn[1] = {m->layer(l, W_DOWN)};
-        launch_gemm_pack(dn, n_o, 1, d.d_ffn, base + off[4 * l + P_DOWN], false, st);
+        launch_gemm_pack(dn, n_o, 1, d.d_ffn, base + off[4 * l + P_DOWN], true, st);
     }
     const void *hw[1] = {m->lm_head()};
     const int n_v[1] = {d.vocab};
@@ -278,7 +278,7 @@ int proj_splits(const psd_model *mdl, int rows, int K, const int *n, int nseg, b
     int N = 0;
     for (int s = 0; s < nseg; ++s) N += n[s];
     if (mdl->w4 && !head && rows <= kStreamMaxRows) return gemm_w4_slots(K, n, nseg, false);
-    if (mdl->packed && rows <= kStreamMaxRows) return gemm_packed_splits(rows, K, n, nseg);
+    if (mdl->packed && rows <= kStreamMaxRows) return gemm_packed_splits(K, n, nseg);
     return gemm_pick_splitk(mdl->d.dtype, rows, K, N, n, nseg);
 }
 
@@ -292,13 +292,11 @@ ForwardPlan plan_projections(const psd_model *mdl, int M) {
     const int n_qkv[3] = {hd, kvd, kvd}, n_o[1] = {d.d_model}, n_gu[2] = {d.d_ffn, d.d_ffn};
     p.folded = mdl->packed && d.dtype == PSD_BF16 && M <= kStreamMaxRows;
     p.sk_qkv = proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
-    // folded: O runs on the column kernel (one owner per output), or, 4-bit, on partial slots with the arrival epilogue
+    // folded: O and down run on the column kernel (one owner per output), or, 4-bit, on partial slots with the arrival epilogue
     p.sk_o = p.folded ? (mdl->w4 ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false);
     p.gated = d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu);
     p.sk_gu = p.gated ? 1 : proj_splits(mdl, M, d.d_model, n_gu, 2, false);
-    // folded: the down projection runs on the unit kernel with the residual epilogue, its partials in slots
-    p.sk_down = p.folded ? (mdl->w4 ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : gemm_resid_slots(gemm_pack_tiles(n_o, 1), d.d_ffn))
-                         : proj_splits(mdl, M, d.d_ffn, n_o, 1, false);
+    p.sk_down = p.folded ? (mdl->w4 ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : 1) : proj_splits(mdl, M, d.d_ffn, n_o, 1, false);
     p.half_copies = d.dtype == PSD_BF16 && (M > kStreamMaxRows || (mdl->w4 && p.folded));
     auto need = [&](int sk, int N) { const size_t b = (size_t)sk * M * N * 4; if (b > p.partial_bytes) p.partial_bytes = b; };
     need(p.sk_qkv, p.width_qkv);
@@ -330,10 +328,11 @@ void plan_layout(const psd_model *mdl, int batch, int n_new, int len_bound, bool
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
     p.off_x = take((size_t)M * d.d_model * 4);
-    p.off_xn = take((size_t)M * d.d_model * act);
+    const int Mx = p.folded ? kStreamMaxRows : M;            // operand order has room for all rows of an MFMA tile
+    p.off_xn = take((size_t)Mx * d.d_model * act);
     p.off_q = take((size_t)M * hd * act);
-    p.off_attn = take((size_t)M * hd * act);
-    p.off_h = take((size_t)M * d.d_ffn * act);
+    p.off_attn = take((size_t)Mx * hd * act);
+    p.off_h = take((size_t)Mx * d.d_ffn * act);
     p.off_xn16 = take(p.half_copies ? (size_t)M * d.d_model * 2 : 0);
     p.off_attn16 = take(p.half_copies ? (size_t)M * hd * 2 : 0);
     p.off_h16 = take(p.half_copies ? (size_t)M * d.d_ffn * 2 : 0);
@@ -353,8 +352,8 @@ ForwardPlan plan_forward(const psd_model *mdl, int batch, int n_new, int n_logit
     return p;
 }
 
-// the largest head_partial_bytes over every number of logit rows (0 .. n_new per sequence).  Below kPairRows
-// rows, from there to kStreamMaxRows, from there to 64 and from there to 128, the slots are one and the same among the counts
+// the largest head_partial_bytes over every number of logit rows (0 .. n_new per sequence).  Up to
+// kStreamMaxRows rows, from there to 64 and from there to 128, the slots are one and the same among the counts
 // that share tiles between blocks, so the largest of those has the most (a count with whole tiles has none); above, it does not
 // grow with the rows as long as they fill the same number of 256-row tiles, so a run of them that starts at one slot is done.
 size_t worst_head_partial_bytes(const psd_model *mdl, int batch, int n_new, bool folded) {
@@ -364,7 +363,7 @@ size_t worst_head_partial_bytes(const psd_model *mdl, int batch, int n_new, bool
         const size_t b = head_partial_bytes(mdl, Ml, folded, slots);
         worst = b > worst ? b : worst;
     };
-    for (int edge : {kPairRows - 1, kStreamMaxRows, 64, 128}) {
+    for (int edge : {kStreamMaxRows, 64, 128}) {
         int Ml = (M < edge ? M : edge) / batch * batch;
         while (mdl->d.dtype == PSD_BF16 && Ml > (edge == 128 ? 64 : kStreamMaxRows) && gemm_tiles_whole(Ml, mdl->d.d_model, n_v, 1)) Ml -= batch;
         if (Ml > 0) at(Ml, nullptr);
@@ -446,6 +445,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
 
     (void)hipGetLastError();
     auto norm_gain = [&](int l) { return l < d.n_layers ? m->layer(l, W_ATTN_NORM) : m->final_norm(); };
+    const bool op_folded = M <= kOpFoldRows;
     unsigned *tile_ctr = p.folded ? (unsigned *)(ws + p.off_tilectr) : nullptr;
     // ql, qj: layer and index of the first segment among the layer's 4-bit projections (q k v o gate up down), if any
     auto gemm = [&](const float *xin, int rows, int K, const void *w0, int n0, const void *w1, int n1,
@@ -454,6 +454,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         g.wpack = rows <= kStreamMaxRows ? wpack : nullptr;
         g.x = xin; g.x_rows_per_group = rows > 0 ? rows : 1; g.x_group_stride = 0; g.x_group_offset = 0;
         g.x16 = xin == xn ? xn16 : (xin == attn ? attn16 : (xin == h ? h16 : nullptr));
+        if (p.folded) { g.x_op = (const uint16_t *)xin; g.op_folded = op_folded; }
         g.w[0] = w0; g.w[1] = w1; g.w[2] = w2; g.n[0] = n0; g.n[1] = n1; g.n[2] = n2;
         g.nseg = w2 ? 3 : (w1 ? 2 : 1);
         g.M = rows; g.K = K; g.N = n0 + n1 + n2; g.partial = dst; g.splitk = sk; g.reduced = nullptr;
@@ -463,24 +464,27 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         for (int sgm = 0; sgm < g.nseg && g.w4; ++sgm) { g.w4_scale[sgm] = m->qscale(ql, qj + sgm); g.w4_zero[sgm] = m->qzero(ql, qj + sgm); }
         launch_gemm(d.dtype, g, st);
     };
-    // Folded mode: no RMSNorm kernel runs.  The projections that write the residual stream add into it and
-    // leave behind x * gain of the next norm (in xn) and per-16-column sums of squares (one slab of M floats
-    // per strip); the projections that read the residual stream take xn as it is, and the kernels that consume
+    // Folded mode: no RMSNorm kernel runs, and xn, attn and h hold their activations in operand order (common.h).  The projections
+    // that write the residual stream add into it and leave behind x * gain of the next norm (in xn) and per-16-column sums of
+    // squares (one slab of M floats per strip); the projections that read the residual stream take xn as it is, and the kernels that consume
     // their output multiply by the row scale rsqrt(mean x^2 + eps).
     float *sumsq = (float *)(ws + p.off_sumsq);
     const int col_tiles = d.d_model / 16;
     const int n_o_fw[1] = {d.d_model};
     RowScale rs{nullptr, 0, 1.0f / (float)d.d_model, d.rms_eps};
     if (p.folded) rs.sumsq = sumsq;
+    uint16_t *xn_op = p.folded ? (uint16_t *)xn : nullptr;
     const float *act = xn;     // what QKV / gate|up / lm_head read: rmsnorm(x) * gain, or x * gain when folded
     auto resid_gemm = [&](const float *xin, int K, const void *w, int sk, const void *wpack, const void *next_gain,
-                          bool by_units, int ql, int qj, bool last = false) {
+                          int ql, int qj, bool last = false) {
         if (p.folded) {
             GemmArgs g{};
             g.wpack = wpack; g.x = xin; g.x_rows_per_group = M; g.w[0] = w; g.n[0] = d.d_model; g.nseg = 1;
-            const bool slots = by_units || m->w4;         // partial slots + arrival epilogue, else one block per 16 columns
+            const bool slots = m->w4;                     // partial slots + arrival epilogue, else one block per 16 columns
             g.M = M; g.K = K; g.N = d.d_model; g.splitk = slots ? sk : 1; g.pack_tiles = gemm_pack_tiles(g.n, 1);
-            g.x_resid = x; g.xg_out = xn; g.xg16_out = xn16; g.gain = next_gain; g.sumsq_out = sumsq; g.w4 = m->w4;
+            g.x_op = (const uint16_t *)xin; g.op_folded = op_folded;
+            g.xg_op = m->w4 && !last ? nullptr : xn_op;   // 4-bit projections read xn16, the head xn
+            g.x_resid = x; g.xg16_out = xn16; g.gain = next_gain; g.sumsq_out = sumsq; g.w4 = m->w4;
             g.x16 = xin == attn ? attn16 : (xin == h ? h16 : nullptr);
             if (slots) { g.tile_counter = tile_ctr; g.partial = partial; }
             launch_gemm(d.dtype, g, st);
@@ -498,8 +502,8 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         if (!p.fused_rope) return PSD_ERR_UNIMPLEMENTED;
         tree_anc = (const uint32_t *)(ws + p.off_tree);      // written by the embedding kernel
     }
-    launch_embed_norm(d.dtype, m->embed(), tokens_dev, x, norm_gain(0), xn, p.folded ? sumsq : nullptr, M, d.d_model,
-                      d.vocab, d.rms_eps, rt, xn16, ZeroFill{tile_ctr, p.folded ? gemm_pack_tiles(n_o_fw, 1) : 0},
+    launch_embed_norm(d.dtype, m->embed(), tokens_dev, x, norm_gain(0), p.folded ? nullptr : xn, p.folded ? sumsq : nullptr, M, d.d_model,
+                      d.vocab, d.rms_eps, rt, xn16, m->w4 && d.n_layers ? nullptr : xn_op, ZeroFill{tile_ctr, p.folded && m->w4 ? gemm_pack_tiles(n_o_fw, 1) : 0},
                       tree, tree ? (uint32_t *)(ws + p.off_tree) : nullptr, st);
     rs.tiles = 1;
     for (int l = 0; l < d.n_layers; ++l) {
@@ -511,23 +515,27 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
                                       d.n_kv_heads, d.d_head, kv->max_len, d.rope_theta, rt.cs, st);
         AttnArgs a{};
         if (p.fused_rope) { a.qkv_partial = partial; a.qkv_splits = p.sk_qkv; a.rs = rs; a.rope_cs = rt.cs; a.tree_anc = tree_anc; }
-        a.q = q; a.k = kl; a.v = vl; a.lens = kv->lens; a.out = p.half_copies ? nullptr : attn; a.out16 = attn16;   // the O projection reads one of the two
+        a.q = q; a.k = kl; a.v = vl; a.lens = kv->lens; a.out16 = attn16;        // the O projection reads one of the three
+        if (!p.half_copies) { if (p.folded) a.out_op = (uint16_t *)attn; else a.out = attn; }
+        a.op_folded = op_folded;
         a.B = B; a.R = n_new; a.h_q = d.n_q_heads; a.h_kv = d.n_kv_heads; a.d_h = d.d_head; a.max_len = kv->max_len;
         a.len_bound = len_bound; a.part_o = (float *)(ws + p.off_po); a.part_ml = (float *)(ws + p.off_pml);
         a.splits = p.attn_splits;
         launch_attention(d.dtype, a, st);
 
-        resid_gemm(attn, hd, m->layer(l, W_O), p.sk_o, m->pack(l, P_O), m->layer(l, W_FFN_NORM), false, l, 3);
+        resid_gemm(attn, hd, m->layer(l, W_O), p.sk_o, m->pack(l, P_O), m->layer(l, W_FFN_NORM), l, 3);
         gemm(act, M, d.d_model, m->layer(l, W_GATE), d.d_ffn, m->layer(l, W_UP), d.d_ffn, nullptr, 0, p.sk_gu,
              p.gated ? nullptr : partial, m->pack(l, P_GU), l, 4);
-        if (!p.gated) launch_reduce_swiglu(partial, p.sk_gu, rs, p.half_copies ? nullptr : h, M, d.d_ffn, h16, st);
-        resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), true, l, 6, l + 1 == d.n_layers);
+        if (!p.gated)
+            launch_reduce_swiglu(partial, p.sk_gu, rs, p.half_copies || p.folded ? nullptr : h, M, d.d_ffn, h16,
+                                 p.folded && !p.half_copies ? (uint16_t *)h : nullptr, st);
+        resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), l, 6, l + 1 == d.n_layers);
     }
     bool advanced = false;                                   // the head's reduction, the last kernel of its kind of pass, does it
     if (n_logit_rows > 0) {
         // lm_head on the last n_logit_rows rows of every sequence (unfolded: xn already holds the final norm)
         GemmArgs hg{};
-        hg.x = act; hg.x16 = xn16; hg.x_rows_per_group = n_logit_rows; hg.x_group_stride = n_new; hg.x_group_offset = n_new - n_logit_rows;
+        hg.x = act; hg.x_op = xn_op; hg.op_folded = op_folded; hg.x16 = xn16; hg.x_rows_per_group = n_logit_rows; hg.x_group_stride = n_new; hg.x_group_offset = n_new - n_logit_rows;
         hg.w[0] = m->lm_head(); hg.n[0] = d.vocab; hg.nseg = 1;
         hg.M = B * n_logit_rows; hg.K = d.d_model; hg.N = d.vocab;
         hg.wpack = hg.M <= kStreamMaxRows ? m->pack_head() : nullptr;

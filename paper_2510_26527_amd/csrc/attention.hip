@@ -553,6 +553,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
             const float L = s_L[qc];
             if (a.out) a.out[row * DH + d] = acc / L;
             if (a.out16) a.out16[row * DH + d] = f32_to_f16_bits(acc / L);
+            if (a.out_op) op_store(a.out_op, (int)(row / a.h_q), (int)(row % a.h_q) * DH + d, a.op_folded, acc / L);
         } else {
             a.part_o[(row * a.splits + split) * DH + d] = acc;
             if (d == 0) {
@@ -795,6 +796,8 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_wide_kernel(AttnArgs a, flo
                     *reinterpret_cast<uint2 *>(a.out16 + out_row[qt] * DH + dt * 16 + 4 * g) =
                         make_uint2(f32_to_f16_bits(r[0]) | ((uint32_t)f32_to_f16_bits(r[1]) << 16),
                                    f32_to_f16_bits(r[2]) | ((uint32_t)f32_to_f16_bits(r[3]) << 16));
+                if (a.out_op)
+                    op_store4(a.out_op, (int)(out_row[qt] / a.h_q), (int)(out_row[qt] % a.h_q) * DH + dt * 16 + 4 * g, a.op_folded, r);
             }
         } else {
             float *po = a.part_o + (out_row[qt] * a.splits + split) * DH;
@@ -825,6 +828,7 @@ __global__ void attn_combine_kernel(AttnArgs a) {
     }
     if (a.out) a.out[row * DH + d] = acc / L;
     if (a.out16) a.out16[row * DH + d] = f32_to_f16_bits(acc / L);
+    if (a.out_op) op_store(a.out_op, (int)(blockIdx.x / a.h_q), (int)(blockIdx.x % a.h_q) * DH + d, a.op_folded, acc / L);
 }
 
 // query tiles of 16 per block: bounded by registers (hi+lo query operands and fp32 outputs)

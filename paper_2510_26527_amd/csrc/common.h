@@ -41,6 +41,34 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return f32_to_bf16_bits(lo) | (f32_to_bf16_bits(hi) << 16);
 }
 
+// Operand order: the activations of a pass of up to 16 rows as the matrix cores take them, so that a wavefront reads the
+// operand of 32 k in whole 1 KB pieces instead of 16 bytes out of every line of every row.  K is cut into steps of 128
+// and these into quarters: quarter q of a step holds k = (q >> 1) * 64 + g * 16 + (q & 1) * 8 + e of lane group g, e < 8, the
+// order in which the packed weights are stored.  A quarter is two fragments of 64 lanes x 8 bf16, the high parts hi = RNE(x) and
+// the remainders lo = RNE(x - hi), lane = 16 g + row; or, folded (up to 8 rows), one fragment whose lanes 16 g + row and
+// 16 g + 8 + row hold both.
+
+__device__ __forceinline__ size_t op_at(int m, int k, bool folded) {          // element index of the high part of x[m][k]
+    const int quarter = (k >> 7) * 4 + ((k >> 6) & 1) * 2 + ((k >> 3) & 1);
+    return (size_t)quarter * (folded ? 512 : 1024) + ((k >> 4) & 3) * 128 + m * 8 + (k & 7);
+}
+__device__ __forceinline__ int op_lo(bool folded) { return folded ? 64 : 512; }       // from there to the remainder
+__device__ __forceinline__ void op_store(uint16_t *op, int m, int k, bool folded, float x) {
+    const uint32_t hi = f32_to_bf16_bits(x);
+    uint16_t *p = op + op_at(m, k, folded);
+    p[0] = (uint16_t)hi;
+    p[op_lo(folded)] = (uint16_t)f32_to_bf16_bits(x - bf16_bits_to_f32(hi));
+}
+// x[m][k .. k + 3], k a multiple of 4
+__device__ __forceinline__ void op_store4(uint16_t *op, int m, int k, bool folded, f32x4 x) {
+    const uint32_t h01 = pack_bf16x2(x[0], x[1]), h23 = pack_bf16x2(x[2], x[3]);
+    uint16_t *p = op + op_at(m, k, folded);
+    *reinterpret_cast<uint2 *>(p) = make_uint2(h01, h23);
+    *reinterpret_cast<uint2 *>(p + op_lo(folded)) =
+        make_uint2(pack_bf16x2(x[0] - __uint_as_float(h01 << 16), x[1] - __uint_as_float(h01 & 0xffff0000u)),
+                   pack_bf16x2(x[2] - __uint_as_float(h23 << 16), x[3] - __uint_as_float(h23 & 0xffff0000u)));
+}
+
 // round-to-nearest-even fp32 -> fp16 bit pattern
 __device__ __forceinline__ uint16_t f32_to_f16_bits(float f) {
     const _Float16 h = (_Float16)f;

@@ -12,9 +12,7 @@
 //                            units of a GEMM are contiguous, and the grid is persistent: each block streams
 //                            an equal, contiguous range of units (stream-K), its four wavefronts on the four
 //                            K quarters of every unit, and writes one partial per tile it touches.
-//                            With RESID (the down projection) the block that arrives last at a tile adds the
-//                            tile's partials and runs the residual epilogue below.
-//   gemm_bf16_column_kernel  M <= 16, the O projection (it writes the residual stream and is short along K): one
+//   gemm_bf16_column_kernel  M <= 16, the projections that write the residual stream (O, down): one
 //                            block per 16 output columns over the whole K range; the residual add, the
 //                            gain-scaled copy and the RMSNorm statistics happen in its epilogue.
 //   gemm_w4_unit_kernel      M <= 16, 4-bit weight-only quantised projections (groups of 128 along K): the unit
@@ -26,8 +24,8 @@
 //                            (weights convert to fp16 exactly, activations are rounded to fp16); the gate|up projection
 //                            applies SwiGLU itself where its tiles alone fill the chip.
 // Activations are fp32 in memory in every case (the tiled kernel reads an fp16 copy its producers leave beside
-// them).  The M <= 16 bf16 kernels feed each activation to the matrix cores as a pair of bf16 values hi + lo (two
-// MFMAs against the same weight operand): with plain bf16 activations the logits of the 7B-shaped random-init
+// them; between the packed M <= 16 kernels they travel as bf16 pairs hi + lo in operand order, common.h).  The M <= 16 bf16
+// kernels feed each activation to the matrix cores as that pair (two MFMAs against the same weight operand): with plain bf16 activations the logits of the 7B-shaped random-init
 // models are 3e-2 off the fp64 result, above the 2e-2 bar; the weights, which are what streams from HBM, stay bf16.
 // Every kernel but the ones with the residual epilogue writes its result as split-K partials [splitk][M][N]
 // (splitk >= 1); the consumer (the fused row-wise kernels, the attention kernel's operand build, or
@@ -316,11 +314,9 @@ __device__ __forceinline__ void resid_tile_finish(const GemmArgs &g, int tile, i
             const size_t o = (size_t)tok * g.N + col;
             v += g.x_resid[o];
             g.x_resid[o] = v;
-            if (g.xg_out) {
-                const float xg = v * (g.gain ? bf16_bits_to_f32(((const uint16_t *)g.gain)[col]) : 1.0f);
-                g.xg_out[o] = xg;
-                if (g.xg16_out) g.xg16_out[o] = f32_to_f16_bits(xg);
-            }
+            const float xg = v * (g.gain ? bf16_bits_to_f32(((const uint16_t *)g.gain)[col]) : 1.0f);
+            if (g.xg_op) op_store(g.xg_op, tok, (int)col, g.op_folded, xg);
+            if (g.xg16_out) g.xg16_out[o] = f32_to_f16_bits(xg);
             sq = v * v;
         }
         sq = wave_sum(sq);                                      // the tile's 64 columns of row tok sit in this wavefront
@@ -334,7 +330,7 @@ __device__ __forceinline__ void resid_tile_finish(const GemmArgs &g, int tile, i
 // holds the sums of its four wavefronts.  They are added in wavefront order and the block writes ONE partial, slot =
 // its index among the blocks that share the tile (the block that finishes the tile zeroes the slots nobody writes),
 // or, RESID, hands them to the arrival epilogue above.  The tile's units are [first, first + upt) of the U that P blocks share.
-template <bool RESID>
+template <bool RESID, bool FOLD = false>
 __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (&red)[4][kSkinnyRows][17], int tile, long first,
                                                 int upt, long U, long P, bool tile_end, int *s_last) {
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
@@ -355,11 +351,13 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
         resid_tile_finish<4>(g, tile, slot, n_contrib, mine, q, 4, row_ok, col, s_last);
     } else if (row_ok) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < (FOLD ? 2 : 4); ++r) {
             const int tok = q + 4 * r;
             if (tok < g.M) {
-                g.partial[((size_t)slot * g.M + tok) * g.N + col] =
-                    ((red[0][lane][tok] + red[1][lane][tok]) + red[2][lane][tok]) + red[3][lane][tok];
+                float v = ((red[0][lane][tok] + red[1][lane][tok]) + red[2][lane][tok]) + red[3][lane][tok];
+                if constexpr (FOLD)                        // the products with the remainders stand eight columns further on
+                    v += ((red[0][lane][tok + 8] + red[1][lane][tok + 8]) + red[2][lane][tok + 8]) + red[3][lane][tok + 8];
+                g.partial[((size_t)slot * g.M + tok) * g.N + col] = v;
                 if (tile_end)
                     for (int jj = slot + 1; jj < g.splitk; ++jj) g.partial[((size_t)jj * g.M + tok) * g.N + col] = 0.f;
             }
@@ -370,161 +368,130 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
 // Block b streams the contiguous units [range_begin(b), range_begin(b + 1)); wavefront q multiplies the q-th 4 KB of
 // every unit (K offsets (q>>1)*64 + (q&1)*8 + 16 gq of the unit's 128), so the four wavefronts of a block read 16 KB
 // in one piece and the blocks of the grid adjacent ranges: the access pattern of a plain streaming read.  Weights
-// and the matching 8 activations per lane travel through two register stages filled by buffer loads that return zeros
-// without touching memory where there is nothing to load, so that every wavefront runs the same straight-line loop, and a
-// stage's data is waited for with the other stage still in flight.  (Single: the block's range is the buffer and ends the
-// weight loads.  PAIR: a load past the range, or of a second tile that is not there, gets an offset beyond any buffer; the
-// buffer itself ends with the packed matrix.)  At the end of a tile (or of the range) the four K quarters are added
-// through LDS in wavefront order and the block writes ONE partial: slot = its index among the blocks that share the tile;
-// the block that finishes a tile zeroes the slots nobody writes.
+// and the matching 8 activations per lane travel through a ring of register stages filled by buffer loads that return zeros
+// past the end of the block's range, so that every wavefront runs the same straight-line loop, and a stage's data is waited for
+// with the other stages still in flight.  At the end of a
+// tile (or of the range) the four K quarters are added through LDS in wavefront order and the block writes ONE partial: slot =
+// its index among the blocks that share the tile; the block that finishes a tile zeroes the slots nobody writes.
 //
-// RESID (the projections that write the residual stream, when a block per 16 columns would be the slower choice):
-// every output element still gets one owner, found at run time.  A block publishes its partial with agent-scope
-// stores, waits for them, and counts itself in on the tile's counter; whichever block arrives last adds the tile's
-// slots in slot order (so the sum does not depend on who that was) and runs the column kernel's epilogue on the
-// tile's 64 columns: residual add, gain-scaled copy, sum of squares per row into sumsq_out[tile][m].  It leaves the
-// counter at zero for the next launch.  No block waits for another.
-//
-// PAIR: the unit is two 16 KB units, the same K step of two neighbouring tiles.  The activations of a K step are then read
-// from L2 and split once for 128 weight rows instead of 64; at 16 rows they weigh half as much as the weights of 64.
-template <bool RESID, bool PAIR>
+// Activations: in operand order, two fragments or (folded) one a quarter; or row-major fp32, split into high part and remainder
+// here (the head of a pass of more than 16 rows).  Row-major, every lane's 16 bytes come out of another line, and at 16 rows
+// the activations cost the vector memory path twice what the weights do.  Measured, QKV, gate|up and head of the 7B shape averaged
+// (us a launch; row-major and two stages in an order of the compiler's / this): 1 row 28.3 / 26.9, 8 rows 28.9 / 27.2, 9 rows
+// 29.2 / 27.7, 16 rows 30.8 (two tiles at a time) / 29.7; plain reads of the same weights 25.4.  Two tiles at a time, which
+// share a K step's activations, gain nothing any more (16 rows 30.6), nor does a fourth stage.
+enum ActForm { kRows, kOp, kOpFolded };
+template <ActForm ACT>
 __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
-    constexpr int H = PAIR ? 2 : 1;
+    constexpr bool FOLD = ACT == kOpFolded;
+    constexpr int R = 3, XV = FOLD ? 1 : 2;                // units in flight per wavefront (its 4 KB of each)
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int i = lane & 15, gq = lane >> 4;
     const int K = g.K, ns = K / kSkinnyStepK;
-    const long U = (long)((g.pack_tiles + H - 1) / H) * ns, P = gridDim.x;
+    const long U = (long)g.pack_tiles * ns, P = gridDim.x;
     const int u0 = (int)range_begin(blockIdx.x, U, P), u1 = (int)range_begin(blockIdx.x + 1, U, P);
     if (u0 >= u1) return;
     const int n_my = u1 - u0;
-    const int tile0 = u0 / ns * H;                         // the block's first tile
-    // the buffer: from that tile to the end of the packed matrix, or, single, the block's units
-    const size_t w_first = PAIR ? (size_t)tile0 * ns : (size_t)u0, w_left = ((size_t)g.pack_tiles * ns - w_first) * kUnitBytes;
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-        (char *)const_cast<void *>(g.wpack) + w_first * kUnitBytes, 0,
-        PAIR ? (int)(w_left < 0x7fffffff ? w_left : 0x7fffffff) : n_my * kUnitBytes, 0x00020000);
-    // activations: offsets from the first row's source row; a row past M points past the buffer and reads zeros
-    const size_t row_first = x_row(g, 0);
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(g.x) + row_first * K, 0, 0x7ffffff0, 0x00020000);
-    const unsigned kq = (unsigned)((q >> 1) * 64 + gq * 16 + (q & 1) * 8) * 4u;
-    const unsigned xbase = i < g.M ? (unsigned)((x_row(g, i) - row_first) * K * 4) + kq : 0x80000000u;
+        (char *)const_cast<void *>(g.wpack) + (size_t)u0 * kUnitBytes, 0, n_my * kUnitBytes, 0x00020000);
+    // activations: a row past M points past the buffer and reads zeros; row-major, offsets from the first row's source row
+    const size_t row_first = ACT == kRows ? x_row(g, 0) : 0;
+    const __amdgpu_buffer_rsrc_t rx =
+        ACT == kRows ? __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(g.x) + row_first * K, 0, 0x7ffffff0, 0x00020000)
+                     : __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(g.x_op), 0, K * (FOLD ? 32 : 64), 0x00020000);
+    constexpr unsigned kStepX = ACT == kRows ? kSkinnyStepK * 4 : kSkinnyStepK * (FOLD ? 32 : 64);   // bytes from one K step to the next
+    unsigned xbase = 0x80000000u;
+    if constexpr (ACT == kRows) {
+        if (i < g.M) xbase = (unsigned)((x_row(g, i) - row_first) * K * 4) + (unsigned)((q >> 1) * 64 + gq * 16 + (q & 1) * 8) * 4u;
+    } else {
+        const int m = FOLD ? i & 7 : i;
+        if (m < g.M) xbase = (unsigned)(q * (FOLD ? 1024 : 2048) + (gq * 16 + (int)x_row(g, m) + (FOLD ? i & 8 : 0)) * 16);
+    }
     const unsigned lane_off = q * 4096u + lane * 16u;
 
-    u32x4 A[2][4], X[PAIR ? 1 : 2][2];
-    auto load_w = [&](u32x4 (&a)[4], unsigned off) {
+    u32x4 A[R][4], X[R][XV];
+    int step_issue = u0 % ns;
+    auto issue = [&](int j, int n) {                       // n = index of the unit inside the block's range
+        const unsigned xo = n < n_my ? xbase + (unsigned)step_issue * kStepX : 0x80000000u;
+        X[j][0] = __builtin_amdgcn_raw_buffer_load_b128(rx, xo, 0, 0);
+        if constexpr (!FOLD) X[j][1] = __builtin_amdgcn_raw_buffer_load_b128(rx, xo + (ACT == kRows ? 16 : 1024), 0, 0);
+        const unsigned wo = (unsigned)n * kUnitBytes + lane_off;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) a[s] = __builtin_amdgcn_raw_buffer_load_b128(rw, off + s * 1024, 0, 2);   // 2: streaming
+        for (int s = 0; s < 4; ++s) A[j][s] = __builtin_amdgcn_raw_buffer_load_b128(rw, wo + s * 1024, 0, 2);   // 2: streaming
+        step_issue = step_issue + 1 == ns ? 0 : step_issue + 1;
+        // The loads stay in this order.  Left to itself the compiler requests the first units in another order than the loop
+        // does, and as loads return in order, a wait for one stage is then a wait for all of them.
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto load_x = [&](u32x4 (&x)[2], unsigned off) {
-        x[0] = __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0);
-        x[1] = __builtin_amdgcn_raw_buffer_load_b128(rx, off + 16, 0, 0);
-    };
-    f32x4 acc[4 * H];
+    f32x4 acc[4];
 #pragma unroll
-    for (int s = 0; s < 4 * H; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-    bf16x8 bh, bl;
-    auto split_x = [&](const u32x4 (&x)[2]) {
-        f32x8 xv;
+    for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int j) {
+        bf16x8 bh, bl;
+        if constexpr (ACT == kRows) {
+            f32x8 xv;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { xv[e] = __uint_as_float(x[0][e]); xv[4 + e] = __uint_as_float(x[1][e]); }
-        split_bf16(xv, &bh, &bl);
-    };
-    // hi parts over all accumulators, then lo parts: no back-to-back MFMAs on one accumulator
-    auto multiply = [&](const u32x4 (&a)[4], int at) {
+            for (int e = 0; e < 4; ++e) { xv[e] = __uint_as_float(X[j][0][e]); xv[4 + e] = __uint_as_float(X[j][XV - 1][e]); }
+            split_bf16(xv, &bh, &bl);
+        } else {
+            bh = __builtin_bit_cast(bf16x8, X[j][0]);
+            bl = __builtin_bit_cast(bf16x8, X[j][XV - 1]);
+        }
+        // hi parts over all accumulators, then lo parts: no back-to-back MFMAs on one accumulator
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-            acc[at + s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[s]), bh, acc[at + s], 0, 0, 0);
+            acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[j][s]), bh, acc[s], 0, 0, 0);
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-            acc[at + s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[s]), bl, acc[at + s], 0, 0, 0);
+        for (int s = 0; s < 4 && !FOLD; ++s)
+            acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[j][s]), bl, acc[s], 0, 0, 0);
     };
     __shared__ float red[4][kSkinnyRows][17];
-    __shared__ int s_last;
-    // acc[s][v] = y[token i][row s*16 + 4*gq + v of the tile] over this wavefront's K quarter
-    auto flush = [&](int tile, long first, bool tile_end) {
+    int step_use = u0 % ns, tile = u0 / ns;
+    long first = (long)tile * ns;                          // first unit of the tile
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
-            if (PAIR && tile + h >= g.pack_tiles) break;                    // the same for all four wavefronts
+    for (int j = 0; j < R; ++j) issue(j, j);
+    for (int base = 0; base < n_my; base += R) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) red[q][s * 16 + 4 * gq + v][i] = acc[h * 4 + s][v];
-            __syncthreads();
-            unit_tile_flush<RESID>(g, red, tile + h, first, ns, U, P, tile_end, &s_last);
-            __syncthreads();
-        }
-#pragma unroll
-        for (int s = 0; s < 4 * H; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-    };
-    int step_use = u0 % ns, tile = tile0;
-    long first = (long)(u0 / ns) * ns;                     // first unit of the tile (or pair)
-    if constexpr (PAIR) {
-        // stage h = tile h of the pair; unit n + 1 of a stage is requested when unit n of it has been multiplied
-        int step_issue = step_use;
-        unsigned at = lane_off + (unsigned)step_issue * kUnitBytes;          // first tile of the unit to request
-        int tile_issue = tile0;
-        const unsigned tile_bytes = (unsigned)ns * kUnitBytes;
-        auto w_off = [&](int n, int h) { return n < n_my && tile_issue + h < g.pack_tiles ? at + h * tile_bytes : 0x80000000u; };
-        auto x_off = [&](int n) { return n < n_my ? xbase + (unsigned)step_issue * (kSkinnyStepK * 4) : 0x80000000u; };
-        auto next = [&]() {
-            if (++step_issue == ns) { step_issue = 0; tile_issue += 2; at += tile_bytes; }       // past the second tile
-            at += kUnitBytes;
-        };
-        load_w(A[0], w_off(0, 0));
-        load_x(X[0], x_off(0));
-        load_w(A[1], w_off(0, 1));
-        next();
-        for (int n = 0; n < n_my; ++n) {
-            split_x(X[0]);
-            multiply(A[0], 0);
-            load_w(A[0], w_off(n + 1, 0));
-            load_x(X[0], x_off(n + 1));
-            multiply(A[1], 4);
-            load_w(A[1], w_off(n + 1, 1));
-            next();
+        for (int j = 0; j < R; ++j) {
+            const int n = base + j;
+            multiply(j);
+            issue(j, n + R);
             const bool tile_end = step_use + 1 == ns;
             step_use = tile_end ? 0 : step_use + 1;
-            if (tile_end || n + 1 == n_my) flush(tile, first, tile_end);
-            if (tile_end) { tile += 2; first += ns; }
-        }
-    } else {
-        constexpr int R = 2;                               // units in flight per wavefront (its 4 KB of each)
-        int step_issue = step_use;
-        auto issue = [&](int j, int n) {                   // n = index of the unit inside the block's range
-            load_w(A[j], (unsigned)n * kUnitBytes + lane_off);
-            load_x(X[j], n < n_my ? xbase + (unsigned)step_issue * (kSkinnyStepK * 4) : 0x80000000u);
-            step_issue = step_issue + 1 == ns ? 0 : step_issue + 1;
-        };
+            if (n < n_my && (tile_end || n + 1 == n_my)) {                  // the same for all four wavefronts
+                // acc[s][v] = y[token i][row s*16 + 4*gq + v of the tile] over this wavefront's K quarter
 #pragma unroll
-        for (int j = 0; j < R; ++j) issue(j, j);
-        for (int base = 0; base < n_my; base += R) {
+                for (int s = 0; s < 4; ++s) {
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const int n = base + j;
-                split_x(X[j]);
-                multiply(A[j], 0);
-                issue(j, n + R);
-                const bool tile_end = step_use + 1 == ns;
-                step_use = tile_end ? 0 : step_use + 1;
-                if (n < n_my && (tile_end || n + 1 == n_my)) flush(tile, first, tile_end);   // the same for all four wavefronts
-                if (tile_end) { ++tile; first += ns; }
+                    for (int v = 0; v < 4; ++v) red[q][s * 16 + 4 * gq + v][i] = acc[s][v];
+                    acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+                __syncthreads();
+                unit_tile_flush<false, FOLD>(g, red, tile, first, ns, U, P, tile_end, nullptr);
+                __syncthreads();
             }
+            if (tile_end) { ++tile; first += ns; }
         }
     }
 }
 
 // ------------------------------------------------------------------------------ bf16 one-slot column kernel
-// For the projections that write the residual stream (N = d_model): one block per 16 output columns over
-// the whole K range, its wavefronts (sixteen for up to 16 rows, eight above: registers) on different K ranges, added through LDS in wavefront order.
+// For the projections that write the residual stream (N = d_model): one block per 16 output columns over the whole K range,
+// its sixteen wavefronts on equal ranges of the K quarters, added through LDS in wavefront order.
 // Every output element has a single owner, so the block finishes the job itself: x_resid[m][n] += y[m][n],
-// xg_out[m][n] = x_resid[m][n] * gain_next[n] (the operand of the next projection, RMSNorm gain folded in),
+// xg_op[m][n] = x_resid[m][n] * gain_next[n] (the operand of the next projection, RMSNorm gain folded in),
 // and the sum of squares of the updated 16 columns per row goes to sumsq_out, from which the consumer of the
 // next projection derives the RMSNorm scale.  No partial slots, no reduce kernel, no norm kernel.
 // Weights are packed strip-major for this kernel (gemm_pack_strip_kernel): strip (16 rows) x K step is 4 KB
 // = 4 slots of 1 KB in lane order, all K steps of a strip contiguous, so a block streams one contiguous
-// range and a wavefront a contiguous part of it, 16 KB in flight at a time.
-constexpr int kColDepth = 4;                       // K steps loaded per round
+// range and a wavefront a contiguous part of it.
+// What bounds it: the block reads all activations, at 16 rows twice as many bytes as weights, so how they are read decides.  They
+// come in operand order, whole 1 KB pieces, D quarters at a time and ahead of these quarters' weights: the weights, which come
+// from farther, are then not waited for twice.  Measured, O and down of the 7B shape averaged (us a launch; O so on row-major
+// activations and down on the unit kernel with the residual epilogue by the last block to arrive at a tile / this): 1 row
+// 14.4 / 13.9, 8 rows 16.5 / 13.4, 9 rows 17.2 / 15.8, 15 rows 19.9 / 16.8; plain reads 10.8.  Weights and activations in turn
+// 18.2 at 15 rows; a ring of quarters that is refilled one by one 19.7, most of it for its loads past the end, which cost
+// like any other though they touch no memory.
 constexpr int kStripVec = 16 * kSkinnyStepK * 2 / 16;   // 16-byte vectors per (strip, step)
 
 __global__ __launch_bounds__(256) void gemm_pack_strip_kernel(const uint16_t *W, int N, int K, u32x4 *dst) {
@@ -594,106 +561,82 @@ __global__ __launch_bounds__(64) void gemm_pack_w4_kernel(const uint8_t *Q, cons
     }
 }
 
-template <int MT, int kColWaves>
-__global__ __launch_bounds__(kColWaves * 64) void gemm_bf16_column_kernel(GemmArgs g) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <bool FOLD>
+__global__ __launch_bounds__(1024) void gemm_bf16_column_kernel(GemmArgs g) {
+    constexpr int W = 16, D = FOLD ? 11 : 8, XV = FOLD ? 1 : 2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i = lane & 15, gq = lane >> 4;
-    const int K = g.K, ns = K / kSkinnyStepK;
-    const int s0 = wave * ns / kColWaves, s1 = (wave + 1) * ns / kColWaves;
+    const int nq = g.K / 32, q0 = wave * nq / W, q1 = (wave + 1) * nq / W;
 
-    // the epilogue's operands, fetched before the main loop: thread t < 256 owns column n = t & 15 of rows mm = t >> 4
-    const int en = threadIdx.x & 15, emm = threadIdx.x >> 4;
+    // the epilogue's operands, fetched before the main loop: thread t < 256 owns column n = t & 15 of row mm = t >> 4
+    const int en = threadIdx.x & 15, tok = threadIdx.x >> 4;
     const int ecol = blockIdx.x * 16 + en;
-    float e_res[MT], e_gain = 1.0f;
-    if (threadIdx.x < 256 && ecol < g.N) {
+    const bool mine = tok < g.M;                            // one of the first 256 threads; N is a multiple of 16
+    // (buffer loads, for the others out of range: a load under a branch would be waited for where the branch ends)
+    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(g.x_resid, 0, g.M * g.N * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(g.gain), 0, g.N * 2, 0x00020000);
+    const uint32_t e_res = __builtin_amdgcn_raw_buffer_load_b32(rr, mine ? (uint32_t)(tok * g.N + ecol) * 4 : 0x80000000u, 0, 0);
+    const uint16_t e_gain = __builtin_amdgcn_raw_buffer_load_b16(rg, (uint32_t)ecol * 2, 0, 0);
+    const u32x4 *wp = reinterpret_cast<const u32x4 *>(g.wpack) + (size_t)blockIdx.x * nq * 64 + lane;
+    const u32x4 *xp = reinterpret_cast<const u32x4 *>(g.x_op) + lane;                 // rows past M hold anything: their columns are dropped
+    f32x4 acc[2];
+    acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 A[D], X[D][XV];
+    auto load_x = [&](int j, int qn) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int tok = mt * 16 + emm;
-            e_res[mt] = tok < g.M && g.x_resid ? g.x_resid[(size_t)tok * g.N + ecol] : 0.f;
-        }
-        if (g.gain) e_gain = bf16_bits_to_f32(((const uint16_t *)g.gain)[ecol]);
+        for (int v = 0; v < XV; ++v) X[j][v] = xp[(size_t)(qn * XV + v) * 64];
+    };
+    auto load_w = [&](int j, int qn) { A[j] = __builtin_nontemporal_load(wp + (size_t)qn * 64); };
+    auto multiply = [&](int j) {
+#pragma unroll
+        for (int v = 0; v < XV; ++v)
+            acc[FOLD ? j & 1 : v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[j]), __builtin_bit_cast(bf16x8, X[j][v]),
+                                                                            acc[FOLD ? j & 1 : v], 0, 0, 0);
+    };
+    int qn = q0;
+    for (; qn + D <= q1; qn += D) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) load_x(j, qn + j);
+#pragma unroll
+        for (int j = 0; j < D; ++j) load_w(j, qn + j);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < D; ++j) multiply(j);
     }
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j)
+        if (qn + j < q1) load_x(j, qn + j);
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j)
+        if (qn + j < q1) load_w(j, qn + j);
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j)
+        if (qn + j < q1) multiply(j);
 
-    const float *xp[MT];
-    bool xvalid[MT];
+    // acc[.][v] = y[token i][column 4*gq + v of the strip] over this wavefront's quarters (FOLD: the products with the
+    // remainders stand eight tokens further on)
+    __shared__ float red[W][16][17];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int tok = mt * 16 + i;
-        xvalid[mt] = tok < g.M;
-        xp[mt] = g.x + x_row(g, min(tok, g.M - 1)) * K + gq * 16;
-    }
-    f32x4 acc[2][MT];
+    for (int v = 0; v < 4; ++v) red[wave][4 * gq + v][i] = acc[0][v] + acc[1][v];
+    __syncthreads();
+    if (threadIdx.x < 256) {
+        float v = 0.f, sq = 0.f;
+        if (tok < (FOLD ? 8 : 16)) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[h][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const u32x4 *wbase = reinterpret_cast<const u32x4 *>(g.wpack) + (size_t)blockIdx.x * ns * kStripVec + lane;
-    for (int step = s0; step < s1; step += kColDepth) {
-        u32x4 a[kColDepth * 4];
-#pragma unroll
-        for (int j = 0; j < kColDepth; ++j)
-            if (step + j < s1) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    a[j * 4 + q] = __builtin_nontemporal_load(wbase + (size_t)(step + j) * kStripVec + q * 64);
-            }
-#pragma unroll
-        for (int j = 0; j < kColDepth; ++j) {
-            if (step + j >= s1) break;
-            f32x8 xv[4][MT];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    xv[q][mt] = load_act8(xp[mt], (step + j) * kSkinnyStepK + (q >> 1) * 64 + (q & 1) * 8, xvalid[mt]);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const bf16x8 aw = __builtin_bit_cast(bf16x8, a[j * 4 + q]);
-                bf16x8 bh[MT], bl[MT];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) split_bf16(xv[q][mt], &bh[mt], &bl[mt]);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[q & 1][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw, bh[mt], acc[q & 1][mt], 0, 0, 0);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[q & 1][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw, bl[mt], acc[q & 1][mt], 0, 0, 0);
-            }
+            for (int w = 0; w < W; ++w) v += FOLD ? red[w][en][tok] + red[w][en][tok + 8] : red[w][en][tok];
         }
-    }
-
-    // acc[.][mt][v] = y[token mt*16 + i][column 4*gq + v of the strip] over this wavefront's K steps
-    __shared__ float red[kColWaves][16][17];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        if (mt) __syncthreads();
-#pragma unroll
-        for (int v = 0; v < 4; ++v) red[wave][4 * gq + v][i] = acc[0][mt][v] + acc[1][mt][v];
-        __syncthreads();
-        if (threadIdx.x < 256) {
-            const int tok = mt * 16 + emm;
-            float v = 0.f, sq = 0.f;
-#pragma unroll
-            for (int w = 0; w < kColWaves; ++w) v += red[w][en][emm];
-            if (tok < g.M && ecol < g.N) {
-                const size_t o = (size_t)tok * g.N + ecol;
-                if (g.x_resid) {
-                    v += e_res[mt];
-                    g.x_resid[o] = v;
-                    if (g.xg_out) g.xg_out[o] = v * e_gain;
-                    sq = v * v;
-                } else {
-                    g.partial[o] = v;                        // one slot: the projection's output itself
-                }
-            }
-            // the 16 columns of one row sit in 16 consecutive lanes
-            sq += __shfl_xor(sq, 8, 64);
-            sq += __shfl_xor(sq, 4, 64);
-            sq += __shfl_xor(sq, 2, 64);
-            sq += __shfl_xor(sq, 1, 64);
-            if (en == 0 && tok < g.M && g.sumsq_out) g.sumsq_out[(size_t)blockIdx.x * g.M + tok] = sq;
+        if (mine) {
+            v += __uint_as_float(e_res);
+            g.x_resid[(size_t)tok * g.N + ecol] = v;
+            if (g.xg_op) op_store(g.xg_op, tok, ecol, FOLD, v * bf16_bits_to_f32(e_gain));
+            sq = v * v;
         }
+        // the 16 columns of one row sit in 16 consecutive lanes
+        sq += __shfl_xor(sq, 8, 64);
+        sq += __shfl_xor(sq, 4, 64);
+        sq += __shfl_xor(sq, 2, 64);
+        sq += __shfl_xor(sq, 1, 64);
+        if (en == 0 && tok < g.M && g.sumsq_out) g.sumsq_out[(size_t)blockIdx.x * g.M + tok] = sq;
     }
 }
 
@@ -1142,25 +1085,15 @@ GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) 
 // (256 x 37888 x 3584, 148 tiles: 95 us; separate, 84 + 11)
 bool gemm_tiled_gates(int M, int K, const int *n) { return M > 128 && gemm_tiled_plan(M, K, n, 2, true).tiles >= 128; }
 
-static int gemm_stream_units(int M, int tiles) { return M >= kPairRows ? (tiles + 1) / 2 : tiles; }
-static int gemm_stream_grid(int M, int tiles, int K) {
-    const long U = (long)gemm_stream_units(M, tiles) * (K / kSkinnyStepK);
+static int gemm_stream_grid(int tiles, int K) {
+    const long U = (long)tiles * (K / kSkinnyStepK);
     return (int)(U < kStreamBlocks ? (U < 1 ? 1 : U) : kStreamBlocks);
 }
 
-// grid of the unit kernel with the residual epilogue: one block per CU, so that few blocks share a tile (the last of
-// them to arrive adds their partials).  Measured on the 7B down projection, O and down averaged: 256 blocks 16.2 us,
-// 384 blocks 18.5 us, 512 blocks 17.8 us, 128 blocks slower still.
-static int gemm_resid_grid(int tiles, int K) {
-    const long U = (long)tiles * (K / kSkinnyStepK);
-    return (int)(U < kStreamBlocks / 2 ? (U < 1 ? 1 : U) : kStreamBlocks / 2);
+static int gemm_stream_slots(int tiles, int K) {
+    return gemm_slots_of(tiles, K / kSkinnyStepK, gemm_stream_grid(tiles, K));
 }
-
 // largest number of blocks that share one tile, i.e. partial slots per output element
-int gemm_resid_slots(int tiles, int K) { return gemm_slots_of(tiles, K / kSkinnyStepK, gemm_resid_grid(tiles, K)); }
-static int gemm_stream_slots(int M, int tiles, int K) {
-    return gemm_slots_of(gemm_stream_units(M, tiles), K / kSkinnyStepK, gemm_stream_grid(M, tiles, K));
-}
 static int gemm_slots_of(int tiles, int units_per_tile, int grid) {
     const long ns = units_per_tile, U = (long)tiles * ns, P = grid;
     long worst = 1;
@@ -1220,9 +1153,7 @@ int gemm_w4_slots(int K, const int *n, int nseg, bool resid) {
     return gemm_slots_of(tiles, w4_quads(K), gemm_w4_grid(tiles, K, resid));
 }
 
-int gemm_packed_splits(int M, int K, const int *n, int nseg) {
-    return gemm_stream_slots(M, tiles_of(n, nseg, kSkinnyRows), K);
-}
+int gemm_packed_splits(int K, const int *n, int nseg) { return gemm_stream_slots(tiles_of(n, nseg, kSkinnyRows), K); }
 
 int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg) {
     (void)N;
@@ -1257,24 +1188,22 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
             launch_kernel(gemm_w4_unit_kernel<false>, grid, 256, 0, stream, g);
         return;
     }
-    if (g.M <= kStreamMaxRows && g.wpack && g.x_resid && g.tile_counter) {
-        ScopedProf sp(PSD_KIND_GEMM_COLUMN, stream);
-        launch_kernel(gemm_bf16_unit_kernel<true, false>, gemm_resid_grid(g.pack_tiles, g.K), 256, 0, stream, g);
-        return;
-    }
     if (g.M <= kStreamMaxRows && g.wpack && g.x_resid) {
         ScopedProf sp(PSD_KIND_GEMM_COLUMN, stream);
-        const int grid = g.N / 16;                        // every segment is a multiple of 64 wide; M <= 16: one row tile
-        launch_kernel(gemm_bf16_column_kernel<1, 16>, grid, 1024, 0, stream, g);
+        const int grid = g.N / 16;                        // every segment is a multiple of 64 wide
+        if (g.op_folded) launch_kernel(gemm_bf16_column_kernel<true>, grid, 1024, 0, stream, g);
+        else launch_kernel(gemm_bf16_column_kernel<false>, grid, 1024, 0, stream, g);
         return;
     }
-    // the unit kernel addresses the activation rows with 32-bit offsets from the first one
+    // the unit kernel addresses the rows of row-major activations with 32-bit offsets from the first one
     const bool x_near = (long)(x_row(g, g.M - 1) - x_row(g, 0) + 1) * g.K * 4 < 0x7fff0000L;
-    if (g.M <= kStreamMaxRows && g.wpack && x_near) {
+    if (g.M <= kStreamMaxRows && g.wpack && (g.x_op || x_near)) {
         ScopedProf sp(PSD_KIND_GEMM_SKINNY, stream);
-        const int grid = gemm_stream_grid(g.M, g.pack_tiles, g.K);
-        if (g.M >= kPairRows) launch_kernel(gemm_bf16_unit_kernel<false, true>, grid, 256, 0, stream, g);
-        else launch_kernel(gemm_bf16_unit_kernel<false, false>, grid, 256, 0, stream, g);
+        const int grid = gemm_stream_grid(g.pack_tiles, g.K);
+        auto go = [&](auto kernel) { launch_kernel(kernel, grid, 256, 0, stream, g); };
+        if (g.x_op && g.op_folded) go(gemm_bf16_unit_kernel<kOpFolded>);
+        else if (g.x_op) go(gemm_bf16_unit_kernel<kOp>);
+        else go(gemm_bf16_unit_kernel<kRows>);
     } else if (g.M <= kStreamMaxRows) {
         ScopedProf sp(PSD_KIND_GEMM_SLOT, stream);
         dim3 grid(tiles_of(g.n, g.nseg, kSkinnyRows), g.splitk);

@@ -39,11 +39,8 @@ void launch_accept_greedy(const AcceptArgs &a, bool vec_ok, hipStream_t stream);
 // LDS-tiled kernel wins (measured on two LLaMA2-7B-shaped layers: 0.28 ms at 16 rows; at 32 rows 0.43 ms
 // streaming against 0.38 ms tiled, at 64 rows 0.66 against 0.38).
 constexpr int kStreamMaxRows = 16;
-// From this many rows on the unit kernel takes tiles in pairs.  Measured (us a launch, QKV, gate|up and head of the 7B shape
-// averaged, pairs / single): 4 rows 29.1 / 28.4, 9 rows 29.7 / 29.1, 12 rows 29.8 / 30.0, 15 rows 30.9 / 32.3, 16 rows
-// 30.5 / 32.6; below, the larger unit's uneven ranges and longer flush cost what it saves.  The residual projections stay
-// single (15 rows 28.2 / 19.9: twice the blocks meet at every arrival).
-constexpr int kPairRows = 13;
+// Up to this many rows a pass' operand-order activations (common.h) are folded: both parts in one fragment.
+constexpr int kOpFoldRows = 8;
 // y[m][n] = sum_k x[m][k] * W[n][k]; W is up to three row-major [n_i][K] matrices whose
 // outputs are concatenated along n (QKV, gate|up).
 // r_m from per-tile sums of squares: rsqrt(sum_t sumsq[t * M + m] * inv_d + eps); sumsq NULL: 1
@@ -57,6 +54,8 @@ struct GemmArgs {
                                   //   (m / x_rows_per_group) * x_group_stride + x_group_offset + m % x_rows_per_group
     const uint16_t *x16;          // optional: the same matrix already rounded to fp16 (what the tiled kernel multiplies)
     int x_rows_per_group, x_group_stride, x_group_offset;
+    const uint16_t *x_op;         // bf16, packed weights, passes of up to 16 rows: the activations in operand order (common.h); x is not read
+    bool op_folded;               //   ... high part and remainder in one fragment (the pass has at most 8 rows)
     const void *w[3];
     int n[3];
     int nseg;
@@ -69,16 +68,16 @@ struct GemmArgs {
     // -- bf16, M <= kStreamMaxRows, packed weights only: RMSNorm folded into the projections around it -----------
     // rmsnorm(x) W^T = r_m * ((x * gain) W^T) with r_m = rsqrt(mean_k x[m][k]^2 + eps).  A projection with x_resid
     // set adds its output into the residual stream x_resid [M][N], writes
-    // xg_out[m][n] = x_resid[m][n] * gain[n] (the operand of the next projection; gain = the next norm's)
+    // xg_op[m][n] = x_resid[m][n] * gain[n] (the operand of the next projection, in operand order; gain = the next norm's)
     // and sumsq_out[strip or tile][m] = sum of x_resid[m][n]^2 over the 16 (column kernel) or 64 (unit kernel)
     // columns one block finishes; the consumer of the next projection's output multiplies by r_m (RowScale).
     float *x_resid;
-    float *xg_out;
-    uint16_t *xg16_out;           // optional: xg_out rounded to fp16 (the operand of the 4-bit projections)
+    uint16_t *xg_op;              // NULL: nobody reads it
+    uint16_t *xg16_out;           // optional: the same rounded to fp16, row-major (the operand of the 4-bit projections)
     const void *gain;             // [N] bf16
-    float *sumsq_out;             // [N/16][M] (column kernel) or [N/64][M] (unit kernel with the residual epilogue)
-    unsigned *tile_counter;       // non-NULL selects the unit kernel for this projection: [N/64] arrival counters, zero
-                                  //   before the launch and left at zero by it; `partial` then holds gemm_resid_slots() slots
+    float *sumsq_out;             // [N/16][M] (column kernel) or [N/64][M] (4-bit)
+    unsigned *tile_counter;       // 4-bit projections with a residual epilogue: [N/64] arrival counters, zero before the
+                                  //   launch and left at zero by it
     // -- 4-bit weights (W4A16, groups of 128 along K): wpack holds the 4-bit quad layout of
     // launch_gemm_pack_w4; the projection writes `splitk` partial slots (gemm_w4_slots)
     bool w4;
@@ -104,9 +103,8 @@ int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg);
 int gemm_pack_tiles(const int *n, int nseg);
 size_t gemm_pack_bytes(const int *n, int nseg, int K);
 int gemm_w4_slots(int K, const int *n, int nseg, bool resid);  // partial slots of a 4-bit projection (resid: the arrival epilogue's grid)
-int gemm_packed_splits(int M, int K, const int *n, int nseg);   // partial slots (the splitk to use) with packed weights
-int gemm_resid_slots(int tiles, int K);                          // partial slots of a projection run with tile_counter
-// strip_major: the layout of the column kernel (the O projection)
+int gemm_packed_splits(int K, const int *n, int nseg);   // partial slots (the splitk to use) with packed weights
+// strip_major: the layout of the column kernel (O and down)
 void launch_gemm_pack(const void *const *w, const int *n, int nseg, int K, void *dst, bool strip_major, hipStream_t stream);
 // 4-bit weight-only quantised projections: q [n][K/2] bytes (low nibble = even k), scale bf16 [n][K/128],
 // zero u8 [n][K/128]; w = scale * (q - zero).  Each n[s] a multiple of 64.
@@ -123,6 +121,8 @@ struct AttnArgs {
     const int32_t *lens;          // [B] valid positions BEFORE this forward
     float *out;                   // [B][R][h_q*d_h] fp32; NULL where only the next one is read
     uint16_t *out16;              // optional: the same rounded to fp16 (the operand of the tiled and the 4-bit O projection)
+    uint16_t *out_op;             // optional: the same in operand order (common.h; the operand of the packed O projection)
+    bool op_folded;
     int B, R, h_q, h_kv, d_h, max_len;
     int len_bound;                // host upper bound of lens[b] + R
     float *part_o;                // split scratch [B][h_q][R][splits][d_h]
@@ -186,9 +186,10 @@ struct ZeroFill {
     int n;
 };
 // tree (or NULL): row r sits at position lens[b] + depth[r], and tree_anc receives the ancestor masks
-// x = embed[token]; then xn = rmsnorm(x) * gain, or (sumsq_out non-NULL) xn = x * gain and sumsq_out[m] = sum_k x[m][k]^2
+// x = embed[token]; then xn = rmsnorm(x) * gain, or (sumsq_out non-NULL) xn = x * gain and sumsq_out[m] = sum_k x[m][k]^2;
+// xn_op (only with sumsq_out): xn goes there in operand order, and xn may be NULL
 void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, float *x, const void *gain, float *xn,
-                       float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, ZeroFill zf,
+                       float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, uint16_t *xn_op, ZeroFill zf,
                        const TreeShape *tree, uint32_t *tree_anc, hipStream_t stream);
 // qkv = sum over splits of partial [S][M][(h_q+2h_kv) d_h] -> rotated q (fp32), rotated k and v appended
 // to the cache (model dtype); cs_table: RopeTable::cs of these rows, NULL: the angles are evaluated again
@@ -198,8 +199,8 @@ void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale 
 // x += sum over splits of partial [S][M][d]; xn = rmsnorm(x) * gain (xn16, if given: the same rounded to fp16, and xn may be NULL)
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
                                  int M, int d, float eps, uint16_t *xn16, hipStream_t stream);
-// h (may be NULL beside h16) = silu(g) * u with [g | u] = sum over splits of partial [S][M][2f]
-void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, hipStream_t stream);
+// h = silu(g) * u with [g | u] = sum over splits of partial [S][M][2f]: any of fp32, fp16 and operand order
+void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, uint16_t *h_op, hipStream_t stream);
 void launch_advance_lens(int32_t *lens, int B, int delta, int max_len, hipStream_t stream);
 void launch_truncate(int32_t *lens, const int32_t *base, const int32_t *keep, int offset, int cap, int B,
                      hipStream_t stream);

@@ -44,7 +44,7 @@ template <typename TW, bool EMBED, int kRowThreads>
 __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *embed, const int32_t *tokens, int vocab,
                                                                     const float *partial, int S, size_t split_stride,
                                                                     float *x, const TW *gain, float *xn, float *sumsq_out,
-                                                                    int d, float eps, RopeTable rt, uint16_t *xn16,
+                                                                    int d, float eps, RopeTable rt, uint16_t *xn16, uint16_t *xn_op,
                                                                     ZeroFill zf, TreeShape tree, uint32_t *tree_anc) {
     constexpr int kMaxV4 = kMaxRowV4 / kRowThreads;
     __shared__ float red[kRowThreads / 64];
@@ -133,6 +133,8 @@ __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *em
         if (i4 < n4) {
             const f32x4 r = v[j] * scale * load_gain4(gain, i4);
             if (xn) orow[i4] = r;
+            if constexpr (EMBED)
+                if (xn_op) op_store4(xn_op, m, 4 * i4, (int)gridDim.x <= kOpFoldRows, r);
             if (xn16)              // the same row rounded to fp16: the operand of the tiled projections
                 reinterpret_cast<uint2 *>(xn16 + (size_t)m * d)[i4] =
                     make_uint2(f32_to_f16_bits(r[0]) | ((uint32_t)f32_to_f16_bits(r[1]) << 16),
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(256) void reduce_rope_append_tiled_kernel(const flo
 // h = silu(g) * u, four columns per thread, one row per blockIdx.y; [g | u] arrive as split-K partials of
 // the gate|up projection
 __global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float *partial, int S, size_t split_stride, RowScale rs,
-                                                            float *h, int M, int f, uint16_t *h16) {
+                                                            float *h, int M, int f, uint16_t *h16, uint16_t *h_op) {
     __shared__ float red[4];
     const int m = blockIdx.y, f4 = f >> 2;
     float ssq = 0.f;
@@ -324,6 +326,7 @@ __global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float *partial
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
     if (h) reinterpret_cast<f32x4 *>(h + (size_t)m * f)[j4] = o;
+    if (h_op) op_store4(h_op, m, 4 * j4, M <= kOpFoldRows, o);
     if (h16)
         reinterpret_cast<uint2 *>(h16 + (size_t)m * f)[j4] =
             make_uint2(f32_to_f16_bits(o[0]) | ((uint32_t)f32_to_f16_bits(o[1]) << 16),
@@ -348,16 +351,16 @@ __global__ void truncate_to_kernel(int32_t *lens, int new_len, int B) {
 }  // namespace
 
 void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, float *x, const void *gain, float *xn,
-                       float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, ZeroFill zf,
+                       float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, uint16_t *xn_op, ZeroFill zf,
                        const TreeShape *tree, uint32_t *tree_anc, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_EMBED, stream);
     const TreeShape ts = tree ? *tree : TreeShape{};
     if (dtype == PSD_BF16)
         launch_kernel(residual_norm_kernel<uint16_t, true, 256>, M, 256, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0,
-                                                                           x, (const uint16_t *)gain, xn, sumsq_out, d, eps, rt, xn16, zf, ts, tree_anc);
+                                                                           x, (const uint16_t *)gain, xn, sumsq_out, d, eps, rt, xn16, xn_op, zf, ts, tree_anc);
     else
         launch_kernel(residual_norm_kernel<float, true, 256>, M, 256, 0, stream, (const float *)embed, tokens, vocab, nullptr, 0, 0, x,
-                                                                        (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, zf, ts, tree_anc);
+                                                                        (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, xn_op, zf, ts, tree_anc);
 }
 
 constexpr int kWideRowMax = 256;       // rows up to which a norm block has 1024 threads
@@ -367,12 +370,12 @@ void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *
     const size_t stride = (size_t)M * d;
     if (dtype == PSD_BF16)
         (M <= kWideRowMax ? launch_kernel(residual_norm_kernel<uint16_t, false, 1024>, M, 1024, 0, stream, nullptr, nullptr, 0, partial, S,
-                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr)
+                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, nullptr, ZeroFill{}, TreeShape{}, nullptr)
                           : launch_kernel(residual_norm_kernel<uint16_t, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S,
-                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr));
+                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, nullptr, ZeroFill{}, TreeShape{}, nullptr));
     else
         launch_kernel(residual_norm_kernel<float, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S, stride, x,
-                                                                         (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr);
+                                                                         (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, nullptr, ZeroFill{}, TreeShape{}, nullptr);
 }
 
 void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale rs, float *q_out, void *k_cache,
@@ -397,10 +400,10 @@ void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale 
                                                                   lens, R, h_q, h_kv, d_h, max_len, theta, cs_table);
 }
 
-void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, hipStream_t stream) {
+void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, uint16_t *h_op, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_SWIGLU, stream);
     const dim3 grid((unsigned)((f / 4 + 255) / 256), (unsigned)M);
-    launch_kernel(reduce_swiglu_kernel, grid, 256, 0, stream, partial, S, (size_t)M * 2 * f, rs, h, M, f, h16);
+    launch_kernel(reduce_swiglu_kernel, grid, 256, 0, stream, partial, S, (size_t)M * 2 * f, rs, h, M, f, h16, h_op);
 }
 
 void launch_advance_lens(int32_t *lens, int B, int delta, int max_len, hipStream_t stream) {

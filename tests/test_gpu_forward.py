@@ -130,6 +130,20 @@ SMALL_MHA = synth.Shape(2, 256, 2, 2, 128, 384, 1000, 1.0e4)          # d_head 1
 SMALL_G7 = synth.Shape(1, 896, 7, 1, 128, 1152, 2048, 1.0e6)          # Qwen2-like group of 7
 
 
+@pytest.mark.parametrize("n_new", [1, 8, 9, 16])
+@pytest.mark.parametrize("d_model,d_ffn", [(128, 128), (384, 1408), (256, 5760), (256, 4224)])
+def test_operand_order_activations(d_model, d_ffn, n_new):
+    """Activations between the packed projections of up to 16 rows, folded (8 rows) and not (9), 1 and 16 rows: K of fewer 32-k
+    quarters than the column kernel has wavefronts (128, 256), of a few each (384, 1408), and of one round of its loads, folded
+    (11: 5760) or not (8: 4224), and a little more."""
+    shape = synth.Shape(1, d_model, d_model // 64, d_model // 64, 64, d_ffn, 200, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 128, seed=n_new, ctx=40, std=0.05, pack=True)
+    toks = synth.make_tokens(shape.vocab, (1, n_new + 3), d_ffn)
+    p.step(toks[:, :n_new], what="all rows' logits")
+    p.step(toks[:, n_new:], n_logit_rows=1, what="the last row's")
+    p.close()
+
+
 @pytest.mark.parametrize("shape,n_new,ctx", [
     (SMALL_GQA, 1, 300), (SMALL_GQA, 5, 200), (SMALL_GQA, 8, 300), (SMALL_GQA, 9, 1000), (SMALL_GQA, 17, 129), (SMALL_GQA, 40, 64),
     (SMALL_MHA, 8, 1024), (SMALL_MHA, 11, 77), (SMALL_MHA, 70, 200), (SMALL_MHA, 130, 0), (SMALL_MHA, 200, 30),
