@@ -274,12 +274,12 @@ struct ForwardPlan {
 };
 
 // partial slots of one projection (or head) over `rows` rows: what its kernel splits K into
-int proj_splits(const psd_model *mdl, int rows, int K, const int *n, int nseg, bool head) {
+int proj_splits(const psd_model *mdl, int rows, int K, const int *n, int nseg, bool head, bool strips = false) {
     int N = 0;
     for (int s = 0; s < nseg; ++s) N += n[s];
     if (mdl->w4 && !head && rows <= kStreamMaxRows) return gemm_w4_slots(K, n, nseg, false);
     if (mdl->packed && rows <= kStreamMaxRows) return gemm_packed_splits(K, n, nseg);
-    return gemm_pick_splitk(mdl->d.dtype, rows, K, N, n, nseg);
+    return gemm_pick_splitk(mdl->d.dtype, rows, K, N, n, nseg, mdl->packed && !strips && (head || !mdl->w4));
 }
 
 // the part of the plan that depends on the number of rows alone
@@ -293,10 +293,10 @@ ForwardPlan plan_projections(const psd_model *mdl, int M) {
     p.folded = mdl->packed && d.dtype == PSD_BF16 && M <= kStreamMaxRows;
     p.sk_qkv = proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
     // folded: O and down run on the column kernel (one owner per output), or, 4-bit, on partial slots with the arrival epilogue
-    p.sk_o = p.folded ? (mdl->w4 ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false);
-    p.gated = d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu);
+    p.sk_o = p.folded ? (mdl->w4 ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false, true);
+    p.gated = d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4);
     p.sk_gu = p.gated ? 1 : proj_splits(mdl, M, d.d_model, n_gu, 2, false);
-    p.sk_down = p.folded ? (mdl->w4 ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : 1) : proj_splits(mdl, M, d.d_ffn, n_o, 1, false);
+    p.sk_down = p.folded ? (mdl->w4 ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : 1) : proj_splits(mdl, M, d.d_ffn, n_o, 1, false, true);
     p.half_copies = d.dtype == PSD_BF16 && (M > kStreamMaxRows || (mdl->w4 && p.folded));
     auto need = [&](int sk, int N) { const size_t b = (size_t)sk * M * N * 4; if (b > p.partial_bytes) p.partial_bytes = b; };
     need(p.sk_qkv, p.width_qkv);
@@ -365,7 +365,7 @@ size_t worst_head_partial_bytes(const psd_model *mdl, int batch, int n_new, bool
     };
     for (int edge : {kStreamMaxRows, 64, 128}) {
         int Ml = (M < edge ? M : edge) / batch * batch;
-        while (mdl->d.dtype == PSD_BF16 && Ml > (edge == 128 ? 64 : kStreamMaxRows) && gemm_tiles_whole(Ml, mdl->d.d_model, n_v, 1)) Ml -= batch;
+        while (mdl->d.dtype == PSD_BF16 && Ml > (edge == 128 ? 64 : kStreamMaxRows) && gemm_tiles_whole(Ml, mdl->d.d_model, n_v, 1, mdl->packed != nullptr)) Ml -= batch;
         if (Ml > 0) at(Ml, nullptr);
     }
     for (int Ml = 129 > batch ? (128 + batch) / batch * batch : batch; Ml <= M;) {
@@ -451,7 +451,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     auto gemm = [&](const float *xin, int rows, int K, const void *w0, int n0, const void *w1, int n1,
                     const void *w2, int n2, int sk, float *dst, const void *wpack, int ql = -1, int qj = -1) {
         GemmArgs g{};
-        g.wpack = rows <= kStreamMaxRows ? wpack : nullptr;
+        g.wpack = wpack;
         g.x = xin; g.x_rows_per_group = rows > 0 ? rows : 1; g.x_group_stride = 0; g.x_group_offset = 0;
         g.x16 = xin == xn ? xn16 : (xin == attn ? attn16 : (xin == h ? h16 : nullptr));
         if (p.folded) { g.x_op = (const uint16_t *)xin; g.op_folded = op_folded; }
@@ -490,7 +490,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
             launch_gemm(d.dtype, g, st);
             rs.tiles = slots ? g.pack_tiles : col_tiles;
         } else {
-            gemm(xin, M, K, w, d.d_model, nullptr, 0, nullptr, 0, sk, partial, wpack, ql, qj);
+            gemm(xin, M, K, w, d.d_model, nullptr, 0, nullptr, 0, sk, partial, nullptr, ql, qj);       // (packed strip-major: for the column kernel alone)
             launch_reduce_residual_norm(d.dtype, partial, sk, x, next_gain, p.half_copies && !last ? nullptr : xn, M, d.d_model, d.rms_eps, xn16, st);
         }
     };
@@ -538,7 +538,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         hg.x = act; hg.x_op = xn_op; hg.op_folded = op_folded; hg.x16 = xn16; hg.x_rows_per_group = n_logit_rows; hg.x_group_stride = n_new; hg.x_group_offset = n_new - n_logit_rows;
         hg.w[0] = m->lm_head(); hg.n[0] = d.vocab; hg.nseg = 1;
         hg.M = B * n_logit_rows; hg.K = d.d_model; hg.N = d.vocab;
-        hg.wpack = hg.M <= kStreamMaxRows ? m->pack_head() : nullptr;
+        hg.wpack = m->pack_head();
         hg.pack_tiles = gemm_pack_tiles(hg.n, 1);
         hg.splitk = p.sk_head;
         const bool two_step = p.sk_head > 1 || p.folded;

@@ -744,6 +744,168 @@ __global__ __launch_bounds__(256) void gemm_w4_unit_kernel(GemmArgs g) {
     }
 }
 
+// ------------------------------------------------------------------------------ bf16 rows kernel (17 to 128 rows, packed weights)
+// Between the unit kernel and the tiled one: the weights go from the packed copy straight into MFMA operands, a strip of 16
+// rows of W per wavefront and 128 k a step, R steps in flight, and become fp16 (exactly) in registers; the fp16 activations, MT
+// tiles of 16 rows, are what a block's eight wavefronts share and go through LDS, one barrier a step.  They travel
+// one step ahead of the weights, so that in the in-order return queue they never wait for them.  NW wavefronts = strips make a tile of
+// 16 NW columns.  The grid is one block per CU; block b takes whole tiles (rows_whole) or, where no tile width fills the chip with
+// whole ones, an equal range of the product's steps.  gated: whole tiles of NW / 2 gate and as many up strips, whose products
+// meet in LDS at the end.
+// LDS: fragment (quarter q, tile mt) of a step is 64 lanes x 16 bytes; lane (i, g) lies at 16 g + (i ^ (4 q + g)): threads write
+// whole rows, 16 bytes to each of 16 fragments, which without the xor were all in one bank (0.65 us a step).
+constexpr int kRowsBlocks = 256, kRowsMax = 128;
+
+template <int NW, int MT>
+__global__ __launch_bounds__(64 * NW) void gemm_bf16_rows_kernel(GemmArgs g) {
+    constexpr int R = 4, NT = 64 * NW;
+    const bool gated = g.swiglu16 != nullptr;
+    constexpr int XV = MT * 16 * 16, XCH = (XV + NT - 1) / NT;        // 16-byte vectors of a step of X, per thread
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, gq = lane >> 4;
+    const int K = g.K, ns = K / kSkinnyStepK;
+    const long U = (long)g.tiled_tiles * ns, P = gridDim.x;
+    const int u0 = __builtin_amdgcn_readfirstlane(g.rows_whole ? (int)range_begin(blockIdx.x, g.tiled_tiles, P) * ns : (int)range_begin(blockIdx.x, U, P));
+    const int u1 = __builtin_amdgcn_readfirstlane(g.rows_whole ? (int)range_begin(blockIdx.x + 1, g.tiled_tiles, P) * ns : (int)range_begin(blockIdx.x + 1, U, P));
+    if (u0 >= u1) return;
+    const int n_my = u1 - u0;
+
+    __shared__ __attribute__((aligned(16))) u32x4 s_x[2][4 * MT * 64];
+    const size_t x_first = x_row(g, 0);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(g.x16) + x_first * K, 0, 0x7ffffff0, 0x00020000);
+    uint32_t xoff[XCH];                                    // consecutive threads: consecutive 16 bytes of a row's 256
+#pragma unroll
+    for (int c = 0; c < XCH; ++c) {
+        const int v = tid + c * NT, m = v >> 4;
+        xoff[c] = v < XV && m < g.M ? (uint32_t)((x_row(g, m) - x_first) * K * 2) + (v & 15) * 16 : 0x80000000u;
+    }
+    u32x4 xr[R][XCH];
+    int xs_step = u0 % ns, xs_n = 0;
+    auto load_x = [&](int j) {
+        const uint32_t dead = xs_n < n_my ? 0u : 0x80000000u;
+#pragma unroll
+        for (int c = 0; c < XCH; ++c) xr[j][c] = __builtin_amdgcn_raw_buffer_load_b128(rx, (xoff[c] + (uint32_t)xs_step * 256) | dead, 0, 0);
+        ++xs_n;
+        xs_step = xs_step + 1 == ns ? 0 : xs_step + 1;
+        __builtin_amdgcn_sched_barrier(0);                 // (as in the unit kernel: the loads stay in this order)
+    };
+    auto store_x = [&](int j, int buf) {
+#pragma unroll
+        for (int c = 0; c < XCH; ++c) {
+            const int v = tid + c * NT, m = v >> 4, piece = v & 15;           // piece = (half, lane group, low bit of the quarter)
+            const int q = (piece >> 3) * 2 + (piece & 1), gg = (piece >> 1) & 3;
+            if (v < XV) s_x[buf][(q * MT + (m >> 4)) * 64 + gg * 16 + ((m & 15) ^ (q * 4 + gg))] = xr[j][c];
+        }
+    };
+
+    u32x4 A[R][4];
+    int is_step = u0 % ns, is_tile = u0 / ns, is_n = 0;
+    __amdgpu_buffer_rsrc_t rw;
+    struct Strip { int seg, row, col0; };                  // which matrix, its first row there, the matrix' first output column
+    auto strip_of = [&](int tile) {                        // this wavefront's strip of a tile
+        if (gated) return Strip{wave < NW / 2 ? 0 : 1, (tile * (NW / 2) + wave % (NW / 2)) * 16, 0};
+        const TileRef t = find_tile(g, tile, 16 * NW);
+        return Strip{t.seg, t.row0 + wave * 16, t.col0};
+    };
+    auto set_tile = [&]() {                                // the buffer: the strip of the tile to request
+        const Strip t = strip_of(is_tile < g.tiled_tiles ? is_tile : 0);
+        int pack0 = 0;
+        for (int sgm = 0; sgm < t.seg; ++sgm) pack0 += (g.n[sgm] + kSkinnyRows - 1) / kSkinnyRows;
+        const int row = t.row;
+        const bool there = is_n < n_my && row < g.n[t.seg];
+        const int tile64 = pack0 + row / kSkinnyRows, strip = row % kSkinnyRows / 16;
+        rw = __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(g.wpack) + (there ? (size_t)tile64 * ns * kUnitBytes + strip * 1024 : 0), 0,
+                                               there ? ns * kUnitBytes - strip * 1024 : 0, 0x00020000);
+    };
+    set_tile();
+    auto issue = [&](int j) {
+        const uint32_t at = (lane * 16u + (uint32_t)is_step * kUnitBytes) | (is_n < n_my ? 0u : 0x80000000u);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) A[j][q] = __builtin_amdgcn_raw_buffer_load_b128(rw, at + q * 4096u, 0, 2);       // 2: streaming
+        ++is_n;
+        if (++is_step == ns) { is_step = 0; ++is_tile; set_tile(); }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    f32x4 acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // acc[mt][v] = y[token mt*16 + i][row wave*16 + 4*gq + v of the tile]
+    __shared__ __attribute__((aligned(16))) f32x4 s_up[NW / 2][MT][64];
+    auto flush = [&](int tile) {
+        const Strip t = strip_of(tile);
+        if (gated) {
+            if (wave >= NW / 2)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) s_up[wave - NW / 2][mt][lane] = acc[mt];
+            __syncthreads();
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const int m = mt * 16 + i;
+                const f32x4 gt = acc[mt];
+                acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (wave >= NW / 2 || m >= g.M || t.row >= g.n[0]) continue;
+                const f32x4 up = s_up[wave][mt][lane];
+                f32x4 h;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) h[v] = gt[v] / (1.0f + expf(-gt[v])) * up[v];
+                *reinterpret_cast<uint2 *>(g.swiglu16 + (size_t)m * g.n[0] + t.row + 4 * gq) =
+                    make_uint2(f32_to_f16_bits(h[0]) | ((uint32_t)f32_to_f16_bits(h[1]) << 16),
+                               f32_to_f16_bits(h[2]) | ((uint32_t)f32_to_f16_bits(h[3]) << 16));
+            }
+            return;                                        // (the barrier of the next step stands before s_up is written again)
+        }
+        const int slot = g.rows_whole ? 0 : (int)(blockIdx.x - range_owner((long)tile * ns, U, P));
+        const int zero_to = (tile + 1) * ns <= u1 ? g.splitk : 0;
+        const bool vec = g.N % 4 == 0 && (uintptr_t)g.partial % 16 == 0;               // (whole tiles of the head go to the caller's logits)
+        const int row = t.row + 4 * gq, rows = g.n[t.seg] - row;                       // rows of the four that exist
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int m = mt * 16 + i;
+            const f32x4 r = acc[mt];
+            acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (m >= g.M) continue;
+            float *p = g.partial + ((size_t)slot * g.M + m) * g.N + t.col0 + row;
+            for (int sl = slot; sl == slot || sl < zero_to; ++sl, p += (size_t)g.M * g.N) {
+                const f32x4 o = sl == slot ? r : f32x4{0.f, 0.f, 0.f, 0.f};
+                if (rows >= 4 && vec) *reinterpret_cast<f32x4 *>(p) = o;
+                else
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (v < rows) p[v] = o[v];
+            }
+        }
+    };
+    load_x(0);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        if (j + 1 < R) load_x(j + 1);
+        issue(j);
+    }
+    store_x(0, 0);
+    load_x(0);
+    int use_step = u0 % ns, tile = u0 / ns;
+    for (int base = 0; base < n_my; base += R) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            if (base + j >= n_my) break;                   // the same for all wavefronts
+            __syncthreads();
+            store_x((j + 1) % R, (j + 1) & 1);
+            load_x((j + 1) % R);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f16x8 w = __builtin_bit_cast(f16x8, bf16x8_to_f16x8(A[j][q]));
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        w, __builtin_bit_cast(f16x8, s_x[j & 1][(q * MT + mt) * 64 + gq * 16 + (i ^ (q * 4 + gq))]), acc[mt], 0, 0, 0);
+            }
+            issue(j);
+            if (++use_step == ns || base + j + 1 == n_my) { flush(tile); use_step = 0; ++tile; }
+        }
+    }
+}
+
 typedef __attribute__((ext_vector_type(2))) uint32_t uint2v;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 // 8 four-bit codes (element e in bits 4e .. 4e+3) -> 8 fp16 weights scale * (q - zero); sz = fp16 scale in the high
@@ -1015,6 +1177,41 @@ int tiles_of(const int *n, int nseg, int rows) {
 }  // namespace
 
 static int gemm_slots_of(int tiles, int units_per_tile, int grid);
+// The rows kernel's tile width and grid.  Whole tiles need no partial slots, no zeroed ones and, in the head, no reduction; so the width
+// of 96, 128 or 160 columns whose whole tiles leave the fewest CUs idle is taken, if that is at most 15 % of them; else tiles of 128
+// are shared, if that gives every block ten steps (below, the tiled kernel's more and shorter blocks start and end sooner).  Measured
+// (45 rows, us with the reduction; tiled kernel / this; columns x K): 32000 x 4096 66.4 / 45.0 (98 % of the CUs), 28672 x 4096 60.9 /
+// 41.1 (87 %), 22016 x 4096 45.1 / 35.2 (96 columns, 90 %), 152064 x 3584 229 / 201, 12288 x 4096 shared 30.8 / 29.3, 4608 x 3584
+// shared 13.6 / 18.3.  From 65 rows on the operands read from LDS, 4 MT KB a wavefront and step, weigh as much as the weights: one
+// round of whole tiles still gains (96 rows, 32000 x 4096 79.1 / 60.1, 22016 x 4096 57.8 / 53.3; 128 rows, 85.4 / 70.5, 28672 x 4096
+// 79.5 / 68.7), more rounds (128 x 152064 x 3584 266 / 281), shared tiles (128 x 12288 x 4096 43.8 / 45.7), ten wavefronts, whose
+// registers spill (two layers and head of the Qwen2-7B shape, 88 rows 631 / 641), or, above 96 rows, six (128 x 22016 x 4096 with
+// SwiGLU 67.6 / 66.9, two layers of the 7B shape 494 / 506) do not.
+RowsPlan gemm_rows_plan(int M, int K, const int *n, int nseg, bool gated) {
+    RowsPlan p{};
+    if (M <= kStreamMaxRows || M > kRowsMax) return p;
+    const int ns = K / kSkinnyStepK;
+    double best = 0.85;
+    for (int nw : {8, 6, 10}) {
+        const int tiles = gated ? (n[0] + 8 * nw - 1) / (8 * nw) : tiles_of(n, nseg, 16 * nw);
+        const int rounds = (tiles + kRowsBlocks - 1) / kRowsBlocks;
+        const double busy = (double)tiles / (rounds * kRowsBlocks);
+        if (busy < best || (M > 64 && (rounds > 1 || nw > 8)) || (M > 96 && nw < 8)) continue;
+        best = busy + 0.01;                                 // (a later width has to be clearly better)
+        p.used = p.whole = true;
+        p.waves = nw;
+        p.tiles = tiles;
+        p.blocks = tiles < kRowsBlocks ? tiles : kRowsBlocks;
+        p.slots = 1;
+    }
+    if (p.used || gated || M > 64) return p;
+    p.waves = 8;
+    p.tiles = tiles_of(n, nseg, 128);
+    p.used = (long)p.tiles * ns >= 10 * kRowsBlocks;
+    p.blocks = kRowsBlocks;
+    if (p.used) p.slots = gemm_slots_of(p.tiles, ns, p.blocks);
+    return p;
+}
 constexpr long kTallKTiles = 1600;
 static int few_row_tile(int M, int K, const int *n, int nseg) {         // 64-row halves of the block tile of up to 128 rows
     return M <= 64 || (long)tiles_of(n, nseg, 256) * (K / kBK) < kTallKTiles ? 1 : 2;
@@ -1026,7 +1223,11 @@ static int few_row_tile(int M, int K, const int *n, int nseg) {         // 64-ro
 // reduction, shared / whole, K = 4096: 64 rows x 65 700 columns 196 / 242, x 100 352 258 / 252, x 256 000 555 / 471; 18 x
 // 151 936 288 / 307; 128 x 73 448 266 / 284, x 100 352 321 / 283, x 256 000 668 / 495; K = 2048: 32 x 140 000 175 / 190,
 // 64 x 110 000 170 / 158, 128 x 65 700 174 / 157.
-bool gemm_tiles_whole(int M, int K, const int *n, int nseg) {
+bool gemm_tiles_whole(int M, int K, const int *n, int nseg, bool packed) {
+    if (packed) {
+        const RowsPlan r = gemm_rows_plan(M, K, n, nseg, false);
+        if (r.used) return r.whole;
+    }
     const int ta = few_row_tile(M, K, n, nseg), nk = K / kBK, tiles = tiles_of(n, nseg, 128 * ta) * (M <= 64 * ta ? 1 : 2);
     const int cap = 512 / ta, idle = (cap - tiles % cap) % cap;
     if (tiles < cap) return false;
@@ -1054,7 +1255,7 @@ GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) 
         best.cols = best.ta == 1 ? 128 : 256;
         best.tiles = tiles_of(n, nseg, best.cols) * (M <= 64 * best.ta ? 1 : 2);
         const long cap = best.ta == 1 ? 512 : 256;
-        if (gemm_tiles_whole(M, K, n, nseg)) {
+        if (gemm_tiles_whole(M, K, n, nseg, false)) {
             best.blocks = best.tiles;
             best.slots = 1;
             return best;
@@ -1083,7 +1284,9 @@ GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) 
 
 // from 128 tiles on (half the CUs busy) not splitting K costs less than a slot of gate and up written and read again
 // (256 x 37888 x 3584, 148 tiles: 95 us; separate, 84 + 11)
-bool gemm_tiled_gates(int M, int K, const int *n) { return M > 128 && gemm_tiled_plan(M, K, n, 2, true).tiles >= 128; }
+bool gemm_tiled_gates(int M, int K, const int *n, bool packed) {
+    return M > 128 ? gemm_tiled_plan(M, K, n, 2, true).tiles >= 128 : packed && gemm_rows_plan(M, K, n, 2, true).used;
+}
 
 static int gemm_stream_grid(int tiles, int K) {
     const long U = (long)tiles * (K / kSkinnyStepK);
@@ -1155,7 +1358,7 @@ int gemm_w4_slots(int K, const int *n, int nseg, bool resid) {
 
 int gemm_packed_splits(int K, const int *n, int nseg) { return gemm_stream_slots(tiles_of(n, nseg, kSkinnyRows), K); }
 
-int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg) {
+int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, bool packed) {
     (void)N;
     if (dtype != PSD_BF16) return 1;
     if (M <= kStreamMaxRows) {
@@ -1167,6 +1370,10 @@ int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg) {
         if (want > cap) want = cap;
         if (want > 16) want = 16;
         return want < 1 ? 1 : want;
+    }
+    if (packed) {
+        const RowsPlan r = gemm_rows_plan(M, K, n, nseg, false);
+        if (r.used) return r.slots;
     }
     return gemm_tiled_plan(M, K, n, nseg, false).slots;
 }
@@ -1208,6 +1415,25 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
         ScopedProf sp(PSD_KIND_GEMM_SLOT, stream);
         dim3 grid(tiles_of(g.n, g.nseg, kSkinnyRows), g.splitk);
         launch_kernel(gemm_bf16_skinny_kernel<1>, grid, 256, 0, stream, g);
+    } else if (const RowsPlan rp = gemm_rows_plan(g.M, g.K, g.n, g.nseg, g.swiglu16 != nullptr); rp.used && g.wpack && !g.w4) {
+        ScopedProf sp(PSD_KIND_GEMM_TILED, stream);
+        GemmArgs t = g;
+        t.tiled_tiles = rp.tiles;
+        t.rows_whole = rp.whole;
+        auto pick = [&](auto waves) {
+            constexpr int NW = decltype(waves)::value;
+            auto go = [&](auto kernel) { launch_kernel(kernel, rp.blocks, 64 * NW, 0, stream, t); };
+            if (g.M <= 32) go(gemm_bf16_rows_kernel<NW, 2>);
+            else if (g.M <= 48) go(gemm_bf16_rows_kernel<NW, 3>);
+            else if (g.M <= 64) go(gemm_bf16_rows_kernel<NW, 4>);
+            else if constexpr (NW <= 8) {                   // (the plan gives ten wavefronts up to 64 rows, six up to 96)
+                if (g.M <= 96) go(gemm_bf16_rows_kernel<NW, 6>);
+                else if constexpr (NW == 8) go(gemm_bf16_rows_kernel<8, 8>);
+            }
+        };
+        if (rp.waves == 6) pick(std::integral_constant<int, 6>{});
+        else if (rp.waves == 8) pick(std::integral_constant<int, 8>{});
+        else pick(std::integral_constant<int, 10>{});
     } else {
         ScopedProf sp(PSD_KIND_GEMM_TILED, stream);
         const GemmTiledPlan p = gemm_tiled_plan(g.M, g.K, g.n, g.nseg, g.swiglu16 != nullptr);

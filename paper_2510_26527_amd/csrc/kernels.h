@@ -84,6 +84,7 @@ struct GemmArgs {
     const void *w4_scale[3], *w4_zero[3];   // M > kStreamMaxRows: w[] are the codes [n][K/2], these the bf16 scales and uint8 zero points [n][K/128]
     // -- M > kStreamMaxRows (the tiled kernel; see GemmTiledPlan) ---------------------------------------------------
     int tiled_tiles;              // set by launch_gemm
+    bool rows_whole;              // set by launch_gemm: blocks of the rows kernel take whole tiles
     uint16_t *swiglu16;           // segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
     RowScale scale;               // applied when writing `reduced` (row = the source row of m)
     int scale_rows;               //   rows per tile slab of scale.sumsq
@@ -95,10 +96,17 @@ struct GemmTiledPlan {
     int tiles, blocks;            // tiles of the product; blocks, each of which takes an equal range of all their K steps
     int slots;                    // partial slots per output
 };
-bool gemm_tiles_whole(int M, int K, const int *n, int nseg);     // up to 128 rows: no tile shared; once true for M rows, for more (to 64, to 128) too
+bool gemm_tiles_whole(int M, int K, const int *n, int nseg, bool packed);     // up to 128 rows: no tile shared; once true for M rows, for more (to 64, to 128) too
 GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated);
-bool gemm_tiled_gates(int M, int K, const int *n);                // whether the gate|up projection n = {f, f} applies SwiGLU itself
-int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg);
+bool gemm_tiled_gates(int M, int K, const int *n, bool packed);                // whether the gate|up projection n = {f, f} applies SwiGLU itself
+// 17 to 128 rows on unit-packed weights: whether the rows kernel takes the product, and how
+struct RowsPlan {
+    bool used, whole;             // whole: no tile is shared between blocks
+    int waves, tiles, blocks, slots;      // wavefronts = 16-column strips of a tile
+};
+RowsPlan gemm_rows_plan(int M, int K, const int *n, int nseg, bool gated);
+// packed: a unit-packed bf16 copy of the weights is there
+int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, bool packed);
 // repacked weights for the M <= kStreamMaxRows path
 int gemm_pack_tiles(const int *n, int nseg);
 size_t gemm_pack_bytes(const int *n, int nseg, int K);

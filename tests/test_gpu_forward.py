@@ -130,6 +130,18 @@ SMALL_MHA = synth.Shape(2, 256, 2, 2, 128, 384, 1000, 1.0e4)          # d_head 1
 SMALL_G7 = synth.Shape(1, 896, 7, 1, 128, 1152, 2048, 1.0e6)          # Qwen2-like group of 7
 
 
+@pytest.mark.parametrize("n_new", [17, 33, 64, 65, 97, 128])
+@pytest.mark.parametrize("d_model,d_ffn,vocab", [(128, 11008, 28001), (128, 14336, 40960), (384, 18944, 512), (1024, 512, 41600)])
+def test_rows_kernel(d_model, d_ffn, vocab, n_new):
+    """17 to 128 rows on packed weights, every number of 16-row tiles (2, 3, 4, 6, 8) at one of its edges: heads in whole tiles of 8
+    strips with a ragged last one (28001), of 10 (40960) and in shared tiles (41600 at K = 1024); gate | up with its SwiGLU in
+    whole tiles of 6 strips, the last one half there (11008), of 8 (14336) and of 10 (18944); one K step and several."""
+    shape = synth.Shape(1, d_model, d_model // 64, d_model // 64, 64, d_ffn, vocab, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 192, seed=n_new, ctx=20, std=0.05, pack=True)
+    p.step(synth.make_tokens(shape.vocab, (1, n_new), d_ffn), what="all rows' logits")
+    p.close()
+
+
 @pytest.mark.parametrize("n_new", [1, 8, 9, 16])
 @pytest.mark.parametrize("d_model,d_ffn", [(128, 128), (384, 1408), (256, 5760), (256, 4224)])
 def test_operand_order_activations(d_model, d_ffn, n_new):
