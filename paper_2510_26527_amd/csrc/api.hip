@@ -306,12 +306,19 @@ ForwardPlan plan_projections(const psd_model *mdl, int M) {
     return p;
 }
 
+// whether the head over Ml rows runs on the unit kernel in whole tiles
+bool head_whole(const psd_model *mdl, int Ml) {
+    const int n_v[1] = {mdl->d.vocab};
+    return mdl->packed && Ml <= kStreamMaxRows && gemm_stream_whole(n_v, 1);
+}
+
 // partial bytes of the head over Ml rows (0: a single split writes the logits in place), and its slots
 size_t head_partial_bytes(const psd_model *mdl, int Ml, bool folded, int *slots) {
     const int n_v[1] = {mdl->d.vocab};
-    const int sk = Ml > 0 ? proj_splits(mdl, Ml, mdl->d.d_model, n_v, 1, true) : 1;
+    const bool whole = head_whole(mdl, Ml);
+    const int sk = Ml > 0 && !whole ? proj_splits(mdl, Ml, mdl->d.d_model, n_v, 1, true) : 1;
     if (slots) *slots = sk;
-    return sk > 1 || folded ? (size_t)sk * Ml * mdl->d.vocab * 4 : 0;
+    return sk > 1 || (folded && !whole) ? (size_t)sk * Ml * mdl->d.vocab * 4 : 0;
 }
 
 // ... and the rest: attention splits, where everything lies in the workspace
@@ -531,7 +538,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
                                  p.folded && !p.half_copies ? (uint16_t *)h : nullptr, st);
         resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), l, 6, l + 1 == d.n_layers);
     }
-    bool advanced = false;                                   // the head's reduction, the last kernel of its kind of pass, does it
+    bool advanced = false;                                   // the head's last kernel, the last one of its kind of pass, does it
     if (n_logit_rows > 0) {
         // lm_head on the last n_logit_rows rows of every sequence (unfolded: xn already holds the final norm)
         GemmArgs hg{};
@@ -541,13 +548,14 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         hg.wpack = m->pack_head();
         hg.pack_tiles = gemm_pack_tiles(hg.n, 1);
         hg.splitk = p.sk_head;
-        const bool two_step = p.sk_head > 1 || p.folded;
+        hg.whole = head_whole(m, hg.M);
+        const bool two_step = !hg.whole && (p.sk_head > 1 || p.folded);
         hg.partial = two_step ? partial : logits_out_dev;
         hg.reduced = two_step ? logits_out_dev : nullptr;
         if (p.folded) { hg.scale = rs; hg.scale_rows = M; }
-        if (hg.reduced) { hg.lens = kv->lens; hg.lens_n = B; hg.lens_add = n_new; hg.lens_max = kv->max_len; }
+        advanced = gemm_moves_lens(d.dtype, hg);
+        if (advanced) { hg.lens = kv->lens; hg.lens_n = B; hg.lens_add = n_new; hg.lens_max = kv->max_len; }
         launch_gemm(d.dtype, hg, st);
-        advanced = hg.reduced != nullptr;
     }
     if (!advanced) launch_advance_lens(kv->lens, B, n_new, kv->max_len, st);
     const psd_status s = check_launch();

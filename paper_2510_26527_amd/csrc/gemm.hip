@@ -107,12 +107,16 @@ __device__ __forceinline__ void store_out(const GemmArgs &g, int ks, int m, int 
 
 
 
+// the kernel that writes the logits also moves the lengths on
+__device__ __forceinline__ void advance_lens(const GemmArgs &g) {
+    for (int b = threadIdx.x; b < g.lens_n; b += blockDim.x) g.lens[b] = min(g.lens[b] + g.lens_add, g.lens_max);
+}
+
 // reduced[m][:] = (sum over splits, in split order) * r_m; one row per blockIdx.y
 __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(GemmArgs g) {
     __shared__ float red[4];
     const int m = blockIdx.y;
-    if (m == 0 && blockIdx.x == 0)
-        for (int b = threadIdx.x; b < g.lens_n; b += 256) g.lens[b] = min(g.lens[b] + g.lens_add, g.lens_max);
+    if (m == 0 && blockIdx.x == 0) advance_lens(g);
     float sc = 1.0f;
     if (g.scale.sumsq) {
         const size_t src = x_row(g, m);
@@ -332,10 +336,10 @@ __device__ __forceinline__ void resid_tile_finish(const GemmArgs &g, int tile, i
 // or, RESID, hands them to the arrival epilogue above.  The tile's units are [first, first + upt) of the U that P blocks share.
 template <bool RESID, bool FOLD = false>
 __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (&red)[4][kSkinnyRows][17], int tile, long first,
-                                                int upt, long U, long P, bool tile_end, int *s_last) {
+                                                int upt, long U, long P, bool tile_end, int *s_last, const float *s_scale = nullptr) {
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const TileRef t = find_tile(g, tile, kSkinnyRows);
-    const long first_owner = range_owner(first, U, P);
+    const long first_owner = g.whole ? blockIdx.x : range_owner(first, U, P);
     const int slot = (int)(blockIdx.x - first_owner);
     const int row = t.row0 + lane;                                  // lane = row of the tile
     const bool row_ok = row < g.n[t.seg];
@@ -357,6 +361,7 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
                 float v = ((red[0][lane][tok] + red[1][lane][tok]) + red[2][lane][tok]) + red[3][lane][tok];
                 if constexpr (FOLD)                        // the products with the remainders stand eight columns further on
                     v += ((red[0][lane][tok + 8] + red[1][lane][tok + 8]) + red[2][lane][tok + 8]) + red[3][lane][tok + 8];
+                if (s_scale && g.whole) v *= s_scale[tok];
                 g.partial[((size_t)slot * g.M + tok) * g.N + col] = v;
                 if (tile_end)
                     for (int jj = slot + 1; jj < g.splitk; ++jj) g.partial[((size_t)jj * g.M + tok) * g.N + col] = 0.f;
@@ -374,6 +379,10 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
 // tile (or of the range) the four K quarters are added through LDS in wavefront order and the block writes ONE partial: slot =
 // its index among the blocks that share the tile; the block that finishes a tile zeroes the slots nobody writes.
 //
+// A head whose whole tiles keep the chip busy (gemm_stream_whole) is given out in whole tiles: the block then applies the rows' scale, works
+// that out itself (its sums of squares requested ahead of the first weights), and writes the logits: no slot and no reduction
+// (128256 x 4096, us with the reduction: 7 rows 166.6 -> 157.6, 14 rows 189.8 -> 171.9).
+//
 // Activations: in operand order, two fragments or (folded) one a quarter; or row-major fp32, split into high part and remainder
 // here (the head of a pass of more than 16 rows).  Row-major, every lane's 16 bytes come out of another line, and at 16 rows
 // the activations cost the vector memory path twice what the weights do.  Measured, QKV, gate|up and head of the 7B shape averaged
@@ -389,11 +398,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
     const int i = lane & 15, gq = lane >> 4;
     const int K = g.K, ns = K / kSkinnyStepK;
     const long U = (long)g.pack_tiles * ns, P = gridDim.x;
-    const int u0 = (int)range_begin(blockIdx.x, U, P), u1 = (int)range_begin(blockIdx.x + 1, U, P);
+    const int u0 = (int)(g.whole ? range_begin(blockIdx.x, g.pack_tiles, P) * ns : range_begin(blockIdx.x, U, P));
+    const int u1 = (int)(g.whole ? range_begin(blockIdx.x + 1, g.pack_tiles, P) * ns : range_begin(blockIdx.x + 1, U, P));
+    if (g.whole && blockIdx.x == 0) advance_lens(g);
     if (u0 >= u1) return;
     const int n_my = u1 - u0;
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         (char *)const_cast<void *>(g.wpack) + (size_t)u0 * kUnitBytes, 0, n_my * kUnitBytes, 0x00020000);
+    // whole: sixteen lanes a row take its sums of squares, the first sixteen each now (past the end: zeros)
+    __shared__ float s_scale[16];
+    const int sm = threadIdx.x >> 4, sl = threadIdx.x & 15;
+    const bool scaled = g.whole && g.scale.sumsq;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(g.scale.sumsq), 0,
+                                                                        scaled ? g.scale.tiles * g.scale_rows * 4 : 0, 0x00020000);
+    const unsigned soff = sm < g.M ? (unsigned)(sl * g.scale_rows + (int)x_row(g, sm)) * 4 : 0x80000000u;
+    uint32_t ssq[16];
+    if (scaled)
+#pragma unroll
+        for (int t = 0; t < 16; ++t) ssq[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, soff + (unsigned)(t * 16 * g.scale_rows) * 4, 0, 0);
     // activations: a row past M points past the buffer and reads zeros; row-major, offsets from the first row's source row
     const size_t row_first = ACT == kRows ? x_row(g, 0) : 0;
     const __amdgpu_buffer_rsrc_t rx =
@@ -450,6 +472,20 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
     long first = (long)tile * ns;                          // first unit of the tile
 #pragma unroll
     for (int j = 0; j < R; ++j) issue(j, j);
+    if (scaled) {                                          // (read after the barrier of the first flush)
+        float v = 0.f;
+#pragma unroll
+        for (int t = 0; t < 16; ++t) v += __uint_as_float(ssq[t]);
+        for (int t = 256 + sl; t < g.scale.tiles; t += 16)
+            v += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, sm < g.M ? (unsigned)(t * g.scale_rows + (int)x_row(g, sm)) * 4 : 0x80000000u, 0, 0));
+        v += __shfl_xor(v, 8, 64);
+        v += __shfl_xor(v, 4, 64);
+        v += __shfl_xor(v, 2, 64);
+        v += __shfl_xor(v, 1, 64);
+        if (sl == 0) s_scale[sm] = 1.0f / sqrtf(v * g.scale.inv_d + g.scale.eps);
+    } else if (g.whole && threadIdx.x < 16) {
+        s_scale[threadIdx.x] = 1.0f;
+    }
     for (int base = 0; base < n_my; base += R) {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
@@ -467,7 +503,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
                     acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
                 __syncthreads();
-                unit_tile_flush<false, FOLD>(g, red, tile, first, ns, U, P, tile_end, nullptr);
+                unit_tile_flush<false, FOLD>(g, red, tile, first, ns, U, P, tile_end, nullptr, s_scale);
                 __syncthreads();
             }
             if (tile_end) { ++tile; first += ns; }
@@ -749,7 +785,7 @@ __global__ __launch_bounds__(256) void gemm_w4_unit_kernel(GemmArgs g) {
 // rows of W per wavefront and 128 k a step, R steps in flight, and become fp16 (exactly) in registers; the fp16 activations, MT
 // tiles of 16 rows, are what a block's eight wavefronts share and go through LDS, one barrier a step.  They travel
 // one step ahead of the weights, so that in the in-order return queue they never wait for them.  NW wavefronts = strips make a tile of
-// 16 NW columns.  The grid is one block per CU; block b takes whole tiles (rows_whole) or, where no tile width fills the chip with
+// 16 NW columns.  The grid is one block per CU; block b takes whole tiles (whole) or, where no tile width fills the chip with
 // whole ones, an equal range of the product's steps.  gated: whole tiles of NW / 2 gate and as many up strips, whose products
 // meet in LDS at the end.
 // LDS: fragment (quarter q, tile mt) of a step is 64 lanes x 16 bytes; lane (i, g) lies at 16 g + (i ^ (4 q + g)): threads write
@@ -765,8 +801,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows_kernel(GemmArgs g) {
     const int i = lane & 15, gq = lane >> 4;
     const int K = g.K, ns = K / kSkinnyStepK;
     const long U = (long)g.tiled_tiles * ns, P = gridDim.x;
-    const int u0 = __builtin_amdgcn_readfirstlane(g.rows_whole ? (int)range_begin(blockIdx.x, g.tiled_tiles, P) * ns : (int)range_begin(blockIdx.x, U, P));
-    const int u1 = __builtin_amdgcn_readfirstlane(g.rows_whole ? (int)range_begin(blockIdx.x + 1, g.tiled_tiles, P) * ns : (int)range_begin(blockIdx.x + 1, U, P));
+    const int u0 = __builtin_amdgcn_readfirstlane(g.whole ? (int)range_begin(blockIdx.x, g.tiled_tiles, P) * ns : (int)range_begin(blockIdx.x, U, P));
+    const int u1 = __builtin_amdgcn_readfirstlane(g.whole ? (int)range_begin(blockIdx.x + 1, g.tiled_tiles, P) * ns : (int)range_begin(blockIdx.x + 1, U, P));
+    if (!g.reduced && blockIdx.x == 0) advance_lens(g);
     if (u0 >= u1) return;
     const int n_my = u1 - u0;
 
@@ -855,7 +892,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows_kernel(GemmArgs g) {
             }
             return;                                        // (the barrier of the next step stands before s_up is written again)
         }
-        const int slot = g.rows_whole ? 0 : (int)(blockIdx.x - range_owner((long)tile * ns, U, P));
+        const int slot = g.whole ? 0 : (int)(blockIdx.x - range_owner((long)tile * ns, U, P));
         const int zero_to = (tile + 1) * ns <= u1 ? g.splitk : 0;
         const bool vec = g.N % 4 == 0 && (uintptr_t)g.partial % 16 == 0;               // (whole tiles of the head go to the caller's logits)
         const int row = t.row + 4 * gq, rows = g.n[t.seg] - row;                       // rows of the four that exist
@@ -978,6 +1015,7 @@ __global__ __launch_bounds__(128 * WN, TA == 1 ? 4 : 1) void gemm_f16_tiled_kern
     const long U = (long)g.tiled_tiles * nk;
     const int u0 = __builtin_amdgcn_readfirstlane((int)range_begin(blk, U, P));
     const int u1 = __builtin_amdgcn_readfirstlane((int)range_begin(blk + 1, U, P));
+    if (!g.reduced && blockIdx.x == 0) advance_lens(g);
 
     // LDS byte addresses of this thread's chunks and operands: stores go to one set of tiles, reads to the other.  They are
     // opaque to the compiler, which would otherwise keep one register per (set, chunk, K step) instead of a base and
@@ -1356,6 +1394,11 @@ int gemm_w4_slots(int K, const int *n, int nseg, bool resid) {
     return gemm_slots_of(tiles, w4_quads(K), gemm_w4_grid(tiles, K, resid));
 }
 
+// whether whole tiles of a head of up to 16 rows leave at most a tenth of the blocks' time idle
+bool gemm_stream_whole(const int *n, int nseg) {
+    const int tiles = tiles_of(n, nseg, kSkinnyRows), rounds = (tiles + kStreamBlocks - 1) / kStreamBlocks;
+    return tiles * 10 >= rounds * kStreamBlocks * 9;
+}
 int gemm_packed_splits(int K, const int *n, int nseg) { return gemm_stream_slots(tiles_of(n, nseg, kSkinnyRows), K); }
 
 int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, bool packed) {
@@ -1376,6 +1419,14 @@ int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, boo
         if (r.used) return r.slots;
     }
     return gemm_tiled_plan(M, K, n, nseg, false).slots;
+}
+
+// the unit kernel addresses the rows of row-major activations with 32-bit offsets from the first one
+static bool unit_reaches(const GemmArgs &g) {
+    return g.x_op || (long)(x_row(g, g.M - 1) - x_row(g, 0) + 1) * g.K * 4 < 0x7fff0000L;
+}
+bool gemm_moves_lens(int dtype, const GemmArgs &g) {
+    return g.reduced || (dtype == PSD_BF16 && (g.M > kStreamMaxRows || (g.whole && unit_reaches(g))));
 }
 
 void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
@@ -1402,11 +1453,9 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
         else launch_kernel(gemm_bf16_column_kernel<false>, grid, 1024, 0, stream, g);
         return;
     }
-    // the unit kernel addresses the rows of row-major activations with 32-bit offsets from the first one
-    const bool x_near = (long)(x_row(g, g.M - 1) - x_row(g, 0) + 1) * g.K * 4 < 0x7fff0000L;
-    if (g.M <= kStreamMaxRows && g.wpack && (g.x_op || x_near)) {
+    if (g.M <= kStreamMaxRows && g.wpack && unit_reaches(g)) {
         ScopedProf sp(PSD_KIND_GEMM_SKINNY, stream);
-        const int grid = gemm_stream_grid(g.pack_tiles, g.K);
+        const int grid = g.whole ? (g.pack_tiles < kStreamBlocks ? g.pack_tiles : kStreamBlocks) : gemm_stream_grid(g.pack_tiles, g.K);
         auto go = [&](auto kernel) { launch_kernel(kernel, grid, 256, 0, stream, g); };
         if (g.x_op && g.op_folded) go(gemm_bf16_unit_kernel<kOpFolded>);
         else if (g.x_op) go(gemm_bf16_unit_kernel<kOp>);
@@ -1419,7 +1468,7 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
         ScopedProf sp(PSD_KIND_GEMM_TILED, stream);
         GemmArgs t = g;
         t.tiled_tiles = rp.tiles;
-        t.rows_whole = rp.whole;
+        t.whole = rp.whole;
         auto pick = [&](auto waves) {
             constexpr int NW = decltype(waves)::value;
             auto go = [&](auto kernel) { launch_kernel(kernel, rp.blocks, 64 * NW, 0, stream, t); };

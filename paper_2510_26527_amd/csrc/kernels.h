@@ -84,11 +84,12 @@ struct GemmArgs {
     const void *w4_scale[3], *w4_zero[3];   // M > kStreamMaxRows: w[] are the codes [n][K/2], these the bf16 scales and uint8 zero points [n][K/128]
     // -- M > kStreamMaxRows (the tiled kernel; see GemmTiledPlan) ---------------------------------------------------
     int tiled_tiles;              // set by launch_gemm
-    bool rows_whole;              // set by launch_gemm: blocks of the rows kernel take whole tiles
+    bool whole;                   // blocks take whole tiles: rows kernel, set by launch_gemm; unit kernel, a head's, set by the caller
+                                  //   (gemm_stream_whole): `partial` are then the logits, the row scale is applied
     uint16_t *swiglu16;           // segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
-    RowScale scale;               // applied when writing `reduced` (row = the source row of m)
+    RowScale scale;               // applied when writing `reduced` or a head in whole tiles (row = the source row of m)
     int scale_rows;               //   rows per tile slab of scale.sumsq
-    int32_t *lens;                // non-NULL: the kernel that writes `reduced` also moves these lens_n lengths on by lens_add
+    int32_t *lens;                // non-NULL: the last kernel also moves these lens_n lengths on by lens_add (gemm_moves_lens)
     int lens_n, lens_add, lens_max;
 };
 struct GemmTiledPlan {
@@ -119,6 +120,8 @@ void launch_gemm_pack(const void *const *w, const int *n, int nseg, int K, void 
 size_t gemm_pack_w4_bytes(const int *n, int nseg, int K);
 void launch_gemm_pack_w4(const void *const *q, const void *const *scale, const void *const *zero, const int *n,
                          int nseg, int K, void *dst, hipStream_t stream);
+bool gemm_stream_whole(const int *n, int nseg);
+bool gemm_moves_lens(int dtype, const GemmArgs &g);               // whether launch_gemm has a kernel that can
 void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream);
 
 // ---------------------------------------------------------------- attention (attention.hip)

@@ -40,7 +40,7 @@ __device__ __forceinline__ f32x4 load_row4(const uint16_t *row, int i4) { return
 // stream, added in split order.  All loads of a row are issued before the first use.  xn NULL: only the fp16 copy is read.
 // A row is one block, so few rows leave most CUs idle and the block's own loads in flight set the time: 1024 threads
 // then hold a whole row of a split at once (45 rows x 4096, 8 splits: 9.6 us with 256 threads, 5.2; 256 rows x 3584: 10.1, 7.0).
-template <typename TW, bool EMBED, int kRowThreads>
+template <typename TW, bool EMBED, int kRowThreads, bool OP = false>
 __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *embed, const int32_t *tokens, int vocab,
                                                                     const float *partial, int S, size_t split_stride,
                                                                     float *x, const TW *gain, float *xn, float *sumsq_out,
@@ -133,8 +133,7 @@ __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *em
         if (i4 < n4) {
             const f32x4 r = v[j] * scale * load_gain4(gain, i4);
             if (xn) orow[i4] = r;
-            if constexpr (EMBED)
-                if (xn_op) op_store4(xn_op, m, 4 * i4, (int)gridDim.x <= kOpFoldRows, r);
+            if constexpr (OP) op_store4(xn_op, m, 4 * i4, (int)gridDim.x <= kOpFoldRows, r);
             if (xn16)              // the same row rounded to fp16: the operand of the tiled projections
                 reinterpret_cast<uint2 *>(xn16 + (size_t)m * d)[i4] =
                     make_uint2(f32_to_f16_bits(r[0]) | ((uint32_t)f32_to_f16_bits(r[1]) << 16),
@@ -355,10 +354,14 @@ void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, floa
                        const TreeShape *tree, uint32_t *tree_anc, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_EMBED, stream);
     const TreeShape ts = tree ? *tree : TreeShape{};
-    if (dtype == PSD_BF16)
-        launch_kernel(residual_norm_kernel<uint16_t, true, 256>, M, 256, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0,
-                                                                           x, (const uint16_t *)gain, xn, sumsq_out, d, eps, rt, xn16, xn_op, zf, ts, tree_anc);
-    else
+    if (dtype == PSD_BF16) {
+        auto go = [&](auto kernel) {
+            launch_kernel(kernel, M, 256, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0, x, (const uint16_t *)gain, xn, sumsq_out,
+                          d, eps, rt, xn16, xn_op, zf, ts, tree_anc);
+        };
+        if (xn_op) go(residual_norm_kernel<uint16_t, true, 256, true>);
+        else go(residual_norm_kernel<uint16_t, true, 256>);
+    } else
         launch_kernel(residual_norm_kernel<float, true, 256>, M, 256, 0, stream, (const float *)embed, tokens, vocab, nullptr, 0, 0, x,
                                                                         (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, xn_op, zf, ts, tree_anc);
 }

@@ -130,6 +130,18 @@ SMALL_MHA = synth.Shape(2, 256, 2, 2, 128, 384, 1000, 1.0e4)          # d_head 1
 SMALL_G7 = synth.Shape(1, 896, 7, 1, 128, 1152, 2048, 1.0e6)          # Qwen2-like group of 7
 
 
+@pytest.mark.parametrize("d_model,batch,n_new,rows", [(128, 1, 1, 1), (128, 1, 8, 8), (128, 2, 5, 3), (384, 1, 16, 16), (128, 2, 20, 1), (4224, 1, 2, 2)])
+def test_head_in_whole_tiles(d_model, batch, n_new, rows):
+    """A head of up to 16 rows whose whole tiles fill the chip writes the logits and moves the lengths itself: folded and not, a
+    subset of the rows, from a pass of more than 16 rows (no row scale), a ragged last tile, more than 256 sums of squares a row
+    (d_model 4224)."""
+    shape = synth.Shape(1, d_model, d_model // 64, d_model // 64, 64, 128, 29505, 1.0e4)
+    p = Pair(shape, torch.bfloat16, batch, 64, seed=n_new, ctx=9, std=0.05, pack=True)
+    p.step(synth.make_tokens(shape.vocab, (batch, n_new), d_model), n_logit_rows=rows, what="the last rows' logits")
+    assert p.kv.lens.cpu().tolist() == [9 + n_new] * batch
+    p.close()
+
+
 @pytest.mark.parametrize("n_new", [17, 33, 64, 65, 97, 128])
 @pytest.mark.parametrize("d_model,d_ffn,vocab", [(128, 11008, 28001), (128, 14336, 40960), (384, 18944, 512), (1024, 512, 41600)])
 def test_rows_kernel(d_model, d_ffn, vocab, n_new):
