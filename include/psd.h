@@ -196,7 +196,7 @@ psd_status psd_spec_accept(const void *p_logits, const void *q_logits, const int
  * library, a fixed PSD_STATIC_SCRATCH_BYTES array in device memory of every GPU the library runs on (held until
  * the process ends).  Arguments, results and error behaviour are those of psd_spec_accept without workspace /
  * ws_bytes; sizes whose psd_spec_accept_workspace_bytes() exceeds PSD_STATIC_SCRATCH_BYTES are refused with
- * PSD_ERR_WORKSPACE before anything is launched (64 x 8 x 32000 needs 0.16 MB, 16 x 16 x 152064 0.35 MB).
+ * PSD_ERR_WORKSPACE before anything is launched (64 x 8 x 32000 needs 0.23 MB, 16 x 16 x 152064 0.35 MB).
  * The call allocates and frees nothing and enqueues only kernels (no memset nodes); the buffer's address on the
  * current GPU is looked up on the first call there (PSD_ERR_HIP if that fails).  All calls on one GPU share
  * the buffer, which keeps the previous call's contents; whatever must start at zero is cleared by the call's

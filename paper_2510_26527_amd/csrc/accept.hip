@@ -32,6 +32,7 @@ constexpr int kThreads = 256;
 constexpr int kLoadsPerLane = 8;
 constexpr double kTieEps = 1e-5;
 constexpr int kMaxChunksE = 128;      // draw-pass chunks per logits row: two per lane of the wavefront that finishes a sequence
+constexpr int kMaxQuarters = 64;      // ... or quarters of chunks, one per lane
 constexpr int kMaxGroup = 8;          // consecutive entries a thread of the draw kernel takes at a time (2 or 8)
 
 template <typename T>
@@ -298,23 +299,27 @@ struct DrawPos {
     }
 };
 
-// per (sequence, chunk): sum a, sum b, both over the entries with t_i > 0, the smallest positive t_i and the
+// per (sequence, piece): sum a, sum b, both over the entries with t_i > 0, the smallest positive t_i and the
 // largest non-positive t_i
 constexpr int kPartStride = 6;
 
-// Grid: rows x n_chunksE blocks.  Every block: first rejection of its sequence, fp64 sums of its chunk of
-// the draw position; the block that arrives last at the sequence's counter finishes the draw (lane k of its first
-// wavefront owns chunks 2k and 2k + 1: n_chunksE <= 128).
-template <typename T, bool VEC, int G>
+// Grid: rows x n_chunksE blocks.  Every block: first rejection of its sequence, fp64 sums of the pieces of its chunk of
+// the draw position; the block that arrives last at the sequence's counter finishes the draw (one or
+// two pieces per lane of its first wavefront).  A piece is the chunk, or, where chunks are of
+// 4096 entries and more and a row has at most 64 pieces, a wavefront's quarter of it (pieceE = chunkE / 4): the walk that finds the entry,
+// two exponentials an entry again, then has a quarter of the chunk to go through.  Draw kernel, us, whole chunks / quarters: 64 x
+// 32 000 entries 22.0 / 19.1 (bf16), 128 x 32 000 34.9 / 27.2, 64 x 32 001 28.8 / 22.8; more pieces cost more to gather than the
+// walk saves: 16 x 152 064 (152 pieces) 30.6 / 34.6, 8 x 128 256 (252) 22.0 / 26.0, 16 x 32 000 (64 of 512) 16.9 / 17.5.
+template <typename T, bool VEC, int G, bool QUARTERS>
 __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
     constexpr int kWaves = kThreads / 64;
     __shared__ SeqStats s_seq;
     __shared__ double s_red[6][kWaves], s_scan[2][kWaves];
-    __shared__ int s_redo[kMaxChunksE];           // chunks whose sign classification has to be redone
-    __shared__ double s_again[kMaxChunksE];       // ... and their weight then
+    __shared__ int s_redo[kMaxChunksE];            // pieces whose sign classification has to be redone
+    __shared__ double s_again[kMaxChunksE];        // ... and their weight then
     __shared__ int s_last, s_any, s_cstar, s_best, s_lastpos, s_fall;
     __shared__ double s_base, s_target, s_inv[2];
-    const int nE = a.n_chunksE;
+    const int nE = a.n_chunksE, nP = a.n_piecesE, pieceE = a.pieceE;
     const int b = blockIdx.x / nE, c = blockIdx.x % nE, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int n, flags;
     decide(a, b, &s_seq, &n, &flags);
@@ -331,10 +336,11 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
 
     // ---- this block's chunk
     {
-        const int e0 = c * a.chunkE, e1 = min(a.V, e0 + a.chunkE);
+        const int e0 = c * a.chunkE + (QUARTERS ? wave * pieceE : 0), e1 = min(a.V, e0 + pieceE);
+        const int step = QUARTERS ? 64 * G : kThreads * G;
         double acc[4] = {0.0, 0.0, 0.0, 0.0};               // sum a, sum b, positive a, positive b
         double tpos = INFINITY, tneg = -INFINITY;
-        for (int i0 = e0 + tid * G; i0 < e1; i0 += G * kThreads) {
+        for (int i0 = e0 + (QUARTERS ? lane : tid) * G; i0 < e1; i0 += step) {
             float lp[G], lq[G];
             w.template load_group<VEC>(i0, e1, lp, lq);
             double ea[G], eb[G], t[G];
@@ -350,31 +356,41 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
                 }
             }
         }
-        // one value per wavefront into LDS, thread 0 folds the four in wavefront order
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[k] = wave_scan_d(acc[k], 0.0, add);
         tpos = wave_scan_d(tpos, INFINITY, lower);
         tneg = wave_scan_d(tneg, -INFINITY, upper);
-        if (lane == 63) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) s_red[k][wave] = acc[k];
-            s_red[4][wave] = tpos;
-            s_red[5][wave] = tneg;
-        }
-        __syncthreads();
-        if (tid == 0) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) acc[k] = ((s_red[k][0] + s_red[k][1]) + s_red[k][2]) + s_red[k][3];
-            tpos = fmin(fmin(s_red[4][0], s_red[4][1]), fmin(s_red[4][2], s_red[4][3]));
-            tneg = fmax(fmax(s_red[5][0], s_red[5][1]), fmax(s_red[5][2], s_red[5][3]));
-            // hand the results on as write-through stores, wait for them to be performed, then count this
-            // block in; whoever counts last reads all of them back with loads of the same scope
-            double *dst = a.part + ((size_t)b * nE + c) * kPartStride;
+        // Hand the results on as write-through stores, wait for them to be performed, then count this block in; whoever counts
+        // last reads all of them back with loads of the same scope.
+        auto publish = [&](int piece) {
+            double *dst = a.part + ((size_t)b * nP + piece) * kPartStride;
 #pragma unroll
             for (int k = 0; k < 4; ++k) __hip_atomic_store(dst + k, acc[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(dst + 4, tpos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(dst + 5, tneg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        };
+        if constexpr (QUARTERS) {
+            if (lane == 63) publish(c * kWaves + wave);
+            __syncthreads();
+        } else {
+            // one value per wavefront into LDS, thread 0 folds the four in wavefront order
+            if (lane == 63) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s_red[k][wave] = acc[k];
+                s_red[4][wave] = tpos;
+                s_red[5][wave] = tneg;
+            }
+            __syncthreads();
+            if (tid == 0) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) acc[k] = ((s_red[k][0] + s_red[k][1]) + s_red[k][2]) + s_red[k][3];
+                tpos = fmin(fmin(s_red[4][0], s_red[4][1]), fmin(s_red[4][2], s_red[4][3]));
+                tneg = fmax(fmax(s_red[5][0], s_red[5][1]), fmax(s_red[5][2], s_red[5][3]));
+                publish(c);
+            }
+        }
+        if (tid == 0) {
             const unsigned old = __hip_atomic_fetch_add(a.counter + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_last = old == (unsigned)nE - 1u;
         }
@@ -382,33 +398,38 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
         if (!s_last) return;
     }
 
-    // ---- the last block of the sequence: its first wavefront takes all chunks' results, two per lane (one round of loads)
+    // ---- the last block of the sequence: its first wavefront takes all pieces' results, one or two per lane (one round of loads)
     const double u = (double)a.u[(size_t)b * (a.gamma + 1) + a.gamma];
-    double pk[2][kPartStride];
+    constexpr int kPiecesPerLane = QUARTERS ? 1 : 2;         // lane l has the pieces kPiecesPerLane l + h
+    auto sum_of = [](auto term) { return QUARTERS ? term(0) : term(0) + term(kPiecesPerLane - 1); };
+    double pk[kPiecesPerLane][kPartStride];
     if (wave == 0) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int k = 2 * lane + h;
-            const double *src = a.part + ((size_t)b * nE + min(k, nE - 1)) * kPartStride;
+        for (int h = 0; h < kPiecesPerLane; ++h) {
+            const int k = kPiecesPerLane * lane + h;
+            const double *src = a.part + ((size_t)b * nP + min(k, nP - 1)) * kPartStride;
 #pragma unroll
             for (int e = 0; e < kPartStride; ++e) {
                 const double v = __hip_atomic_load(src + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                pk[h][e] = k < nE ? v : (e < 4 ? 0.0 : (e == 4 ? (double)INFINITY : -(double)INFINITY));
+                pk[h][e] = k < nP ? v : (e < 4 ? 0.0 : (e == 4 ? (double)INFINITY : -(double)INFINITY));
             }
         }
-        const double zp = wave_total_d(pk[0][0] + pk[1][0]), zq = wave_total_d(pk[0][1] + pk[1][1]);
-        // chunks with a t_i between 0 and eps (or too close to tell): every entry's sign again, from the fp64 weights
-        bool redo[2] = {false, false};
+        const double zp = wave_total_d(sum_of([&](int h) { return pk[h][0]; }));
+        const double zq = wave_total_d(sum_of([&](int h) { return pk[h][1]; }));
+        // pieces with a t_i between 0 and eps (or too close to tell): every entry's sign again, from the fp64 weights
+        bool redo = false;
         if (d.have_q) {
             const double eps = log(zp / zq) - w.delta;
             const double lo = fmin(0.0, eps) - kSignTol, hi = fmax(0.0, eps) + kSignTol;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                redo[h] = 2 * lane + h < nE && (!(eps == eps) || pk[h][5] >= lo || pk[h][4] <= hi);
-                s_redo[2 * lane + h] = redo[h] ? 1 : 0;
+            for (int h = 0; h < kPiecesPerLane; ++h) {
+                const int k = kPiecesPerLane * lane + h;
+                const bool r = k < nP && (!(eps == eps) || pk[h][5] >= lo || pk[h][4] <= hi);
+                if (k < nP) s_redo[k] = r ? 1 : 0;
+                redo = redo || r;
             }
         }
-        const bool any = __ballot(redo[0] || redo[1]) != 0;
+        const bool any = __ballot(redo) != 0;
         if (lane == 0) {
             s_inv[0] = 1.0 / zp;
             s_inv[1] = d.have_q ? 1.0 / zq : 0.0;
@@ -420,9 +441,9 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
     __syncthreads();
     const double inv_zp = s_inv[0], inv_zq = s_inv[1];
     if (s_any) {                                                 // the same for the whole block
-        for (int k = 0; k < nE; ++k) {
+        for (int k = 0; k < nP; ++k) {
             if (!s_redo[k]) continue;
-            const int f0 = k * a.chunkE, f1 = min(a.V, f0 + a.chunkE);
+            const int f0 = k * pieceE, f1 = min(a.V, f0 + pieceE);
             double pa = 0.0, pb = 0.0;
             for (int i0 = f0 + tid * G; i0 < f1; i0 += G * kThreads) {
                 float lp[G], lq[G];
@@ -446,32 +467,47 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
         __syncthreads();
     }
     if (wave == 0) {
-        double wk[2];
+        double wk[kPiecesPerLane];
+        auto sum = [&]() { return sum_of([&](int h) { return wk[h]; }); };
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int k = 2 * lane + h;
+        for (int h = 0; h < kPiecesPerLane; ++h) {
+            const int k = kPiecesPerLane * lane + h;
             wk[h] = pk[h][2] * inv_zp - pk[h][3] * inv_zq;
-            if (s_any && k < nE && s_redo[k]) wk[h] = s_again[k];
+            if (s_any && k < nP && s_redo[k]) wk[h] = s_again[k];
         }
-        double incl = wave_prefix_sum_d(wk[0] + wk[1]), mass = lane_value_d(incl, 63);
+        double incl = wave_prefix_sum_d(sum()), mass = lane_value_d(incl, 63);
         const bool fall = d.have_q && !(mass > 0.0);             // residual mass 0: draw from p itself
         if (fall) {
-            wk[0] = pk[0][0] * inv_zp;
-            wk[1] = pk[1][0] * inv_zp;
-            incl = wave_prefix_sum_d(wk[0] + wk[1]);
+#pragma unroll
+            for (int h = 0; h < kPiecesPerLane; ++h) wk[h] = pk[h][0] * inv_zp;
+            incl = wave_prefix_sum_d(sum());
             mass = 1.0;                                          // sum of a_i / Zp
         }
-        // first chunk whose inclusive prefix exceeds t
-        const double t = u * mass, base1 = incl - wk[1], base0 = base1 - wk[0];
-        const bool over0 = 2 * lane < nE && base0 + wk[0] > t, over1 = 2 * lane + 1 < nE && base1 + wk[1] > t;
-        const unsigned long long over = __ballot(over0 || over1), held = __ballot(wk[0] > 0.0 || wk[1] > 0.0);
-        const bool crossing = over != 0;
-        // rounding left no crossing: last chunk with weight, whose walk then only looks for its last entry with weight
-        const int pick = crossing ? __ffsll(over) - 1 : (held ? 63 - __clzll(held) : 0);
+        // first piece whose inclusive prefix exceeds t
+        const double t = u * mass;
+        double base[kPiecesPerLane];
+        base[0] = incl - sum();
+#pragma unroll
+        for (int h = 1; h < kPiecesPerLane; ++h) base[h] = base[h - 1] + wk[h - 1];
+        int over = kPiecesPerLane, held = -1;                    // this lane's first piece beyond t, its last one with weight
+#pragma unroll
+        for (int h = kPiecesPerLane - 1; h >= 0; --h)
+            if (kPiecesPerLane * lane + h < nP && base[h] + wk[h] > t) over = h;
+#pragma unroll
+        for (int h = 0; h < kPiecesPerLane; ++h)
+            if (wk[h] > 0.0) held = h;
+        const unsigned long long overs = __ballot(over < kPiecesPerLane), helds = __ballot(held >= 0);
+        const bool crossing = overs != 0;
+        // rounding left no crossing: last piece with weight, whose walk then only looks for its last entry with weight
+        const int pick = crossing ? __ffsll(overs) - 1 : (helds ? 63 - __clzll(helds) : 0);
         if (lane == pick) {
-            const bool second = crossing ? !over0 : wk[1] > 0.0;
-            s_cstar = 2 * lane + (second ? 1 : 0);
-            s_base = crossing ? (second ? base1 : base0) : -(double)INFINITY;
+            const int h = crossing ? over : (held > 0 ? held : 0);
+            double at = base[0];
+#pragma unroll
+            for (int k = 1; k < kPiecesPerLane; ++k)
+                if (h == k) at = base[k];
+            s_cstar = kPiecesPerLane * lane + h;
+            s_base = crossing ? at : -(double)INFINITY;
             s_target = t;
             s_fall = fall ? 1 : 0;
         }
@@ -480,20 +516,21 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
     const int cs = s_cstar;
     const bool no_crossing = s_base == -INFINITY, fall_back_to_p = s_fall != 0;
     const double t = s_target;
-    const int f0 = cs * a.chunkE, f1 = min(a.V, f0 + a.chunkE);
-    // walk the chunk in tiles of 256 x G entries, G consecutive entries per thread, carrying the prefix
+    const int f0 = cs * pieceE, f1 = min(a.V, f0 + pieceE);
+    // walk the piece in tiles of 256 x GW entries, GW consecutive entries per thread, carrying the prefix
     double before = no_crossing ? 0.0 : s_base;    // weight in front of the current tile
     int found = 0x7fffffff, lastpos = -1, turn = 0;
-    for (int t0 = f0; t0 < f1; t0 += kThreads * G, turn ^= 1) {
-        const int g0 = t0 + tid * G;
-        const bool active = g0 < f1;              // idle threads re-read the chunk's first group and count nothing
-        const int i0 = active ? g0 : f0, i1 = active ? min(f1, g0 + G) : f0;
-        double wv[G];
+    constexpr int GW = QUARTERS ? 4 : G;                   // (a quarter of a chunk: more threads with fewer entries each)
+    for (int t0 = f0; t0 < f1; t0 += kThreads * GW, turn ^= 1) {
+        const int g0 = t0 + tid * GW;
+        const bool active = g0 < f1;              // idle threads re-read the piece's first group and count nothing
+        const int i0 = active ? g0 : f0, i1 = active ? min(f1, g0 + GW) : f0;
+        double wv[GW];
         double local = 0.0;
-        float lp[G], lq[G];
+        float lp[GW], lq[GW];
         w.template load_group<VEC>(i0, active ? i1 : f1, lp, lq);
 #pragma unroll
-        for (int j = 0; j < G; ++j) {
+        for (int j = 0; j < GW; ++j) {
             double ea, eb, tt;
             w.eval(lp[j], lq[j], &ea, &eb, &tt);
             const double r = ea * inv_zp - eb * inv_zq;
@@ -509,7 +546,7 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
         for (int wvi = 0; wvi < wave; ++wvi) run += s_scan[turn][wvi];
         run += incl - local;
 #pragma unroll
-        for (int j = 0; j < G; ++j) {
+        for (int j = 0; j < GW; ++j) {
             if (i0 + j < i1) {
                 if (wv[j] > 0.0) lastpos = i0 + j;
                 run += wv[j];
@@ -544,7 +581,7 @@ static WsLayout ws_layout(const AcceptArgs &a) {
     size_t at = 0;
     l.stats = at;   at += align256(rows * (a.n_p_rows + a.gamma) * a.n_chunksA * sizeof(float2));
     l.xlogit = at;  at += align256(rows * (a.gamma > 0 ? a.gamma : 1) * 2 * sizeof(float));
-    l.part = at;    at += align256(rows * a.n_chunksE * kPartStride * sizeof(double));
+    l.part = at;    at += align256(rows * a.n_piecesE * kPartStride * sizeof(double));
     l.counter = at; at += align256(rows * sizeof(uint32_t));
     l.flags = at;   at += align256(rows * sizeof(int32_t));
     l.total = at;
@@ -563,7 +600,8 @@ size_t accept_workspace_bytes(const AcceptArgs &a) { return ws_layout(a).total; 
 // 96 x 10 000 23.8 / 16.0 / 19.9 / 24.2, 64 x 32 000 45 / 25.9 / 21.7 / 26.1, 128 x 32 000 68 / 42.5 / 37.5 / 34.7, 192 x
 // 32 000 91 / 60 / 47.7 / 39.5, 32 x 152 064 66 / 48 / 37.5 / 41.7; unaligned rows, 128 x 32 001 70 / 50 / 44.6 / 47.9.  The last form needs the least workspace: it is
 // also taken where the finer one would not fit the built-in scratch buffer.
-static void accept_draw_chunks(AcceptArgs *a, bool vec, bool coarse) {
+// pieces: whether the sums of a chunk's quarters may be kept (where it pays: accept_draw_kernel)
+static void accept_draw_chunks(AcceptArgs *a, bool vec, bool coarse, bool pieces) {
     const long rows = a->rows > 0 ? a->rows : 1;
     const int V = a->V;
     auto blocks = [&](int ce) { return rows * ((V + ce - 1) / ce); };
@@ -587,6 +625,9 @@ static void accept_draw_chunks(AcceptArgs *a, bool vec, bool coarse) {
     if ((V + ce - 1) / ce > kMaxChunksE) ce = round_up((V + kMaxChunksE - 1) / kMaxChunksE, 256);
     a->chunkE = ce;
     a->n_chunksE = (V + ce - 1) / ce;
+    const bool quarters = pieces && ce >= 4096 && a->n_chunksE * 4 <= kMaxQuarters;
+    a->pieceE = quarters ? ce / 4 : ce;
+    a->n_piecesE = quarters ? a->n_chunksE * 4 : a->n_chunksE;
 }
 
 void accept_plan(int rows, int gamma, int n_p_rows, int V, int dtype, bool vec, AcceptArgs *a) {
@@ -596,8 +637,11 @@ void accept_plan(int rows, int gamma, int n_p_rows, int V, int dtype, bool vec, 
     const int nU = (V + kThreads * kLoadsPerLane - 1) / (kThreads * kLoadsPerLane);
     a->chunkA = (V + nU - 1) / nU;
     a->n_chunksA = (V + a->chunkA - 1) / a->chunkA;
-    accept_draw_chunks(a, false, false);
-    accept_draw_chunks(a, vec, accept_workspace_bytes(*a) > PSD_STATIC_SCRATCH_BYTES);
+    accept_draw_chunks(a, false, false, false);
+    const bool coarse = accept_workspace_bytes(*a) > PSD_STATIC_SCRATCH_BYTES;
+    accept_draw_chunks(a, false, coarse, true);                  // and so does whether the chunks come in pieces
+    const bool pieces = a->pieceE < a->chunkE && accept_workspace_bytes(*a) <= PSD_STATIC_SCRATCH_BYTES;
+    accept_draw_chunks(a, vec, coarse, pieces);
     const int epl = !vec ? 1 : (dtype == PSD_BF16 ? 8 : 4);
     const int cap = kThreads * kLoadsPerLane * epl;            // elements one block can hold
     const int nA = (V + cap - 1) / cap;
@@ -627,8 +671,14 @@ static void launch_accept_t(const AcceptArgs &a, bool vec_ok, hipStream_t stream
     dim3 gridE((unsigned)a.rows * a.n_chunksE);
     ScopedProf sp(PSD_KIND_ACCEPT_DRAW, stream);
     auto go = [&](auto kernel) { launch_kernel(kernel, gridE, kThreads, 0, stream, a); };
-    if (a.groupE == 2) { if (vec_ok) go(accept_draw_kernel<T, true, 2>); else go(accept_draw_kernel<T, false, 2>); }
-    else { if (vec_ok) go(accept_draw_kernel<T, true, kMaxGroup>); else go(accept_draw_kernel<T, false, kMaxGroup>); }
+    auto pick = [&](auto vec) {
+        constexpr bool VEC = decltype(vec)::value != 0;
+        if (a.groupE == 2) go(accept_draw_kernel<T, VEC, 2, false>);
+        else if (a.pieceE < a.chunkE) go(accept_draw_kernel<T, VEC, kMaxGroup, true>);
+        else go(accept_draw_kernel<T, VEC, kMaxGroup, false>);
+    };
+    if (vec_ok) pick(Int<1>{});
+    else pick(Int<0>{});
 }
 
 void launch_accept(const AcceptArgs &a, bool vec_ok, hipStream_t stream) {

@@ -18,10 +18,11 @@ struct AcceptArgs {
     float temperature;
     int chunkA, n_chunksA;        // statistics pass: elements per block, blocks per logits row
     int chunkE, n_chunksE;        // draw pass chunking
+    int pieceE, n_piecesE;        // entries whose sums are kept together (a chunk or a quarter of one), how many per row
     int groupE;                   // consecutive entries per thread of it
     float2 *stats;                // [rows][n_p_rows+gamma][n_chunksA] (max raw logit, sum exp)
     float *xlogit;                // [rows][gamma][2] the draft token's logit under p and under q
-    double *part;                 // [rows][n_chunksE][6] fp64 chunk sums of the draw position (accept.hip)
+    double *part;                 // [rows][n_piecesE][6] fp64 sums of the draw position (accept.hip)
     uint32_t *counter;            // [rows] chunks of the draw position done so far
     int32_t *out_n, *out_tok, *flags;
 };

@@ -71,6 +71,15 @@ def test_draw_chunk_edges(rows, gamma, V, dtype):
 
 
 @pytest.mark.parametrize("rows,gamma,V,dtype", [
+    (64, 1, 28672, torch.bfloat16), (64, 1, 28673, torch.float32), (40, 1, 65536, torch.float32), (40, 1, 65537, torch.bfloat16),
+    (130, 1, 24584, torch.float32), (96, 1, 65544, torch.bfloat16)])
+def test_draw_quarters(rows, gamma, V, dtype):
+    """The sums of a chunk's quarters kept one by one: whole chunks of 4096, a last chunk of one entry (three empty quarters), 64
+    quarters and one chunk more (no quarters), chunks of 8192 with a short last one; draws that take each path at random."""
+    _compare(synth.make_accept_inputs(rows, gamma, V, seed=V + rows, n_p_rows=gamma + 1, dtype=dtype))
+
+
+@pytest.mark.parametrize("rows,gamma,V,dtype", [
     (8, 2, 16384, torch.float32), (8, 2, 16385, torch.bfloat16), (1, 3, 128256, torch.bfloat16), (2, 1, 262145, torch.float32),
     (128, 2, 8193, torch.float32), (103, 1, 10001, torch.float32), (96, 1, 40968, torch.bfloat16), (95, 1, 40968, torch.bfloat16), (96, 1, 40961, torch.float32)])
 def test_draw_chunk_sizes(rows, gamma, V, dtype):
