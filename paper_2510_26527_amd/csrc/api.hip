@@ -279,7 +279,7 @@ int proj_splits(const psd_model *mdl, int rows, int K, const int *n, int nseg, b
     for (int s = 0; s < nseg; ++s) N += n[s];
     if (mdl->w4 && !head && rows <= kStreamMaxRows) return gemm_w4_slots(K, n, nseg, false);
     if (mdl->packed && rows <= kStreamMaxRows) return gemm_packed_splits(K, n, nseg);
-    return gemm_pick_splitk(mdl->d.dtype, rows, K, N, n, nseg, mdl->packed && !strips && (head || !mdl->w4));
+    return gemm_pick_splitk(mdl->d.dtype, rows, K, N, n, nseg, mdl->packed && !strips && (head || !mdl->w4), mdl->w4 && !head);
 }
 
 // the part of the plan that depends on the number of rows alone

@@ -102,7 +102,7 @@ __device__ __forceinline__ f32x8 load_act8(const float *xrow, int k, bool valid)
 }
 
 __device__ __forceinline__ void store_out(const GemmArgs &g, int ks, int m, int col, float v) {
-    g.partial[((size_t)ks * g.M + m) * g.N + col] = v;
+    g.partial[((size_t)ks * g.M + m) * g.N + g.col_first + col] = v;
 }
 
 
@@ -1284,8 +1284,21 @@ bool gemm_tiles_whole(int M, int K, const int *n, int nseg, bool packed) {
 // Above: 256 rows; the columns and the (even) K split with the least estimated
 // time: rounds of 256 blocks x K tiles x the measured time of one (us: 1.15, 1.65, 1.9 for 128, 192, 256 columns) plus 4
 // per round for filling and emptying the pipeline, plus a partial slot of M x N written and read at about 3 TB/s per
-// split.  gated: 128 gate and 128 up columns per tile, never split (the two factors meet in one lane).
-GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) {
+// split; or, where a last round would leave CUs idle, two launches: whole rounds of 256 or 192 columns, then the rest of the
+// columns in narrower tiles, 3 us more for the launch (bf16).  One launch / two: 2001 x 12288 x 4096 230 / 218 us, 4096 x 6144 x
+// 4096 219 / 210, 4096 x 4608 x 3584 174 / 158, 256 x 152064 x 3584 340 / 326, 1024 x 152064 x 3584 1109 / 1090; where the estimate
+// is less than 2 % lower nothing is won (512 x 152064 x 3584 572 / 582, 272 x 152064 504 / 506).  gated: 128 gate and 128 up columns
+// per tile, never split (the two factors meet in one lane).
+// tiled_rest: the columns of each segment that are left behind the first `tiles` tiles of `cols` columns
+static void tiled_rest(const int *n, int nseg, int cols, int tiles, int *rest) {
+    for (int s = 0; s < nseg; ++s) {
+        const int t = (n[s] + cols - 1) / cols, done = tiles < t ? tiles : t;
+        rest[s] = n[s] - done * cols > 0 ? n[s] - done * cols : 0;
+        tiles -= done;
+    }
+}
+constexpr double kTileUs[3] = {1.15, 1.65, 1.9};           // a K tile of 256 rows x 128, 192, 256 columns
+GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated, bool w4) {
     GemmTiledPlan best{};
     const int nk = K / kBK;
     if (M <= 128 && !gated) {
@@ -1313,8 +1326,26 @@ GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) 
         const int tiles = (gated ? n[0] / 128 : tiles_of(n, nseg, cols)) * m_tiles;
         for (int c = 1; c <= (gated ? 1 : 16) && (c == 1 || nk / c >= 4); ++c) {
             const long rounds = ((long)tiles * c + 255) / 256;
-            const double cost = rounds * ((nk + c - 1) / c * (cols == 256 ? 1.9 : (cols == 192 ? 1.65 : 1.15)) + 4.0) + c * slot_us;
+            const double cost = rounds * ((nk + c - 1) / c * kTileUs[cols / 64 - 2] + 4.0) + c * slot_us;
             if (cost < least) { least = cost; best.cols = cols; best.tiles = tiles; best.blocks = tiles * c; best.slots = c; }
+        }
+    }
+    if (gated || w4) return best;
+    least *= 0.98;
+    for (int cols = 192; cols <= 256; cols += 64) {
+        const int strips = tiles_of(n, nseg, cols), rounds = strips * m_tiles / 256;      // tiles side by side; rounds they fill
+        const int first = rounds * 256 / m_tiles;                                         // of them in the first launch
+        if (rounds == 0 || first == strips) continue;
+        int n2[3];
+        tiled_rest(n, nseg, cols, first, n2);
+        for (int cols2 = 128; cols2 < cols; cols2 += 64) {
+            const int tiles2 = tiles_of(n2, nseg, cols2) * m_tiles, rounds2 = (tiles2 + 255) / 256;
+            const double cost = rounds * (nk * kTileUs[cols / 64 - 2] + 4.0) + rounds2 * (nk * kTileUs[cols2 / 64 - 2] + 4.0) + 3.0 + slot_us;
+            if (cost < least) {
+                least = cost;
+                best.cols = cols; best.tiles = best.blocks = first * m_tiles; best.slots = 1;
+                best.first = first; best.cols2 = cols2; best.tiles2 = tiles2;
+            }
         }
     }
     return best;
@@ -1323,7 +1354,7 @@ GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated) 
 // from 128 tiles on (half the CUs busy) not splitting K costs less than a slot of gate and up written and read again
 // (256 x 37888 x 3584, 148 tiles: 95 us; separate, 84 + 11)
 bool gemm_tiled_gates(int M, int K, const int *n, bool packed) {
-    return M > 128 ? gemm_tiled_plan(M, K, n, 2, true).tiles >= 128 : packed && gemm_rows_plan(M, K, n, 2, true).used;
+    return M > 128 ? gemm_tiled_plan(M, K, n, 2, true, false).tiles >= 128 : packed && gemm_rows_plan(M, K, n, 2, true).used;
 }
 
 static int gemm_stream_grid(int tiles, int K) {
@@ -1401,7 +1432,7 @@ bool gemm_stream_whole(const int *n, int nseg) {
 }
 int gemm_packed_splits(int K, const int *n, int nseg) { return gemm_stream_slots(tiles_of(n, nseg, kSkinnyRows), K); }
 
-int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, bool packed) {
+int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, bool packed, bool w4) {
     (void)N;
     if (dtype != PSD_BF16) return 1;
     if (M <= kStreamMaxRows) {
@@ -1418,7 +1449,7 @@ int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, boo
         const RowsPlan r = gemm_rows_plan(M, K, n, nseg, false);
         if (r.used) return r.slots;
     }
-    return gemm_tiled_plan(M, K, n, nseg, false).slots;
+    return gemm_tiled_plan(M, K, n, nseg, false, w4).slots;
 }
 
 // the unit kernel addresses the rows of row-major activations with 32-bit offsets from the first one
@@ -1485,27 +1516,48 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
         else pick(std::integral_constant<int, 10>{});
     } else {
         ScopedProf sp(PSD_KIND_GEMM_TILED, stream);
-        const GemmTiledPlan p = gemm_tiled_plan(g.M, g.K, g.n, g.nseg, g.swiglu16 != nullptr);
+        const GemmTiledPlan p = gemm_tiled_plan(g.M, g.K, g.n, g.nseg, g.swiglu16 != nullptr, g.w4);
+        auto run = [&](const GemmArgs &t, int cols, int blocks) {
+            auto go = [&](auto kernel, int threads) {
+                // opt in to more than 64 KB of dynamic LDS: a property of the function on the current device, set before
+                // every launch (a cheap host call) so that no process-wide flag has to remember who set it where
+                const size_t lds = (size_t)(64 * p.ta + cols) * kLdsStride * sizeof(uint16_t) * 2;
+                (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          (int)lds);
+                launch_kernel(kernel, blocks, threads, lds, stream, t);
+            };
+            auto pick = [&](auto w4) {
+                constexpr bool W4 = decltype(w4)::value;
+                if (p.ta == 1) go(gemm_f16_tiled_kernel<1, 1, 4, W4>, 512);
+                else if (p.ta == 2) go(gemm_f16_tiled_kernel<2, 2, 4, W4>, 512);
+                else if (cols == 128) go(gemm_f16_tiled_kernel<4, 1, 4, W4>, 512);
+                else if (cols == 192) go(gemm_f16_tiled_kernel<4, 3, 2, W4>, 256);
+                else go(gemm_f16_tiled_kernel<4, 2, 4, W4>, 512);
+            };
+            if (t.w4) pick(std::true_type{});
+            else pick(std::false_type{});
+        };
         GemmArgs t = g;
         t.tiled_tiles = p.tiles;
-        auto go = [&](auto kernel, int threads) {
-            // opt in to more than 64 KB of dynamic LDS: a property of the function on the current device, set before
-            // every launch (a cheap host call) so that no process-wide flag has to remember who set it where
-            const size_t lds = (size_t)(64 * p.ta + p.cols) * kLdsStride * sizeof(uint16_t) * 2;
-            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)lds);
-            launch_kernel(kernel, p.blocks, threads, lds, stream, t);
-        };
-        auto pick = [&](auto w4) {
-            constexpr bool W4 = decltype(w4)::value;
-            if (p.ta == 1) go(gemm_f16_tiled_kernel<1, 1, 4, W4>, 512);
-            else if (p.ta == 2) go(gemm_f16_tiled_kernel<2, 2, 4, W4>, 512);
-            else if (p.cols == 128) go(gemm_f16_tiled_kernel<4, 1, 4, W4>, 512);
-            else if (p.cols == 192) go(gemm_f16_tiled_kernel<4, 3, 2, W4>, 256);
-            else go(gemm_f16_tiled_kernel<4, 2, 4, W4>, 512);
-        };
-        if (g.w4) pick(std::true_type{});
-        else pick(std::false_type{});
+        if (p.first == 0) {
+            run(t, p.cols, p.blocks);
+        } else {                                            // the first tiles' columns of every segment, then the rest of them
+            GemmArgs u = g;
+            tiled_rest(g.n, g.nseg, p.cols, p.first, u.n);
+            t.nseg = u.nseg = 0;
+            for (int s = 0; s < g.nseg; ++s) {
+                const int done = g.n[s] - u.n[s], left = u.n[s];
+                if (done > 0) { t.n[t.nseg++] = done; u.col_first += done; }
+                if (left > 0) {
+                    u.w[u.nseg] = (const char *)g.w[s] + (size_t)done * g.K * 2;
+                    u.n[u.nseg++] = left;
+                }
+            }
+            u.lens_n = 0;
+            u.tiled_tiles = p.tiles2;
+            run(t, p.cols, p.blocks);
+            run(u, p.cols2, p.tiles2);
+        }
     }
     if (g.reduced) {
         const dim3 grid((unsigned)((g.N + 255) / 256), (unsigned)g.M);

@@ -85,6 +85,7 @@ struct GemmArgs {
     const void *w4_scale[3], *w4_zero[3];   // M > kStreamMaxRows: w[] are the codes [n][K/2], these the bf16 scales and uint8 zero points [n][K/128]
     // -- M > kStreamMaxRows (the tiled kernel; see GemmTiledPlan) ---------------------------------------------------
     int tiled_tiles;              // set by launch_gemm
+    int col_first;                // tiled kernel: output column of the first segment's first row (set by launch_gemm)
     bool whole;                   // blocks take whole tiles: rows kernel, set by launch_gemm; unit kernel, a head's, set by the caller
                                   //   (gemm_stream_whole): `partial` are then the logits, the row scale is applied
     uint16_t *swiglu16;           // segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
@@ -97,9 +98,11 @@ struct GemmTiledPlan {
     int ta, cols;                 // block tile: 64 ta rows x cols columns
     int tiles, blocks;            // tiles of the product; blocks, each of which takes an equal range of all their K steps
     int slots;                    // partial slots per output
+    int first, cols2, tiles2;     // first > 0: only the first `first` tiles side by side are of this kind; the columns left over go in a
+                                  //   second launch, in tiles2 tiles of cols2 columns
 };
 bool gemm_tiles_whole(int M, int K, const int *n, int nseg, bool packed);     // up to 128 rows: no tile shared; once true for M rows, for more (to 64, to 128) too
-GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated);
+GemmTiledPlan gemm_tiled_plan(int M, int K, const int *n, int nseg, bool gated, bool w4);
 bool gemm_tiled_gates(int M, int K, const int *n, bool packed);                // whether the gate|up projection n = {f, f} applies SwiGLU itself
 // 17 to 128 rows on unit-packed weights: whether the rows kernel takes the product, and how
 struct RowsPlan {
@@ -108,7 +111,7 @@ struct RowsPlan {
 };
 RowsPlan gemm_rows_plan(int M, int K, const int *n, int nseg, bool gated);
 // packed: a unit-packed bf16 copy of the weights is there
-int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, bool packed);
+int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, bool packed, bool w4);
 // repacked weights for the M <= kStreamMaxRows path
 int gemm_pack_tiles(const int *n, int nseg);
 size_t gemm_pack_bytes(const int *n, int nseg, int K);

@@ -154,6 +154,17 @@ def test_rows_kernel(d_model, d_ffn, vocab, n_new):
     p.close()
 
 
+@pytest.mark.parametrize("heads,vocab,n_new,rows", [(2, 48900, 300, 300), (32, 512, 1500, 1), (32, 512, 2200, 1)])
+def test_tiles_of_two_widths(heads, vocab, n_new, rows):
+    """A projection of which a first launch does whole rounds of wide tiles and a second the other columns in narrower ones: a head
+    with a ragged last tile; Q, K and V with the line inside V (1500 rows) and inside K, all of V behind it (2200).  Scores have a spread of std^2 d_model; a score at four times that, with
+    its factors in bf16, moves its probability by 4 std^2 d_model 2^-9: 0.6 % at 0.02, 4 % at 0.05, past the tolerance."""
+    shape = synth.Shape(1, 2048, heads, heads, 128, 128, vocab, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 2304, seed=n_new, ctx=0, std=0.02)
+    p.step(synth.make_tokens(shape.vocab, (1, n_new), heads), n_logit_rows=rows, what="the logits")
+    p.close()
+
+
 @pytest.mark.parametrize("n_new", [1, 8, 9, 16])
 @pytest.mark.parametrize("d_model,d_ffn", [(128, 128), (384, 1408), (256, 5760), (256, 4224)])
 def test_operand_order_activations(d_model, d_ffn, n_new):
