@@ -31,7 +31,7 @@ def weight_stream_bytes(shape):
 
 def stream_kernel_bytes(shape):
     """The share of weight_stream_bytes read by gemm_bf16_unit_kernel: the QKV, gate|up and lm_head
-    projections (O runs on the column kernel, down on the unit kernel with the residual epilogue)."""
+    projections (O and down run on the column kernel)."""
     s = shape
     hd, kvd = s.n_q_heads * s.d_head, s.n_kv_heads * s.d_head
     return 2 * (s.n_layers * (s.d_model * (hd + 2 * kvd) + 2 * s.d_model * s.d_ffn) + s.vocab * s.d_model)
@@ -193,7 +193,7 @@ def main():
 
     shape, gamma, ctx, max_len, temperature = synth.LLAMA2_7B, 8, 1024, 1088, 1.0
     w_cpu = synth.make_weights(shape, 3, torch.bfloat16)
-    model = runtime.Model(shape, w_cpu, dev).pack()      # streaming copy of the weights for steps of <= 16 rows
+    model = runtime.Model(shape, w_cpu, dev).pack()      # streaming copy of the weights
     kv = runtime.KVCache(model, 1, max_len)
     ks, vs = synth.make_kv_fill(shape, 1, ctx, 4, torch.bfloat16)
     kv.load(ks, vs, ctx)
@@ -287,7 +287,7 @@ def main():
                 "measured_stream_read_GB/s": ceilings["stream_read_GB/s"],
                 "frac_of_measured_stream_read": achieved / ceilings["stream_read_GB/s"]}
     gemm_ms = sk_ms
-    others = (("gemm_column", "gemm_bf16_column_kernel (O) and gemm_bf16_unit_kernel<true> (down): the projections with the residual add",
+    others = (("gemm_column", "gemm_bf16_column_kernel (O, down): the projections with the residual add",
                w_bytes - stream_bytes),)
     roofline["other_gemms"] = []
     for kind, label, nbytes in others:
@@ -664,7 +664,8 @@ def chain_cpu_baseline(g, levels, weights, n_prompt, max_len):
 def sweep_workload(args, dev):
     """The four projections of LLaMA2-7B-shaped layers (plus a 32000-row lm_head) at M = 8 ... 4096 rows: one
     forward of a two-layer model per M on an empty cache; GEMM time from the per-launch timers.  Up to 16 rows
-    the projections stream the weights (HBM-bound, GB/s); above, they run on the LDS-tiled MFMA kernel (TFLOP/s)."""
+    the projections stream the weights (HBM-bound, GB/s), up to 128 those but O and down do; above, they run on the
+    LDS-tiled MFMA kernel (TFLOP/s)."""
     import torch
     import paper_2510_26527_amd as psd
     from paper_2510_26527_amd import runtime, synth
@@ -698,7 +699,7 @@ def sweep_workload(args, dev):
                      "frac_of_bf16_mfma_peak": flops / (g_ms * 1e-3) / 2.5e15,
                      "weight_GB/s": 2.0 * params / (g_ms * 1e-3) / 1e9,
                      "frac_of_hbm_peak": 2.0 * params / (g_ms * 1e-3) / 8e12,
-                     "kernel": "weight streaming" if M <= 16 else "LDS-tiled MFMA"})
+                     "kernel": "weight streaming" if M <= 16 else "weight streaming (O, down: LDS-tiled)" if M <= 128 else "LDS-tiled MFMA"})
         kv.close()
         del logits
     print(json.dumps({"metric": "projection GEMMs of a LLaMA2-7B-shaped layer over M", "unit": "TFLOP/s and GB/s",

@@ -107,15 +107,17 @@ psd_status psd_model_create_w4(const psd_model_desc *desc, const void *const *we
                                const void *const *scale_ptrs, const void *const *zero_ptrs,
                                int32_t n_quant_ptrs, psd_model **out);
 
-/* Optional streaming copy of the projection weights for verify steps of up to 16 rows
- * (batch * n_new <= 16), where the forward pass is bound by reading the weights once from HBM.
+/* Optional streaming copy of the projection weights for verify steps and batches of up to 128 rows
+ * (batch * n_new <= 128), where the forward pass is bound by reading the weights once from HBM.
  * psd_model_pack rewrites every projection matrix into caller memory in the order the
- * wavefronts of the streaming GEMM load it (64-row x 128-column units of 16 KB, each stored
- * as the 64 lanes' 16-byte operands, units of one projection contiguous), so that each
+ * wavefronts of the streaming GEMMs load it (64-row x 128-column units of 16 KB, each stored
+ * as the 64 lanes' 16-byte operands, units of one projection contiguous; for the O and down
+ * projections 16 rows x all columns in one piece), so that each
  * wavefront reads one contiguous byte range.  packed_mem: device, 256-byte aligned, at least
  * psd_model_packed_bytes() bytes (about the size of the weights), kept alive with the model;
  * the row-major weights stay in use for larger steps and must stay alive too.  After a
- * successful call, forwards with batch * n_new <= 16 read the packed copy; results are the same
+ * successful call, forwards with batch * n_new <= 16 read the packed copy, and those of up to 128 rows
+ * for QKV, gate|up and the head where a projection's tiles fill the chip; results are the same
  * up to fp32 summation order.  Call it before sizing workspaces: the workspace need changes.
  * PSD_BF16 models only (PSD_ERR_DTYPE otherwise); psd_model_packed_bytes returns 0 for others. */
 size_t psd_model_packed_bytes(const psd_model *m);
@@ -287,8 +289,8 @@ psd_status psd_kv_compact_tree(psd_kv *kv, const int32_t *base_lens_dev, const i
 #define PSD_KIND_EMBED 0
 #define PSD_KIND_RMSNORM 1
 #define PSD_KIND_GEMM_F32 2
-#define PSD_KIND_GEMM_SKINNY 3       /* bf16 weight-streaming GEMM over packed 16 KB units, M <= 16 */
-#define PSD_KIND_GEMM_TILED 4        /* LDS-tiled GEMM of bf16 models (fp16 MFMA), M > 16 */
+#define PSD_KIND_GEMM_SKINNY 3       /* bf16 weight-streaming GEMM over packed 16 KB units, M <= 16 (heads in whole tiles: with their epilogue) */
+#define PSD_KIND_GEMM_TILED 4        /* GEMM of bf16 models with fp16 MFMA, M > 16: LDS-tiled, or (packed, M <= 128) on streamed units */
 #define PSD_KIND_GEMM_REDUCE 5       /* split-K reduction */
 #define PSD_KIND_ROPE_APPEND 6
 #define PSD_KIND_ATTN 7

@@ -12,6 +12,8 @@
 //                            units of a GEMM are contiguous, and the grid is persistent: each block streams
 //                            an equal, contiguous range of units (stream-K), its four wavefronts on the four
 //                            K quarters of every unit, and writes one partial per tile it touches.
+//   gemm_bf16_rows_kernel    17 to 128 rows on the same units: the weights stream into MFMA operands as above, the
+//                            activations (fp16) go through LDS; whole tiles where they fill the chip.
 //   gemm_bf16_column_kernel  M <= 16, the projections that write the residual stream (O, down): one
 //                            block per 16 output columns over the whole K range; the residual add, the
 //                            gain-scaled copy and the RMSNorm statistics happen in its epilogue.
@@ -20,14 +22,15 @@
 //                            integers against fp16-rounded activations, scale and zero point applied per group in
 //                            fp32; one partial slot per block and tile, or (O, down) the residual epilogue run by
 //                            the block that arrives last.
-//   gemm_f16_tiled_kernel    M > 16.  (64, 128 or 256) x (128, 192, 256) x 64 LDS-staged tiles, 32x32x16 fp16 MFMA
+//   gemm_f16_tiled_kernel    M > 16 otherwise.  (64, 128 or 256) x (128, 192, 256) x 64 LDS-staged tiles, 32x32x16 fp16 MFMA
 //                            (weights convert to fp16 exactly, activations are rounded to fp16); the gate|up projection
 //                            applies SwiGLU itself where its tiles alone fill the chip.
-// Activations are fp32 in memory in every case (the tiled kernel reads an fp16 copy its producers leave beside
+// Activations are fp32 in memory in every case (the rows and tiled kernels read an fp16 copy their producers leave beside
 // them; between the packed M <= 16 kernels they travel as bf16 pairs hi + lo in operand order, common.h).  The M <= 16 bf16
-// kernels feed each activation to the matrix cores as that pair (two MFMAs against the same weight operand): with plain bf16 activations the logits of the 7B-shaped random-init
-// models are 3e-2 off the fp64 result, above the 2e-2 bar; the weights, which are what streams from HBM, stay bf16.
-// Every kernel but the ones with the residual epilogue writes its result as split-K partials [splitk][M][N]
+// kernels feed each activation to the matrix cores as that pair (two MFMAs against the same weight operand): with plain
+// bf16 activations the logits of the 7B-shaped random-init models are 3e-2 off the fp64 result, above the 2e-2 bar; the
+// weights, which are what streams from HBM, stay bf16.
+// Every kernel but the ones with an epilogue of their own (residual, SwiGLU, logits in whole tiles) writes its result as split-K partials [splitk][M][N]
 // (splitk >= 1); the consumer (the fused row-wise kernels, the attention kernel's operand build, or
 // gemm_splitk_reduce_kernel for the logits) adds them in split order, so results are bit-reproducible.
 #include <type_traits>

@@ -36,8 +36,8 @@ void launch_accept_greedy(const AcceptArgs &a, bool vec_ok, hipStream_t stream);
 
 // ---------------------------------------------------------------- GEMMs (gemm.hip)
 // Up to this many rows (one 16-row MFMA tile) the bf16 projections stream the weights straight into MFMA
-// operands (HBM-bound); above it the activation operand traffic of that scheme outgrows the weights and the
-// LDS-tiled kernel wins (measured on two LLaMA2-7B-shaped layers: 0.28 ms at 16 rows; at 32 rows 0.43 ms
+// operands (HBM-bound); above it the activation operand traffic of that scheme outgrows the weights and kernels that stage
+// the activations in LDS win (measured on two LLaMA2-7B-shaped layers: 0.28 ms at 16 rows; at 32 rows 0.43 ms
 // streaming against 0.38 ms tiled, at 64 rows 0.66 against 0.38).
 constexpr int kStreamMaxRows = 16;
 // Up to this many rows a pass' operand-order activations (common.h) are folded: both parts in one fragment.
