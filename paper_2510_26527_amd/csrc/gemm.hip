@@ -105,7 +105,7 @@ __device__ __forceinline__ f32x8 load_act8(const float *xrow, int k, bool valid)
 }
 
 __device__ __forceinline__ void store_out(const GemmArgs &g, int ks, int m, int col, float v) {
-    g.partial[((size_t)ks * g.M + m) * g.N + g.col_first + col] = v;
+    g.partial[((size_t)ks * g.M + m) * g.N + col] = v;
 }
 
 
@@ -1547,10 +1547,10 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
         } else {                                            // the first tiles' columns of every segment, then the rest of them
             GemmArgs u = g;
             tiled_rest(g.n, g.nseg, p.cols, p.first, u.n);
-            t.nseg = u.nseg = 0;
+            t.nseg = u.nseg = 0;                            // (both write into rows of g.N outputs)
             for (int s = 0; s < g.nseg; ++s) {
                 const int done = g.n[s] - u.n[s], left = u.n[s];
-                if (done > 0) { t.n[t.nseg++] = done; u.col_first += done; }
+                if (done > 0) { t.n[t.nseg++] = done; u.partial += done; }
                 if (left > 0) {
                     u.w[u.nseg] = (const char *)g.w[s] + (size_t)done * g.K * 2;
                     u.n[u.nseg++] = left;

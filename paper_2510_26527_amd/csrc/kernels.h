@@ -85,7 +85,6 @@ struct GemmArgs {
     const void *w4_scale[3], *w4_zero[3];   // M > kStreamMaxRows: w[] are the codes [n][K/2], these the bf16 scales and uint8 zero points [n][K/128]
     // -- M > kStreamMaxRows (the tiled kernel; see GemmTiledPlan) ---------------------------------------------------
     int tiled_tiles;              // set by launch_gemm
-    int col_first;                // tiled kernel: output column of the first segment's first row (set by launch_gemm)
     bool whole;                   // blocks take whole tiles: rows kernel, set by launch_gemm; unit kernel, a head's, set by the caller
                                   //   (gemm_stream_whole): `partial` are then the logits, the row scale is applied
     uint16_t *swiglu16;           // segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
