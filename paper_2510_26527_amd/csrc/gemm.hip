@@ -1018,7 +1018,6 @@ __global__ __launch_bounds__(128 * WN, TA == 1 ? 4 : 1) void gemm_f16_tiled_kern
     const long U = (long)g.tiled_tiles * nk;
     const int u0 = __builtin_amdgcn_readfirstlane((int)range_begin(blk, U, P));
     const int u1 = __builtin_amdgcn_readfirstlane((int)range_begin(blk + 1, U, P));
-    if (!g.reduced && blockIdx.x == 0) advance_lens(g);
 
     // LDS byte addresses of this thread's chunks and operands: stores go to one set of tiles, reads to the other.  They are
     // opaque to the compiler, which would otherwise keep one register per (set, chunk, K step) instead of a base and
@@ -1207,6 +1206,7 @@ __global__ __launch_bounds__(128 * WN, TA == 1 ? 4 : 1) void gemm_f16_tiled_kern
                     }
         }
     }
+    if (!g.reduced && blockIdx.x == 0) advance_lens(g);     // (in front of the loads a 256-row step of 28 layers took 40 us longer)
 }
 
 int tiles_of(const int *n, int nseg, int rows) {
