@@ -519,7 +519,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
     // ---- write: directly when there is one split, else the unnormalised partial.  One thread per query row works
     // out where the row goes and how its slabs combine; the element loop then only multiplies and adds.
     __shared__ float s_f[NSLAB][QT * 16], s_M[QT * 16], s_L[QT * 16];
-    __shared__ int s_row[QT * 16];
+    __shared__ int s_row[QT * 16], s_op[QT * 16];      // where the row goes: in row-major outputs, in operand order
     if (threadIdx.x < QT * 16) {
         const int qc = threadIdx.x;
         const int qi = qchunk * QT * 16 + qc;
@@ -527,6 +527,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
         if (qi < NQ) {
             const int hl = qi / a.R, r = qi % a.R;
             row = (b * a.R + r) * a.h_q + hk * group + hl;                           // [B][R][h_q]
+            if (a.out_op) s_op[qc] = (int)op_at(b * a.R + r, (hk * group + hl) * DH, a.op_folded);
         }
         float M = sm_m[0][qc];
 #pragma unroll
@@ -553,7 +554,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
             const float L = s_L[qc];
             if (a.out) a.out[row * DH + d] = acc / L;
             if (a.out16) a.out16[row * DH + d] = f32_to_f16_bits(acc / L);
-            if (a.out_op) op_store(a.out_op, (int)(row / a.h_q), (int)(row % a.h_q) * DH + d, a.op_folded, acc / L);
+            if (a.out_op) op_store(a.out_op + s_op[qc], 0, d, a.op_folded, acc / L);      // (a head starts on a multiple of 64)
         } else {
             a.part_o[(row * a.splits + split) * DH + d] = acc;
             if (d == 0) {
@@ -574,7 +575,9 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
 // bf16 high + low pair and frees the registers for what bounds this kernel, the bytes a CU keeps in flight: two
 // 64-key tiles travel in registers (stage = tile parity) while a third is multiplied, and the next tile is stored
 // into the second set of LDS tiles in the middle of the current one's MFMAs (one barrier per tile).
-template <int DH, int QW, int NW>
+// OP: the output in operand order (passes of up to 16 rows), a build of its own: with these stores in it the row-major one is
+// 2 200 instructions longer, and slower though it skips them (us a launch, 7B shape, 16 sequences x 20 rows 23.1 / 21.5, 12 x 20 22.0 / 20.6).
+template <int DH, int QW, int NW, bool OP>
 __global__ __launch_bounds__(NW * 64) void attn_mfma_wide_kernel(AttnArgs a, float scale_log2, int range) {
     constexpr int KS = DH / 32, DT = DH / 16;
     constexpr int KSTRIDE = DH + 8;            // fp16 elements per staged K row (+16 B: conflict-free reads)
@@ -787,17 +790,23 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_wide_kernel(AttnArgs a, flo
         if (limit[qt] < 0) continue;
         if (a.splits == 1) {
             const float inv = 1.0f / L;
+            uint16_t *op = nullptr;
+            if constexpr (OP) {          // (a head starts on a multiple of 64)
+                const int row = (int)out_row[qt];
+                op = a.out_op + op_at(row / a.h_q, row % a.h_q * DH, a.op_folded);
+            }
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-            {
+            for (int dt = 0; dt < DT; ++dt) {
                 const f32x4 r = o[qt][dt] * inv;
+                if constexpr (OP) {
+                    op_store4(op, 0, dt * 16 + 4 * g, a.op_folded, r);
+                    continue;
+                }
                 if (a.out) *reinterpret_cast<f32x4 *>(a.out + out_row[qt] * DH + dt * 16 + 4 * g) = r;
                 if (a.out16)
                     *reinterpret_cast<uint2 *>(a.out16 + out_row[qt] * DH + dt * 16 + 4 * g) =
                         make_uint2(f32_to_f16_bits(r[0]) | ((uint32_t)f32_to_f16_bits(r[1]) << 16),
                                    f32_to_f16_bits(r[2]) | ((uint32_t)f32_to_f16_bits(r[3]) << 16));
-                if (a.out_op)
-                    op_store4(a.out_op, (int)(out_row[qt] / a.h_q), (int)(out_row[qt] % a.h_q) * DH + dt * 16 + 4 * g, a.op_folded, r);
             }
         } else {
             float *po = a.part_o + (out_row[qt] * a.splits + split) * DH;
@@ -946,8 +955,13 @@ static void launch_mfma(const AttnArgs &a, hipStream_t stream) {
             // overlap each other's LDS reads, exponentials and MFMAs (measured at 16 sequences x 4 KV heads x 112 query
             // rows x 4096 keys: 43.6 us per layer against 61.1 us), although every K / V^T tile is then read from LDS
             // by eight wavefronts instead of four.
-            if (rows == 64) go(attn_mfma_wide_kernel<DH, 1, 4>, 256);
-            else go(attn_mfma_wide_kernel<DH, 1, 8>, 512);
+            auto pick = [&](auto op) {
+                constexpr bool OP = decltype(op)::value;
+                if (rows == 64) go(attn_mfma_wide_kernel<DH, 1, 4, OP>, 256);
+                else go(attn_mfma_wide_kernel<DH, 1, 8, OP>, 512);
+            };
+            if (a.out_op && a.splits == 1) pick(std::true_type{});       // (with several splits the combine kernel writes it)
+            else pick(std::false_type{});
         }
         if (a.splits > 1) {
             ScopedProf sp(PSD_KIND_ATTN_COMBINE, stream);
