@@ -319,7 +319,7 @@ __global__ __launch_bounds__(kThreads) void accept_draw_kernel(AcceptArgs a) {
     __shared__ double s_again[kMaxChunksE];        // ... and their weight then
     __shared__ int s_last, s_any, s_cstar, s_best, s_lastpos, s_fall;
     __shared__ double s_base, s_target, s_inv[2];
-    const int nE = a.n_chunksE, nP = a.n_piecesE, pieceE = a.pieceE;
+    const int nE = a.n_chunksE, nP = QUARTERS ? a.n_piecesE : nE, pieceE = QUARTERS ? a.pieceE : a.chunkE;
     const int b = blockIdx.x / nE, c = blockIdx.x % nE, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int n, flags;
     decide(a, b, &s_seq, &n, &flags);

@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
     const long U = (long)g.pack_tiles * ns, P = gridDim.x;
     const int u0 = (int)(g.whole ? range_begin(blockIdx.x, g.pack_tiles, P) * ns : range_begin(blockIdx.x, U, P));
     const int u1 = (int)(g.whole ? range_begin(blockIdx.x + 1, g.pack_tiles, P) * ns : range_begin(blockIdx.x + 1, U, P));
-    if (g.whole && blockIdx.x == 0) advance_lens(g);
+    if (g.lens_n && blockIdx.x == 0) advance_lens(g);
     if (u0 >= u1) return;
     const int n_my = u1 - u0;
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
@@ -806,7 +806,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows_kernel(GemmArgs g) {
     const long U = (long)g.tiled_tiles * ns, P = gridDim.x;
     const int u0 = __builtin_amdgcn_readfirstlane(g.whole ? (int)range_begin(blockIdx.x, g.tiled_tiles, P) * ns : (int)range_begin(blockIdx.x, U, P));
     const int u1 = __builtin_amdgcn_readfirstlane(g.whole ? (int)range_begin(blockIdx.x + 1, g.tiled_tiles, P) * ns : (int)range_begin(blockIdx.x + 1, U, P));
-    if (!g.reduced && blockIdx.x == 0) advance_lens(g);
+    if (g.lens_n && blockIdx.x == 0) advance_lens(g);
     if (u0 >= u1) return;
     const int n_my = u1 - u0;
 
@@ -1010,10 +1010,11 @@ __global__ __launch_bounds__(128 * WN, TA == 1 ? 4 : 1) void gemm_f16_tiled_kern
     const int li = lane & 31, lg = lane >> 5;
     const int wm = (wave / WN) * (BM / 2), wn = (wave % WN) * (32 * TB);   // this wavefront's corner of the block tile
     const int K = g.K, nk = K / kBK, m_tiles = (g.M + BM - 1) / BM;
+    const bool moves_lens = g.lens_n > 0 && blockIdx.x == 0;
     const bool gated = g.swiglu16 != nullptr;
     // Blocks that follow each other in the work order share weight tiles: they go to the same XCD (dispatch is round
     // robin over the eight), whose L2 then serves the second reader.
-    const int P = gridDim.x, xcd = blockIdx.x % 8;
+    const int P = g.blocks, xcd = blockIdx.x % 8;
     const int blk = xcd * (P / 8) + min(xcd, P % 8) + (int)blockIdx.x / 8;
     const long U = (long)g.tiled_tiles * nk;
     const int u0 = __builtin_amdgcn_readfirstlane((int)range_begin(blk, U, P));
@@ -1206,7 +1207,7 @@ __global__ __launch_bounds__(128 * WN, TA == 1 ? 4 : 1) void gemm_f16_tiled_kern
                     }
         }
     }
-    if (!g.reduced && blockIdx.x == 0) advance_lens(g);     // (in front of the loads a 256-row step of 28 layers took 40 us longer)
+    if (moves_lens) advance_lens(g);
 }
 
 int tiles_of(const int *n, int nseg, int rows) {
@@ -1463,7 +1464,9 @@ bool gemm_moves_lens(int dtype, const GemmArgs &g) {
     return g.reduced || (dtype == PSD_BF16 && (g.M > kStreamMaxRows || (g.whole && unit_reaches(g))));
 }
 
-void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
+void launch_gemm(int dtype, const GemmArgs &args, hipStream_t stream) {
+    GemmArgs g = args;
+    if (args.reduced) g.lens_n = 0;                        // the reduction behind it does
     if (dtype != PSD_BF16) {
         ScopedProf sp(PSD_KIND_GEMM_F32, stream);
         launch_kernel(gemm_f32_kernel, (g.N + 3) / 4, 256, 0, stream, g);
@@ -1520,7 +1523,8 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
     } else {
         ScopedProf sp(PSD_KIND_GEMM_TILED, stream);
         const GemmTiledPlan p = gemm_tiled_plan(g.M, g.K, g.n, g.nseg, g.swiglu16 != nullptr, g.w4);
-        auto run = [&](const GemmArgs &t, int cols, int blocks) {
+        auto run = [&](GemmArgs &t, int cols, int blocks) {
+            t.blocks = blocks;
             auto go = [&](auto kernel, int threads) {
                 // opt in to more than 64 KB of dynamic LDS: a property of the function on the current device, set before
                 // every launch (a cheap host call) so that no process-wide flag has to remember who set it where
@@ -1562,10 +1566,10 @@ void launch_gemm(int dtype, const GemmArgs &g, hipStream_t stream) {
             run(u, p.cols2, p.tiles2);
         }
     }
-    if (g.reduced) {
+    if (args.reduced) {
         const dim3 grid((unsigned)((g.N + 255) / 256), (unsigned)g.M);
         ScopedProf sp(PSD_KIND_GEMM_REDUCE, stream);
-        launch_kernel(gemm_splitk_reduce_kernel, grid, 256, 0, stream, g);
+        launch_kernel(gemm_splitk_reduce_kernel, grid, 256, 0, stream, args);
     }
 }
 

@@ -18,13 +18,13 @@ struct AcceptArgs {
     float temperature;
     int chunkA, n_chunksA;        // statistics pass: elements per block, blocks per logits row
     int chunkE, n_chunksE;        // draw pass chunking
-    int pieceE, n_piecesE;        // entries whose sums are kept together (a chunk or a quarter of one), how many per row
     int groupE;                   // consecutive entries per thread of it
     float2 *stats;                // [rows][n_p_rows+gamma][n_chunksA] (max raw logit, sum exp)
     float *xlogit;                // [rows][gamma][2] the draft token's logit under p and under q
     double *part;                 // [rows][n_piecesE][6] fp64 sums of the draw position (accept.hip)
     uint32_t *counter;            // [rows] chunks of the draw position done so far
     int32_t *out_n, *out_tok, *flags;
+    int pieceE, n_piecesE;        // draw pass: entries whose sums are kept together (a chunk or a quarter of one), how many per row
 };
 // vec: rows are 16-byte aligned and V is a multiple of the elements per 16-byte load
 void accept_plan(int rows, int gamma, int n_p_rows, int V, int dtype, bool vec, AcceptArgs *a);
@@ -50,27 +50,36 @@ struct RowScale {
     int tiles;
     float inv_d, eps;
 };
+// What the kernels read first stands first: a block begins by waiting for the 64-byte lines of arguments that it needs, every launch
+// brings them in anew (the implicit ones, the grid's size among them, lie behind this struct).  Tiled launches of 22 rows, us, with
+// M, K, n, the tile count and the grid's size on four lines / on the first: 4608 x 3584 12.3 / 11.9, 3584 x 3584 11.0 / 10.5.
 struct GemmArgs {
-    const float *x;               // fp32 activations, K contiguous; row m is read from source row
-                                  //   (m / x_rows_per_group) * x_group_stride + x_group_offset + m % x_rows_per_group
-    const uint16_t *x16;          // optional: the same matrix already rounded to fp16 (what the tiled kernel multiplies)
-    int x_rows_per_group, x_group_stride, x_group_offset;
-    const uint16_t *x_op;         // bf16, packed weights, passes of up to 16 rows: the activations in operand order (common.h); x is not read
-    bool op_folded;               //   ... high part and remainder in one fragment (the pass has at most 8 rows)
-    const void *w[3];
+    int M, K, N, nseg;            // N = sum n[i]
     int n[3];
-    int nseg;
-    int M, K, N;                  // N = sum n[i]
-    const void *wpack;            // optional repacked copy of all segments (bf16, M <= kStreamMaxRows): see gemm.hip
-    int pack_tiles;               //   its number of 64-row tiles
-    float *partial;               // [splitk][M][N] fp32: split s holds its share of the K sum
     int splitk;
+    int tiled_tiles, blocks;      // M > kStreamMaxRows: tiles of the product, and the tiled kernel's grid; set by launch_gemm
+    int pack_tiles;               // 64-row tiles of wpack
+    int lens_n;                   // lengths that the kernel moves on (`lens`); set only for the last kernel (gemm_moves_lens)
+    bool whole;                   // blocks take whole tiles: rows kernel, set by launch_gemm; unit kernel, a head's, set by the caller
+                                  //   (gemm_stream_whole): `partial` are then the logits, the row scale is applied
+    bool w4;                      // 4-bit weights, see below
+    bool op_folded;               // x_op, xg_op: high part and remainder in one fragment (at most 8 rows)
+    const uint16_t *x16;          // M > kStreamMaxRows and 4-bit projections: the activations rounded to fp16
+    float *partial;               // [splitk][M][N] fp32: split s holds its share of the K sum
+    const void *w[3];
+    const void *wpack;            // optional repacked copy of all segments (bf16: M <= 128; 4-bit: M <= kStreamMaxRows): see gemm.hip
+    int x_rows_per_group, x_group_stride, x_group_offset;      // row m is read from source row
+                                  //   (m / x_rows_per_group) * x_group_stride + x_group_offset + m % x_rows_per_group
+    int scale_rows;               // rows per tile slab of scale.sumsq
+    uint16_t *swiglu16;           // M > kStreamMaxRows; segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
+    const uint16_t *x_op;         // bf16, packed weights, M <= kStreamMaxRows: the activations in operand order (common.h); x is not read
+    const float *x;               // fp32 activations, K contiguous
     float *reduced;               // if non-NULL: [M][N] <- sum over splits (logits), times the row scale if given
     // -- bf16, M <= kStreamMaxRows, packed weights only: RMSNorm folded into the projections around it -----------
     // rmsnorm(x) W^T = r_m * ((x * gain) W^T) with r_m = rsqrt(mean_k x[m][k]^2 + eps).  A projection with x_resid
     // set adds its output into the residual stream x_resid [M][N], writes
     // xg_op[m][n] = x_resid[m][n] * gain[n] (the operand of the next projection, in operand order; gain = the next norm's)
-    // and sumsq_out[strip or tile][m] = sum of x_resid[m][n]^2 over the 16 (column kernel) or 64 (unit kernel)
+    // and sumsq_out[strip or tile][m] = sum of x_resid[m][n]^2 over the 16 (column kernel) or 64 (4-bit projections)
     // columns one block finishes; the consumer of the next projection's output multiplies by r_m (RowScale).
     float *x_resid;
     uint16_t *xg_op;              // NULL: nobody reads it
@@ -81,17 +90,10 @@ struct GemmArgs {
                                   //   launch and left at zero by it
     // -- 4-bit weights (W4A16, groups of 128 along K): wpack holds the 4-bit quad layout of
     // launch_gemm_pack_w4; the projection writes `splitk` partial slots (gemm_w4_slots)
-    bool w4;
     const void *w4_scale[3], *w4_zero[3];   // M > kStreamMaxRows: w[] are the codes [n][K/2], these the bf16 scales and uint8 zero points [n][K/128]
-    // -- M > kStreamMaxRows (the tiled kernel; see GemmTiledPlan) ---------------------------------------------------
-    int tiled_tiles;              // set by launch_gemm
-    bool whole;                   // blocks take whole tiles: rows kernel, set by launch_gemm; unit kernel, a head's, set by the caller
-                                  //   (gemm_stream_whole): `partial` are then the logits, the row scale is applied
-    uint16_t *swiglu16;           // segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
     RowScale scale;               // applied when writing `reduced` or a head in whole tiles (row = the source row of m)
-    int scale_rows;               //   rows per tile slab of scale.sumsq
-    int32_t *lens;                // non-NULL: the last kernel also moves these lens_n lengths on by lens_add (gemm_moves_lens)
-    int lens_n, lens_add, lens_max;
+    int32_t *lens;                // lens_n of them move on by lens_add, up to lens_max
+    int lens_add, lens_max;
 };
 struct GemmTiledPlan {
     int ta, cols;                 // block tile: 64 ta rows x cols columns

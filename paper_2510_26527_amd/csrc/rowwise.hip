@@ -44,8 +44,8 @@ template <typename TW, bool EMBED, int kRowThreads, bool OP = false>
 __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *embed, const int32_t *tokens, int vocab,
                                                                     const float *partial, int S, size_t split_stride,
                                                                     float *x, const TW *gain, float *xn, float *sumsq_out,
-                                                                    int d, float eps, RopeTable rt, uint16_t *xn16, uint16_t *xn_op,
-                                                                    ZeroFill zf, TreeShape tree, uint32_t *tree_anc) {
+                                                                    int d, float eps, RopeTable rt, uint16_t *xn16,
+                                                                    ZeroFill zf, TreeShape tree, uint32_t *tree_anc, uint16_t *xn_op) {
     constexpr int kMaxV4 = kMaxRowV4 / kRowThreads;
     __shared__ float red[kRowThreads / 64];
     const int m = blockIdx.x, tid = threadIdx.x, n4 = d >> 2;
@@ -357,13 +357,13 @@ void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, floa
     if (dtype == PSD_BF16) {
         auto go = [&](auto kernel) {
             launch_kernel(kernel, M, 256, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0, x, (const uint16_t *)gain, xn, sumsq_out,
-                          d, eps, rt, xn16, xn_op, zf, ts, tree_anc);
+                          d, eps, rt, xn16, zf, ts, tree_anc, xn_op);
         };
         if (xn_op) go(residual_norm_kernel<uint16_t, true, 256, true>);
         else go(residual_norm_kernel<uint16_t, true, 256>);
     } else
         launch_kernel(residual_norm_kernel<float, true, 256>, M, 256, 0, stream, (const float *)embed, tokens, vocab, nullptr, 0, 0, x,
-                                                                        (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, xn_op, zf, ts, tree_anc);
+                                                                        (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, zf, ts, tree_anc, xn_op);
 }
 
 constexpr int kWideRowMax = 256;       // rows up to which a norm block has 1024 threads
@@ -373,12 +373,12 @@ void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *
     const size_t stride = (size_t)M * d;
     if (dtype == PSD_BF16)
         (M <= kWideRowMax ? launch_kernel(residual_norm_kernel<uint16_t, false, 1024>, M, 1024, 0, stream, nullptr, nullptr, 0, partial, S,
-                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, nullptr, ZeroFill{}, TreeShape{}, nullptr)
+                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, nullptr)
                           : launch_kernel(residual_norm_kernel<uint16_t, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S,
-                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, nullptr, ZeroFill{}, TreeShape{}, nullptr));
+                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, nullptr));
     else
         launch_kernel(residual_norm_kernel<float, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S, stride, x,
-                                                                         (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, nullptr, ZeroFill{}, TreeShape{}, nullptr);
+                                                                         (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, nullptr);
 }
 
 void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale rs, float *q_out, void *k_cache,
