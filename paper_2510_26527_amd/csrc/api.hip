@@ -480,7 +480,11 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     const int n_o_fw[1] = {d.d_model};
     RowScale rs{nullptr, 0, 1.0f / (float)d.d_model, d.rms_eps};
     if (p.folded) rs.sumsq = sumsq;
-    uint16_t *xn_op = p.folded ? (uint16_t *)xn : nullptr;
+    // What the head reads in operand order: all rows of a folded pass, or, of a longer one, the up to 16 rows that get logits, one
+    // behind the other, from the last norm.
+    const bool head_op = m->packed && !p.folded && n_logit_rows > 0 && B * n_logit_rows <= kStreamMaxRows;
+    uint16_t *xn_op = p.folded || head_op ? (uint16_t *)xn : nullptr;
+    const OpRows head_rows{head_op ? xn_op : nullptr, n_new, n_new - n_logit_rows, B * n_logit_rows <= kOpFoldRows};
     const float *act = xn;     // what QKV / gate|up / lm_head read: rmsnorm(x) * gain, or x * gain when folded
     auto resid_gemm = [&](const float *xin, int K, const void *w, int sk, const void *wpack, const void *next_gain,
                           int ql, int qj, bool last = false) {
@@ -498,7 +502,9 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
             rs.tiles = slots ? g.pack_tiles : col_tiles;
         } else {
             gemm(xin, M, K, w, d.d_model, nullptr, 0, nullptr, 0, sk, partial, nullptr, ql, qj);       // (packed strip-major: for the column kernel alone)
-            launch_reduce_residual_norm(d.dtype, partial, sk, x, next_gain, p.half_copies && !last ? nullptr : xn, M, d.d_model, d.rms_eps, xn16, st);
+            const bool to_head = last && head_op;
+            launch_reduce_residual_norm(d.dtype, partial, sk, x, next_gain, to_head || (p.half_copies && !last) ? nullptr : xn, M, d.d_model, d.rms_eps,
+                                        to_head ? nullptr : xn16, to_head ? head_rows : OpRows{}, st);
         }
     };
     RopeTable rt{};
@@ -509,8 +515,11 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         if (!p.fused_rope) return PSD_ERR_UNIMPLEMENTED;
         tree_anc = (const uint32_t *)(ws + p.off_tree);      // written by the embedding kernel
     }
-    launch_embed_norm(d.dtype, m->embed(), tokens_dev, x, norm_gain(0), p.folded ? nullptr : xn, p.folded ? sumsq : nullptr, M, d.d_model,
-                      d.vocab, d.rms_eps, rt, xn16, m->w4 && d.n_layers ? nullptr : xn_op, ZeroFill{tile_ctr, p.folded && m->w4 ? gemm_pack_tiles(n_o_fw, 1) : 0},
+    OpRows first_rows{};                                     // (4-bit projections read xn16)
+    if (p.folded && !(m->w4 && d.n_layers)) first_rows = OpRows{xn_op, M, 0, op_folded};
+    else if (head_op && !d.n_layers) first_rows = head_rows;
+    launch_embed_norm(d.dtype, m->embed(), tokens_dev, x, norm_gain(0), p.folded || first_rows.op ? nullptr : xn, p.folded ? sumsq : nullptr, M, d.d_model,
+                      d.vocab, d.rms_eps, rt, xn16, first_rows, ZeroFill{tile_ctr, p.folded && m->w4 ? gemm_pack_tiles(n_o_fw, 1) : 0},
                       tree, tree ? (uint32_t *)(ws + p.off_tree) : nullptr, st);
     rs.tiles = 1;
     for (int l = 0; l < d.n_layers; ++l) {
@@ -542,7 +551,9 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     if (n_logit_rows > 0) {
         // lm_head on the last n_logit_rows rows of every sequence (unfolded: xn already holds the final norm)
         GemmArgs hg{};
-        hg.x = act; hg.x_op = xn_op; hg.op_folded = op_folded; hg.x16 = xn16; hg.x_rows_per_group = n_logit_rows; hg.x_group_stride = n_new; hg.x_group_offset = n_new - n_logit_rows;
+        hg.x = act; hg.x16 = xn16; hg.x_rows_per_group = n_logit_rows; hg.x_group_stride = n_new; hg.x_group_offset = n_new - n_logit_rows;
+        hg.x_op = xn_op; hg.op_folded = p.folded ? op_folded : head_rows.folded;
+        if (head_op) { hg.x_group_stride = n_logit_rows; hg.x_group_offset = 0; }
         hg.w[0] = m->lm_head(); hg.n[0] = d.vocab; hg.nseg = 1;
         hg.M = B * n_logit_rows; hg.K = d.d_model; hg.N = d.vocab;
         hg.wpack = m->pack_head();

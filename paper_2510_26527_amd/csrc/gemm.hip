@@ -386,16 +386,13 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
 // that out itself (its sums of squares requested ahead of the first weights), and writes the logits: no slot and no reduction
 // (128256 x 4096, us with the reduction: 7 rows 166.6 -> 157.6, 14 rows 189.8 -> 171.9).
 //
-// Activations: in operand order, two fragments or (folded) one a quarter; or row-major fp32, split into high part and remainder
-// here (the head of a pass of more than 16 rows).  Row-major, every lane's 16 bytes come out of another line, and at 16 rows
-// the activations cost the vector memory path twice what the weights do.  Measured, QKV, gate|up and head of the 7B shape averaged
+// Activations: in operand order, two fragments or (folded) one a quarter.  Row-major, as fp32 split here, every lane's 16 bytes come
+// out of another line, and at 16 rows they cost the vector memory path twice what the weights do.  Measured, QKV, gate|up and head of the 7B shape averaged
 // (us a launch; row-major and two stages in an order of the compiler's / this): 1 row 28.3 / 26.9, 8 rows 28.9 / 27.2, 9 rows
 // 29.2 / 27.7, 16 rows 30.8 (two tiles at a time) / 29.7; plain reads of the same weights 25.4.  Two tiles at a time, which
 // share a K step's activations, gain nothing any more (16 rows 30.6), nor does a fourth stage.
-enum ActForm { kRows, kOp, kOpFolded };
-template <ActForm ACT>
+template <bool FOLD>
 __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
-    constexpr bool FOLD = ACT == kOpFolded;
     constexpr int R = 3, XV = FOLD ? 1 : 2;                // units in flight per wavefront (its 4 KB of each)
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int i = lane & 15, gq = lane >> 4;
@@ -419,19 +416,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
     if (scaled)
 #pragma unroll
         for (int t = 0; t < 16; ++t) ssq[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, soff + (unsigned)(t * 16 * g.scale_rows) * 4, 0, 0);
-    // activations: a row past M points past the buffer and reads zeros; row-major, offsets from the first row's source row
-    const size_t row_first = ACT == kRows ? x_row(g, 0) : 0;
-    const __amdgpu_buffer_rsrc_t rx =
-        ACT == kRows ? __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(g.x) + row_first * K, 0, 0x7ffffff0, 0x00020000)
-                     : __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(g.x_op), 0, K * (FOLD ? 32 : 64), 0x00020000);
-    constexpr unsigned kStepX = ACT == kRows ? kSkinnyStepK * 4 : kSkinnyStepK * (FOLD ? 32 : 64);   // bytes from one K step to the next
-    unsigned xbase = 0x80000000u;
-    if constexpr (ACT == kRows) {
-        if (i < g.M) xbase = (unsigned)((x_row(g, i) - row_first) * K * 4) + (unsigned)((q >> 1) * 64 + gq * 16 + (q & 1) * 8) * 4u;
-    } else {
-        const int m = FOLD ? i & 7 : i;
-        if (m < g.M) xbase = (unsigned)(q * (FOLD ? 1024 : 2048) + (gq * 16 + (int)x_row(g, m) + (FOLD ? i & 8 : 0)) * 16);
-    }
+    // activations: a row past M points past the buffer and reads zeros
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(g.x_op), 0, K * (FOLD ? 32 : 64), 0x00020000);
+    constexpr unsigned kStepX = kSkinnyStepK * (FOLD ? 32 : 64);             // bytes from one K step to the next
+    const int xm = FOLD ? i & 7 : i;
+    const unsigned xbase = xm < g.M ? (unsigned)(q * (FOLD ? 1024 : 2048) + (gq * 16 + (int)x_row(g, xm) + (FOLD ? i & 8 : 0)) * 16) : 0x80000000u;
     const unsigned lane_off = q * 4096u + lane * 16u;
 
     u32x4 A[R][4], X[R][XV];
@@ -439,7 +428,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
     auto issue = [&](int j, int n) {                       // n = index of the unit inside the block's range
         const unsigned xo = n < n_my ? xbase + (unsigned)step_issue * kStepX : 0x80000000u;
         X[j][0] = __builtin_amdgcn_raw_buffer_load_b128(rx, xo, 0, 0);
-        if constexpr (!FOLD) X[j][1] = __builtin_amdgcn_raw_buffer_load_b128(rx, xo + (ACT == kRows ? 16 : 1024), 0, 0);
+        if constexpr (!FOLD) X[j][1] = __builtin_amdgcn_raw_buffer_load_b128(rx, xo + 1024, 0, 0);
         const unsigned wo = (unsigned)n * kUnitBytes + lane_off;
 #pragma unroll
         for (int s = 0; s < 4; ++s) A[j][s] = __builtin_amdgcn_raw_buffer_load_b128(rw, wo + s * 1024, 0, 2);   // 2: streaming
@@ -452,16 +441,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto multiply = [&](int j) {
-        bf16x8 bh, bl;
-        if constexpr (ACT == kRows) {
-            f32x8 xv;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { xv[e] = __uint_as_float(X[j][0][e]); xv[4 + e] = __uint_as_float(X[j][XV - 1][e]); }
-            split_bf16(xv, &bh, &bl);
-        } else {
-            bh = __builtin_bit_cast(bf16x8, X[j][0]);
-            bl = __builtin_bit_cast(bf16x8, X[j][XV - 1]);
-        }
+        const bf16x8 bh = __builtin_bit_cast(bf16x8, X[j][0]), bl = __builtin_bit_cast(bf16x8, X[j][XV - 1]);
         // hi parts over all accumulators, then lo parts: no back-to-back MFMAs on one accumulator
 #pragma unroll
         for (int s = 0; s < 4; ++s)
@@ -1456,12 +1436,8 @@ int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, boo
     return gemm_tiled_plan(M, K, n, nseg, false, w4).slots;
 }
 
-// the unit kernel addresses the rows of row-major activations with 32-bit offsets from the first one
-static bool unit_reaches(const GemmArgs &g) {
-    return g.x_op || (long)(x_row(g, g.M - 1) - x_row(g, 0) + 1) * g.K * 4 < 0x7fff0000L;
-}
 bool gemm_moves_lens(int dtype, const GemmArgs &g) {
-    return g.reduced || (dtype == PSD_BF16 && (g.M > kStreamMaxRows || (g.whole && unit_reaches(g))));
+    return g.reduced || (dtype == PSD_BF16 && (g.M > kStreamMaxRows || g.whole));
 }
 
 void launch_gemm(int dtype, const GemmArgs &args, hipStream_t stream) {
@@ -1490,13 +1466,12 @@ void launch_gemm(int dtype, const GemmArgs &args, hipStream_t stream) {
         else launch_kernel(gemm_bf16_column_kernel<false>, grid, 1024, 0, stream, g);
         return;
     }
-    if (g.M <= kStreamMaxRows && g.wpack && unit_reaches(g)) {
+    if (g.M <= kStreamMaxRows && g.wpack) {
         ScopedProf sp(PSD_KIND_GEMM_SKINNY, stream);
         const int grid = g.whole ? (g.pack_tiles < kStreamBlocks ? g.pack_tiles : kStreamBlocks) : gemm_stream_grid(g.pack_tiles, g.K);
         auto go = [&](auto kernel) { launch_kernel(kernel, grid, 256, 0, stream, g); };
-        if (g.x_op && g.op_folded) go(gemm_bf16_unit_kernel<kOpFolded>);
-        else if (g.x_op) go(gemm_bf16_unit_kernel<kOp>);
-        else go(gemm_bf16_unit_kernel<kRows>);
+        if (g.op_folded) go(gemm_bf16_unit_kernel<true>);
+        else go(gemm_bf16_unit_kernel<false>);
     } else if (g.M <= kStreamMaxRows) {
         ScopedProf sp(PSD_KIND_GEMM_SLOT, stream);
         dim3 grid(tiles_of(g.n, g.nseg, kSkinnyRows), g.splitk);

@@ -72,8 +72,8 @@ struct GemmArgs {
                                   //   (m / x_rows_per_group) * x_group_stride + x_group_offset + m % x_rows_per_group
     int scale_rows;               // rows per tile slab of scale.sumsq
     uint16_t *swiglu16;           // M > kStreamMaxRows; segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
-    const uint16_t *x_op;         // bf16, packed weights, M <= kStreamMaxRows: the activations in operand order (common.h); x is not read
-    const float *x;               // fp32 activations, K contiguous
+    const uint16_t *x_op;         // bf16, packed weights, M <= kStreamMaxRows: the activations in operand order (common.h)
+    const float *x;               // fp32 activations, K contiguous: fp32 models, and bf16 ones without packed weights up to kStreamMaxRows rows
     float *reduced;               // if non-NULL: [M][N] <- sum over splits (logits), times the row scale if given
     // -- bf16, M <= kStreamMaxRows, packed weights only: RMSNorm folded into the projections around it -----------
     // rmsnorm(x) W^T = r_m * ((x * gain) W^T) with r_m = rsqrt(mean_k x[m][k]^2 + eps).  A projection with x_resid
@@ -201,20 +201,27 @@ struct ZeroFill {
     unsigned *words;              // n 32-bit words set to zero by the first kernel of a forward pass (NULL / 0: none)
     int n;
 };
+// xn in operand order (common.h), one behind the other: rows first .. per_group - 1 of each group of per_group rows, 16 at most
+struct OpRows {
+    uint16_t *op;                 // NULL: not wanted
+    int per_group, first;
+    bool folded;
+};
 // tree (or NULL): row r sits at position lens[b] + depth[r], and tree_anc receives the ancestor masks
 // x = embed[token]; then xn = rmsnorm(x) * gain, or (sumsq_out non-NULL) xn = x * gain and sumsq_out[m] = sum_k x[m][k]^2;
-// xn_op (only with sumsq_out): xn goes there in operand order, and xn may be NULL
+// with `op` xn goes there too, and may be NULL
 void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, float *x, const void *gain, float *xn,
-                       float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, uint16_t *xn_op, ZeroFill zf,
+                       float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, OpRows op, ZeroFill zf,
                        const TreeShape *tree, uint32_t *tree_anc, hipStream_t stream);
 // qkv = sum over splits of partial [S][M][(h_q+2h_kv) d_h] -> rotated q (fp32), rotated k and v appended
 // to the cache (model dtype); cs_table: RopeTable::cs of these rows, NULL: the angles are evaluated again
 void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale rs, float *q_out, void *k_cache,
                                void *v_cache, const int32_t *lens, int B, int R, int h_q, int h_kv, int d_h,
                                int max_len, float theta, const float2 *cs_table, hipStream_t stream);
-// x += sum over splits of partial [S][M][d]; xn = rmsnorm(x) * gain (xn16, if given: the same rounded to fp16, and xn may be NULL)
+// x += sum over splits of partial [S][M][d]; xn = rmsnorm(x) * gain (xn16, if given: the same rounded to fp16; xn may be NULL
+// beside that or op)
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
-                                 int M, int d, float eps, uint16_t *xn16, hipStream_t stream);
+                                 int M, int d, float eps, uint16_t *xn16, OpRows op, hipStream_t stream);
 // h = silu(g) * u with [g | u] = sum over splits of partial [S][M][2f]: any of fp32, fp16 and operand order
 void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, uint16_t *h_op, hipStream_t stream);
 void launch_advance_lens(int32_t *lens, int B, int delta, int max_len, hipStream_t stream);

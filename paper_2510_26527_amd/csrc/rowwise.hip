@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *em
                                                                     const float *partial, int S, size_t split_stride,
                                                                     float *x, const TW *gain, float *xn, float *sumsq_out,
                                                                     int d, float eps, RopeTable rt, uint16_t *xn16,
-                                                                    ZeroFill zf, TreeShape tree, uint32_t *tree_anc, uint16_t *xn_op) {
+                                                                    ZeroFill zf, TreeShape tree, uint32_t *tree_anc, OpRows op) {
     constexpr int kMaxV4 = kMaxRowV4 / kRowThreads;
     __shared__ float red[kRowThreads / 64];
     const int m = blockIdx.x, tid = threadIdx.x, n4 = d >> 2;
@@ -127,13 +127,14 @@ __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *em
         scale = 1.0f;
     }
     f32x4 *orow = reinterpret_cast<f32x4 *>(xn + (size_t)m * d);
+    const int op_r = OP ? m % op.per_group - op.first : -1, op_row = OP ? m / op.per_group * (op.per_group - op.first) + op_r : 0;
 #pragma unroll
     for (int j = 0; j < kMaxV4; ++j) {
         const int i4 = tid + j * kRowThreads;
         if (i4 < n4) {
             const f32x4 r = v[j] * scale * load_gain4(gain, i4);
             if (xn) orow[i4] = r;
-            if constexpr (OP) op_store4(xn_op, m, 4 * i4, (int)gridDim.x <= kOpFoldRows, r);
+            if (OP && op_r >= 0) op_store4(op.op, op_row, 4 * i4, op.folded, r);
             if (xn16)              // the same row rounded to fp16: the operand of the tiled projections
                 reinterpret_cast<uint2 *>(xn16 + (size_t)m * d)[i4] =
                     make_uint2(f32_to_f16_bits(r[0]) | ((uint32_t)f32_to_f16_bits(r[1]) << 16),
@@ -350,35 +351,42 @@ __global__ void truncate_to_kernel(int32_t *lens, int new_len, int B) {
 }  // namespace
 
 void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, float *x, const void *gain, float *xn,
-                       float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, uint16_t *xn_op, ZeroFill zf,
+                       float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, OpRows op, ZeroFill zf,
                        const TreeShape *tree, uint32_t *tree_anc, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_EMBED, stream);
     const TreeShape ts = tree ? *tree : TreeShape{};
     if (dtype == PSD_BF16) {
         auto go = [&](auto kernel) {
             launch_kernel(kernel, M, 256, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0, x, (const uint16_t *)gain, xn, sumsq_out,
-                          d, eps, rt, xn16, zf, ts, tree_anc, xn_op);
+                          d, eps, rt, xn16, zf, ts, tree_anc, op);
         };
-        if (xn_op) go(residual_norm_kernel<uint16_t, true, 256, true>);
+        if (op.op) go(residual_norm_kernel<uint16_t, true, 256, true>);
         else go(residual_norm_kernel<uint16_t, true, 256>);
     } else
         launch_kernel(residual_norm_kernel<float, true, 256>, M, 256, 0, stream, (const float *)embed, tokens, vocab, nullptr, 0, 0, x,
-                                                                        (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, zf, ts, tree_anc, xn_op);
+                                                                        (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, zf, ts, tree_anc, op);
 }
 
 constexpr int kWideRowMax = 256;       // rows up to which a norm block has 1024 threads
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
-                                 int M, int d, float eps, uint16_t *xn16, hipStream_t stream) {
+                                 int M, int d, float eps, uint16_t *xn16, OpRows op, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_RMSNORM, stream);
     const size_t stride = (size_t)M * d;
-    if (dtype == PSD_BF16)
-        (M <= kWideRowMax ? launch_kernel(residual_norm_kernel<uint16_t, false, 1024>, M, 1024, 0, stream, nullptr, nullptr, 0, partial, S,
-                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, nullptr)
-                          : launch_kernel(residual_norm_kernel<uint16_t, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S,
-                                          stride, x, (const uint16_t *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, nullptr));
-    else
+    if (dtype == PSD_BF16) {
+        auto go = [&](auto kernel, int threads) {
+            launch_kernel(kernel, M, threads, 0, stream, nullptr, nullptr, 0, partial, S, stride, x, (const uint16_t *)gain, xn, nullptr, d, eps,
+                          RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, op);
+        };
+        auto pick = [&](auto with_op) {
+            constexpr bool OP = decltype(with_op)::value;
+            if (M <= kWideRowMax) go(residual_norm_kernel<uint16_t, false, 1024, OP>, 1024);
+            else go(residual_norm_kernel<uint16_t, false, 256, OP>, 256);
+        };
+        if (op.op) pick(std::true_type{});
+        else pick(std::false_type{});
+    } else
         launch_kernel(residual_norm_kernel<float, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S, stride, x,
-                                                                         (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, nullptr);
+                      (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, op);
 }
 
 void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale rs, float *q_out, void *k_cache,

@@ -142,6 +142,27 @@ def test_head_in_whole_tiles(d_model, batch, n_new, rows):
     p.close()
 
 
+@pytest.mark.parametrize("layers,batch,n_new,rows,vocab", [(1, 2, 20, 4, 200), (1, 3, 9, 3, 29505), (1, 1, 300, 16, 200)])
+def test_head_over_few_rows_of_a_long_pass(layers, batch, n_new, rows, vocab):
+    """The up to 16 rows with logits of a longer pass reach the packed head in operand order, one sequence's behind the other's: up
+    to 8 rows (folded) and more, from the norm of up to 256 rows and above."""
+    shape = synth.Shape(layers, 128, 2, 2, 64, 128, vocab, 1.0e4)
+    p = Pair(shape, torch.bfloat16, batch, 320, seed=n_new, ctx=9, std=0.05, pack=True)
+    p.step(synth.make_tokens(shape.vocab, (batch, n_new), rows), n_logit_rows=rows, what="the last rows' logits")
+    assert p.kv.lens.cpu().tolist() == [9 + n_new] * batch
+    p.close()
+
+
+@pytest.mark.parametrize("d_head", [64, 128])
+def test_staged_attention_in_operand_order(d_head):
+    """Packed pass of 16 rows whose LDS-staged attention has more than 64 query rows per KV head and one split of the cache, so that it
+    writes the operand order itself."""
+    shape = synth.Shape(1, 8 * d_head, 8, 1, d_head, 256, 200, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 64, seed=d_head, ctx=20, std=0.05, pack=True)
+    p.step(synth.make_tokens(shape.vocab, (1, 16), 3), what="16 rows x 8 heads")
+    p.close()
+
+
 @pytest.mark.parametrize("n_new", [17, 33, 64, 65, 97, 128])
 @pytest.mark.parametrize("d_model,d_ffn,vocab", [(128, 11008, 28001), (128, 14336, 40960), (384, 18944, 512), (1024, 512, 41600)])
 def test_rows_kernel(d_model, d_ffn, vocab, n_new):
