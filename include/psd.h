@@ -111,7 +111,7 @@ psd_status psd_model_create_w4(const psd_model_desc *desc, const void *const *we
  * (batch * n_new <= 128), where the forward pass is bound by reading the weights once from HBM.
  * psd_model_pack rewrites every projection matrix into caller memory in the order the
  * wavefronts of the streaming GEMMs load it (64-row x 128-column units of 16 KB, each stored
- * as the 64 lanes' 16-byte operands, units of one projection contiguous; for the O and down
+ * as the 64 lanes' 16-byte operands, units of one projection contiguous; for the O and most models' down
  * projections 16 rows x all columns in one piece), so that each
  * wavefront reads one contiguous byte range.  packed_mem: device, 256-byte aligned, at least
  * psd_model_packed_bytes() bytes (about the size of the weights), kept alive with the model;

@@ -215,7 +215,7 @@ psd_status psd_model_pack(psd_model *m, void *packed_mem, size_t packed_bytes, v
         const int n_gu[2] = {d.d_ffn, d.d_ffn};
         launch_gemm_pack(gu, n_gu, 2, d.d_model, base + off[4 * l + P_GU], false, st);
         const void *dn[1] = {m->layer(l, W_DOWN)};
-        launch_gemm_pack(dn, n_o, 1, d.d_ffn, base + off[4 * l + P_DOWN], true, st);
+        launch_gemm_pack(dn, n_o, 1, d.d_ffn, base + off[4 * l + P_DOWN], !gemm_down_by_units(d.d_model, d.d_ffn), st);
     }
     const void *hw[1] = {m->lm_head()};
     const int n_v[1] = {d.vocab};
@@ -269,6 +269,7 @@ struct ForwardPlan {
     bool half_copies;             // bf16, M > kStreamMaxRows or 4-bit projections: the producers also leave fp16 copies of the activations
     bool folded;                  // RMSNorm folded into the projections (bf16, packed weights, M <= kStreamMaxRows)
     bool fused_rope;              // the attention kernel reduces, rotates and appends q / k / v itself
+    bool down_by_units;           // the folded down projection runs on the unit kernel, its tiles finished by the last block to arrive
     bool gated;                   // bf16, M > kStreamMaxRows: the gate|up projection applies SwiGLU itself
     size_t partial_bytes;         // of the layers' projections
 };
@@ -292,11 +293,13 @@ ForwardPlan plan_projections(const psd_model *mdl, int M) {
     const int n_qkv[3] = {hd, kvd, kvd}, n_o[1] = {d.d_model}, n_gu[2] = {d.d_ffn, d.d_ffn};
     p.folded = mdl->packed && d.dtype == PSD_BF16 && M <= kStreamMaxRows;
     p.sk_qkv = proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
-    // folded: O and down run on the column kernel (one owner per output), or, 4-bit, on partial slots with the arrival epilogue
+    // folded: O and down run on the column kernel (one owner per output), or, 4-bit and some down, on partial slots with the arrival epilogue
     p.sk_o = p.folded ? (mdl->w4 ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false, true);
     p.gated = d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4);
     p.sk_gu = p.gated ? 1 : proj_splits(mdl, M, d.d_model, n_gu, 2, false);
-    p.sk_down = p.folded ? (mdl->w4 ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : 1) : proj_splits(mdl, M, d.d_ffn, n_o, 1, false, true);
+    p.down_by_units = p.folded && !mdl->w4 && gemm_down_by_units(d.d_model, d.d_ffn);
+    p.sk_down = p.down_by_units ? gemm_resid_slots(gemm_pack_tiles(n_o, 1), d.d_ffn)
+                : p.folded ? (mdl->w4 ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : 1) : proj_splits(mdl, M, d.d_ffn, n_o, 1, false, true);
     p.half_copies = d.dtype == PSD_BF16 && (M > kStreamMaxRows || (mdl->w4 && p.folded));
     auto need = [&](int sk, int N) { const size_t b = (size_t)sk * M * N * 4; if (b > p.partial_bytes) p.partial_bytes = b; };
     need(p.sk_qkv, p.width_qkv);
@@ -348,7 +351,7 @@ void plan_layout(const psd_model *mdl, int batch, int n_new, int len_bound, bool
     p.off_pml = take(p.attn_splits > 1 ? (size_t)M * d.n_q_heads * p.attn_splits * 2 * 4 : 0);
     p.off_sumsq = take(p.folded ? (size_t)(d.d_model / 16) * M * 4 : 0);
     p.off_rope = take(d.dtype == PSD_BF16 ? (size_t)M * (d.d_head / 2) * sizeof(float2) : 0);
-    p.off_tilectr = take(p.folded ? (size_t)gemm_pack_tiles(n_o, 1) * 4 : 0);
+    p.off_tilectr = take(p.down_by_units || (p.folded && mdl->w4) ? (size_t)gemm_pack_tiles(n_o, 1) * 4 : 0);       // arrival counters
     p.off_tree = take(p.fused_rope ? (size_t)kTreeMaxNodes * 4 : 0);      // ancestor masks of a tree pass
     p.total = off;
 }
@@ -453,7 +456,8 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     (void)hipGetLastError();
     auto norm_gain = [&](int l) { return l < d.n_layers ? m->layer(l, W_ATTN_NORM) : m->final_norm(); };
     const bool op_folded = M <= kOpFoldRows;
-    unsigned *tile_ctr = p.folded ? (unsigned *)(ws + p.off_tilectr) : nullptr;
+    const bool arrivals = p.folded && (m->w4 || p.down_by_units);        // some tiles are finished by the last block to arrive
+    unsigned *tile_ctr = arrivals ? (unsigned *)(ws + p.off_tilectr) : nullptr;
     // ql, qj: layer and index of the first segment among the layer's 4-bit projections (q k v o gate up down), if any
     auto gemm = [&](const float *xin, int rows, int K, const void *w0, int n0, const void *w1, int n1,
                     const void *w2, int n2, int sk, float *dst, const void *wpack, int ql = -1, int qj = -1) {
@@ -487,11 +491,11 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     const OpRows head_rows{head_op ? xn_op : nullptr, n_new, n_new - n_logit_rows, B * n_logit_rows <= kOpFoldRows};
     const float *act = xn;     // what QKV / gate|up / lm_head read: rmsnorm(x) * gain, or x * gain when folded
     auto resid_gemm = [&](const float *xin, int K, const void *w, int sk, const void *wpack, const void *next_gain,
-                          int ql, int qj, bool last = false) {
+                          bool by_units, int ql, int qj, bool last = false) {
         if (p.folded) {
             GemmArgs g{};
             g.wpack = wpack; g.x = xin; g.x_rows_per_group = M; g.w[0] = w; g.n[0] = d.d_model; g.nseg = 1;
-            const bool slots = m->w4;                     // partial slots + arrival epilogue, else one block per 16 columns
+            const bool slots = by_units || m->w4;         // partial slots + arrival epilogue, else one block per 16 columns
             g.M = M; g.K = K; g.N = d.d_model; g.splitk = slots ? sk : 1; g.pack_tiles = gemm_pack_tiles(g.n, 1);
             g.x_op = (const uint16_t *)xin; g.op_folded = op_folded;
             g.xg_op = m->w4 && !last ? nullptr : xn_op;   // 4-bit projections read xn16, the head xn
@@ -519,7 +523,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     if (p.folded && !(m->w4 && d.n_layers)) first_rows = OpRows{xn_op, M, 0, op_folded};
     else if (head_op && !d.n_layers) first_rows = head_rows;
     launch_embed_norm(d.dtype, m->embed(), tokens_dev, x, norm_gain(0), p.folded || first_rows.op ? nullptr : xn, p.folded ? sumsq : nullptr, M, d.d_model,
-                      d.vocab, d.rms_eps, rt, xn16, first_rows, ZeroFill{tile_ctr, p.folded && m->w4 ? gemm_pack_tiles(n_o_fw, 1) : 0},
+                      d.vocab, d.rms_eps, rt, xn16, first_rows, ZeroFill{tile_ctr, arrivals ? gemm_pack_tiles(n_o_fw, 1) : 0},
                       tree, tree ? (uint32_t *)(ws + p.off_tree) : nullptr, st);
     rs.tiles = 1;
     for (int l = 0; l < d.n_layers; ++l) {
@@ -539,13 +543,13 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         a.splits = p.attn_splits;
         launch_attention(d.dtype, a, st);
 
-        resid_gemm(attn, hd, m->layer(l, W_O), p.sk_o, m->pack(l, P_O), m->layer(l, W_FFN_NORM), l, 3);
+        resid_gemm(attn, hd, m->layer(l, W_O), p.sk_o, m->pack(l, P_O), m->layer(l, W_FFN_NORM), false, l, 3);
         gemm(act, M, d.d_model, m->layer(l, W_GATE), d.d_ffn, m->layer(l, W_UP), d.d_ffn, nullptr, 0, p.sk_gu,
              p.gated ? nullptr : partial, m->pack(l, P_GU), l, 4);
         if (!p.gated)
             launch_reduce_swiglu(partial, p.sk_gu, rs, p.half_copies || p.folded ? nullptr : h, M, d.d_ffn, h16,
                                  p.folded && !p.half_copies ? (uint16_t *)h : nullptr, st);
-        resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), l, 6, l + 1 == d.n_layers);
+        resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), p.down_by_units, l, 6, l + 1 == d.n_layers);
     }
     bool advanced = false;                                   // the head's last kernel, the last one of its kind of pass, does it
     if (n_logit_rows > 0) {

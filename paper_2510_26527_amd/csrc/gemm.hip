@@ -12,9 +12,11 @@
 //                            units of a GEMM are contiguous, and the grid is persistent: each block streams
 //                            an equal, contiguous range of units (stream-K), its four wavefronts on the four
 //                            K quarters of every unit, and writes one partial per tile it touches.
+//                            With RESID (the down projection of wide models and very long ones) the block that arrives
+//                            last at a tile adds the tile's partials and runs the residual epilogue below.
 //   gemm_bf16_rows_kernel    17 to 128 rows on the same units: the weights stream into MFMA operands as above, the
 //                            activations (fp16) go through LDS; whole tiles where they fill the chip.
-//   gemm_bf16_column_kernel  M <= 16, the projections that write the residual stream (O, down): one
+//   gemm_bf16_column_kernel  M <= 16, the projections that write the residual stream (O, most models' down): one
 //                            block per 16 output columns over the whole K range; the residual add, the
 //                            gain-scaled copy and the RMSNorm statistics happen in its epilogue.
 //   gemm_w4_unit_kernel      M <= 16, 4-bit weight-only quantised projections (groups of 128 along K): the unit
@@ -347,23 +349,25 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
     const int row = t.row0 + lane;                                  // lane = row of the tile
     const bool row_ok = row < g.n[t.seg];
     const size_t col = (size_t)t.col0 + row;
+    constexpr int NR = FOLD ? 2 : 4;
+    auto sum = [&](int tok) {
+        float v = ((red[0][lane][tok] + red[1][lane][tok]) + red[2][lane][tok]) + red[3][lane][tok];
+        if constexpr (FOLD)                                // the products with the remainders stand eight columns further on
+            v += ((red[0][lane][tok + 8] + red[1][lane][tok + 8]) + red[2][lane][tok + 8]) + red[3][lane][tok + 8];
+        return v;
+    };
     if constexpr (RESID) {
         const int n_contrib = (int)(range_owner(first + upt - 1, U, P) - first_owner) + 1;
-        float mine[4];
+        float mine[NR];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int tok = q + 4 * r;
-            mine[r] = ((red[0][lane][tok] + red[1][lane][tok]) + red[2][lane][tok]) + red[3][lane][tok];
-        }
-        resid_tile_finish<4>(g, tile, slot, n_contrib, mine, q, 4, row_ok, col, s_last);
+        for (int r = 0; r < NR; ++r) mine[r] = sum(q + 4 * r);
+        resid_tile_finish<NR>(g, tile, slot, n_contrib, mine, q, 4, row_ok, col, s_last);
     } else if (row_ok) {
 #pragma unroll
-        for (int r = 0; r < (FOLD ? 2 : 4); ++r) {
+        for (int r = 0; r < NR; ++r) {
             const int tok = q + 4 * r;
             if (tok < g.M) {
-                float v = ((red[0][lane][tok] + red[1][lane][tok]) + red[2][lane][tok]) + red[3][lane][tok];
-                if constexpr (FOLD)                        // the products with the remainders stand eight columns further on
-                    v += ((red[0][lane][tok + 8] + red[1][lane][tok + 8]) + red[2][lane][tok + 8]) + red[3][lane][tok + 8];
+                float v = sum(tok);
                 if (s_scale && g.whole) v *= s_scale[tok];
                 g.partial[((size_t)slot * g.M + tok) * g.N + col] = v;
                 if (tile_end)
@@ -386,12 +390,17 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
 // that out itself (its sums of squares requested ahead of the first weights), and writes the logits: no slot and no reduction
 // (128256 x 4096, us with the reduction: 7 rows 166.6 -> 157.6, 14 rows 189.8 -> 171.9).
 //
+// RESID: every output element still gets one owner, found at run time.  A block publishes its partial with agent-scope stores, waits for
+// them, and counts itself in on the tile's counter; whichever block arrives last adds the tile's slots in slot order (so the sum does
+// not depend on who that was) and runs the column kernel's epilogue on the tile's 64 columns, sum of squares per row into
+// sumsq_out[tile][m].  It leaves the counter at zero for the next launch.  No block waits for another.
+//
 // Activations: in operand order, two fragments or (folded) one a quarter.  Row-major, as fp32 split here, every lane's 16 bytes come
 // out of another line, and at 16 rows they cost the vector memory path twice what the weights do.  Measured, QKV, gate|up and head of the 7B shape averaged
 // (us a launch; row-major and two stages in an order of the compiler's / this): 1 row 28.3 / 26.9, 8 rows 28.9 / 27.2, 9 rows
 // 29.2 / 27.7, 16 rows 30.8 (two tiles at a time) / 29.7; plain reads of the same weights 25.4.  Two tiles at a time, which
 // share a K step's activations, gain nothing any more (16 rows 30.6), nor does a fourth stage.
-template <bool FOLD>
+template <bool FOLD, bool RESID>
 __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
     constexpr int R = 3, XV = FOLD ? 1 : 2;                // units in flight per wavefront (its 4 KB of each)
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
@@ -451,6 +460,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
             acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[j][s]), bl, acc[s], 0, 0, 0);
     };
     __shared__ float red[4][kSkinnyRows][17];
+    __shared__ int s_last;
     int step_use = u0 % ns, tile = u0 / ns;
     long first = (long)tile * ns;                          // first unit of the tile
 #pragma unroll
@@ -486,7 +496,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
                     acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
                 __syncthreads();
-                unit_tile_flush<false, FOLD>(g, red, tile, first, ns, U, P, tile_end, nullptr, s_scale);
+                unit_tile_flush<RESID, FOLD>(g, red, tile, first, ns, U, P, tile_end, &s_last, s_scale);
                 __syncthreads();
             }
             if (tile_end) { ++tile; first += ns; }
@@ -1349,6 +1359,23 @@ static int gemm_stream_grid(int tiles, int K) {
 static int gemm_stream_slots(int tiles, int K) {
     return gemm_slots_of(tiles, K / kSkinnyStepK, gemm_stream_grid(tiles, K));
 }
+// Whether the down projection of up to 16 rows runs on the unit kernel, its tiles finished by the last block to arrive, and not on
+// the column kernel: a property of the model, since each has a layout of its own.  A column block walks all of K beside all of its
+// activations: from 257 strips of 16 columns on some CUs have two such walks one after the other; and a long one, where all strips
+// together are little to read, leaves HBM waiting.  Measured, two layers, us, column / unit (1, 8, 9, 16 rows): d_model 4096, d_ffn
+// 11008 217 / 220, 226 / 233, 238 / 241, 241 / 246; 4608, 12288 282 / 263, 287 / 277, 309 / 290, 306 / 290; 6144, 16384 393 / 380,
+// 402 / 391, 435 / 408, 433 / 414; 8192, 28672 694 / 687, 713 / 703, 757 / 725, 761 / 724; 2048, 16384 170 / 162, 174 / 176, 193 / 189,
+// 186 / 192; 4096, 28672 351 / 349, 365 / 367, 383 / 379, 383 / 392; 3584, 18944 255 / 252, 262 / 272, 279 / 279, 279 / 278; few tiles make
+// many arrivals at each: 1024, 11008 122 / 123, 130 / 143, 141 / 154, 137 / 164.
+bool gemm_down_by_units(int d_model, int d_ffn) { return d_model > 16 * kStreamBlocks / 2 || (d_ffn >= 16384 && d_ffn >= 7 * d_model); }
+
+// grid of the unit kernel with the residual epilogue: one block per CU, so that few blocks share a tile (the last of them to arrive
+// adds their partials).  512 blocks, us as above: 6144, 16384 379, 397, 413, 421; 4608, 12288 265, 280, 297, 305.
+static int gemm_resid_grid(int tiles, int K) {
+    const long U = (long)tiles * (K / kSkinnyStepK);
+    return (int)(U < kStreamBlocks / 2 ? (U < 1 ? 1 : U) : kStreamBlocks / 2);
+}
+int gemm_resid_slots(int tiles, int K) { return gemm_slots_of(tiles, K / kSkinnyStepK, gemm_resid_grid(tiles, K)); }
 // largest number of blocks that share one tile, i.e. partial slots per output element
 static int gemm_slots_of(int tiles, int units_per_tile, int grid) {
     const long ns = units_per_tile, U = (long)tiles * ns, P = grid;
@@ -1459,6 +1486,13 @@ void launch_gemm(int dtype, const GemmArgs &args, hipStream_t stream) {
             launch_kernel(gemm_w4_unit_kernel<false>, grid, 256, 0, stream, g);
         return;
     }
+    if (g.M <= kStreamMaxRows && g.wpack && g.x_resid && g.tile_counter) {
+        ScopedProf sp(PSD_KIND_GEMM_COLUMN, stream);
+        const int grid = gemm_resid_grid(g.pack_tiles, g.K);
+        if (g.op_folded) launch_kernel(gemm_bf16_unit_kernel<true, true>, grid, 256, 0, stream, g);
+        else launch_kernel(gemm_bf16_unit_kernel<false, true>, grid, 256, 0, stream, g);
+        return;
+    }
     if (g.M <= kStreamMaxRows && g.wpack && g.x_resid) {
         ScopedProf sp(PSD_KIND_GEMM_COLUMN, stream);
         const int grid = g.N / 16;                        // every segment is a multiple of 64 wide
@@ -1470,8 +1504,8 @@ void launch_gemm(int dtype, const GemmArgs &args, hipStream_t stream) {
         ScopedProf sp(PSD_KIND_GEMM_SKINNY, stream);
         const int grid = g.whole ? (g.pack_tiles < kStreamBlocks ? g.pack_tiles : kStreamBlocks) : gemm_stream_grid(g.pack_tiles, g.K);
         auto go = [&](auto kernel) { launch_kernel(kernel, grid, 256, 0, stream, g); };
-        if (g.op_folded) go(gemm_bf16_unit_kernel<true>);
-        else go(gemm_bf16_unit_kernel<false>);
+        if (g.op_folded) go(gemm_bf16_unit_kernel<true, false>);
+        else go(gemm_bf16_unit_kernel<false, false>);
     } else if (g.M <= kStreamMaxRows) {
         ScopedProf sp(PSD_KIND_GEMM_SLOT, stream);
         dim3 grid(tiles_of(g.n, g.nseg, kSkinnyRows), g.splitk);

@@ -79,15 +79,15 @@ struct GemmArgs {
     // rmsnorm(x) W^T = r_m * ((x * gain) W^T) with r_m = rsqrt(mean_k x[m][k]^2 + eps).  A projection with x_resid
     // set adds its output into the residual stream x_resid [M][N], writes
     // xg_op[m][n] = x_resid[m][n] * gain[n] (the operand of the next projection, in operand order; gain = the next norm's)
-    // and sumsq_out[strip or tile][m] = sum of x_resid[m][n]^2 over the 16 (column kernel) or 64 (4-bit projections)
+    // and sumsq_out[strip or tile][m] = sum of x_resid[m][n]^2 over the 16 (column kernel) or 64 (with tile_counter)
     // columns one block finishes; the consumer of the next projection's output multiplies by r_m (RowScale).
     float *x_resid;
     uint16_t *xg_op;              // NULL: nobody reads it
     uint16_t *xg16_out;           // optional: the same rounded to fp16, row-major (the operand of the 4-bit projections)
     const void *gain;             // [N] bf16
-    float *sumsq_out;             // [N/16][M] (column kernel) or [N/64][M] (4-bit)
-    unsigned *tile_counter;       // 4-bit projections with a residual epilogue: [N/64] arrival counters, zero before the
-                                  //   launch and left at zero by it
+    float *sumsq_out;             // [N/16][M] (column kernel) or [N/64][M] (with tile_counter)
+    unsigned *tile_counter;       // non-NULL: by tiles of 64 columns that several blocks share and the last to arrive finishes (4-bit, unit
+                                  //   kernel): [N/64] arrival counters, zero before the launch and left at zero by it
     // -- 4-bit weights (W4A16, groups of 128 along K): wpack holds the 4-bit quad layout of
     // launch_gemm_pack_w4; the projection writes `splitk` partial slots (gemm_w4_slots)
     const void *w4_scale[3], *w4_zero[3];   // M > kStreamMaxRows: w[] are the codes [n][K/2], these the bf16 scales and uint8 zero points [n][K/128]
@@ -117,8 +117,10 @@ int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, boo
 int gemm_pack_tiles(const int *n, int nseg);
 size_t gemm_pack_bytes(const int *n, int nseg, int K);
 int gemm_w4_slots(int K, const int *n, int nseg, bool resid);  // partial slots of a 4-bit projection (resid: the arrival epilogue's grid)
+bool gemm_down_by_units(int d_model, int d_ffn);          // bf16, packed: the down projection runs with tile_counter, on unit-major weights
+int gemm_resid_slots(int tiles, int K);                  // ... its partial slots
 int gemm_packed_splits(int K, const int *n, int nseg);   // partial slots (the splitk to use) with packed weights
-// strip_major: the layout of the column kernel (O and down)
+// strip_major: the layout of the column kernel
 void launch_gemm_pack(const void *const *w, const int *n, int nseg, int K, void *dst, bool strip_major, hipStream_t stream);
 // 4-bit weight-only quantised projections: q [n][K/2] bytes (low nibble = even k), scale bf16 [n][K/128],
 // zero u8 [n][K/128]; w = scale * (q - zero).  Each n[s] a multiple of 64.

@@ -200,6 +200,20 @@ def test_operand_order_activations(d_model, d_ffn, n_new):
     p.close()
 
 
+@pytest.mark.parametrize("n_new", [1, 8, 9, 16])
+@pytest.mark.parametrize("d_model,d_ffn", [(4224, 128), (4224, 1152), (128, 16384)])
+def test_down_projection_by_units(d_model, d_ffn, n_new):
+    """The down projection of wide models, and of a d_ffn seven times as long, on the unit kernel: every tile by one block (66 tiles of
+    one K step), shared unevenly (66 of 9 steps by 256 blocks), and by 128 blocks each (2 of 128); folded (8 rows) and not.  The
+    second step finds the arrival counters as the first left them."""
+    shape = synth.Shape(2, d_model, 2, 2, 64, d_ffn, 200, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 128, seed=n_new, ctx=40, std=0.02 if d_ffn > 8192 else 0.05, pack=True)
+    toks = synth.make_tokens(shape.vocab, (1, 2 * n_new), d_ffn)
+    p.step(toks[:, :n_new], what="all rows' logits")
+    p.step(toks[:, n_new:], n_logit_rows=1, what="the last row's")
+    p.close()
+
+
 @pytest.mark.parametrize("shape,n_new,ctx", [
     (SMALL_GQA, 1, 300), (SMALL_GQA, 5, 200), (SMALL_GQA, 8, 300), (SMALL_GQA, 9, 1000), (SMALL_GQA, 17, 129), (SMALL_GQA, 40, 64),
     (SMALL_MHA, 8, 1024), (SMALL_MHA, 11, 77), (SMALL_MHA, 70, 200), (SMALL_MHA, 130, 0), (SMALL_MHA, 200, 30),
