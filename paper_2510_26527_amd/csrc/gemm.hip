@@ -1218,11 +1218,13 @@ static int gemm_slots_of(int tiles, int units_per_tile, int grid);
 // round of whole tiles still gains (96 rows, 32000 x 4096 79.1 / 60.1, 22016 x 4096 57.8 / 53.3; 128 rows, 85.4 / 70.5, 28672 x 4096
 // 79.5 / 68.7), more rounds (128 x 152064 x 3584 266 / 281), shared tiles (128 x 12288 x 4096 43.8 / 45.7), ten wavefronts, whose
 // registers spill (two layers and head of the Qwen2-7B shape, 88 rows 631 / 641), or, above 96 rows, six (128 x 22016 x 4096 with
-// SwiGLU 67.6 / 66.9, two layers of the 7B shape 494 / 506) do not.
+// SwiGLU 67.6 / 66.9, two layers of the 7B shape 494 / 506) do not; nor do products of fewer than six K steps, most of whose time is the
+// outputs, here in pieces of 64 bytes (a layer and head 32000 x 512, 96 rows 77.5 / 80.6, 128 rows 79.9 / 85.1; 32000 x 768 102.5 / 93.2).
 RowsPlan gemm_rows_plan(int M, int K, const int *n, int nseg, bool gated) {
     RowsPlan p{};
     if (M <= kStreamMaxRows || M > kRowsMax) return p;
     const int ns = K / kSkinnyStepK;
+    if (M > 64 && !gated && ns < 6) return p;
     double best = 0.85;
     for (int nw : {8, 6, 10}) {
         const int tiles = gated ? (n[0] + 8 * nw - 1) / (8 * nw) : tiles_of(n, nseg, 16 * nw);
