@@ -72,10 +72,11 @@ def test_draw_chunk_edges(rows, gamma, V, dtype):
 
 @pytest.mark.parametrize("rows,gamma,V,dtype", [
     (64, 1, 28672, torch.bfloat16), (64, 1, 28673, torch.float32), (40, 1, 65536, torch.float32), (40, 1, 65537, torch.bfloat16),
-    (130, 1, 24584, torch.float32), (96, 1, 65544, torch.bfloat16)])
+    (130, 1, 24584, torch.float32), (96, 1, 65544, torch.bfloat16), (96, 1, 57352, torch.bfloat16), (128, 1, 65536, torch.float32)])
 def test_draw_quarters(rows, gamma, V, dtype):
     """The sums of a chunk's quarters kept one by one: whole chunks of 4096, a last chunk of one entry (three empty quarters), 64
-    quarters and one chunk more (no quarters), chunks of 8192 with a short last one; draws that take each path at random."""
+    quarters and one chunk more (no quarters), chunks of 4096 with a short last one, of 8192 without quarters (65544: unaligned rows
+    would need 68), of 8192 with a last one of 8 entries (57352) and whole ones (65536); draws that take each path at random."""
     _compare(synth.make_accept_inputs(rows, gamma, V, seed=V + rows, n_p_rows=gamma + 1, dtype=dtype))
 
 

@@ -125,6 +125,15 @@ def test_fp32_batch_with_ragged_lengths_and_truncate():
     p.close()
 
 
+def step_launches(p, *args, **kwargs):
+    """One checked step, and how often each kind of kernel was launched: which path a call took."""
+    psd.psd_profile_enable(1000)
+    p.step(*args, **kwargs)
+    counts = {kind: n for kind, (_, n) in psd.psd_profile_collect().items()}
+    psd.psd_profile_enable(0)
+    return counts
+
+
 SMALL_GQA = synth.Shape(2, 256, 4, 2, 64, 512, 1024, 1.0e4)           # d_head 64, group 2
 SMALL_MHA = synth.Shape(2, 256, 2, 2, 128, 384, 1000, 1.0e4)          # d_head 128, ragged vocab tiles
 SMALL_G7 = synth.Shape(1, 896, 7, 1, 128, 1152, 2048, 1.0e6)          # Qwen2-like group of 7
@@ -137,7 +146,8 @@ def test_head_in_whole_tiles(d_model, batch, n_new, rows):
     (d_model 4224)."""
     shape = synth.Shape(1, d_model, d_model // 64, d_model // 64, 64, 128, 29505, 1.0e4)
     p = Pair(shape, torch.bfloat16, batch, 64, seed=n_new, ctx=9, std=0.05, pack=True)
-    p.step(synth.make_tokens(shape.vocab, (batch, n_new), d_model), n_logit_rows=rows, what="the last rows' logits")
+    ran = step_launches(p, synth.make_tokens(shape.vocab, (batch, n_new), d_model), n_logit_rows=rows, what="the last rows' logits")
+    assert ran["gemm_reduce"] == 0 and ran["lens"] == 0
     assert p.kv.lens.cpu().tolist() == [9 + n_new] * batch
     p.close()
 
@@ -166,12 +176,39 @@ def test_staged_attention_in_operand_order(d_head):
 @pytest.mark.parametrize("n_new", [17, 33, 64, 65, 97, 128])
 @pytest.mark.parametrize("d_model,d_ffn,vocab", [(128, 11008, 28001), (128, 14336, 40960), (384, 18944, 512), (1024, 512, 41600)])
 def test_rows_kernel(d_model, d_ffn, vocab, n_new):
-    """17 to 128 rows on packed weights, every number of 16-row tiles (2, 3, 4, 6, 8) at one of its edges: heads in whole tiles of 8
-    strips with a ragged last one (28001), of 10 (40960) and in shared tiles (41600 at K = 1024); gate | up with its SwiGLU in
-    whole tiles of 6 strips, the last one half there (11008), of 8 (14336) and of 10 (18944); one K step and several."""
+    """17 to 128 rows on packed weights, every number of 16-row tiles (2, 3, 4, 6, 8) at one of its edges: gate | up with its SwiGLU in
+    whole tiles of 6 strips, the last one half there (11008), of 8 (14336) and of 10 (18944; 65 rows and more: LDS-tiled); up to 64
+    rows heads in whole tiles of 8 strips with a ragged last one (28001), of 10 (40960) and in shared tiles (41600 at K = 1024); one K
+    step and three, so that a block is through before its ring of four steps turns."""
     shape = synth.Shape(1, d_model, d_model // 64, d_model // 64, 64, d_ffn, vocab, 1.0e4)
     p = Pair(shape, torch.bfloat16, 1, 192, seed=n_new, ctx=20, std=0.05, pack=True)
-    p.step(synth.make_tokens(shape.vocab, (1, n_new), d_ffn), what="all rows' logits")
+    ran = step_launches(p, synth.make_tokens(shape.vocab, (1, n_new), d_ffn), what="all rows' logits")
+    most = {11008: 96, 14336: 128, 18944: 64, 512: 0}[d_ffn]              # rows up to which gate | up is in whole tiles
+    assert ran["swiglu"] == (0 if n_new <= most else 1)
+    if n_new <= 64 and vocab > 512:
+        assert ran["gemm_reduce"] == (1 if vocab == 41600 else 0)
+    p.close()
+
+
+@pytest.mark.parametrize("d_model,d_ffn,vocab,n_new", [
+    (1024, 11008, 28001, 17), (1024, 11008, 28001, 65), (1024, 11008, 28001, 96), (1024, 14336, 32000, 65), (1024, 14336, 32000, 128),
+    (1024, 18944, 40960, 33), (1024, 18944, 40960, 64), (128, 28672, 512, 45), (1024, 28672, 128256, 17), (1024, 28672, 128256, 64)])
+def test_rows_kernel_walks_its_ring(d_model, d_ffn, vocab, n_new):
+    """Eight K steps and more: a block's ring of four steps turns, for 6, 8 and 10 strips, gate | up and head, and 2 to 8 row tiles; and
+    blocks of several whole tiles, the next one requested while this one is multiplied: two of gate | up (28672, of one K step and of
+    eight), four of a head (128256)."""
+    shape = synth.Shape(1, d_model, d_model // 64, d_model // 64, 64, d_ffn, vocab, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 192, seed=n_new, ctx=20, std=0.02, pack=True)
+    ran = step_launches(p, synth.make_tokens(shape.vocab, (1, n_new), d_ffn), what="all rows' logits")
+    assert ran["swiglu"] == 0 and (vocab == 512 or ran["gemm_reduce"] == 0)
+    p.close()
+
+
+def test_rows_kernel_shares_tiles_of_three_segments():
+    """Q, K and V of 33 tiles each, shared by all blocks: a block goes on from one segment to the next in the middle of its range."""
+    shape = synth.Shape(1, 4224, 66, 66, 64, 128, 200, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 128, seed=4, ctx=20, std=0.02, pack=True)
+    p.step(synth.make_tokens(shape.vocab, (1, 50), 6), what="50 rows")
     p.close()
 
 
@@ -182,7 +219,8 @@ def test_tiles_of_two_widths(heads, vocab, n_new, rows):
     its factors in bf16, moves its probability by 4 std^2 d_model 2^-9: 0.6 % at 0.02, 4 % at 0.05, past the tolerance."""
     shape = synth.Shape(1, 2048, heads, heads, 128, 128, vocab, 1.0e4)
     p = Pair(shape, torch.bfloat16, 1, 2304, seed=n_new, ctx=0, std=0.02)
-    p.step(synth.make_tokens(shape.vocab, (1, n_new), heads), n_logit_rows=rows, what="the logits")
+    ran = step_launches(p, synth.make_tokens(shape.vocab, (1, n_new), heads), n_logit_rows=rows, what="the logits")
+    assert ran["gemm_tiled"] == (6 if rows > 1 else 5)          # four projections, the long pass' head, and one launch more
     p.close()
 
 
