@@ -1,8 +1,8 @@
 // Verify attention on gfx950: the n_new query rows of a verify step against the model's KV
 // cache, causal among the new rows, grouped-query heads sharing their K/V loads.
 //
-//   attn_simple_kernel   any dtype, one wavefront per (sequence, row, head): scores to LDS,
-//                        softmax, then P.V.  Used by fp32 models (parity, not speed).
+//   attn_simple_kernel   fp32 models, one wavefront per (sequence, row, head): scores to LDS,
+//                        softmax, then P.V (parity, not speed).
 //   attn_mfma_kernel     bf16.  Split over the KV length (grid.x) and, inside a block, over its
 //                        four wavefronts; each wavefront streams 64-key tiles of K and of the
 //                        transposed V straight from HBM into MFMA operand registers with
@@ -36,7 +36,6 @@
 namespace psd {
 namespace {
 
-template <typename TC>
 __global__ __launch_bounds__(64) void attn_simple_kernel(AttnArgs a, float scale) {
     extern __shared__ float sc[];
     const int lane = threadIdx.x;
@@ -45,12 +44,12 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(AttnArgs a, float scale
     const int n_keys = min(a.lens[b] + r + 1, a.max_len);
     const int hk = h / (a.h_q / a.h_kv);
     const float *q = a.q + ((size_t)m * a.h_q + h) * d_h;
-    const TC *K = (const TC *)a.k + ((size_t)b * a.h_kv + hk) * a.max_len * d_h;
-    const TC *Vt = (const TC *)a.v + ((size_t)b * a.h_kv + hk) * d_h * (size_t)a.max_len;
+    const float *K = (const float *)a.k + ((size_t)b * a.h_kv + hk) * a.max_len * d_h;
+    const float *Vt = (const float *)a.v + ((size_t)b * a.h_kv + hk) * d_h * (size_t)a.max_len;
     float mx = -INFINITY;
     for (int k = lane; k < n_keys; k += 64) {
         float s = 0.f;
-        for (int d = 0; d < d_h; ++d) s += q[d] * load_elem(K, (size_t)k * d_h + d);
+        for (int d = 0; d < d_h; ++d) s += q[d] * K[(size_t)k * d_h + d];
         s *= scale;
         sc[k] = s;
         mx = fmaxf(mx, s);
@@ -67,7 +66,7 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(AttnArgs a, float scale
     float *out = a.out + ((size_t)m * a.h_q + h) * d_h;
     for (int d = lane; d < d_h; d += 64) {
         float acc = 0.f;
-        for (int k = 0; k < n_keys; ++k) acc += sc[k] * load_elem(Vt, (size_t)d * a.max_len + k);
+        for (int k = 0; k < n_keys; ++k) acc += sc[k] * Vt[(size_t)d * a.max_len + k];
         out[d] = acc / sum;
     }
 }
@@ -1007,8 +1006,7 @@ void launch_attention(int dtype, const AttnArgs &a, hipStream_t stream) {
     dim3 grid(a.h_q, a.B * a.R);
     const size_t smem = (size_t)a.len_bound * sizeof(float);
     ScopedProf sp(PSD_KIND_ATTN, stream);
-    if (dtype == PSD_BF16) launch_kernel(attn_simple_kernel<uint16_t>, grid, 64, smem, stream, a, scale);
-    else launch_kernel(attn_simple_kernel<float>, grid, 64, smem, stream, a, scale);
+    launch_kernel(attn_simple_kernel, grid, 64, smem, stream, a, scale);       // (bf16 models have a d_head of 64 or 128)
 }
 
 }  // namespace psd

@@ -776,7 +776,7 @@ __global__ __launch_bounds__(256) void gemm_w4_unit_kernel(GemmArgs g) {
 // ------------------------------------------------------------------------------ bf16 rows kernel (17 to 128 rows, packed weights)
 // Between the unit kernel and the tiled one: the weights go from the packed copy straight into MFMA operands, a strip of 16
 // rows of W per wavefront and 128 k a step, R steps in flight, and become fp16 (exactly) in registers; the fp16 activations, MT
-// tiles of 16 rows, are what a block's eight wavefronts share and go through LDS, one barrier a step.  They travel
+// tiles of 16 rows, are what a block's wavefronts share and go through LDS, one barrier a step.  They travel
 // one step ahead of the weights, so that in the in-order return queue they never wait for them.  NW wavefronts = strips make a tile of
 // 16 NW columns.  The grid is one block per CU; block b takes whole tiles (whole) or, where no tile width fills the chip with
 // whole ones, an equal range of the product's steps.  gated: whole tiles of NW / 2 gate and as many up strips, whose products
