@@ -31,7 +31,7 @@ def weight_stream_bytes(shape):
 
 def stream_kernel_bytes(shape):
     """The share of weight_stream_bytes read by gemm_bf16_unit_kernel: the QKV, gate|up and lm_head
-    projections (O and down run on the column kernel)."""
+    projections (O and down run on the column kernel in this shape)."""
     s = shape
     hd, kvd = s.n_q_heads * s.d_head, s.n_kv_heads * s.d_head
     return 2 * (s.n_layers * (s.d_model * (hd + 2 * kvd) + 2 * s.d_model * s.d_ffn) + s.vocab * s.d_model)
@@ -664,8 +664,8 @@ def chain_cpu_baseline(g, levels, weights, n_prompt, max_len):
 def sweep_workload(args, dev):
     """The four projections of LLaMA2-7B-shaped layers (plus a 32000-row lm_head) at M = 8 ... 4096 rows: one
     forward of a two-layer model per M on an empty cache; GEMM time from the per-launch timers.  Up to 16 rows
-    the projections stream the weights (HBM-bound, GB/s), up to 128 those but O and down do; above, they run on the
-    LDS-tiled MFMA kernel (TFLOP/s)."""
+    the projections stream the weights (HBM-bound, GB/s), up to 64 those but O and down do, up to 96 gate|up and lm_head, up to
+    128 lm_head alone; the others run on the LDS-tiled MFMA kernel (TFLOP/s)."""
     import torch
     import paper_2510_26527_amd as psd
     from paper_2510_26527_amd import runtime, synth
@@ -699,7 +699,10 @@ def sweep_workload(args, dev):
                      "frac_of_bf16_mfma_peak": flops / (g_ms * 1e-3) / 2.5e15,
                      "weight_GB/s": 2.0 * params / (g_ms * 1e-3) / 1e9,
                      "frac_of_hbm_peak": 2.0 * params / (g_ms * 1e-3) / 8e12,
-                     "kernel": "weight streaming" if M <= 16 else "weight streaming (O, down: LDS-tiled)" if M <= 128 else "LDS-tiled MFMA"})
+                     "kernel": next(label for most, label in ((16, "weight streaming"), (64, "weight streaming (O, down: LDS-tiled)"),
+                                                              (96, "gate|up, lm_head: weight streaming; else LDS-tiled"),
+                                                              (128, "lm_head: weight streaming; else LDS-tiled"),
+                                                              (M, "LDS-tiled MFMA")) if M <= most)})
         kv.close()
         del logits
     print(json.dumps({"metric": "projection GEMMs of a LLaMA2-7B-shaped layer over M", "unit": "TFLOP/s and GB/s",
