@@ -208,17 +208,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
 #pragma unroll
                         for (int tt = 0; tt < 4; ++tt) ssq += r < 4 ? raw[0][tt] : raw[1][tt];
                     } else {
-                        // four requested at a time (one: two blocks per CU cover for each other, and registers spill).  9 rows,
-                        // 256 sums each, us a launch, one / four: 16.8 / 16.1 (64 sums, by one: 15.2).
-                        constexpr int C = NSUB == 1 ? 1 : 4;
-                        for (int t0 = lane; t0 < a.rs.tiles; t0 += 64 * C) {
-                            float v[C];
-#pragma unroll
-                            for (int tt = 0; tt < C; ++tt)
-                                v[tt] = t0 + 64 * tt < a.rs.tiles ? a.rs.sumsq[(size_t)(t0 + 64 * tt) * (a.B * a.R) + b * a.R + r] : 0.f;
-#pragma unroll
-                            for (int tt = 0; tt < C; ++tt) ssq += v[tt];
-                        }
+                        for (int t = lane; t < a.rs.tiles; t += 64) ssq += a.rs.sumsq[(size_t)t * (a.B * a.R) + b * a.R + r];
                     }
                     sc = 1.0f / sqrtf(wave_sum(ssq) * a.rs.inv_d + a.rs.eps);
                 }
