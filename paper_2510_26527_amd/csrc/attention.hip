@@ -518,7 +518,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
     // ---- write: directly when there is one split, else the unnormalised partial.  One thread per query row works
     // out where the row goes and how its slabs combine; the element loop then only multiplies and adds.
     __shared__ float s_f[NSLAB][QT * 16], s_M[QT * 16], s_L[QT * 16];
-    __shared__ int s_row[QT * 16], s_op[QT * 16];      // where the row goes: in row-major outputs, in operand order
+    __shared__ int s_row[QT * 16];
     if (threadIdx.x < QT * 16) {
         const int qc = threadIdx.x;
         const int qi = qchunk * QT * 16 + qc;
@@ -526,7 +526,6 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
         if (qi < NQ) {
             const int hl = qi / a.R, r = qi % a.R;
             row = (b * a.R + r) * a.h_q + hk * group + hl;                           // [B][R][h_q]
-            if (a.out_op) s_op[qc] = (int)op_at(b * a.R + r, (hk * group + hl) * DH, a.op_folded);
         }
         float M = sm_m[0][qc];
 #pragma unroll
@@ -553,7 +552,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
             const float L = s_L[qc];
             if (a.out) a.out[row * DH + d] = acc / L;
             if (a.out16) a.out16[row * DH + d] = f32_to_f16_bits(acc / L);
-            if (a.out_op) op_store(a.out_op + s_op[qc], 0, d, a.op_folded, acc / L);      // (a head starts on a multiple of 64)
+            if (a.out_op) op_store(a.out_op, (int)(row / a.h_q), (int)(row % a.h_q) * DH + d, a.op_folded, acc / L);
         } else {
             a.part_o[(row * a.splits + split) * DH + d] = acc;
             if (d == 0) {

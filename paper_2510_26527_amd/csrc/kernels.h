@@ -139,6 +139,8 @@ struct AttnArgs {
     const int32_t *lens;          // [B] valid positions BEFORE this forward
     float *out;                   // [B][R][h_q*d_h] fp32; NULL where only the next one is read
     uint16_t *out16;              // optional: the same rounded to fp16 (the operand of the tiled and the 4-bit O projection)
+    uint16_t *out_op;             // optional: the same in operand order (common.h; the operand of the packed O projection)
+    bool op_folded;
     int B, R, h_q, h_kv, d_h, max_len;
     int len_bound;                // host upper bound of lens[b] + R
     float *part_o;                // split scratch [B][h_q][R][splits][d_h]
@@ -155,8 +157,6 @@ struct AttnArgs {
     // Token tree (fused build only): tree_anc[r] has bit j set when row j of the step is row r itself or one of its
     // ancestors; row r then sees the cache and exactly those rows.  NULL: rows see the rows before them.
     const uint32_t *tree_anc;
-    uint16_t *out_op;             // optional: `out` in operand order (common.h; the operand of the packed O projection)
-    bool op_folded;
 };
 // whether launch_attention builds its operands itself for this shape (then no rotation / append kernel runs before it)
 bool attn_fuses_rope(int dtype, int R, int h_q, int h_kv, int d_h, bool tree);
