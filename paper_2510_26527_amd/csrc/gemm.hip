@@ -396,10 +396,10 @@ __device__ __forceinline__ void unit_tile_flush(const GemmArgs &g, const float (
 // sumsq_out[tile][m].  It leaves the counter at zero for the next launch.  No block waits for another.
 //
 // Activations: in operand order, two fragments or (folded) one a quarter.  Row-major, as fp32 split here, every lane's 16 bytes come
-// out of another line, and at 16 rows they cost the vector memory path twice what the weights do.  Measured, QKV, gate|up and head of the 7B shape averaged
-// (us a launch; row-major and two stages in an order of the compiler's / this): 1 row 28.3 / 26.9, 8 rows 28.9 / 27.2, 9 rows
-// 29.2 / 27.7, 16 rows 30.8 (two tiles at a time) / 29.7; plain reads of the same weights 25.4.  Two tiles at a time, which
-// share a K step's activations, gain nothing any more (16 rows 30.6), nor does a fourth stage.
+// out of another line, and at 16 rows they cost the vector memory path twice what the weights do.  Measured, QKV, gate|up and head of
+// the 32-layer 7B shape averaged (us a launch; row-major and two stages in an order of the compiler's / this): 1 row 24.0 / 23.6, 8 rows
+// 25.1 / 24.7, 9 rows 25.5 / 25.2, 16 rows 27.2 (two tiles at a time) / 26.4; plain reads of the same weights 22.1.  Two tiles at a time,
+// which share a K step's activations, gain nothing in operand order (two layers and head, 16 rows 30.6 / 29.7), nor does a fourth stage.
 template <bool FOLD, bool RESID>
 __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
     constexpr int R = 3, XV = FOLD ? 1 : 2;                // units in flight per wavefront (its 4 KB of each)
@@ -516,11 +516,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
 // range and a wavefront a contiguous part of it.
 // What bounds it: the block reads all activations, at 16 rows twice as many bytes as weights, so how they are read decides.  They
 // come in operand order, whole 1 KB pieces, D quarters at a time and ahead of these quarters' weights: the weights, which come
-// from farther, are then not waited for twice.  Measured, O and down of the 7B shape averaged (us a launch; O so on row-major
+// from farther, are then not waited for twice.  Measured, O and down of the 32-layer 7B shape averaged (us a launch; O so on row-major
 // activations and down on the unit kernel with the residual epilogue by the last block to arrive at a tile / this): 1 row
-// 14.4 / 13.9, 8 rows 16.5 / 13.4, 9 rows 17.2 / 15.8, 15 rows 19.9 / 16.8; plain reads 10.8.  Weights and activations in turn
+// 14.1 / 13.1, 8 rows 16.3 / 13.4, 9 rows 17.2 / 15.9, 16 rows 20.2 / 16.2; plain reads 10.7.  Weights and activations in turn
 // 18.2 at 15 rows; a ring of quarters that is refilled one by one 19.7, most of it for its loads past the end, which cost
-// like any other though they touch no memory.
+// like any other though they touch no memory.  How many quarters at a time hardly matters: 8, 10, 11, 12 or 13 folded and 6 to 9 not are
+// within 0.3 us of each other at 1, 8, 9 and 16 rows of 1024 x 4096, 2048 x 5632, 3584 x 18944 and 4096 x 4096, 11008 and 14336; these
+// leave no spills at 1024 threads (128 registers).
 constexpr int kStripVec = 16 * kSkinnyStepK * 2 / 16;   // 16-byte vectors per (strip, step)
 
 __global__ __launch_bounds__(256) void gemm_pack_strip_kernel(const uint16_t *W, int N, int K, u32x4 *dst) {
