@@ -289,7 +289,7 @@ psd_status psd_kv_compact_tree(psd_kv *kv, const int32_t *base_lens_dev, const i
 #define PSD_KIND_EMBED 0
 #define PSD_KIND_RMSNORM 1
 #define PSD_KIND_GEMM_F32 2
-#define PSD_KIND_GEMM_SKINNY 3       /* bf16 weight-streaming GEMM over packed 16 KB units, M <= 16 (heads in whole tiles: with their epilogue) */
+#define PSD_KIND_GEMM_SKINNY 3       /* bf16 weight-streaming GEMM over packed 16 KB units, M <= 16: by 16 KB units, or QKV and gate|up by bands (gate|up with SwiGLU; heads in whole tiles with their epilogue) */
 #define PSD_KIND_GEMM_TILED 4        /* GEMM of bf16 models with fp16 MFMA, M > 16: LDS-tiled, or (packed, M <= 128) on streamed units */
 #define PSD_KIND_GEMM_REDUCE 5       /* split-K reduction */
 #define PSD_KIND_ROPE_APPEND 6

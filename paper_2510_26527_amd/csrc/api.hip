@@ -157,16 +157,16 @@ static void pack_layout(const psd_model *m, std::vector<size_t> *off, size_t *to
     const int n_qkv[3] = {hd, kvd, kvd}, n_o[1] = {d.d_model}, n_gu[2] = {d.d_ffn, d.d_ffn}, n_v[1] = {d.vocab};
     size_t at = 0;
     off->clear();
-    auto bytes = [&](const int *n, int nseg, int K) {
-        return align256(m->w4 ? gemm_pack_w4_bytes(n, nseg, K) : gemm_pack_bytes(n, nseg, K));
+    auto bytes = [&](const int *n, int nseg, int K, GemmBands b = kUnitBands) {
+        return align256(m->w4 ? gemm_pack_w4_bytes(n, nseg, K) : gemm_pack_bytes(n, nseg, K, b));
     };
     for (int l = 0; l < d.n_layers; ++l) {
-        off->push_back(at); at += bytes(n_qkv, 3, d.d_model);
+        off->push_back(at); at += bytes(n_qkv, 3, d.d_model, gemm_qkv_bands(n_qkv));
         off->push_back(at); at += bytes(n_o, 1, hd);
-        off->push_back(at); at += bytes(n_gu, 2, d.d_model);
+        off->push_back(at); at += bytes(n_gu, 2, d.d_model, gemm_gate_bands(d.d_ffn));
         off->push_back(at); at += bytes(n_o, 1, d.d_ffn);
     }
-    off->push_back(at); at += gemm_pack_bytes(n_v, 1, d.d_model);
+    off->push_back(at); at += gemm_pack_bytes(n_v, 1, d.d_model, kUnitBands);
     *total = at;
 }
 
@@ -207,19 +207,20 @@ psd_status psd_model_pack(psd_model *m, void *packed_mem, size_t packed_bytes, v
     for (int l = 0; l < d.n_layers && !m->w4; ++l) {
         const void *qkv[3] = {m->layer(l, W_Q), m->layer(l, W_K), m->layer(l, W_V)};
         const int n_qkv[3] = {hd, kvd, kvd};
-        launch_gemm_pack(qkv, n_qkv, 3, d.d_model, base + off[4 * l + P_QKV], false, st);
+        launch_gemm_pack(qkv, n_qkv, 3, d.d_model, base + off[4 * l + P_QKV], gemm_qkv_bands(n_qkv), st);
         const void *o[1] = {m->layer(l, W_O)};
         const int n_o[1] = {d.d_model};
-        launch_gemm_pack(o, n_o, 1, hd, base + off[4 * l + P_O], true, st);
+        launch_gemm_pack_strips(o[0], d.d_model, hd, base + off[4 * l + P_O], st);
         const void *gu[2] = {m->layer(l, W_GATE), m->layer(l, W_UP)};
         const int n_gu[2] = {d.d_ffn, d.d_ffn};
-        launch_gemm_pack(gu, n_gu, 2, d.d_model, base + off[4 * l + P_GU], false, st);
+        launch_gemm_pack(gu, n_gu, 2, d.d_model, base + off[4 * l + P_GU], gemm_gate_bands(d.d_ffn), st);
         const void *dn[1] = {m->layer(l, W_DOWN)};
-        launch_gemm_pack(dn, n_o, 1, d.d_ffn, base + off[4 * l + P_DOWN], !gemm_down_by_units(d.d_model, d.d_ffn), st);
+        if (gemm_down_by_units(d.d_model, d.d_ffn)) launch_gemm_pack(dn, n_o, 1, d.d_ffn, base + off[4 * l + P_DOWN], kUnitBands, st);
+        else launch_gemm_pack_strips(dn[0], d.d_model, d.d_ffn, base + off[4 * l + P_DOWN], st);
     }
     const void *hw[1] = {m->lm_head()};
     const int n_v[1] = {d.vocab};
-    launch_gemm_pack(hw, n_v, 1, d.d_model, base + off[4 * d.n_layers], false, st);
+    launch_gemm_pack(hw, n_v, 1, d.d_model, base + off[4 * d.n_layers], kUnitBands, st);
     const psd_status s = check_launch();
     if (s == PSD_OK) {
         m->packed = base;
@@ -270,7 +271,7 @@ struct ForwardPlan {
     bool folded;                  // RMSNorm folded into the projections (bf16, packed weights, M <= kStreamMaxRows)
     bool fused_rope;              // the attention kernel reduces, rotates and appends q / k / v itself
     bool down_by_units;           // the folded down projection runs on the unit kernel, its tiles finished by the last block to arrive
-    bool gated;                   // bf16, M > kStreamMaxRows: the gate|up projection applies SwiGLU itself
+    bool gated;                   // bf16: the gate|up projection applies SwiGLU itself
     size_t partial_bytes;         // of the layers' projections
 };
 
@@ -292,10 +293,10 @@ ForwardPlan plan_projections(const psd_model *mdl, int M) {
     p.width_qkv = hd + 2 * kvd;
     const int n_qkv[3] = {hd, kvd, kvd}, n_o[1] = {d.d_model}, n_gu[2] = {d.d_ffn, d.d_ffn};
     p.folded = mdl->packed && d.dtype == PSD_BF16 && M <= kStreamMaxRows;
-    p.sk_qkv = proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
+    p.sk_qkv = p.folded && !mdl->w4 && gemm_qkv_bands(n_qkv).owned ? 1 : proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
     // folded: O and down run on the column kernel (one owner per output), or, 4-bit and some down, on partial slots with the arrival epilogue
     p.sk_o = p.folded ? (mdl->w4 ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false, true);
-    p.gated = d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4);
+    p.gated = p.folded ? !mdl->w4 : d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4);
     p.sk_gu = p.gated ? 1 : proj_splits(mdl, M, d.d_model, n_gu, 2, false);
     p.down_by_units = p.folded && !mdl->w4 && gemm_down_by_units(d.d_model, d.d_ffn);
     p.sk_down = p.down_by_units ? gemm_resid_slots(gemm_pack_tiles(n_o, 1), d.d_ffn)
@@ -458,6 +459,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     const bool op_folded = M <= kOpFoldRows;
     const bool arrivals = p.folded && (m->w4 || p.down_by_units);        // some tiles are finished by the last block to arrive
     unsigned *tile_ctr = arrivals ? (unsigned *)(ws + p.off_tilectr) : nullptr;
+    RowScale rs{nullptr, 0, 1.0f / (float)d.d_model, d.rms_eps};
     // ql, qj: layer and index of the first segment among the layer's 4-bit projections (q k v o gate up down), if any
     auto gemm = [&](const float *xin, int rows, int K, const void *w0, int n0, const void *w1, int n1,
                     const void *w2, int n2, int sk, float *dst, const void *wpack, int ql = -1, int qj = -1) {
@@ -470,7 +472,11 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         g.nseg = w2 ? 3 : (w1 ? 2 : 1);
         g.M = rows; g.K = K; g.N = n0 + n1 + n2; g.partial = dst; g.splitk = sk; g.reduced = nullptr;
         g.pack_tiles = gemm_pack_tiles(g.n, g.nseg);
-        if (p.gated && dst == nullptr) g.swiglu16 = h16;
+        g.bands = g.nseg == 3 ? gemm_qkv_bands(g.n) : g.nseg == 2 ? gemm_gate_bands(n0) : kUnitBands;
+        if (p.gated && dst == nullptr) {
+            if (p.folded) { g.swiglu_op = (uint16_t *)h; g.scale = rs; }
+            else g.swiglu16 = h16;
+        }
         g.w4 = m->w4 && qj >= 0;
         for (int sgm = 0; sgm < g.nseg && g.w4; ++sgm) { g.w4_scale[sgm] = m->qscale(ql, qj + sgm); g.w4_zero[sgm] = m->qzero(ql, qj + sgm); }
         launch_gemm(d.dtype, g, st);
@@ -482,7 +488,6 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     float *sumsq = (float *)(ws + p.off_sumsq);
     const int col_tiles = d.d_model / 16;
     const int n_o_fw[1] = {d.d_model};
-    RowScale rs{nullptr, 0, 1.0f / (float)d.d_model, d.rms_eps};
     if (p.folded) rs.sumsq = sumsq;
     // What the head reads in operand order: all rows of a folded pass, or, of a longer one, the up to 16 rows that get logits, one
     // behind the other, from the last norm.
@@ -499,7 +504,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
             g.M = M; g.K = K; g.N = d.d_model; g.splitk = slots ? sk : 1; g.pack_tiles = gemm_pack_tiles(g.n, 1);
             g.x_op = (const uint16_t *)xin; g.op_folded = op_folded;
             g.xg_op = m->w4 && !last ? nullptr : xn_op;   // 4-bit projections read xn16, the head xn
-            g.x_resid = x; g.xg16_out = xn16; g.gain = next_gain; g.sumsq_out = sumsq; g.w4 = m->w4;
+            g.bands = kUnitBands; g.x_resid = x; g.xg16_out = xn16; g.gain = next_gain; g.sumsq_out = sumsq; g.w4 = m->w4;
             g.x16 = xin == attn ? attn16 : (xin == h ? h16 : nullptr);
             if (slots) { g.tile_counter = tile_ctr; g.partial = partial; }
             launch_gemm(d.dtype, g, st);
@@ -547,8 +552,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         gemm(act, M, d.d_model, m->layer(l, W_GATE), d.d_ffn, m->layer(l, W_UP), d.d_ffn, nullptr, 0, p.sk_gu,
              p.gated ? nullptr : partial, m->pack(l, P_GU), l, 4);
         if (!p.gated)
-            launch_reduce_swiglu(partial, p.sk_gu, rs, p.half_copies || p.folded ? nullptr : h, M, d.d_ffn, h16,
-                                 p.folded && !p.half_copies ? (uint16_t *)h : nullptr, st);
+            launch_reduce_swiglu(partial, p.sk_gu, rs, p.half_copies ? nullptr : h, M, d.d_ffn, h16, st);
         resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), p.down_by_units, l, 6, l + 1 == d.n_layers);
     }
     bool advanced = false;                                   // the head's last kernel, the last one of its kind of pass, does it
@@ -562,6 +566,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         hg.M = B * n_logit_rows; hg.K = d.d_model; hg.N = d.vocab;
         hg.wpack = m->pack_head();
         hg.pack_tiles = gemm_pack_tiles(hg.n, 1);
+        hg.bands = kUnitBands;
         hg.splitk = p.sk_head;
         hg.whole = head_whole(m, hg.M);
         const bool two_step = !hg.whole && (p.sk_head > 1 || p.folded);

@@ -7,13 +7,15 @@
 //                            streaming: W rows go straight from global memory into MFMA A-operand registers
 //                            with 16-byte loads (no LDS), the few activation rows are the B operand, K is
 //                            split over the four wavefronts of a block and over blocks.
-//   gemm_bf16_unit_kernel    M <= 16 on weights repacked by gemm_pack_kernel: the same MFMA tiling, but every
+//   gemm_bf16_unit_kernel    M <= 16 (heads, narrow QKV) on weights repacked by gemm_pack_kernel: the same MFMA tiling, but every
 //                            16 KB unit (64 rows x 128 k) is stored in exactly the order the lanes load it,
 //                            units of a GEMM are contiguous, and the grid is persistent: each block streams
 //                            an equal, contiguous range of units (stream-K), its four wavefronts on the four
 //                            K quarters of every unit, and writes one partial per tile it touches.
 //                            With RESID (the down projection of wide models and very long ones) the block that arrives
 //                            last at a tile adds the tile's partials and runs the residual epilogue below.
+//   gemm_bf16_band_kernel    M <= 16: QKV (wide ones) and gate|up, one block per band of 16-row strips over the whole K range; gate|up with
+//                            the row scale and SwiGLU in its epilogue.
 //   gemm_bf16_rows_kernel    17 to 128 rows on the same units: the weights stream into MFMA operands as above, the
 //                            activations (fp16) go through LDS; whole tiles where they fill the chip.
 //   gemm_bf16_column_kernel  M <= 16, the projections that write the residual stream (O, most models' down): one
@@ -258,22 +260,41 @@ __global__ __launch_bounds__(256) void gemm_bf16_skinny_kernel(GemmArgs g) {
 // the 4 KB of K quarter q are contiguous.  Rows past the end of a matrix are stored as zeros.
 constexpr int kUnitBytes = kSkinnyRows * kSkinnyStepK * 2;
 constexpr int kUnitVec = kUnitBytes / 16;          // 16-byte vectors per unit
+constexpr int kBandBlocks = 256, kBandMost = 7;
 
-__global__ __launch_bounds__(256) void gemm_pack_kernel(const uint16_t *W, int N, int K, u32x4 *dst) {
-    // one thread per 16-byte vector of the packed copy
-    const size_t vec = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const int ns = K / kSkinnyStepK;
-    const size_t n_units = (size_t)((N + kSkinnyRows - 1) / kSkinnyRows) * ns;
-    if (vec >= n_units * kUnitVec) return;
-    const size_t unit = vec / kUnitVec;
-    const int within = (int)(vec % kUnitVec), slot = within >> 6, lane = within & 63;
-    const int tile = (int)(unit / ns), step = (int)(unit % ns);
-    const int q = slot >> 2, strip = slot & 3, i = lane & 15, gq = lane >> 4;
-    const int row = tile * kSkinnyRows + strip * 16 + i;
-    const int k = step * kSkinnyStepK + (q >> 1) * 64 + gq * 16 + (q & 1) * 8;
-    u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    if (row < N) v = *reinterpret_cast<const u32x4 *>(W + (size_t)row * K + k);
-    dst[vec] = v;
+// GemmBands (kernels.h): a band of S strips is ns steps of 4 S KB, a step its four K quarters, a quarter the S strips' slots: what the
+// unit above is for S = 4.
+struct PackArgs {
+    const uint16_t *w[3];
+    int n[3], nseg, K;
+    GemmBands bands;
+    u32x4 *dst;
+};
+__host__ __device__ __forceinline__ int strips_of(int n) { return (n + kSkinnyRows - 1) / kSkinnyRows * 4; }
+// where the strip of 16 rows that begins at `row` of matrix `seg` lies: its band and its place there
+struct BandRef { int band, slot; };
+__device__ __forceinline__ BandRef band_of(const GemmBands &b, const int *n, int seg, int row) {
+    int strip = row / 16;
+    for (int s = 0; s < seg && !b.paired; ++s) strip += strips_of(n[s]);
+    const int band = b.strips == 1 ? strip : (int)__umulhi((uint32_t)strip, b.inverse);
+    return {band + seg * b.paired, strip - band * b.strips};
+}
+
+__global__ __launch_bounds__(256) void gemm_pack_kernel(PackArgs p) {
+    // one block per (band, K step), one thread per 16-byte vector of a 4 KB piece
+    const int S = p.bands.strips, ns = p.K / kSkinnyStepK, band = (int)(blockIdx.x / (unsigned)ns), step = (int)(blockIdx.x % (unsigned)ns);
+    const int half = p.bands.paired;
+    u32x4 *dst = p.dst + (size_t)blockIdx.x * S * 256;
+    for (int v = threadIdx.x; v < S * 256; v += 256) {
+        const int piece = v >> 6, lane = v & 63, q = piece / S, slot = piece % S, i = lane & 15, gq = lane >> 4;
+        int seg = 0, strip = band * S + slot;
+        if (p.bands.paired && band >= half) { seg = 1; strip -= half * S; }
+        for (; !p.bands.paired && seg < p.nseg - 1 && strip >= strips_of(p.n[seg]); ++seg) strip -= strips_of(p.n[seg]);
+        const int row = strip * 16 + i, k = step * kSkinnyStepK + (q >> 1) * 64 + gq * 16 + (q & 1) * 8;
+        u32x4 x = u32x4{0u, 0u, 0u, 0u};
+        if (row < p.n[seg]) x = *reinterpret_cast<const u32x4 *>(p.w[seg] + (size_t)row * p.K + k);
+        dst[v] = x;
+    }
 }
 
 // first unit of block b when U units are dealt to P blocks in contiguous, near-equal ranges
@@ -500,6 +521,122 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
                 __syncthreads();
             }
             if (tile_end) { ++tile; first += ns; }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------ bf16 band kernel (M <= 16: QKV, gate|up)
+// One block per band of S strips over the whole K range (GATED: the gate band and the up band of the same columns), on weights packed
+// in these bands (gemm_qkv_bands, gemm_gate_bands), so that a block streams one contiguous range (GATED: two).  Wavefront (q, half) takes
+// K quarter q of the even or the odd steps, through a ring of two; the eight wavefronts' sums meet in LDS.  Every output has one owner:
+// QKV writes one partial slot, gate|up scales its rows, applies SwiGLU and writes the operand of the down projection, so neither needs
+// partial slots of several blocks to be written and read, nor gate|up the launch that did.
+// What bounds it: streaming the weights (180 MB of the 7B shape's gate|up in 31 us = 5.9 TB/s, its QKV of 101 MB in 18 at 15 rows) and the
+// fixed cost of a launch.  Against the unit kernel with shared tiles, and the SwiGLU launch behind it, on one box: gate|up 32.5 + 4.9 -> 30.9 us
+// and QKV 19.6 -> 18.3 at 15 rows; the 32-layer 7B step at 8 rows 3 340 -> 3 070, two layers of the 8B shape at 11 rows 409 -> 397.
+// The blocks begin at different steps of their bands: bands lie a multiple of a large power of two apart, and in step all blocks would
+// ask the same channels at once (7B step 3 100 -> 3 079 us; beginnings 1, 3, 4 or 5 steps apart are no better than 2).  One stage in
+// flight: 3 135 us, three: 3 123.  Slots of a step ordered strip by strip, or the gate and up strips of a step side by side: no change here,
+// the latter 1 % slower in the rows kernel.
+template <bool FOLD, int S, bool GATED>
+__global__ __launch_bounds__(512) void gemm_bf16_band_kernel(GemmArgs g) {
+    constexpr int R = 2, XV = FOLD ? 1 : 2, NS = GATED ? 2 * S : S;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int q = wave & 3, half = wave >> 2;
+    const int i = lane & 15, gq = lane >> 4;
+    const int K = g.K, ns = K / kSkinnyStepK;
+    // GATED: the rows' sums of squares, requested ahead of the first weights: 32 threads a row, the first eight strips or tiles each
+    __shared__ float s_scale[16];
+    const int sm = threadIdx.x >> 5, sl = threadIdx.x & 31;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(g.scale.sumsq), 0, g.scale.tiles * g.M * 4, 0x00020000);
+    const uint32_t soff = sm < g.M ? (uint32_t)(sl * g.M + sm) * 4 : 0x80000000u;
+    uint32_t ssq[8];
+    if constexpr (GATED)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) ssq[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, soff + (uint32_t)(t * 32 * g.M) * 4, 0, 0);
+    constexpr uint32_t kPiece = S * 1024, kStepW = 4 * kPiece;               // a quarter of a step, a step
+    auto band = [&](unsigned b) {
+        return __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(g.wpack) + (size_t)b * ns * kStepW, 0, ns * kStepW, 0x00020000);
+    };
+    const __amdgpu_buffer_rsrc_t rw = band(blockIdx.x), ru = band(GATED ? blockIdx.x + gridDim.x : blockIdx.x);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(g.x_op), 0, K * (FOLD ? 32 : 64), 0x00020000);
+    constexpr uint32_t kStepX = kSkinnyStepK * (FOLD ? 32 : 64);
+    const int xm = FOLD ? i & 7 : i;
+    const uint32_t xbase = xm < g.M ? (uint32_t)(q * (FOLD ? 1024 : 2048) + lane * 16) : 0x80000000u;       // a row past M reads zeros
+    const uint32_t wbase = q * kPiece + lane * 16;
+    const int turn = (int)(2 * blockIdx.x % (unsigned)ns);
+
+    u32x4 A[R][NS], X[R][XV];
+    auto issue = [&](int j, int n) {                       // this wavefront's n-th step; past the last one, zeros
+        const int at = 2 * n + half, step = at + turn < ns ? at + turn : at + turn - ns;
+        const uint32_t xo = at < ns ? xbase + (uint32_t)step * kStepX : 0x80000000u, wo = at < ns ? wbase + (uint32_t)step * kStepW : 0x80000000u;
+        X[j][0] = __builtin_amdgcn_raw_buffer_load_b128(rx, xo, 0, 0);
+        if constexpr (!FOLD) X[j][1] = __builtin_amdgcn_raw_buffer_load_b128(rx, xo + 1024, 0, 0);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) A[j][s] = __builtin_amdgcn_raw_buffer_load_b128(s < S ? rw : ru, wo + s % S * 1024, 0, 2);      // 2: streaming
+        __builtin_amdgcn_sched_barrier(0);                 // (as in the unit kernel: the loads stay in this order)
+    };
+    f32x4 acc[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int j) {
+#pragma unroll
+        for (int v = 0; v < XV; ++v)
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[j][s]), __builtin_bit_cast(bf16x8, X[j][v]), acc[s], 0, 0, 0);
+    };
+#pragma unroll
+    for (int j = 0; j < R; ++j) issue(j, j);
+    if constexpr (GATED) {
+        float v = 0.f;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v += __uint_as_float(ssq[t]);
+        for (int t = 256 + sl; t < g.scale.tiles; t += 32)
+            v += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, sm < g.M ? (uint32_t)(t * g.M + sm) * 4 : 0x80000000u, 0, 0));
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if (sl == 0) s_scale[sm] = 1.0f / sqrtf(v * g.scale.inv_d + g.scale.eps);
+    }
+    const int n_my = (ns + 1) / 2;
+    for (int base = 0; base + R < n_my; base += R) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            multiply(j);
+            issue(j, base + j + R);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) multiply(j);
+    // acc[s][v] = y[token i][column 4*gq + v of strip s] over this wavefront's quarters: the odd steps' wavefronts hand theirs over first
+    __shared__ float red[4][NS * 16][17];
+    if (half)
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[q][s * 16 + 4 * gq + v][i] = acc[s][v];
+    __syncthreads();
+    if (!half)
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[q][s * 16 + 4 * gq + v][i] += acc[s][v];
+    __syncthreads();
+    constexpr int kCols = S * 16;
+    for (int e = threadIdx.x; e < kCols * (FOLD ? 8 : 16); e += 512) {
+        const int col = e % kCols, tok = e / kCols, c = blockIdx.x * kCols + col;
+        auto sum = [&](int row) {
+            float v = ((red[0][row][tok] + red[1][row][tok]) + red[2][row][tok]) + red[3][row][tok];
+            if constexpr (FOLD)                            // the products with the remainders stand eight columns further on
+                v += ((red[0][row][tok + 8] + red[1][row][tok + 8]) + red[2][row][tok + 8]) + red[3][row][tok + 8];
+            return v;
+        };
+        if (tok >= g.M || c >= (GATED ? g.n[0] : g.N)) continue;
+        if constexpr (GATED) {
+            const float gt = sum(col) * s_scale[tok], up = sum(kCols + col) * s_scale[tok];
+            op_store(g.swiglu_op, tok, c, FOLD, gt / (1.0f + expf(-gt)) * up);
+        } else {
+            g.partial[(size_t)tok * g.N + c] = sum(col);
         }
     }
 }
@@ -785,12 +922,13 @@ __global__ __launch_bounds__(256) void gemm_w4_unit_kernel(GemmArgs g) {
 // meet in LDS at the end.
 // LDS: fragment (quarter q, tile mt) of a step is 64 lanes x 16 bytes; lane (i, g) lies at 16 g + (i ^ (4 q + g)): threads write
 // whole rows, 16 bytes to each of 16 fragments, which without the xor were all in one bank (0.65 us a step).
+// GATED is a build of its own: with both epilogues inlined at every ring stage the code of the loop is twice as long, which shows in
+// launches of one round (a head of 32000 x 4096 at 45 rows 44.8 -> 44.5 us, two layers and head of the 7B shape 333 -> 330.5).
 constexpr int kRowsBlocks = 256, kRowsMax = 128;
 
-template <int NW, int MT>
+template <int NW, int MT, bool GATED>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows_kernel(GemmArgs g) {
     constexpr int R = 4, NT = 64 * NW;
-    const bool gated = g.swiglu16 != nullptr;
     constexpr int XV = MT * 16 * 16, XCH = (XV + NT - 1) / NT;        // 16-byte vectors of a step of X, per thread
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, gq = lane >> 4;
@@ -831,30 +969,30 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows_kernel(GemmArgs g) {
         }
     };
 
+    const uint32_t piece_w = (uint32_t)g.bands.strips * 1024u, step_w = 4 * piece_w;       // a quarter of a band's step, a step
     u32x4 A[R][4];
     int is_step = u0 % ns, is_tile = u0 / ns, is_n = 0;
     __amdgpu_buffer_rsrc_t rw;
     struct Strip { int seg, row, col0; };                  // which matrix, its first row there, the matrix' first output column
     auto strip_of = [&](int tile) {                        // this wavefront's strip of a tile
-        if (gated) return Strip{wave < NW / 2 ? 0 : 1, (tile * (NW / 2) + wave % (NW / 2)) * 16, 0};
-        const TileRef t = find_tile(g, tile, 16 * NW);
-        return Strip{t.seg, t.row0 + wave * 16, t.col0};
+        if constexpr (GATED) return Strip{wave < NW / 2 ? 0 : 1, (tile * (NW / 2) + wave % (NW / 2)) * 16, 0};
+        else {
+            const TileRef t = find_tile(g, tile, 16 * NW);
+            return Strip{t.seg, t.row0 + wave * 16, t.col0};
+        }
     };
     auto set_tile = [&]() {                                // the buffer: the strip of the tile to request
         const Strip t = strip_of(is_tile < g.tiled_tiles ? is_tile : 0);
-        int pack0 = 0;
-        for (int sgm = 0; sgm < t.seg; ++sgm) pack0 += (g.n[sgm] + kSkinnyRows - 1) / kSkinnyRows;
-        const int row = t.row;
-        const bool there = is_n < n_my && row < g.n[t.seg];
-        const int tile64 = pack0 + row / kSkinnyRows, strip = row % kSkinnyRows / 16;
-        rw = __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(g.wpack) + (there ? (size_t)tile64 * ns * kUnitBytes + strip * 1024 : 0), 0,
-                                               there ? ns * kUnitBytes - strip * 1024 : 0, 0x00020000);
+        const bool there = is_n < n_my && t.row < g.n[t.seg];
+        const BandRef at = band_of(g.bands, g.n, t.seg, t.row);
+        rw = __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(g.wpack) + (there ? (size_t)at.band * ns * step_w + at.slot * 1024 : 0), 0,
+                                               there ? ns * step_w - at.slot * 1024 : 0, 0x00020000);
     };
     set_tile();
     auto issue = [&](int j) {
-        const uint32_t at = (lane * 16u + (uint32_t)is_step * kUnitBytes) | (is_n < n_my ? 0u : 0x80000000u);
+        const uint32_t at = (lane * 16u + (uint32_t)is_step * step_w) | (is_n < n_my ? 0u : 0x80000000u);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) A[j][q] = __builtin_amdgcn_raw_buffer_load_b128(rw, at + q * 4096u, 0, 2);       // 2: streaming
+        for (int q = 0; q < 4; ++q) A[j][q] = __builtin_amdgcn_raw_buffer_load_b128(rw, at + q * piece_w, 0, 2);       // 2: streaming
         ++is_n;
         if (++is_step == ns) { is_step = 0; ++is_tile; set_tile(); }
         __builtin_amdgcn_sched_barrier(0);
@@ -863,10 +1001,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows_kernel(GemmArgs g) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     // acc[mt][v] = y[token mt*16 + i][row wave*16 + 4*gq + v of the tile]
-    __shared__ __attribute__((aligned(16))) f32x4 s_up[NW / 2][MT][64];
+    __shared__ __attribute__((aligned(16))) f32x4 s_up[GATED ? NW / 2 : 1][MT][64];
     auto flush = [&](int tile) {
         const Strip t = strip_of(tile);
-        if (gated) {
+        if constexpr (GATED) {
             if (wave >= NW / 2)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) s_up[wave - NW / 2][mt][lane] = acc[mt];
@@ -885,26 +1023,27 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows_kernel(GemmArgs g) {
                     make_uint2(f32_to_f16_bits(h[0]) | ((uint32_t)f32_to_f16_bits(h[1]) << 16),
                                f32_to_f16_bits(h[2]) | ((uint32_t)f32_to_f16_bits(h[3]) << 16));
             }
-            return;                                        // (the barrier of the next step stands before s_up is written again)
-        }
-        const int slot = g.whole ? 0 : (int)(blockIdx.x - range_owner((long)tile * ns, U, P));
-        const int zero_to = (tile + 1) * ns <= u1 ? g.splitk : 0;
-        const bool vec = g.N % 4 == 0 && (uintptr_t)g.partial % 16 == 0;               // (whole tiles of the head go to the caller's logits)
-        const int row = t.row + 4 * gq, rows = g.n[t.seg] - row;                       // rows of the four that exist
+            // (the barrier of the next step stands before s_up is written again)
+        } else {
+            const int slot = g.whole ? 0 : (int)(blockIdx.x - range_owner((long)tile * ns, U, P));
+            const int zero_to = (tile + 1) * ns <= u1 ? g.splitk : 0;
+            const bool vec = g.N % 4 == 0 && (uintptr_t)g.partial % 16 == 0;               // (whole tiles of the head go to the caller's logits)
+            const int row = t.row + 4 * gq, rows = g.n[t.seg] - row;                       // rows of the four that exist
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int m = mt * 16 + i;
-            const f32x4 r = acc[mt];
-            acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (m >= g.M) continue;
-            float *p = g.partial + ((size_t)slot * g.M + m) * g.N + t.col0 + row;
-            for (int sl = slot; sl == slot || sl < zero_to; ++sl, p += (size_t)g.M * g.N) {
-                const f32x4 o = sl == slot ? r : f32x4{0.f, 0.f, 0.f, 0.f};
-                if (rows >= 4 && vec) *reinterpret_cast<f32x4 *>(p) = o;
-                else
+            for (int mt = 0; mt < MT; ++mt) {
+                const int m = mt * 16 + i;
+                const f32x4 r = acc[mt];
+                acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (m >= g.M) continue;
+                float *p = g.partial + ((size_t)slot * g.M + m) * g.N + t.col0 + row;
+                for (int sl = slot; sl == slot || sl < zero_to; ++sl, p += (size_t)g.M * g.N) {
+                    const f32x4 o = sl == slot ? r : f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (rows >= 4 && vec) *reinterpret_cast<f32x4 *>(p) = o;
+                    else
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (v < rows) p[v] = o[v];
+                        for (int v = 0; v < 4; ++v)
+                            if (v < rows) p[v] = o[v];
+                }
             }
         }
     };
@@ -1355,6 +1494,29 @@ bool gemm_tiled_gates(int M, int K, const int *n, bool packed) {
     return M > 128 ? gemm_tiled_plan(M, K, n, 2, true, false).tiles >= 128 : packed && gemm_rows_plan(M, K, n, 2, true).used;
 }
 
+// The bands of the projections that the band kernel runs: the width whose blocks, one a band, leave the fewest CUs idle in their last
+// round, the wider one where two leave as many (a block reads all activations).
+static int band_strips(int strips, int least, int most, double *busy) {
+    int best = least;
+    *busy = 0.;
+    for (int s = least; s <= most; ++s) {
+        const int blocks = (strips + s - 1) / s, rounds = (blocks + kBandBlocks - 1) / kBandBlocks;
+        const double share = (double)strips / ((double)s * rounds * kBandBlocks);
+        if (share > *busy - 1e-9) { *busy = share; best = s; }
+    }
+    return best;
+}
+static uint32_t inverse_of(int s) { return (uint32_t)((0xffffffffull + s) / s); }        // ceil(2^32 / s), s > 1
+GemmBands gemm_gate_bands(int f) {
+    double busy;
+    const int s = band_strips(strips_of(f), 1, kBandMost, &busy);
+    return GemmBands{s, (strips_of(f) + s - 1) / s, inverse_of(s), true};
+}
+GemmBands gemm_qkv_bands(const int *n) {
+    double busy;
+    const int s = band_strips(tiles_of(n, 3, kSkinnyRows) * 4, 3, 6, &busy);
+    return busy >= 0.85 ? GemmBands{s, 0, inverse_of(s), true} : kUnitBands;
+}
 static int gemm_stream_grid(int tiles, int K) {
     const long U = (long)tiles * (K / kSkinnyStepK);
     return (int)(U < kStreamBlocks ? (U < 1 ? 1 : U) : kStreamBlocks);
@@ -1392,21 +1554,25 @@ static int gemm_slots_of(int tiles, int units_per_tile, int grid) {
 }
 
 int gemm_pack_tiles(const int *n, int nseg) { return tiles_of(n, nseg, kSkinnyRows); }
-size_t gemm_pack_bytes(const int *n, int nseg, int K) {
-    return (size_t)tiles_of(n, nseg, kSkinnyRows) * (K / kSkinnyStepK) * kUnitBytes;
+static int gemm_band_count(const int *n, int nseg, GemmBands b) {
+    if (b.paired) return 2 * b.paired;
+    int strips = 0;
+    for (int s = 0; s < nseg; ++s) strips += strips_of(n[s]);
+    return (strips + b.strips - 1) / b.strips;
+}
+size_t gemm_pack_bytes(const int *n, int nseg, int K, GemmBands b) {
+    return (size_t)gemm_band_count(n, nseg, b) * b.strips * 16 * K * 2;
 }
 
-void launch_gemm_pack(const void *const *w, const int *n, int nseg, int K, void *dst, bool strip_major, hipStream_t stream) {
-    char *out = (char *)dst;
-    for (int s = 0; s < nseg; ++s) {
-        const size_t units = (size_t)((n[s] + kSkinnyRows - 1) / kSkinnyRows) * (K / kSkinnyStepK);
-        const size_t vecs = units * kUnitVec;
-        if (strip_major)
-            launch_kernel(gemm_pack_strip_kernel, (unsigned)((vecs + 255) / 256), 256, 0, stream, (const uint16_t *)w[s], n[s], K, (u32x4 *)out);
-        else
-            launch_kernel(gemm_pack_kernel, (unsigned)((vecs + 255) / 256), 256, 0, stream, (const uint16_t *)w[s], n[s], K, (u32x4 *)out);
-        out += units * kUnitBytes;
-    }
+void launch_gemm_pack(const void *const *w, const int *n, int nseg, int K, void *dst, GemmBands b, hipStream_t stream) {
+    PackArgs p{};
+    for (int s = 0; s < nseg; ++s) { p.w[s] = (const uint16_t *)w[s]; p.n[s] = n[s]; }
+    p.nseg = nseg; p.K = K; p.bands = b; p.dst = (u32x4 *)dst;
+    launch_kernel(gemm_pack_kernel, (unsigned)gemm_band_count(n, nseg, b) * (K / kSkinnyStepK), 256, 0, stream, p);
+}
+void launch_gemm_pack_strips(const void *w, int n, int K, void *dst, hipStream_t stream) {
+    const size_t vecs = (size_t)((n + kSkinnyRows - 1) / kSkinnyRows) * (K / kSkinnyStepK) * kUnitVec;
+    launch_kernel(gemm_pack_strip_kernel, (unsigned)((vecs + 255) / 256), 256, 0, stream, (const uint16_t *)w, n, K, (u32x4 *)dst);
 }
 
 size_t gemm_pack_w4_bytes(const int *n, int nseg, int K) {
@@ -1504,6 +1670,26 @@ void launch_gemm(int dtype, const GemmArgs &args, hipStream_t stream) {
         else launch_kernel(gemm_bf16_column_kernel<false>, grid, 1024, 0, stream, g);
         return;
     }
+    if (g.M <= kStreamMaxRows && g.wpack && g.bands.owned) {
+        ScopedProf sp(PSD_KIND_GEMM_SKINNY, stream);
+        const int bands = gemm_band_count(g.n, g.nseg, g.bands), blocks = g.bands.paired ? bands / 2 : bands;
+        auto go = [&](auto strips, auto gated) {
+            constexpr int S = decltype(strips)::value;
+            constexpr bool G = decltype(gated)::value;
+            if (g.op_folded) launch_kernel(gemm_bf16_band_kernel<true, S, G>, blocks, 512, 0, stream, g);
+            else launch_kernel(gemm_bf16_band_kernel<false, S, G>, blocks, 512, 0, stream, g);
+        };
+        auto among = [&](auto gated, auto... strips) {      // (the widths that gemm_gate_bands and gemm_qkv_bands give)
+            ((g.bands.strips == decltype(strips)::value ? go(strips, gated) : void()), ...);
+        };
+        using std::integral_constant;
+        if (g.bands.paired)
+            among(std::true_type{}, integral_constant<int, 1>{}, integral_constant<int, 2>{}, integral_constant<int, 3>{}, integral_constant<int, 4>{},
+                  integral_constant<int, 5>{}, integral_constant<int, 6>{}, integral_constant<int, 7>{});
+        else
+            among(std::false_type{}, integral_constant<int, 3>{}, integral_constant<int, 4>{}, integral_constant<int, 5>{}, integral_constant<int, 6>{});
+        return;
+    }
     if (g.M <= kStreamMaxRows && g.wpack) {
         ScopedProf sp(PSD_KIND_GEMM_SKINNY, stream);
         const int grid = g.whole ? (g.pack_tiles < kStreamBlocks ? g.pack_tiles : kStreamBlocks) : gemm_stream_grid(g.pack_tiles, g.K);
@@ -1519,20 +1705,25 @@ void launch_gemm(int dtype, const GemmArgs &args, hipStream_t stream) {
         GemmArgs t = g;
         t.tiled_tiles = rp.tiles;
         t.whole = rp.whole;
-        auto pick = [&](auto waves) {
+        auto pick = [&](auto waves, auto gated) {
             constexpr int NW = decltype(waves)::value;
+            constexpr bool G = decltype(gated)::value;
             auto go = [&](auto kernel) { launch_kernel(kernel, rp.blocks, 64 * NW, 0, stream, t); };
-            if (g.M <= 32) go(gemm_bf16_rows_kernel<NW, 2>);
-            else if (g.M <= 48) go(gemm_bf16_rows_kernel<NW, 3>);
-            else if (g.M <= 64) go(gemm_bf16_rows_kernel<NW, 4>);
+            if (g.M <= 32) go(gemm_bf16_rows_kernel<NW, 2, G>);
+            else if (g.M <= 48) go(gemm_bf16_rows_kernel<NW, 3, G>);
+            else if (g.M <= 64) go(gemm_bf16_rows_kernel<NW, 4, G>);
             else if constexpr (NW <= 8) {                   // (the plan gives ten wavefronts up to 64 rows, six up to 96)
-                if (g.M <= 96) go(gemm_bf16_rows_kernel<NW, 6>);
-                else if constexpr (NW == 8) go(gemm_bf16_rows_kernel<8, 8>);
+                if (g.M <= 96) go(gemm_bf16_rows_kernel<NW, 6, G>);
+                else if constexpr (NW == 8) go(gemm_bf16_rows_kernel<8, 8, G>);
             }
         };
-        if (rp.waves == 6) pick(std::integral_constant<int, 6>{});
-        else if (rp.waves == 8) pick(std::integral_constant<int, 8>{});
-        else pick(std::integral_constant<int, 10>{});
+        auto widths = [&](auto gated) {
+            if (rp.waves == 6) pick(std::integral_constant<int, 6>{}, gated);
+            else if (rp.waves == 8) pick(std::integral_constant<int, 8>{}, gated);
+            else pick(std::integral_constant<int, 10>{}, gated);
+        };
+        if (g.swiglu16) widths(std::true_type{});
+        else widths(std::false_type{});
     } else {
         ScopedProf sp(PSD_KIND_GEMM_TILED, stream);
         const GemmTiledPlan p = gemm_tiled_plan(g.M, g.K, g.n, g.nseg, g.swiglu16 != nullptr, g.w4);

@@ -53,6 +53,15 @@ struct RowScale {
 // What the kernels read first stands first: a block begins by waiting for the 64-byte lines of arguments that it needs, every launch
 // brings them in anew (the implicit ones, the grid's size among them, lie behind this struct).  Tiled launches of 22 rows, us, with
 // M, K, n, the tile count and the grid's size on four lines / on the first: 4608 x 3584 12.3 / 11.9, 3584 x 3584 11.0 / 10.5.
+// How a packed copy groups its strips of 16 rows: `strips` of them a band, the strips of all matrices one behind the other, or, paired
+// (gate|up), each matrix in whole bands.  Bands of four are the 64-row tiles of the unit kernel.
+struct GemmBands {
+    int strips;
+    int paired;                   // bands of each matrix; 0: not paired
+    uint32_t inverse;             // ceil(2^32 / strips)
+    bool owned;                   // up to kStreamMaxRows rows the band kernel runs: one block a band, or a pair of them
+};
+constexpr GemmBands kUnitBands{4, 0, 1u << 30, false};
 struct GemmArgs {
     int M, K, N, nseg;            // N = sum n[i]
     int n[3];
@@ -94,6 +103,9 @@ struct GemmArgs {
     RowScale scale;               // applied when writing `reduced` or a head in whole tiles (row = the source row of m)
     int32_t *lens;                // lens_n of them move on by lens_add, up to lens_max
     int lens_add, lens_max;
+    // (behind the rest: ahead of it they moved what the tiled kernel reads first, 2 us over the launches of a small model's two layers)
+    uint16_t *swiglu_op;          // bf16, packed weights, M <= kStreamMaxRows; segments are (gate, up): silu(gate) * up, scaled, in operand order
+    GemmBands bands;              // of wpack
 };
 struct GemmTiledPlan {
     int ta, cols;                 // block tile: 64 ta rows x cols columns
@@ -115,13 +127,15 @@ RowsPlan gemm_rows_plan(int M, int K, const int *n, int nseg, bool gated);
 int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, bool packed, bool w4);
 // repacked weights for the M <= kStreamMaxRows path
 int gemm_pack_tiles(const int *n, int nseg);
-size_t gemm_pack_bytes(const int *n, int nseg, int K);
+GemmBands gemm_gate_bands(int f);
+GemmBands gemm_qkv_bands(const int *n);
+size_t gemm_pack_bytes(const int *n, int nseg, int K, GemmBands b);
 int gemm_w4_slots(int K, const int *n, int nseg, bool resid);  // partial slots of a 4-bit projection (resid: the arrival epilogue's grid)
 bool gemm_down_by_units(int d_model, int d_ffn);          // bf16, packed: the down projection runs with tile_counter, on unit-major weights
 int gemm_resid_slots(int tiles, int K);                  // ... its partial slots
 int gemm_packed_splits(int K, const int *n, int nseg);   // partial slots (the splitk to use) with packed weights
-// strip_major: the layout of the column kernel
-void launch_gemm_pack(const void *const *w, const int *n, int nseg, int K, void *dst, bool strip_major, hipStream_t stream);
+void launch_gemm_pack(const void *const *w, const int *n, int nseg, int K, void *dst, GemmBands b, hipStream_t stream);
+void launch_gemm_pack_strips(const void *w, int n, int K, void *dst, hipStream_t stream);      // the layout of the column kernel
 // 4-bit weight-only quantised projections: q [n][K/2] bytes (low nibble = even k), scale bf16 [n][K/128],
 // zero u8 [n][K/128]; w = scale * (q - zero).  Each n[s] a multiple of 64.
 size_t gemm_pack_w4_bytes(const int *n, int nseg, int K);
@@ -224,8 +238,8 @@ void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale 
 // beside that or op)
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
                                  int M, int d, float eps, uint16_t *xn16, OpRows op, hipStream_t stream);
-// h = silu(g) * u with [g | u] = sum over splits of partial [S][M][2f]: any of fp32, fp16 and operand order
-void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, uint16_t *h_op, hipStream_t stream);
+// h = silu(g) * u with [g | u] = sum over splits of partial [S][M][2f]: fp32, fp16 or both
+void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, hipStream_t stream);
 void launch_advance_lens(int32_t *lens, int B, int delta, int max_len, hipStream_t stream);
 void launch_truncate(int32_t *lens, const int32_t *base, const int32_t *keep, int offset, int cap, int B,
                      hipStream_t stream);

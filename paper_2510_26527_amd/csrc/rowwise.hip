@@ -304,7 +304,7 @@ __global__ __launch_bounds__(256) void reduce_rope_append_tiled_kernel(const flo
 // h = silu(g) * u, four columns per thread, one row per blockIdx.y; [g | u] arrive as split-K partials of
 // the gate|up projection
 __global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float *partial, int S, size_t split_stride, RowScale rs,
-                                                            float *h, int M, int f, uint16_t *h16, uint16_t *h_op) {
+                                                            float *h, int M, int f, uint16_t *h16) {
     __shared__ float red[4];
     const int m = blockIdx.y, f4 = f >> 2;
     float ssq = 0.f;
@@ -326,7 +326,6 @@ __global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float *partial
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
     if (h) reinterpret_cast<f32x4 *>(h + (size_t)m * f)[j4] = o;
-    if (h_op) op_store4(h_op, m, 4 * j4, M <= kOpFoldRows, o);
     if (h16)
         reinterpret_cast<uint2 *>(h16 + (size_t)m * f)[j4] =
             make_uint2(f32_to_f16_bits(o[0]) | ((uint32_t)f32_to_f16_bits(o[1]) << 16),
@@ -411,10 +410,10 @@ void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale 
                                                                   lens, R, h_q, h_kv, d_h, max_len, theta, cs_table);
 }
 
-void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, uint16_t *h_op, hipStream_t stream) {
+void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_SWIGLU, stream);
     const dim3 grid((unsigned)((f / 4 + 255) / 256), (unsigned)M);
-    launch_kernel(reduce_swiglu_kernel, grid, 256, 0, stream, partial, S, (size_t)M * 2 * f, rs, h, M, f, h16, h_op);
+    launch_kernel(reduce_swiglu_kernel, grid, 256, 0, stream, partial, S, (size_t)M * 2 * f, rs, h, M, f, h16);
 }
 
 void launch_advance_lens(int32_t *lens, int B, int delta, int max_len, hipStream_t stream) {

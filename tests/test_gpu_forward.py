@@ -238,6 +238,21 @@ def test_operand_order_activations(d_model, d_ffn, n_new):
     p.close()
 
 
+@pytest.mark.parametrize("n_new", [1, 8, 9, 16, 17])
+@pytest.mark.parametrize("d_model,hq,hk,d_ffn", [
+    (128, 2, 2, 128), (384, 2, 1, 4224), (128, 44, 22, 11008), (256, 64, 32, 14464), (128, 80, 40, 18944), (640, 64, 64, 24448), (128, 2, 2, 28544)])
+def test_projections_in_bands(d_model, hq, hk, d_ffn, n_new):
+    """QKV and gate|up by bands: gate bands of 1 to 7 strips, whole and with a last one of fewer; QKV in bands of 3 (the last one not full),
+    4, 5 and 6 strips, or, narrow, on shared tiles; one, two, three and five K steps for two groups of wavefronts; folded (8 rows) and not.
+    17 rows: the rows kernel on the same packed copies."""
+    shape = synth.Shape(1, d_model, hq, hk, 128, d_ffn, 200, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 64, seed=n_new, ctx=9, std=0.02, pack=True)
+    ran = step_launches(p, synth.make_tokens(shape.vocab, (1, n_new), d_ffn), what="all rows' logits")
+    if n_new <= 16:
+        assert ran["swiglu"] == 0 and ran["gemm_skinny"] == 3
+    p.close()
+
+
 @pytest.mark.parametrize("n_new", [1, 8, 9, 16])
 @pytest.mark.parametrize("d_model,d_ffn", [(4224, 128), (4224, 1152), (128, 16384)])
 def test_down_projection_by_units(d_model, d_ffn, n_new):
