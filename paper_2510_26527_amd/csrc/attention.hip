@@ -573,6 +573,10 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
 // bf16 high + low pair and frees the registers for what bounds this kernel, the bytes a CU keeps in flight: two
 // 64-key tiles travel in registers (stage = tile parity) while a third is multiplied, and the next tile is stored
 // into the second set of LDS tiles in the middle of the current one's MFMAs (one barrier per tile).
+// Keys: up to the position of the block's last row, so a prompt's blocks walk half of them on average.  Where no keys are split, the
+// blocks go out by how many they walk, longest first: chunks from the last rows to the first, a chunk's place within each query head of
+// the group, heads innermost (2001 rows of the 7B shape: all keys 131 us a launch, seen keys 122 in grid order, 78 in this one; first
+// half of the blocks descending and the second ascending 91).
 // OP: the output in operand order (passes of up to 16 rows), a build of its own: with these stores in it the row-major one is
 // 2 200 instructions longer, and slower though it skips them (us a launch, 7B shape, 16 sequences x 20 rows 23.1 / 21.5, 12 x 20 22.0 / 20.6).
 template <int DH, int QW, int NW, bool OP>
@@ -584,13 +588,23 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_wide_kernel(AttnArgs a, flo
     extern __shared__ __attribute__((aligned(16))) uint16_t lds_wide[];      // two sets of (K tile, V^T tile)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, g = lane >> 4;
-    const int split = blockIdx.x, qchunk = blockIdx.y;
-    const int b = blockIdx.z / a.h_kv, hk = blockIdx.z % a.h_kv;
+    const int split = blockIdx.x;
+    int qchunk = blockIdx.y, bh = blockIdx.z;
+    if (gridDim.x == 1 && gridDim.y > 1) {                  // the chunks that see the most keys first
+        const int C = gridDim.y, group = a.h_q / a.h_kv, whole = C / group, rest = C - whole * group;
+        const int L = blockIdx.y + C * blockIdx.z, at = L / (int)gridDim.z, inner = at - rest;
+        qchunk = inner < 0 ? C - 1 - at : inner % group * whole + whole - 1 - inner / group;
+        bh = L % (int)gridDim.z;
+    }
+    const int b = bh / a.h_kv, hk = bh % a.h_kv;
     const int group = a.h_q / a.h_kv;
     const int NQ = group * a.R;
     const int S_b = a.lens[b];
     const int n_keys = min(S_b + a.R, a.max_len);
-    const int kb0 = split * range, kb1 = min(n_keys, kb0 + range);
+    // no row of the block sees past the last one's position (a block that reaches into the next query head's rows: past the step's last)
+    const int q0 = qchunk * NW * QW * 16, q1 = min(NQ, q0 + NW * QW * 16) - 1;
+    const int seen = S_b + (q0 / a.R == q1 / a.R ? q1 % a.R : a.R - 1) + 1;
+    const int kb0 = split * range, kb1 = min(min(n_keys, seen), kb0 + range);
     const size_t max_len = a.max_len;
     const uint16_t *Kc = (const uint16_t *)a.k + ((size_t)b * a.h_kv + hk) * max_len * DH;
     const uint16_t *Vt = (const uint16_t *)a.v + ((size_t)b * a.h_kv + hk) * DH * max_len;
