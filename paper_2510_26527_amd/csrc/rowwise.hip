@@ -38,8 +38,10 @@ __device__ __forceinline__ f32x4 load_row4(const uint16_t *row, int i4) { return
 // One block per row: x (+)= source, then xn = x * rsqrt(mean(x^2) + eps) * gain.  The source is either
 // an embedding row (EMBED) or the split-K partial sums of the projection that feeds the residual
 // stream, added in split order.  All loads of a row are issued before the first use.  xn NULL: only the fp16 copy is read.
-// A row is one block, so few rows leave most CUs idle and the block's own loads in flight set the time: 1024 threads
-// then hold a whole row of a split at once (45 rows x 4096, 8 splits: 9.6 us with 256 threads, 5.2; 256 rows x 3584: 10.1, 7.0).
+// What bounds it: a block's own loads in flight.  1024 threads hold a whole row of a split at once, in few registers, so that two blocks
+// a CU are full (us a launch, 256 threads / 1024: 45 rows x 4096, 8 splits 9.6 / 5.2; 256 rows x 3584 10.1 / 7.0; 2001 rows x 4096, one split
+// 35.6 / 21.3 = 5.4 TB/s, two splits 40.4 / 24.8; 512 threads 24.7 and 28.2).  The embedding, whose first wavefront or two work out angles in
+// fp64 meanwhile, so only for as many rows as are resident at once (1 row 6.2 / 5.0, 15 rows 7.2 / 5.1, 256 rows 8.9 / 6.6, 2001 rows 20.1 / 26.3).
 template <typename TW, bool EMBED, int kRowThreads, bool OP = false>
 __global__ __launch_bounds__(kRowThreads) void residual_norm_kernel(const TW *embed, const int32_t *tokens, int vocab,
                                                                     const float *partial, int S, size_t split_stride,
@@ -349,24 +351,29 @@ __global__ void truncate_to_kernel(int32_t *lens, int new_len, int B) {
 
 }  // namespace
 
+constexpr int kWideEmbedMax = 512;     // rows of an embedding launch up to which a block has 1024 threads: all of them fit the chip at once
 void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, float *x, const void *gain, float *xn,
                        float *sumsq_out, int M, int d, int vocab, float eps, RopeTable rt, uint16_t *xn16, OpRows op, ZeroFill zf,
                        const TreeShape *tree, uint32_t *tree_anc, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_EMBED, stream);
     const TreeShape ts = tree ? *tree : TreeShape{};
     if (dtype == PSD_BF16) {
-        auto go = [&](auto kernel) {
-            launch_kernel(kernel, M, 256, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0, x, (const uint16_t *)gain, xn, sumsq_out,
+        auto go = [&](auto kernel, int threads) {
+            launch_kernel(kernel, M, threads, 0, stream, (const uint16_t *)embed, tokens, vocab, nullptr, 0, 0, x, (const uint16_t *)gain, xn, sumsq_out,
                           d, eps, rt, xn16, zf, ts, tree_anc, op);
         };
-        if (op.op) go(residual_norm_kernel<uint16_t, true, 256, true>);
-        else go(residual_norm_kernel<uint16_t, true, 256>);
+        auto pick = [&](auto with_op) {
+            constexpr bool OP = decltype(with_op)::value;
+            if (M <= kWideEmbedMax) go(residual_norm_kernel<uint16_t, true, 1024, OP>, 1024);
+            else go(residual_norm_kernel<uint16_t, true, 256, OP>, 256);
+        };
+        if (op.op) pick(std::true_type{});
+        else pick(std::false_type{});
     } else
         launch_kernel(residual_norm_kernel<float, true, 256>, M, 256, 0, stream, (const float *)embed, tokens, vocab, nullptr, 0, 0, x,
                                                                         (const float *)gain, xn, sumsq_out, d, eps, rt, xn16, zf, ts, tree_anc, op);
 }
 
-constexpr int kWideRowMax = 256;       // rows up to which a norm block has 1024 threads
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
                                  int M, int d, float eps, uint16_t *xn16, OpRows op, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_RMSNORM, stream);
@@ -376,13 +383,8 @@ void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *
             launch_kernel(kernel, M, threads, 0, stream, nullptr, nullptr, 0, partial, S, stride, x, (const uint16_t *)gain, xn, nullptr, d, eps,
                           RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, op);
         };
-        auto pick = [&](auto with_op) {
-            constexpr bool OP = decltype(with_op)::value;
-            if (M <= kWideRowMax) go(residual_norm_kernel<uint16_t, false, 1024, OP>, 1024);
-            else go(residual_norm_kernel<uint16_t, false, 256, OP>, 256);
-        };
-        if (op.op) pick(std::true_type{});
-        else pick(std::false_type{});
+        if (op.op) go(residual_norm_kernel<uint16_t, false, 1024, true>, 1024);
+        else go(residual_norm_kernel<uint16_t, false, 1024, false>, 1024);
     } else
         launch_kernel(residual_norm_kernel<float, false, 256>, M, 256, 0, stream, nullptr, nullptr, 0, partial, S, stride, x,
                       (const float *)gain, xn, nullptr, d, eps, RopeTable{}, xn16, ZeroFill{}, TreeShape{}, nullptr, op);
