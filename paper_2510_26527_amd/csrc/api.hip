@@ -295,12 +295,12 @@ ForwardPlan plan_projections(const psd_model *mdl, int M) {
     p.folded = mdl->packed && d.dtype == PSD_BF16 && M <= kStreamMaxRows;
     p.sk_qkv = p.folded && !mdl->w4 && gemm_qkv_bands(n_qkv).owned ? 1 : proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
     // folded: O and down run on the column kernel (one owner per output), or, 4-bit and some down, on partial slots with the arrival epilogue
-    p.sk_o = p.folded ? (mdl->w4 ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false, true);
-    p.gated = p.folded ? !mdl->w4 : d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4);
+    p.sk_o = p.folded ? (mdl->w4 && gemm_down_by_units(d.d_model, hd) ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false, true);
+    p.gated = p.folded || (d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4));
     p.sk_gu = p.gated ? 1 : proj_splits(mdl, M, d.d_model, n_gu, 2, false);
     p.down_by_units = p.folded && !mdl->w4 && gemm_down_by_units(d.d_model, d.d_ffn);
     p.sk_down = p.down_by_units ? gemm_resid_slots(gemm_pack_tiles(n_o, 1), d.d_ffn)
-                : p.folded ? (mdl->w4 ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : 1) : proj_splits(mdl, M, d.d_ffn, n_o, 1, false, true);
+                : p.folded ? (mdl->w4 && gemm_down_by_units(d.d_model, d.d_ffn) ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : 1) : proj_splits(mdl, M, d.d_ffn, n_o, 1, false, true);
     p.half_copies = d.dtype == PSD_BF16 && (M > kStreamMaxRows || (mdl->w4 && p.folded));
     auto need = [&](int sk, int N) { const size_t b = (size_t)sk * M * N * 4; if (b > p.partial_bytes) p.partial_bytes = b; };
     need(p.sk_qkv, p.width_qkv);
@@ -474,8 +474,9 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         g.pack_tiles = gemm_pack_tiles(g.n, g.nseg);
         g.bands = g.nseg == 3 ? gemm_qkv_bands(g.n) : g.nseg == 2 ? gemm_gate_bands(n0) : kUnitBands;
         if (p.gated && dst == nullptr) {
-            if (p.folded) { g.swiglu_op = (uint16_t *)h; g.scale = rs; }
-            else g.swiglu16 = h16;
+            if (p.folded) g.scale = rs;
+            if (p.half_copies) g.swiglu16 = h16;
+            else g.swiglu_op = (uint16_t *)h;
         }
         g.w4 = m->w4 && qj >= 0;
         for (int sgm = 0; sgm < g.nseg && g.w4; ++sgm) { g.w4_scale[sgm] = m->qscale(ql, qj + sgm); g.w4_zero[sgm] = m->qzero(ql, qj + sgm); }
@@ -500,7 +501,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         if (p.folded) {
             GemmArgs g{};
             g.wpack = wpack; g.x = xin; g.x_rows_per_group = M; g.w[0] = w; g.n[0] = d.d_model; g.nseg = 1;
-            const bool slots = by_units || m->w4;         // partial slots + arrival epilogue, else one block per 16 columns
+            const bool slots = m->w4 ? gemm_down_by_units(d.d_model, K) : by_units;         // partial slots + arrival epilogue, else one block per 16 columns
             g.M = M; g.K = K; g.N = d.d_model; g.splitk = slots ? sk : 1; g.pack_tiles = gemm_pack_tiles(g.n, 1);
             g.x_op = (const uint16_t *)xin; g.op_folded = op_folded;
             g.xg_op = m->w4 && !last ? nullptr : xn_op;   // 4-bit projections read xn16, the head xn
@@ -552,7 +553,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         gemm(act, M, d.d_model, m->layer(l, W_GATE), d.d_ffn, m->layer(l, W_UP), d.d_ffn, nullptr, 0, p.sk_gu,
              p.gated ? nullptr : partial, m->pack(l, P_GU), l, 4);
         if (!p.gated)
-            launch_reduce_swiglu(partial, p.sk_gu, rs, p.half_copies ? nullptr : h, M, d.d_ffn, h16, st);
+            launch_reduce_swiglu(partial, p.sk_gu, p.half_copies ? nullptr : h, M, d.d_ffn, h16, st);
         resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), p.down_by_units, l, 6, l + 1 == d.n_layers);
     }
     bool advanced = false;                                   // the head's last kernel, the last one of its kind of pass, does it

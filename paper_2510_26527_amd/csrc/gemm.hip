@@ -24,8 +24,10 @@
 //   gemm_w4_unit_kernel      M <= 16, 4-bit weight-only quantised projections (groups of 128 along K): the unit
 //                            kernel's stream-K over quads of four K steps, the codes multiplied as exact fp16
 //                            integers against fp16-rounded activations, scale and zero point applied per group in
-//                            fp32; one partial slot per block and tile, or (O, down) the residual epilogue run by
+//                            fp32; one partial slot per block and tile, or (O, down of wide models) the residual epilogue run by
 //                            the block that arrives last.
+//   gemm_w4_column_kernel, gemm_w4_gate_kernel   the same arithmetic with one owner per output: O and down by strips of 16 columns, gate|up
+//                            by tiles of 64 with the row scale and SwiGLU in its epilogue.
 //   gemm_f16_tiled_kernel    M > 16 otherwise.  (64, 128 or 256) x (128, 192, 256) x 64 LDS-staged tiles, 32x32x16 fp16 MFMA
 //                            (weights convert to fp16 exactly, activations are rounded to fp16); the gate|up projection
 //                            applies SwiGLU itself where its tiles alone fill the chip.
@@ -822,6 +824,37 @@ __global__ __launch_bounds__(1024) void gemm_bf16_column_kernel(GemmArgs g) {
 // would overflow): half the bytes every block re-reads from L2, which weigh as much as the 4-bit weights themselves.
 constexpr int kW4Ring = 2;                         // quads in flight per wavefront (its K step of each)
 
+// One K step (group) of NS strips: acc[s][v] += y[token 4 gq + v][row i of strip s]; codes, scale words and activations as the packing and
+// the fp16 copy hold them (see above)
+template <int NS>
+__device__ __forceinline__ void w4_step(const u32x4 (&C)[NS], const uint32_t (&S)[NS], const u32x4 (&X)[4], f32x4 (&acc)[NS]) {
+    const u32x4 ones4 = u32x4{0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
+    const f16x8 ones = __builtin_bit_cast(f16x8, ones4);
+    f32x4 u[NS], xs = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NS; ++s) u[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+        const f16x8 xa = __builtin_bit_cast(f16x8, X[kb]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const uint32_t w = C[s][kb];
+            const u32x4 wi = u32x4{(w & 0x000F000Fu) | 0x64006400u, ((w >> 4) & 0x000F000Fu) | 0x64006400u,
+                                   ((w >> 8) & 0x000F000Fu) | 0x64006400u, ((w >> 12) & 0x000F000Fu) | 0x64006400u};
+            u[s] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa, __builtin_bit_cast(f16x8, wi), u[s], 0, 0, 0);
+        }
+        xs = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa, ones, xs, 0, 0, 0);       // sum of x over the group
+    }
+    // u[s][v] = sum over the group of x[token 4 gq + v] * (1024 + q[row s*16 + i]); xs[v] = sum of x[token 4 gq + v]
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const float sc = __uint_as_float(S[s] & 0xffff0000u);
+        const float zf = (float)__builtin_bit_cast(_Float16, (uint16_t)(S[s] & 0xffffu));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[s][v] += sc * (u[s][v] - zf * xs[v]);
+    }
+}
+
 template <bool RESID>
 __global__ __launch_bounds__(256) void gemm_w4_unit_kernel(GemmArgs g) {
     constexpr int R = kW4Ring;
@@ -854,8 +887,6 @@ __global__ __launch_bounds__(256) void gemm_w4_unit_kernel(GemmArgs g) {
         for (int kb = 0; kb < 4; ++kb) X[j][kb] = __builtin_amdgcn_raw_buffer_load_b128(rx, xoff + kb * 64, 0, 0);
         quad_issue = quad_issue + 1 == nq ? 0 : quad_issue + 1;
     };
-    const u32x4 ones4 = u32x4{0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
-    const f16x8 ones = __builtin_bit_cast(f16x8, ones4);
     f32x4 acc[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -869,30 +900,8 @@ __global__ __launch_bounds__(256) void gemm_w4_unit_kernel(GemmArgs g) {
         for (int j = 0; j < R; ++j) {
             const int n = base + j;
             if (n >= n_my) break;                                           // the same for all four wavefronts
-            f32x4 u[4], xs = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < 4; ++s) u[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                const f16x8 xa = __builtin_bit_cast(f16x8, X[j][kb]);
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const uint32_t w = C[j][s][kb];
-                    const u32x4 wi = u32x4{(w & 0x000F000Fu) | 0x64006400u, ((w >> 4) & 0x000F000Fu) | 0x64006400u,
-                                           ((w >> 8) & 0x000F000Fu) | 0x64006400u, ((w >> 12) & 0x000F000Fu) | 0x64006400u};
-                    u[s] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa, __builtin_bit_cast(f16x8, wi), u[s], 0, 0, 0);
-                }
-                xs = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa, ones, xs, 0, 0, 0);       // sum of x over the group
-            }
-            // u[s][v] = sum over the group of x[token 4 gq + v] * (1024 + q[row s*16 + i]); xs[v] = sum of x[token 4 gq + v]
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const uint32_t sz = S[j][s];
-                const float sc = __uint_as_float(sz & 0xffff0000u);
-                const float zf = (float)__builtin_bit_cast(_Float16, (uint16_t)(sz & 0xffffu));
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[s][v] += sc * (u[s][v] - zf * xs[v]);
-            }
+            const uint32_t sw[4] = {S[j][0], S[j][1], S[j][2], S[j][3]};
+            w4_step<4>(C[j], sw, X[j], acc);
             issue(j, n + R);
             const bool tile_end = quad_use + 1 == nq;
             quad_use = tile_end ? 0 : quad_use + 1;
@@ -909,6 +918,168 @@ __global__ __launch_bounds__(256) void gemm_w4_unit_kernel(GemmArgs g) {
             }
             if (tile_end) ++tile;
         }
+    }
+}
+
+// The 4-bit O and down projections: the column kernel's scheme (one block per 16 output columns, sixteen wavefronts on equal ranges of the K
+// steps, one owner per output, its epilogue) on the quad layout, whose steps of a tile are contiguous: a block reads its strip's 1 KB of
+// each and the strip's scale words out of the 256 bytes behind them.  What bounds it: the trip to memory and the activations, twice the
+// codes' bytes at 7 rows; but a block ends with its own sums, where the unit kernel's end with an arrival (5 us of a launch of 11 or 15).  Two
+// layers and a small head, the other projections alike (us, by units / this): 4096 x 14336 1 row 141 / 131, 7 rows 146 / 137, 16 rows
+// 172 / 161; 2048 x 8192 7 rows 112 / 94; 1024 x 4096 7 rows 104 / 84.  Not for more than 256 strips, whose blocks come in two rounds, nor
+// for a K seven times the width (gemm_down_by_units): 5120 x 13824 7 rows 175 / 190, 8192 x 28672 258 / 297, 4096 x 28672 178 / 178 and
+// at 16 rows 209 / 220.
+__global__ __launch_bounds__(1024) void gemm_w4_column_kernel(GemmArgs g) {
+    constexpr int W = 16, D = 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = lane & 15, gq = lane >> 4;
+    const int K = g.K, ns = K / kSkinnyStepK, s0 = wave * ns / W, s1 = (wave + 1) * ns / W, strip = blockIdx.x & 3;
+    const size_t tile_bytes = (size_t)w4_quads(K) * kW4QuadBytes;
+
+    const int en = threadIdx.x & 15, tok = threadIdx.x >> 4;                 // (the epilogue's operands: as in the column kernel)
+    const int ecol = blockIdx.x * 16 + en;
+    const bool mine = tok < g.M;
+    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(g.x_resid, 0, g.M * g.N * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(g.gain), 0, g.N * 2, 0x00020000);
+    const uint32_t e_res = __builtin_amdgcn_raw_buffer_load_b32(rr, mine ? (uint32_t)(tok * g.N + ecol) * 4 : 0x80000000u, 0, 0);
+    const uint16_t e_gain = __builtin_amdgcn_raw_buffer_load_b16(rg, (uint32_t)ecol * 2, 0, 0);
+
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        (char *)const_cast<void *>(g.wpack) + (blockIdx.x >> 2) * tile_bytes, 0, (int)tile_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(g.x16), 0, g.M * K * 2, 0x00020000);
+    const uint32_t xbase = i < g.M ? (uint32_t)(i * K * 2) + gq * 16u : 0x80000000u;      // a row past M reads zeros
+    const uint32_t cbase = strip * 1024u + lane * 16u, sbase = 4096u + i * 16u + strip * 4u;
+    u32x4 C[D][1], X[D][4];
+    uint32_t S[D][1];
+    f32x4 acc[1];
+    acc[0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto load_x = [&](int j, int st) {
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) X[j][kb] = __builtin_amdgcn_raw_buffer_load_b128(rx, xbase + (uint32_t)st * (kSkinnyStepK * 2) + kb * 64, 0, 0);
+    };
+    auto load_w = [&](int j, int st) {
+        C[j][0] = __builtin_amdgcn_raw_buffer_load_b128(rw, (uint32_t)st * kW4StepBytes + cbase, 0, 2);      // 2: streaming
+        S[j][0] = __builtin_amdgcn_raw_buffer_load_b32(rw, (uint32_t)st * kW4StepBytes + sbase, 0, 0);
+    };
+    int st = s0;
+    for (; st + D <= s1; st += D) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) load_x(j, st + j);
+#pragma unroll
+        for (int j = 0; j < D; ++j) load_w(j, st + j);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < D; ++j) w4_step<1>(C[j], S[j], X[j], acc);
+    }
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j)
+        if (st + j < s1) load_x(j, st + j);
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j)
+        if (st + j < s1) load_w(j, st + j);
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j)
+        if (st + j < s1) w4_step<1>(C[j], S[j], X[j], acc);
+
+    __shared__ float red[W][16][17];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][i][4 * gq + v] = acc[0][v];
+    __syncthreads();
+    if (threadIdx.x < 256) {
+        float v = 0.f, sq = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) v += red[w][en][tok];
+        if (mine) {
+            const size_t o = (size_t)tok * g.N + ecol;
+            v += __uint_as_float(e_res);
+            g.x_resid[o] = v;
+            const float xg = v * bf16_bits_to_f32(e_gain);
+            if (g.xg_op) op_store(g.xg_op, tok, ecol, g.op_folded, xg);
+            if (g.xg16_out) g.xg16_out[o] = f32_to_f16_bits(xg);
+            sq = v * v;
+        }
+        sq += __shfl_xor(sq, 8, 64);
+        sq += __shfl_xor(sq, 4, 64);
+        sq += __shfl_xor(sq, 2, 64);
+        sq += __shfl_xor(sq, 1, 64);
+        if (en == 0 && tok < g.M && g.sumsq_out) g.sumsq_out[(size_t)blockIdx.x * g.M + tok] = sq;
+    }
+}
+
+// The 4-bit gate|up projection with SwiGLU: one block per tile of 64 columns over the whole K range, four wavefronts on its gate rows and four
+// on its up rows, each on one step of every quad; the block scales its rows, applies SwiGLU and writes the fp16 operand of the down projection:
+// no partial slots and no launch to add them (two layers of the 8B shape and its head, 7 rows 303 -> 289 us; of 8192 x 28672 274 -> 258).
+__global__ __launch_bounds__(512) void gemm_w4_gate_kernel(GemmArgs g) {
+    constexpr int R = kW4Ring;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int q = wave & 3, up = wave >> 2;
+    const int i = lane & 15, gq = lane >> 4;
+    const int K = g.K, ns = K / kSkinnyStepK, nq = w4_quads(K), tiles = gridDim.x;
+    // the rows' sums of squares, requested ahead of the first weights: 32 threads a row, the first eight strips or tiles each
+    __shared__ float s_scale[16];
+    const int sm = threadIdx.x >> 5, sl = threadIdx.x & 31;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(g.scale.sumsq), 0, g.scale.tiles * g.M * 4, 0x00020000);
+    const uint32_t soff = sm < g.M ? (uint32_t)(sl * g.M + sm) * 4 : 0x80000000u;
+    uint32_t ssq[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) ssq[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, soff + (uint32_t)(t * 32 * g.M) * 4, 0, 0);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        (char *)const_cast<void *>(g.wpack) + (size_t)(blockIdx.x + up * tiles) * nq * kW4QuadBytes, 0, nq * kW4QuadBytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(g.x16), 0, g.M * K * 2, 0x00020000);
+    const uint32_t xbase = i < g.M ? (uint32_t)(i * K * 2) + gq * 16u : 0x80000000u;
+    u32x4 C[R][4], S[R], X[R][4];
+    auto issue = [&](int j, int n) {                       // quad n; past the last one, zeros
+        const uint32_t woff = (uint32_t)n * kW4QuadBytes + q * kW4StepBytes;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) C[j][s] = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + s * 1024 + lane * 16u, 0, 2);
+        S[j] = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + 4096 + i * 16u, 0, 2);
+        const int step = n * 4 + q;
+        const uint32_t xoff = step < ns ? xbase + (uint32_t)step * (kSkinnyStepK * 2) : 0x80000000u;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) X[j][kb] = __builtin_amdgcn_raw_buffer_load_b128(rx, xoff + kb * 64, 0, 0);
+    };
+    f32x4 acc[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int j) {
+        const uint32_t sw[4] = {S[j][0], S[j][1], S[j][2], S[j][3]};
+        w4_step<4>(C[j], sw, X[j], acc);
+    };
+#pragma unroll
+    for (int j = 0; j < R; ++j) issue(j, j);
+    {
+        float v = 0.f;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v += __uint_as_float(ssq[t]);
+        for (int t = 256 + sl; t < g.scale.tiles; t += 32)
+            v += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, sm < g.M ? (uint32_t)(t * g.M + sm) * 4 : 0x80000000u, 0, 0));
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if (sl == 0) s_scale[sm] = 1.0f / sqrtf(v * g.scale.inv_d + g.scale.eps);
+    }
+    for (int base = 0; base + R < nq; base += R) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            multiply(j);
+            issue(j, base + j + R);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) multiply(j);
+    __shared__ float red[2][4][kSkinnyRows][17];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[up][q][s * 16 + i][4 * gq + v] = acc[s][v];
+    __syncthreads();
+    const int row = threadIdx.x & 63, c = blockIdx.x * kSkinnyRows + row;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int tok = (threadIdx.x >> 6) + 8 * t;
+        if (tok >= g.M) break;
+        const float gt = (((red[0][0][row][tok] + red[0][1][row][tok]) + red[0][2][row][tok]) + red[0][3][row][tok]) * s_scale[tok];
+        const float uv = (((red[1][0][row][tok] + red[1][1][row][tok]) + red[1][2][row][tok]) + red[1][3][row][tok]) * s_scale[tok];
+        g.swiglu16[(size_t)tok * g.n[0] + c] = f32_to_f16_bits(gt / (1.0f + expf(-gt)) * uv);
     }
 }
 
@@ -1648,7 +1819,9 @@ void launch_gemm(int dtype, const GemmArgs &args, hipStream_t stream) {
     if (g.M <= kStreamMaxRows && g.wpack && g.w4) {
         // 32-bit offsets from the first activation row: these projections read M <= 16 consecutive rows
         ScopedProf sp(PSD_KIND_GEMM_W4, stream);
-        const bool resid = g.x_resid && g.tile_counter;
+        if (g.swiglu16) { launch_kernel(gemm_w4_gate_kernel, g.pack_tiles / 2, 512, 0, stream, g); return; }
+        if (g.x_resid && !g.tile_counter) { launch_kernel(gemm_w4_column_kernel, g.N / 16, 1024, 0, stream, g); return; }
+        const bool resid = g.x_resid;
         const int grid = gemm_w4_grid(g.pack_tiles, g.K, resid);
         if (resid)
             launch_kernel(gemm_w4_unit_kernel<true>, grid, 256, 0, stream, g);

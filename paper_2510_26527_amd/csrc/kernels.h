@@ -80,7 +80,7 @@ struct GemmArgs {
     int x_rows_per_group, x_group_stride, x_group_offset;      // row m is read from source row
                                   //   (m / x_rows_per_group) * x_group_stride + x_group_offset + m % x_rows_per_group
     int scale_rows;               // rows per tile slab of scale.sumsq
-    uint16_t *swiglu16;           // M > kStreamMaxRows; segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
+    uint16_t *swiglu16;           // M > kStreamMaxRows and 4-bit ones; segments are (gate, up): [M][n[0]] fp16 <- silu(gate) * up instead of `partial`
     const uint16_t *x_op;         // bf16, packed weights, M <= kStreamMaxRows: the activations in operand order (common.h)
     const float *x;               // fp32 activations, K contiguous: fp32 models, and bf16 ones without packed weights up to kStreamMaxRows rows
     float *reduced;               // if non-NULL: [M][N] <- sum over splits (logits), times the row scale if given
@@ -131,7 +131,7 @@ GemmBands gemm_gate_bands(int f);
 GemmBands gemm_qkv_bands(const int *n);
 size_t gemm_pack_bytes(const int *n, int nseg, int K, GemmBands b);
 int gemm_w4_slots(int K, const int *n, int nseg, bool resid);  // partial slots of a 4-bit projection (resid: the arrival epilogue's grid)
-bool gemm_down_by_units(int d_model, int d_ffn);          // bf16, packed: the down projection runs with tile_counter, on unit-major weights
+bool gemm_down_by_units(int d_model, int d_ffn);          // packed: the down projection (4-bit: O too) runs with tile_counter, on unit-major weights
 int gemm_resid_slots(int tiles, int K);                  // ... its partial slots
 int gemm_packed_splits(int K, const int *n, int nseg);   // partial slots (the splitk to use) with packed weights
 void launch_gemm_pack(const void *const *w, const int *n, int nseg, int K, void *dst, GemmBands b, hipStream_t stream);
@@ -239,7 +239,7 @@ void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale 
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
                                  int M, int d, float eps, uint16_t *xn16, OpRows op, hipStream_t stream);
 // h = silu(g) * u with [g | u] = sum over splits of partial [S][M][2f]: fp32, fp16 or both
-void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, hipStream_t stream);
+void launch_reduce_swiglu(const float *partial, int S, float *h, int M, int f, uint16_t *h16, hipStream_t stream);
 void launch_advance_lens(int32_t *lens, int B, int delta, int max_len, hipStream_t stream);
 void launch_truncate(int32_t *lens, const int32_t *base, const int32_t *keep, int offset, int cap, int B,
                      hipStream_t stream);

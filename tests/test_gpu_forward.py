@@ -586,6 +586,21 @@ def test_w4_small_models(shape, steps, ctx):
     p.close()
 
 
+@pytest.mark.parametrize("n_new", [1, 9, 16])
+@pytest.mark.parametrize("d_model,d_ffn", [(128, 128), (640, 2176), (256, 14336), (4224, 384), (128, 16384)])
+def test_w4_projections_with_one_owner_per_output(d_model, d_ffn, n_new):
+    """4-bit O and down by strips: one K step for sixteen wavefronts (128), 5 and 17, and 112 (7 each, a burst of four and one of three);
+    down, and for a wide model O too, by units (4224; 16384 against 128); gate|up by tiles of 64 columns over K of one quad that is
+    not full, of one and a quarter, and of more."""
+    shape = synth.Shape(2, d_model, 2, 1, 64, d_ffn, 200, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 64, seed=n_new, ctx=20, std=0.02, w4=True)
+    toks = synth.make_tokens(shape.vocab, (1, n_new + 2), d_ffn)
+    ran = step_launches(p, toks[:, :n_new], what="all rows' logits")
+    assert ran["swiglu"] == 0
+    p.step(toks[:, n_new:], n_logit_rows=1, what="the last row's")
+    p.close()
+
+
 def test_w4_more_than_16_rows():
     """More than 16 rows in one call run on the tiled kernel with the 4-bit weights dequantised on their way into
     LDS: a long step of one sequence (a prompt), logits for the trailing rows only or for all of them, then steps of
