@@ -271,6 +271,7 @@ struct ForwardPlan {
     bool folded;                  // RMSNorm folded into the projections (bf16, packed weights, M <= kStreamMaxRows)
     bool fused_rope;              // the attention kernel reduces, rotates and appends q / k / v itself
     bool down_by_units;           // the folded down projection runs on the unit kernel, its tiles finished by the last block to arrive
+    bool qkv_scaled;              // the QKV projection applies the norm's row scale itself, in one partial slot
     bool gated;                   // bf16: the gate|up projection applies SwiGLU itself
     size_t partial_bytes;         // of the layers' projections
 };
@@ -293,7 +294,8 @@ ForwardPlan plan_projections(const psd_model *mdl, int M) {
     p.width_qkv = hd + 2 * kvd;
     const int n_qkv[3] = {hd, kvd, kvd}, n_o[1] = {d.d_model}, n_gu[2] = {d.d_ffn, d.d_ffn};
     p.folded = mdl->packed && d.dtype == PSD_BF16 && M <= kStreamMaxRows;
-    p.sk_qkv = p.folded && !mdl->w4 && gemm_qkv_bands(n_qkv).owned ? 1 : proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
+    p.qkv_scaled = p.folded && !mdl->w4 && gemm_qkv_bands(n_qkv).owned;
+    p.sk_qkv = p.qkv_scaled ? 1 : proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
     // folded: O and down run on the column kernel (one owner per output), or, 4-bit and some down, on partial slots with the arrival epilogue
     p.sk_o = p.folded ? (mdl->w4 && gemm_down_by_units(d.d_model, hd) ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false, true);
     p.gated = p.folded || (d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4));
@@ -473,8 +475,8 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         g.M = rows; g.K = K; g.N = n0 + n1 + n2; g.partial = dst; g.splitk = sk; g.reduced = nullptr;
         g.pack_tiles = gemm_pack_tiles(g.n, g.nseg);
         g.bands = g.nseg == 3 ? gemm_qkv_bands(g.n) : g.nseg == 2 ? gemm_gate_bands(n0) : kUnitBands;
+        if (p.folded) g.scale = rs;                          // (the kernels with one owner per output apply it)
         if (p.gated && dst == nullptr) {
-            if (p.folded) g.scale = rs;
             if (p.half_copies) g.swiglu16 = h16;
             else g.swiglu_op = (uint16_t *)h;
         }
@@ -535,12 +537,13 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     for (int l = 0; l < d.n_layers; ++l) {
         gemm(act, M, d.d_model, m->layer(l, W_Q), hd, m->layer(l, W_K), kvd, m->layer(l, W_V), kvd, p.sk_qkv, partial,
              m->pack(l, P_QKV), l, 0);
+        const RowScale qkv_rs = p.qkv_scaled ? RowScale{} : rs;           // for whoever reads the partial sums
         char *kl = (char *)kv->k + (size_t)l * kv_layer, *vl = (char *)kv->v + (size_t)l * kv_layer;
         if (!p.fused_rope)
-            launch_reduce_rope_append(d.dtype, partial, p.sk_qkv, rs, q, kl, vl, kv->lens, B, n_new, d.n_q_heads,
+            launch_reduce_rope_append(d.dtype, partial, p.sk_qkv, qkv_rs, q, kl, vl, kv->lens, B, n_new, d.n_q_heads,
                                       d.n_kv_heads, d.d_head, kv->max_len, d.rope_theta, rt.cs, st);
         AttnArgs a{};
-        if (p.fused_rope) { a.qkv_partial = partial; a.qkv_splits = p.sk_qkv; a.rs = rs; a.rope_cs = rt.cs; a.tree_anc = tree_anc; }
+        if (p.fused_rope) { a.qkv_partial = partial; a.qkv_splits = p.sk_qkv; a.rs = qkv_rs; a.rope_cs = rt.cs; a.tree_anc = tree_anc; }
         a.q = q; a.k = kl; a.v = vl; a.lens = kv->lens; a.out16 = attn16;        // the O projection reads one of the three
         if (!p.half_copies) { if (p.folded) a.out_op = (uint16_t *)attn; else a.out = attn; }
         a.op_folded = op_folded;

@@ -531,7 +531,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_unit_kernel(GemmArgs g) {
 // One block per band of S strips over the whole K range (GATED: the gate band and the up band of the same columns), on weights packed
 // in these bands (gemm_qkv_bands, gemm_gate_bands), so that a block streams one contiguous range (GATED: two).  Wavefront (q, half) takes
 // K quarter q of the even or the odd steps, through a ring of two; the eight wavefronts' sums meet in LDS.  Every output has one owner:
-// QKV writes one partial slot, gate|up scales its rows, applies SwiGLU and writes the operand of the down projection, so neither needs
+// QKV scales its rows and writes one partial slot, gate|up scales, applies SwiGLU and writes the operand of the down projection, so neither needs
 // partial slots of several blocks to be written and read, nor gate|up the launch that did.
 // What bounds it: streaming the weights (180 MB of the 7B shape's gate|up in 31 us = 5.9 TB/s, its QKV of 101 MB in 18 at 15 rows) and the
 // fixed cost of a launch.  Against the unit kernel with shared tiles, and the SwiGLU launch behind it, on one box: gate|up 32.5 + 4.9 -> 30.9 us
@@ -547,15 +547,14 @@ __global__ __launch_bounds__(512) void gemm_bf16_band_kernel(GemmArgs g) {
     const int q = wave & 3, half = wave >> 2;
     const int i = lane & 15, gq = lane >> 4;
     const int K = g.K, ns = K / kSkinnyStepK;
-    // GATED: the rows' sums of squares, requested ahead of the first weights: 32 threads a row, the first eight strips or tiles each
+    // the rows' sums of squares, requested ahead of the first weights: 32 threads a row, the first eight strips or tiles each
     __shared__ float s_scale[16];
     const int sm = threadIdx.x >> 5, sl = threadIdx.x & 31;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(g.scale.sumsq), 0, g.scale.tiles * g.M * 4, 0x00020000);
     const uint32_t soff = sm < g.M ? (uint32_t)(sl * g.M + sm) * 4 : 0x80000000u;
     uint32_t ssq[8];
-    if constexpr (GATED)
 #pragma unroll
-        for (int t = 0; t < 8; ++t) ssq[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, soff + (uint32_t)(t * 32 * g.M) * 4, 0, 0);
+    for (int t = 0; t < 8; ++t) ssq[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, soff + (uint32_t)(t * 32 * g.M) * 4, 0, 0);
     constexpr uint32_t kPiece = S * 1024, kStepW = 4 * kPiece;               // a quarter of a step, a step
     auto band = [&](unsigned b) {
         return __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(g.wpack) + (size_t)b * ns * kStepW, 0, ns * kStepW, 0x00020000);
@@ -590,7 +589,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_band_kernel(GemmArgs g) {
     };
 #pragma unroll
     for (int j = 0; j < R; ++j) issue(j, j);
-    if constexpr (GATED) {
+    {
         float v = 0.f;
 #pragma unroll
         for (int t = 0; t < 8; ++t) v += __uint_as_float(ssq[t]);
@@ -638,7 +637,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_band_kernel(GemmArgs g) {
             const float gt = sum(col) * s_scale[tok], up = sum(kCols + col) * s_scale[tok];
             op_store(g.swiglu_op, tok, c, FOLD, gt / (1.0f + expf(-gt)) * up);
         } else {
-            g.partial[(size_t)tok * g.N + c] = sum(col);
+            g.partial[(size_t)tok * g.N + c] = sum(col) * s_scale[tok];
         }
     }
 }
