@@ -1275,9 +1275,10 @@ __device__ __forceinline__ u32x4 w4x8_to_f16x8(uint32_t raw, uint32_t sz) {
 // bf16 high + low pair.  Activations beyond +-65504 would overflow; none of the decoder's normalised or gated
 // activations come near.  Rows are padded to 72 elements (144 B): conflict-free 16-byte reads.  LDS is dynamic.
 //
-// What bounds it.  With many rows: instruction issue around the MFMAs (at 2048 x 8192 x 8192 the MFMAs and the barrier alone
+// What bounds it.  With many rows: the power the chip allows, i.e. its clock: 2001 x 11008 x 4096 takes 185 us on normal operands and
+// 129 (1.39 PFLOP/s) on all-zero ones, 2001 x 4096 x 22016 396 and 281 (at 2048 x 8192 x 8192 the MFMAs and the barrier alone
 // run at 1.57 PFLOP/s, with the LDS reads and stores 1.31, with the global loads too 1.12; reading both operands from L2
-// only gains nothing).  So the K loop is one straight line without a branch: every load is a buffer load whose range says
+// only gains nothing).  The loads alone are not it: tiles enter a CU at 80 to 99 B/ns while the blocks of an XCD are in step.  So the K loop is one straight line without a branch: every load is a buffer load whose range says
 // what exists (rows past the end and K tiles past the last read nothing), the next tile goes into a second set of LDS
 // tiles spread over three of the four MFMA groups of the current one, its registers are refilled with the tile after
 // it at once, the operands of the next 16 K are read ahead of the MFMAs of the current ones, and there is one barrier
@@ -1290,7 +1291,9 @@ __device__ __forceinline__ u32x4 w4x8_to_f16x8(uint32_t raw, uint32_t sz) {
 // layers and a head of the 7B shape 384 -> 374); at 65 to 128 rows that gains nothing (128 x 12288 x 4096 35.5 / 37.3).
 // Neither does a second K tile in registers (26.5), nor asking for both halves of a 256-byte row piece together (28.5),
 // nor reading the weights from the packed copy in contiguous 8 KB pieces (27.3).
-// Tried and not kept: tiles shared by several blocks added up by the last of them (256 x 256 fp32 through agent-scope
+// Tried and not kept: an order of reads, stores and MFMAs held by scheduling barriers (1 to 5 % slower), prefetches of later K tiles into L2
+// (3 %), four wavefronts of 128 x 128 with the activations straight into three stages of LDS (10 %; zeros 156 us for the 129 above),
+// 256 x 160 gate|up tiles for 256 rows (96 -> 95 us); tiles shared by several blocks added up by the last of them (256 x 256 fp32 through agent-scope
 // stores and loads: 140 us instead of 70 at 2001 x 4096 x 4096); an XCD-contiguous block order alone (no change: not
 // bound by L2 misses); four wavefronts of 128 x 128 (5 % slower than eight of 128 x 64: one wavefront per SIMD does not
 // cover its own load issue).
