@@ -100,7 +100,7 @@ struct GemmArgs {
     // -- 4-bit weights (W4A16, groups of 128 along K): wpack holds the 4-bit quad layout of
     // launch_gemm_pack_w4; the projection writes `splitk` partial slots (gemm_w4_slots)
     const void *w4_scale[3], *w4_zero[3];   // M > kStreamMaxRows: w[] are the codes [n][K/2], these the bf16 scales and uint8 zero points [n][K/128]
-    RowScale scale;               // applied when writing `reduced` or a head in whole tiles (row = the source row of m)
+    RowScale scale;               // applied when writing `reduced`, a head in whole tiles (row = the source row of m), or by bands or 4-bit gate tiles
     int32_t *lens;                // lens_n of them move on by lens_add, up to lens_max
     int lens_add, lens_max;
     // (behind the rest: ahead of it they moved what the tiled kernel reads first, 2 us over the launches of a small model's two layers)
