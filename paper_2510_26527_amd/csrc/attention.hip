@@ -917,6 +917,10 @@ int attn_pick_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int le
         const int range = ((cached + old_splits - 1) / old_splits + step - 1) / step * step;   // whole steps per block
         return (cached + range - 1) / range + 1;
     }
+    // Many rows over few keys: writing and adding two partial rows for each costs more than one block's walk of up to 512 keys.  Two splits
+    // / one (us, two layers and head of the 7B shape): 260 rows 580 / 570, 450 rows 664 / 652, 300 rows on 200 keys 605 / 594; from 8 192
+    // rows x heads on only: 200 rows x 32 heads on 300 keys 472 / 475, 8 x 16 x 32 on 400 keys (8B shape) 418 / 428.
+    if (len_bound <= 512 && (long)B * R * h_q >= 8192) return 1;
     const int by_len = (len_bound + kKeysPerBlockIter - 1) / kKeysPerBlockIter;
     int s = by_len < by_grid ? by_len : by_grid;
     return s < 1 ? 1 : s;
