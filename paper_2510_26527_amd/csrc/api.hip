@@ -394,7 +394,7 @@ bool forward_shape_ok(const psd_model *m, int batch, int n_new) {
     if (batch <= 0 || batch > 65535 || n_new <= 0) return false;
     if ((long)batch * n_new > 65535) return false;
     if ((long)batch * m->d.n_kv_heads > 65535) return false;      // grid z of the attention launch
-    if ((long)(m->d.n_q_heads / m->d.n_kv_heads) * n_new > 4096) return false;
+    if ((long)(m->d.n_q_heads / m->d.n_kv_heads) * n_new > kMaxGroupRows) return false;
     return true;
 }
 

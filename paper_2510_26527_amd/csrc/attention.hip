@@ -574,13 +574,12 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
 // 64-key tiles travel in registers (stage = tile parity) while a third is multiplied, and the next tile is stored
 // into the second set of LDS tiles in the middle of the current one's MFMAs (one barrier per tile).
 // Keys: up to the position of the block's last row, so a prompt's blocks walk half of them on average.  Where no keys are split, the
-// blocks go out by how many they walk, longest first: chunks from the last rows to the first, a chunk's place within each query head of
-// the group, heads innermost (2001 rows of the 7B shape: all keys 131 us a launch, seen keys 122 in grid order, 78 in this one; first
-// half of the blocks descending and the second ascending 91).
+// blocks go out by how many they walk, longest first (attn_chunk_order), heads innermost (2001 rows of the 7B shape: all keys 131 us a
+// launch, seen keys 122 in grid order, 78 in this one; first half of the blocks descending and the second ascending 91).
 // OP: the output in operand order (passes of up to 16 rows), a build of its own: with these stores in it the row-major one is
 // 2 200 instructions longer, and slower though it skips them (us a launch, 7B shape, 16 sequences x 20 rows 23.1 / 21.5, 12 x 20 22.0 / 20.6).
 template <int DH, int QW, int NW, bool OP>
-__global__ __launch_bounds__(NW * 64) void attn_mfma_wide_kernel(AttnArgs a, float scale_log2, int range) {
+__global__ __launch_bounds__(NW * 64) void attn_mfma_wide_kernel(AttnArgs a, float scale_log2, int range, ChunkOrder order) {
     constexpr int KS = DH / 32, DT = DH / 16;
     constexpr int KSTRIDE = DH + 8;            // fp16 elements per staged K row (+16 B: conflict-free reads)
     constexpr int VSTRIDE = 64 + 8;            // fp16 elements per staged V^T row
@@ -589,21 +588,13 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_wide_kernel(AttnArgs a, flo
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, g = lane >> 4;
     const int split = blockIdx.x;
-    int qchunk = blockIdx.y, bh = blockIdx.z;
-    if (gridDim.x == 1 && gridDim.y > 1) {                  // the chunks that see the most keys first
-        const int C = gridDim.y, group = a.h_q / a.h_kv, whole = C / group, rest = C - whole * group;
-        const int L = blockIdx.y + C * blockIdx.z, at = L / (int)gridDim.z, inner = at - rest;
-        qchunk = inner < 0 ? C - 1 - at : inner % group * whole + whole - 1 - inner / group;
-        bh = L % (int)gridDim.z;
-    }
+    const int qchunk = order.heads_inner ? order.chunk[blockIdx.z] : blockIdx.y, bh = order.heads_inner ? blockIdx.y : blockIdx.z;
     const int b = bh / a.h_kv, hk = bh % a.h_kv;
     const int group = a.h_q / a.h_kv;
     const int NQ = group * a.R;
     const int S_b = a.lens[b];
     const int n_keys = min(S_b + a.R, a.max_len);
-    // no row of the block sees past the last one's position (a block that reaches into the next query head's rows: past the step's last)
-    const int q0 = qchunk * NW * QW * 16, q1 = min(NQ, q0 + NW * QW * 16) - 1;
-    const int seen = S_b + (q0 / a.R == q1 / a.R ? q1 % a.R : a.R - 1) + 1;
+    const int seen = S_b + chunk_last_row(qchunk, NW * QW * 16, a.R, group) + 1;             // no row of the block sees past it
     const int kb0 = split * range, kb1 = min(min(n_keys, seen), kb0 + range);
     const size_t max_len = a.max_len;
     const uint16_t *Kc = (const uint16_t *)a.k + ((size_t)b * a.h_kv + hk) * max_len * DH;
@@ -866,6 +857,19 @@ inline int q_tiles(int NQ) { return NQ <= 16 ? 1 : 2; }
 inline bool use_wide(int NQ, bool tree) { return NQ > 32 || (!tree && NQ > 10); }
 inline int wide_rows(int NQ) { return NQ <= 64 ? 64 : 128; }
 
+// The LDS-staged kernel's chunks of `rows` query rows in the order of the keys that they see, most first (equal ones as they come).
+ChunkOrder attn_chunk_order(int R, int group, int rows) {
+    ChunkOrder o{};
+    o.heads_inner = 1;
+    const int C = (group * R + rows - 1) / rows;
+    for (int c = 0; c < C; ++c) {
+        int at = c;
+        for (; at > 0 && chunk_last_row(o.chunk[at - 1], rows, R, group) < chunk_last_row(c, rows, R, group); --at) o.chunk[at] = o.chunk[at - 1];
+        o.chunk[at] = (uint8_t)c;
+    }
+    return o;
+}
+
 bool attn_fuses_rope(int dtype, int R, int h_q, int h_kv, int d_h, bool tree) {
     return dtype == PSD_BF16 && (d_h == 64 || d_h == 128) && R <= 32 && !use_wide((h_q / h_kv) * R, tree);
 }
@@ -958,14 +962,16 @@ static void launch_mfma(const AttnArgs &a, hipStream_t stream) {
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
     if (wide) {
         const int rows = wide_rows(NQ);
-        dim3 wgrid(a.splits, (NQ + rows - 1) / rows, a.B * a.h_kv);
+        const unsigned wchunks = (NQ + rows - 1) / rows, heads = a.B * a.h_kv;
+        const ChunkOrder order = a.splits == 1 && wchunks > 1 ? attn_chunk_order(a.R, a.h_q / a.h_kv, rows) : ChunkOrder{};
+        const dim3 wgrid = order.heads_inner ? dim3(1, heads, wchunks) : dim3(a.splits, wchunks, heads);
         {
             ScopedProf sp(PSD_KIND_ATTN, stream);
             // two sets of (64 keys x (DH + 8), DH x (64 + 8)) fp16 tiles: more than the 64 KB a kernel gets unasked at d_head 128
             const size_t lds = 2 * (size_t)(64 * (DH + 8) + DH * 72) * sizeof(uint16_t);
             auto go = [&](auto kernel, int threads) {
                 (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                launch_kernel(kernel, wgrid, threads, lds, stream, a, scale_log2, range);
+                launch_kernel(kernel, wgrid, threads, lds, stream, a, scale_log2, range, order);
             };
             // 128 rows: eight wavefronts with one query tile each rather than four with two.  Two wavefronts per SIMD
             // overlap each other's LDS reads, exponentials and MFMAs (measured at 16 sequences x 4 KV heads x 112 query

@@ -172,6 +172,19 @@ struct AttnArgs {
     // ancestors; row r then sees the cache and exactly those rows.  NULL: rows see the rows before them.
     const uint32_t *tree_anc;
 };
+constexpr int kMaxGroupRows = 4096;        // query rows per KV head (group * R) of a forward pass
+// The order of the LDS-staged kernel's blocks: heads_inner: chunk[i] is the i-th chunk of query rows, of all heads before the next one;
+// else each head's chunks one behind the other.
+struct ChunkOrder {
+    uint8_t heads_inner, chunk[kMaxGroupRows / 128];
+};
+ChunkOrder attn_chunk_order(int R, int group, int rows);
+// the step's row (0 .. R - 1) whose position bounds what the query rows [c * rows, (c + 1) * rows) of a KV head see; query row i is row i % R
+// of head i / R of the group (a chunk that reaches into the next head's rows: the last one)
+__host__ __device__ inline int chunk_last_row(int c, int rows, int R, int group) {
+    const int q0 = c * rows, q1 = (group * R < q0 + rows ? group * R : q0 + rows) - 1;
+    return q0 / R == q1 / R ? q1 % R : R - 1;
+}
 // whether launch_attention builds its operands itself for this shape (then no rotation / append kernel runs before it)
 bool attn_fuses_rope(int dtype, int R, int h_q, int h_kv, int d_h, bool tree);
 int attn_max_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int len_bound, bool tree);

@@ -1,0 +1,43 @@
+"""CPU-side checks of the rules that choose kernels, block orders and packings: host functions of the library, called by
+their C++ names, compared with what they claim over the sizes they accept."""
+import ctypes
+import os
+import re
+import subprocess
+
+import pytest
+
+import paper_2510_26527_amd as psd
+
+
+@pytest.fixture(scope="module")
+def rule():
+    """rule(name, restype, *argtypes): the library's host function psd::name."""
+    if not os.path.exists(psd.LIB_PATH):
+        from paper_2510_26527_amd import build
+        build.build()
+    lib = psd.lib()
+    syms = subprocess.run(["nm", "-D", "--defined-only", psd.LIB_PATH], check=True, capture_output=True, text=True).stdout.split()
+
+    def find(name, restype, *argtypes):
+        f = getattr(lib, next(s for s in syms if re.match(rf"_ZN3psd{len(name)}{name}E", s)))
+        f.restype, f.argtypes = restype, argtypes
+        return f
+    return find
+
+
+class ChunkOrder(ctypes.Structure):
+    _fields_ = [("heads_inner", ctypes.c_uint8), ("chunk", ctypes.c_uint8 * 32)]
+
+
+@pytest.mark.parametrize("group", [1, 2, 3, 4, 7, 8, 16, 32, 64])
+def test_attention_chunks_go_out_longest_first(rule, group):
+    """Every chunk of 128 query rows once, in the order of the keys it sees: the position of its last row, counted row by row."""
+    order = rule("attn_chunk_order", ChunkOrder, ctypes.c_int, ctypes.c_int, ctypes.c_int)
+    for R in range(max(1, 65 // group), 4096 // group + 1, 1 if group > 16 else 7):
+        rows = [i % R for i in range(group * R)]
+        seen = [max(rows[c:c + 128]) for c in range(0, group * R, 128)]
+        o = order(R, group, 128)
+        chunks = list(o.chunk[:len(seen)])
+        assert o.heads_inner == 1 and sorted(chunks) == list(range(len(seen))), (R, group)
+        assert all(seen[a] >= seen[b] for a, b in zip(chunks, chunks[1:])), (R, group, chunks)
