@@ -213,14 +213,16 @@ def test_rows_kernel_shares_tiles_of_three_segments():
 
 
 @pytest.mark.parametrize("hq,hk,batch,n_new,ctx", [(1, 1, 1, 130, 0), (3, 1, 2, 70, 9), (8, 2, 1, 200, 33), (7, 1, 2, 75, 0), (5, 1, 1, 129, 100), (2, 2, 2, 700, 0),
-                                                    (32, 32, 1, 258, 0), (64, 16, 1, 140, 372)])
+                                                    (32, 32, 1, 258, 0), (64, 16, 1, 140, 372), (32, 32, 8, 130, 670)])
 def test_attention_of_a_prompt(hq, hk, batch, n_new, ctx):
     """Blocks of 128 query rows that walk the keys their rows see, longest first: one and several query heads per KV head, fewer blocks
     than heads in the group (70 rows), blocks that reach into the next head's rows, heads of several blocks with some left over, ragged
-    lengths; and enough rows (8 192 with the heads) over up to 512 keys for one split."""
+    lengths; enough rows (8 192 with the heads) over up to 512 keys for one split; and so many heads on so many keys (256 on 800) that each
+    head's blocks stay side by side."""
     shape = synth.Shape(1, 128, hq, hk, 128, 128, 200, 1.0e4)
     lens = [ctx - 8 * b for b in range(batch)] if ctx else None
-    p = Pair(shape, torch.bfloat16, batch, (ctx + n_new + 63) // 64 * 64, seed=n_new, ctx=ctx, lens=lens, std=0.05)
+    p = Pair(shape, torch.bfloat16, batch, (ctx + n_new + 63) // 64 * 64, seed=n_new, ctx=ctx, lens=lens, std=0.05,
+             oracle_rows=[0, batch - 1] if batch > 2 else None)
     p.step(synth.make_tokens(shape.vocab, (batch, n_new), hq), what="all rows' logits")
     p.close()
 
