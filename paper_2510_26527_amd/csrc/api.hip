@@ -298,7 +298,7 @@ ForwardPlan plan_projections(const psd_model *mdl, int M) {
     p.sk_qkv = p.qkv_scaled ? 1 : proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
     // folded: O and down run on the column kernel (one owner per output), or, 4-bit and some down, on partial slots with the arrival epilogue
     p.sk_o = p.folded ? (mdl->w4 && gemm_down_by_units(d.d_model, hd) ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false, true);
-    p.gated = p.folded || (d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4));
+    p.gated = p.folded ? !mdl->w4 || gemm_w4_gates(d.d_model, d.d_ffn) : (d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4));
     p.sk_gu = p.gated ? 1 : proj_splits(mdl, M, d.d_model, n_gu, 2, false);
     p.down_by_units = p.folded && !mdl->w4 && gemm_down_by_units(d.d_model, d.d_ffn);
     p.sk_down = p.down_by_units ? gemm_resid_slots(gemm_pack_tiles(n_o, 1), d.d_ffn)
@@ -556,7 +556,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         gemm(act, M, d.d_model, m->layer(l, W_GATE), d.d_ffn, m->layer(l, W_UP), d.d_ffn, nullptr, 0, p.sk_gu,
              p.gated ? nullptr : partial, m->pack(l, P_GU), l, 4);
         if (!p.gated)
-            launch_reduce_swiglu(partial, p.sk_gu, p.half_copies ? nullptr : h, M, d.d_ffn, h16, st);
+            launch_reduce_swiglu(partial, p.sk_gu, rs, p.half_copies ? nullptr : h, M, d.d_ffn, h16, st);
         resid_gemm(h, d.d_ffn, m->layer(l, W_DOWN), p.sk_down, m->pack(l, P_DOWN), norm_gain(l + 1), p.down_by_units, l, 6, l + 1 == d.n_layers);
     }
     bool advanced = false;                                   // the head's last kernel, the last one of its kind of pass, does it

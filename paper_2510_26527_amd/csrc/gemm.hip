@@ -27,7 +27,7 @@
 //                            fp32; one partial slot per block and tile, or (O, down of wide models) the residual epilogue run by
 //                            the block that arrives last.
 //   gemm_w4_column_kernel, gemm_w4_gate_kernel   the same arithmetic with one owner per output: O and down by strips of 16 columns, gate|up
-//                            by tiles of 64 with the row scale and SwiGLU in its epilogue.
+//                            by tiles of 64 with the row scale and SwiGLU in its epilogue (where they fill the chip).
 //   gemm_f16_tiled_kernel    M > 16 otherwise.  (64, 128 or 256) x (128, 192, 256) x 64 LDS-staged tiles, 32x32x16 fp16 MFMA
 //                            (weights convert to fp16 exactly, activations are rounded to fp16); the gate|up projection
 //                            applies SwiGLU itself where its tiles alone fill the chip.
@@ -1777,6 +1777,17 @@ static int gemm_w4_grid(int tiles, int K, bool resid) {
 int gemm_w4_slots(int K, const int *n, int nseg, bool resid) {
     const int tiles = tiles_of(n, nseg, kSkinnyRows);
     return gemm_slots_of(tiles, w4_quads(K), gemm_w4_grid(tiles, K, resid));
+}
+
+// Whether the gate|up projection of up to 16 rows runs by tiles, SwiGLU in it (gemm_w4_gate_kernel).  A block then walks all of K for its gate
+// and its up tile, and where the last round of tiles leaves many CUs without one, the longest walk is longer than in equal ranges by more
+// than the partial slots and the SwiGLU launch cost: from 18 quads on.  By ranges / by tiles, us, two layers, 1 and 9 rows, K x tiles (quads
+// longer): 8192 x 264 (30) 178 / 191, 199 / 214; 6656 x 280 (22) 165 / 175, 190 / 200; 6656 x 64 (18) 116 / 123, 136 / 144; but 6656 x 336 (16) 184 /
+// 186, 209 / 211; 4096 x 264 (14) 131 / 130, 147 / 148; 8192 x 400 (14) 208 / 204, 236 / 228; 4096 x 224 (2) 303 / 289 at 7 rows.
+bool gemm_w4_gates(int d_model, int d_ffn) {
+    const int tiles = (d_ffn + kSkinnyRows - 1) / kSkinnyRows, quads = w4_quads(d_model), cus = kStreamBlocks / 2;
+    const int grid = gemm_w4_grid(2 * tiles, d_model, false), in_range = (2 * tiles * quads + grid - 1) / grid;
+    return 2 * quads * ((tiles + cus - 1) / cus) - in_range * ((grid + cus - 1) / cus) < 18;
 }
 
 // whether whole tiles of a head of up to 16 rows leave at most a tenth of the blocks' time idle

@@ -130,6 +130,7 @@ int gemm_pack_tiles(const int *n, int nseg);
 GemmBands gemm_gate_bands(int f);
 GemmBands gemm_qkv_bands(const int *n);
 size_t gemm_pack_bytes(const int *n, int nseg, int K, GemmBands b);
+bool gemm_w4_gates(int d_model, int d_ffn);              // ... and the gate|up projection applies SwiGLU itself, up to kStreamMaxRows rows
 int gemm_w4_slots(int K, const int *n, int nseg, bool resid);  // partial slots of a 4-bit projection (resid: the arrival epilogue's grid)
 bool gemm_down_by_units(int d_model, int d_ffn);          // packed: the down projection (4-bit: O too) runs with tile_counter, on unit-major weights
 int gemm_resid_slots(int tiles, int K);                  // ... its partial slots
@@ -252,7 +253,7 @@ void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale 
 void launch_reduce_residual_norm(int dtype, const float *partial, int S, float *x, const void *gain, float *xn,
                                  int M, int d, float eps, uint16_t *xn16, OpRows op, hipStream_t stream);
 // h = silu(g) * u with [g | u] = sum over splits of partial [S][M][2f]: fp32, fp16 or both
-void launch_reduce_swiglu(const float *partial, int S, float *h, int M, int f, uint16_t *h16, hipStream_t stream);
+void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, hipStream_t stream);
 void launch_advance_lens(int32_t *lens, int B, int delta, int max_len, hipStream_t stream);
 void launch_truncate(int32_t *lens, const int32_t *base, const int32_t *keep, int offset, int cap, int B,
                      hipStream_t stream);

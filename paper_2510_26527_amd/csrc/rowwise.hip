@@ -304,17 +304,28 @@ __global__ __launch_bounds__(256) void reduce_rope_append_tiled_kernel(const flo
 }
 
 // h = silu(g) * u, four columns per thread, one row per blockIdx.y; [g | u] arrive as split-K partials of
-// the gate|up projection
-__global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float *partial, int S, size_t split_stride, float *h, int f, uint16_t *h16) {
+// the gate|up projection, to be scaled by the row's factor where its norm is folded into the projection
+__global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float *partial, int S, size_t split_stride, RowScale rs, float *h, int f,
+                                                            uint16_t *h16) {
+    __shared__ float red[4];
     const int m = blockIdx.y, f4 = f >> 2;
     const int j4 = blockIdx.x * 256 + threadIdx.x;
-    if (j4 >= f4) return;
+    float ssq = 0.f;
+    if (rs.sumsq)
+        for (int t = threadIdx.x; t < rs.tiles; t += 256) ssq += rs.sumsq[(size_t)t * gridDim.y + m];
     f32x4 g = f32x4{0.f, 0.f, 0.f, 0.f}, u = g;
-    for (int sp = 0; sp < S; ++sp) {
-        const f32x4 *row = reinterpret_cast<const f32x4 *>(partial + sp * split_stride + (size_t)m * 2 * f);
-        g += row[j4];
-        u += row[f4 + j4];
+    if (j4 < f4)
+        for (int sp = 0; sp < S; ++sp) {
+            const f32x4 *row = reinterpret_cast<const f32x4 *>(partial + sp * split_stride + (size_t)m * 2 * f);
+            g += row[j4];
+            u += row[f4 + j4];
+        }
+    if (rs.sumsq) {
+        const float sc = 1.0f / sqrtf(block_sum4(ssq, red) * rs.inv_d + rs.eps);
+        g *= sc;
+        u *= sc;
     }
+    if (j4 >= f4) return;
     f32x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
@@ -403,10 +414,10 @@ void launch_reduce_rope_append(int dtype, const float *partial, int S, RowScale 
                                                                   lens, R, h_q, h_kv, d_h, max_len, theta, cs_table);
 }
 
-void launch_reduce_swiglu(const float *partial, int S, float *h, int M, int f, uint16_t *h16, hipStream_t stream) {
+void launch_reduce_swiglu(const float *partial, int S, RowScale rs, float *h, int M, int f, uint16_t *h16, hipStream_t stream) {
     ScopedProf sp(PSD_KIND_SWIGLU, stream);
     const dim3 grid((unsigned)((f / 4 + 255) / 256), (unsigned)M);
-    launch_kernel(reduce_swiglu_kernel, grid, 256, 0, stream, partial, S, (size_t)M * 2 * f, h, f, h16);
+    launch_kernel(reduce_swiglu_kernel, grid, 256, 0, stream, partial, S, (size_t)M * 2 * f, rs, h, f, h16);
 }
 
 void launch_advance_lens(int32_t *lens, int B, int delta, int max_len, hipStream_t stream) {

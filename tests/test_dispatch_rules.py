@@ -41,3 +41,11 @@ def test_attention_chunks_go_out_longest_first(rule, group):
         chunks = list(o.chunk[:len(seen)])
         assert o.heads_inner == 1 and sorted(chunks) == list(range(len(seen))), (R, group)
         assert all(seen[a] >= seen[b] for a, b in zip(chunks, chunks[1:])), (R, group, chunks)
+
+
+@pytest.mark.parametrize("d_model,d_ffn,by_tiles", [
+    (6656, 17920, False), (8192, 16896, False), (6656, 4096, False), (5120, 128, False),
+    (3584, 18944, True), (4096, 14336, True), (8192, 28672, True), (5120, 27648, True), (4096, 16896, True)])
+def test_4bit_gate_up_by_tiles_where_they_fill_the_chip(rule, d_model, d_ffn, by_tiles):
+    """On each side of the line: widths measured to be faster in equal ranges of K, with a SwiGLU launch, and by tiles."""
+    assert rule("gemm_w4_gates", ctypes.c_bool, ctypes.c_int, ctypes.c_int)(d_model, d_ffn) == by_tiles

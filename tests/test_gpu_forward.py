@@ -604,6 +604,18 @@ def test_w4_projections_with_one_owner_per_output(d_model, d_ffn, n_new):
     p.close()
 
 
+@pytest.mark.parametrize("n_new", [1, 16])
+@pytest.mark.parametrize("d_ffn", [128, 1152])
+def test_w4_gate_up_in_ranges(d_ffn, n_new):
+    """4-bit gate|up of a wide model whose tiles leave most CUs idle (2 and 18 of them, K of ten quads): equal ranges of K in partial slots, the
+    row scale and SwiGLU where they are added."""
+    shape = synth.Shape(2, 5120, 2, 1, 64, d_ffn, 200, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 64, seed=n_new, ctx=20, std=0.02, w4=True)
+    ran = step_launches(p, synth.make_tokens(shape.vocab, (1, n_new), d_ffn), what="all rows' logits")
+    assert ran["swiglu"] == 2
+    p.close()
+
+
 def test_w4_more_than_16_rows():
     """More than 16 rows in one call run on the tiled kernel with the 4-bit weights dequantised on their way into
     LDS: a long step of one sequence (a prompt), logits for the trailing rows only or for all of them, then steps of
