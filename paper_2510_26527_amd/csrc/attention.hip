@@ -588,7 +588,7 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_wide_kernel(AttnArgs a, flo
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, g = lane >> 4;
     const int split = blockIdx.x;
-    const int qchunk = order.heads_inner ? order.chunk[blockIdx.z] : blockIdx.y, bh = order.heads_inner ? blockIdx.y : blockIdx.z;
+    const int qchunk = order.heads_inner ? order.at(blockIdx.z) : blockIdx.y, bh = order.heads_inner ? blockIdx.y : blockIdx.z;
     const int b = bh / a.h_kv, hk = bh % a.h_kv;
     const int group = a.h_q / a.h_kv;
     const int NQ = group * a.R;
@@ -872,11 +872,13 @@ ChunkOrder attn_chunk_order(int R, int group, int rows) {
     ChunkOrder o{};
     o.heads_inner = 1;
     const int C = (group * R + rows - 1) / rows;
+    uint8_t sorted[kMaxGroupRows / 128];
     for (int c = 0; c < C; ++c) {
         int at = c;
-        for (; at > 0 && chunk_last_row(o.chunk[at - 1], rows, R, group) < chunk_last_row(c, rows, R, group); --at) o.chunk[at] = o.chunk[at - 1];
-        o.chunk[at] = (uint8_t)c;
+        for (; at > 0 && chunk_last_row(sorted[at - 1], rows, R, group) < chunk_last_row(c, rows, R, group); --at) sorted[at] = sorted[at - 1];
+        sorted[at] = (uint8_t)c;
     }
+    for (int c = 0; c < C; ++c) o.chunk[c / 4] |= (uint32_t)sorted[c] << 8 * (c % 4);
     return o;
 }
 

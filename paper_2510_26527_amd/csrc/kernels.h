@@ -175,9 +175,11 @@ struct AttnArgs {
 };
 constexpr int kMaxGroupRows = 4096;        // query rows per KV head (group * R) of a forward pass
 // The order of the LDS-staged kernel's blocks: heads_inner: chunk[i] is the i-th chunk of query rows, of all heads before the next one;
-// else each head's chunks one behind the other.
+// else each head's chunks one behind the other.  Four chunks to a word, which a block reads with the scalar unit: a byte comes through the
+// vector one, and with it every bound and address that follows would be held per lane (1 to 2 us a launch).
 struct ChunkOrder {
-    uint8_t heads_inner, chunk[kMaxGroupRows / 128];
+    uint32_t heads_inner, chunk[kMaxGroupRows / 128 / 4];
+    __host__ __device__ __forceinline__ int at(unsigned i) const { return (int)(chunk[i / 4] >> 8 * (i % 4) & 255u); }
 };
 ChunkOrder attn_chunk_order(int R, int group, int rows);
 // the step's row (0 .. R - 1) whose position bounds what the query rows [c * rows, (c + 1) * rows) of a KV head see; query row i is row i % R

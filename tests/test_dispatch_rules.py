@@ -27,7 +27,7 @@ def rule():
 
 
 class ChunkOrder(ctypes.Structure):
-    _fields_ = [("heads_inner", ctypes.c_uint8), ("chunk", ctypes.c_uint8 * 32)]
+    _fields_ = [("heads_inner", ctypes.c_uint32), ("chunk", ctypes.c_uint8 * 32)]
 
 
 @pytest.mark.parametrize("group", [1, 2, 3, 4, 7, 8, 16, 32, 64])
