@@ -933,10 +933,15 @@ int attn_pick_splits(int dtype, int B, int R, int h_q, int h_kv, int d_h, int le
         const int range = ((cached + old_splits - 1) / old_splits + step - 1) / step * step;   // whole steps per block
         return (cached + range - 1) / range + 1;
     }
-    // Many rows over few keys: writing and adding two partial rows for each costs more than one block's walk of up to 512 keys.  Two splits
-    // / one (us, two layers and head of the 7B shape): 260 rows 580 / 570, 450 rows 664 / 652, 300 rows on 200 keys 605 / 594; from 8 192
-    // rows x heads on only: 200 rows x 32 heads on 300 keys 472 / 475, 8 x 16 x 32 on 400 keys (8B shape) 418 / 428.
-    if (len_bound <= 512 && (long)B * R * h_q >= 8192) return 1;
+    // Many rows over few keys: writing and adding two partial rows for each costs more than one block's walk of up to 512 keys, if one split
+    // gives the chip enough blocks; of 64-wide heads, whose partial rows are half as long, up to 448 keys or with more of them.  Two splits / one
+    // (us, two layers and head of the 7B shape): 260 rows 580 / 570, 450 rows 664 / 652, 300 rows on 200 keys 605 / 594; but 200 rows x 32 heads
+    // on 300 keys 472 / 475, 8 x 16 x 32 on 400 (8B shape) 418 / 428.  Two narrow layers, query / KV heads, rows on cached keys: 32 / 8, 2 x 129 on
+    // 383 (80 blocks) 188 / 184, 28 / 4, 375 (84) 190 / 187, 40 / 8, 263 (88) 193 / 185; but 32 / 8, 256 on 256 (64) 180 / 183, 28 / 4, 293 on 219 (68)
+    // 185 / 187, 40 / 8, 205 on 307 (72) 178 / 180.  64-wide: 16 / 16, 2 x 257 (96) 174 / 170, 32 / 8, 2 x 256 on 256 (128) 180 / 176; but 16 / 16, 512 (64)
+    // 172 / 177, 2 x 257 on 255 (96) 174 / 177.
+    const int blocks = B * h_kv * chunks;
+    if (len_bound <= 512 && (long)B * R * h_q >= 8192 && (d_h == 128 ? blocks >= 80 : blocks >= 128 || len_bound <= 448)) return 1;
     const int by_len = (len_bound + kKeysPerBlockIter - 1) / kKeysPerBlockIter;
     int s = by_len < by_grid ? by_len : by_grid;
     return s < 1 ? 1 : s;

@@ -49,3 +49,13 @@ def test_attention_chunks_go_out_longest_first(rule, group):
 def test_4bit_gate_up_by_tiles_where_they_fill_the_chip(rule, d_model, d_ffn, by_tiles):
     """On each side of the line: widths measured to be faster in equal ranges of K, with a SwiGLU launch, and by tiles."""
     assert rule("gemm_w4_gates", ctypes.c_bool, ctypes.c_int, ctypes.c_int)(d_model, d_ffn) == by_tiles
+
+
+@pytest.mark.parametrize("B,R,h_q,h_kv,d_h,keys,splits", [
+    (1, 256, 32, 8, 128, 512, 2), (1, 293, 28, 4, 128, 512, 2), (1, 205, 40, 8, 128, 512, 2), (1, 512, 16, 16, 64, 512, 2), (2, 257, 16, 16, 64, 449, 2),
+    (2, 129, 32, 8, 128, 512, 1), (1, 258, 32, 32, 128, 258, 1), (3, 150, 32, 8, 128, 510, 1), (2, 257, 16, 16, 64, 448, 1), (2, 256, 32, 8, 64, 512, 1),
+    (2, 256, 32, 8, 64, 513, 2), (1, 200, 32, 32, 128, 500, 2)])
+def test_short_prompts_keep_two_splits_where_one_leaves_cus_idle(rule, B, R, h_q, h_kv, d_h, keys, splits):
+    """Up to 512 keys in one split: 8192 rows x heads and 80 blocks of 128 query rows; of 64-wide heads 128 blocks, or up to 448 keys."""
+    pick = rule("attn_pick_splits", ctypes.c_int, *[ctypes.c_int] * 7, ctypes.c_bool)
+    assert pick(psd.PSD_BF16, B, R, h_q, h_kv, d_h, keys, False) == splits
