@@ -262,7 +262,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_skinny_kernel(GemmArgs g) {
 // the 4 KB of K quarter q are contiguous.  Rows past the end of a matrix are stored as zeros.
 constexpr int kUnitBytes = kSkinnyRows * kSkinnyStepK * 2;
 constexpr int kUnitVec = kUnitBytes / 16;          // 16-byte vectors per unit
-constexpr int kBandBlocks = 256, kBandMost = 7;
+constexpr int kBandBlocks = 256;
+constexpr int kGateLeast = 1, kGateMost = 7, kQkvLeast = 3, kQkvMost = 6;      // strips a band (the widths that are built)
 
 // GemmBands (kernels.h): a band of S strips is ns steps of 4 S KB, a step its four K quarters, a quarter the S strips' slots: what the
 // unit above is for S = 4.
@@ -1682,12 +1683,18 @@ static int band_strips(int strips, int least, int most, double *busy) {
 static uint32_t inverse_of(int s) { return (uint32_t)((0xffffffffull + s) / s); }        // ceil(2^32 / s), s > 1
 GemmBands gemm_gate_bands(int f) {
     double busy;
-    const int s = band_strips(strips_of(f), 1, kBandMost, &busy);
+    const int s = band_strips(strips_of(f), kGateLeast, kGateMost, &busy);
     return GemmBands{s, (strips_of(f) + s - 1) / s, inverse_of(s), true};
 }
+// QKV: bands where they keep at least 85 % of the CUs busy, else units in equal ranges.  Two layers, us, units / bands, 1 and 16 rows: 672 strips
+// (88 %, bands of 3) x 4096 127 / 124, 140 / 136; 960 (94 %, 4) x 8192 217 / 214, 256 / 247; 1344 (88 %, 6) x 4096 159 / 158, 180 / 173; below
+// the line 576 strips (75 %) x 2048 100 / 96, x 4096 118 / 117, but x 8192 178 / 180 and 210 / 215; 384 (50 %) x 4096 115 / 118, 131 / 134, x 8192
+// 170 / 181; 192 (25 %) x 8192 147 / 167.  The line is one for all K (a wide model has most to lose: 672 x 8192 192 / 192, 219 / 222).
+// Bands of one or two strips lose, since every block reads all activations; bands of six fill the chip up to 1536 strips (24 576 columns),
+// and two rounds of narrower ones do beyond.
 GemmBands gemm_qkv_bands(const int *n) {
     double busy;
-    const int s = band_strips(tiles_of(n, 3, kSkinnyRows) * 4, 3, 6, &busy);
+    const int s = band_strips(tiles_of(n, 3, kSkinnyRows) * 4, kQkvLeast, kQkvMost, &busy);
     return busy >= 0.85 ? GemmBands{s, 0, inverse_of(s), true} : kUnitBands;
 }
 static int gemm_stream_grid(int tiles, int K) {
@@ -1817,6 +1824,14 @@ int gemm_pick_splitk(int dtype, int M, int K, int N, const int *n, int nseg, boo
     return gemm_tiled_plan(M, K, n, nseg, false, w4).slots;
 }
 
+// calls go with `strips` as a constant, one of Least .. Most: the range of the rule that chose it
+template <int Least, int Most, typename Go>
+static void with_width(int strips, Go go) {
+    if constexpr (Least < Most)
+        if (strips != Least) return with_width<Least + 1, Most>(strips, go);
+    go(std::integral_constant<int, Least>{});
+}
+
 bool gemm_moves_lens(int dtype, const GemmArgs &g) {
     return g.reduced || (dtype == PSD_BF16 && (g.M > kStreamMaxRows || g.whole));
 }
@@ -1865,15 +1880,8 @@ void launch_gemm(int dtype, const GemmArgs &args, hipStream_t stream) {
             if (g.op_folded) launch_kernel(gemm_bf16_band_kernel<true, S, G>, blocks, 512, 0, stream, g);
             else launch_kernel(gemm_bf16_band_kernel<false, S, G>, blocks, 512, 0, stream, g);
         };
-        auto among = [&](auto gated, auto... strips) {      // (the widths that gemm_gate_bands and gemm_qkv_bands give)
-            ((g.bands.strips == decltype(strips)::value ? go(strips, gated) : void()), ...);
-        };
-        using std::integral_constant;
-        if (g.bands.paired)
-            among(std::true_type{}, integral_constant<int, 1>{}, integral_constant<int, 2>{}, integral_constant<int, 3>{}, integral_constant<int, 4>{},
-                  integral_constant<int, 5>{}, integral_constant<int, 6>{}, integral_constant<int, 7>{});
-        else
-            among(std::false_type{}, integral_constant<int, 3>{}, integral_constant<int, 4>{}, integral_constant<int, 5>{}, integral_constant<int, 6>{});
+        if (g.bands.paired) with_width<kGateLeast, kGateMost>(g.bands.strips, [&](auto strips) { go(strips, std::true_type{}); });
+        else with_width<kQkvLeast, kQkvMost>(g.bands.strips, [&](auto strips) { go(strips, std::false_type{}); });
         return;
     }
     if (g.M <= kStreamMaxRows && g.wpack) {

@@ -59,3 +59,23 @@ def test_short_prompts_keep_two_splits_where_one_leaves_cus_idle(rule, B, R, h_q
     """Up to 512 keys in one split: 8192 rows x heads and 80 blocks of 128 query rows; of 64-wide heads 128 blocks, or up to 448 keys."""
     pick = rule("attn_pick_splits", ctypes.c_int, *[ctypes.c_int] * 7, ctypes.c_bool)
     assert pick(psd.PSD_BF16, B, R, h_q, h_kv, d_h, keys, False) == splits
+
+
+class GemmBands(ctypes.Structure):
+    _fields_ = [("strips", ctypes.c_int), ("paired", ctypes.c_int), ("inverse", ctypes.c_uint32), ("owned", ctypes.c_bool)]
+
+
+def test_bands_are_of_the_widths_that_are_built(rule):
+    """Every width of a model: gate|up in whole bands of 1 to 7 strips of each matrix, QKV in bands of 3 to 6 or on shared 64-row tiles; and the
+    band of a strip as the kernels find it, by the inverse of the width."""
+    gate = rule("gemm_gate_bands", GemmBands, ctypes.c_int)
+    qkv = rule("gemm_qkv_bands", GemmBands, ctypes.POINTER(ctypes.c_int))
+    def band(b, strip):
+        return strip if b.strips == 1 else strip * b.inverse >> 32
+    for n in range(64, 64 * 1024, 64):
+        b = gate(n)
+        assert b.owned and 1 <= b.strips <= 7 and b.paired == -(-n // (16 * b.strips)), n
+        assert all(band(b, s) == s // b.strips for s in {0, b.strips - 1, b.strips, n // 16 - 1}), n
+        b = qkv((ctypes.c_int * 3)(n, 64, 64))
+        assert not b.paired and (3 <= b.strips <= 6 if b.owned else b.strips == 4), n
+        assert all(band(b, s) == s // b.strips for s in {0, b.strips - 1, b.strips, n // 16 + 7}), n
