@@ -79,3 +79,23 @@ def test_bands_are_of_the_widths_that_are_built(rule):
         b = qkv((ctypes.c_int * 3)(n, 64, 64))
         assert not b.paired and (3 <= b.strips <= 6 if b.owned else b.strips == 4), n
         assert all(band(b, s) == s // b.strips for s in {0, b.strips - 1, b.strips, n // 16 + 7}), n
+
+
+class RowsPlan(ctypes.Structure):
+    _fields_ = [("used", ctypes.c_bool), ("whole", ctypes.c_bool), ("waves", ctypes.c_int), ("tiles", ctypes.c_int), ("blocks", ctypes.c_int),
+                ("slots", ctypes.c_int)]
+
+
+@pytest.mark.parametrize("d_model,hq,hk,d_head,strips,rows", [
+    (4096, 32, 32, 128, 3, "shared"), (3840, 44, 22, 128, 3, "shared"), (2944, 58, 29, 128, 4, "shared"), (2176, 78, 39, 128, 5, "shared"),
+    (1792, 64, 64, 128, 6, "shared"), (640, 64, 64, 128, 6, "no"), (512, 60, 60, 128, 6, "whole"), (128, 44, 22, 128, 3, "no"), (256, 64, 32, 128, 4, "no"), (128, 80, 40, 128, 5, "no"), (4224, 66, 66, 64, 0, "shared")])
+def test_qkv_bands_and_who_reads_them(rule, d_model, hq, hk, d_head, strips, rows):
+    """What the GPU tests of the band kernel and of the rows kernel take their sizes for: the width of the QKV bands (0: shared 64-row tiles, not
+    bands), and whether 17 to 64 rows read them in shared tiles, in whole ones, or not (the tiled kernel on the row-major weights)."""
+    n = (ctypes.c_int * 3)(hq * d_head, hk * d_head, hk * d_head)
+    b = rule("gemm_qkv_bands", GemmBands, ctypes.POINTER(ctypes.c_int))(n)
+    assert (b.strips if b.owned else 0) == strips
+    plan = rule("gemm_rows_plan", RowsPlan, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.c_int, ctypes.c_bool)
+    for M in (17, 45, 64):
+        p = plan(M, d_model, n, 3, False)
+        assert ("whole" if p.whole else "shared" if p.used else "no") == rows, M

@@ -259,12 +259,25 @@ def test_operand_order_activations(d_model, d_ffn, n_new):
 def test_projections_in_bands(d_model, hq, hk, d_ffn, n_new):
     """QKV and gate|up by bands: gate bands of 1 to 7 strips, whole and with a last one of fewer; QKV in bands of 3 (the last one not full),
     4, 5 and 6 strips, or, narrow, on shared tiles; one, two, three and five K steps for two groups of wavefronts; folded (8 rows) and not.
-    17 rows: the rows kernel on the same packed copies."""
+    17 rows: the rows kernel on the same packed copies of gate|up (of QKV in these few steps of K the tiled kernel; the next test has more)."""
     shape = synth.Shape(1, d_model, hq, hk, 128, d_ffn, 200, 1.0e4)
     p = Pair(shape, torch.bfloat16, 1, 64, seed=n_new, ctx=9, std=0.02, pack=True)
     ran = step_launches(p, synth.make_tokens(shape.vocab, (1, n_new), d_ffn), what="all rows' logits")
     if n_new <= 16:
         assert ran["swiglu"] == 0 and ran["gemm_skinny"] == 3
+    p.close()
+
+
+@pytest.mark.parametrize("n_new", [16, 17, 45, 64])
+@pytest.mark.parametrize("d_model,hq,hk", [(4096, 32, 32), (3840, 44, 22), (2944, 58, 29), (2176, 78, 39), (1792, 64, 64), (512, 60, 60)])
+def test_rows_kernel_reads_bands(d_model, hq, hk, n_new):
+    """QKV in bands of 3, 3, 4, 5 and 6 strips, read by the rows kernel in tiles of eight strips that blocks share: tiles that begin in the middle of a
+    band, bands (of 3 and 5) that hold the end of Q and the beginning of K, a last one that is not full; and bands of 6 in whole tiles of 6.
+    16 rows: the band kernel itself."""
+    shape = synth.Shape(1, d_model, hq, hk, 128, 128, 200, 1.0e4)
+    p = Pair(shape, torch.bfloat16, 1, 128, seed=n_new, ctx=20, std=0.02, pack=True)
+    ran = step_launches(p, synth.make_tokens(shape.vocab, (1, n_new), hq), n_logit_rows=3, what="three rows' logits")
+    assert n_new > 16 or ran["gemm_skinny"] == 3
     p.close()
 
 
