@@ -270,7 +270,7 @@ struct ForwardPlan {
     bool half_copies;             // bf16, M > kStreamMaxRows or 4-bit projections: the producers also leave fp16 copies of the activations
     bool folded;                  // RMSNorm folded into the projections (bf16, packed weights, M <= kStreamMaxRows)
     bool fused_rope;              // the attention kernel reduces, rotates and appends q / k / v itself
-    bool down_by_units;           // the folded down projection runs on the unit kernel, its tiles finished by the last block to arrive
+    bool o_by_units, down_by_units;       // the folded O / down projection runs on the unit kernels, its tiles finished by the last block to arrive
     bool qkv_scaled;              // the QKV projection applies the norm's row scale itself, in one partial slot
     bool gated;                   // bf16: the gate|up projection applies SwiGLU itself
     size_t partial_bytes;         // of the layers' projections
@@ -296,13 +296,17 @@ ForwardPlan plan_projections(const psd_model *mdl, int M) {
     p.folded = mdl->packed && d.dtype == PSD_BF16 && M <= kStreamMaxRows;
     p.qkv_scaled = p.folded && !mdl->w4 && gemm_qkv_bands(n_qkv).owned;
     p.sk_qkv = p.qkv_scaled ? 1 : proj_splits(mdl, M, d.d_model, n_qkv, 3, false);
-    // folded: O and down run on the column kernel (one owner per output), or, 4-bit and some down, on partial slots with the arrival epilogue
-    p.sk_o = p.folded ? (mdl->w4 && gemm_down_by_units(d.d_model, hd) ? gemm_w4_slots(hd, n_o, 1, true) : 1) : proj_splits(mdl, M, hd, n_o, 1, false, true);
+    // folded: O and down run on the column kernels (one owner per output), or, some down and 4-bit O, on partial slots with the arrival epilogue
+    p.o_by_units = p.folded && mdl->w4 && gemm_down_by_units(d.d_model, hd);
+    p.down_by_units = p.folded && gemm_down_by_units(d.d_model, d.d_ffn);
+    auto resid_splits = [&](int K, bool by_units) {
+        if (!p.folded) return proj_splits(mdl, M, K, n_o, 1, false, true);
+        return !by_units ? 1 : mdl->w4 ? gemm_w4_slots(K, n_o, 1, true) : gemm_resid_slots(gemm_pack_tiles(n_o, 1), K);
+    };
+    p.sk_o = resid_splits(hd, p.o_by_units);
+    p.sk_down = resid_splits(d.d_ffn, p.down_by_units);
     p.gated = p.folded ? !mdl->w4 || gemm_w4_gates(d.d_model, d.d_ffn) : (d.dtype == PSD_BF16 && M > kStreamMaxRows && gemm_tiled_gates(M, d.d_model, n_gu, mdl->packed && !mdl->w4));
     p.sk_gu = p.gated ? 1 : proj_splits(mdl, M, d.d_model, n_gu, 2, false);
-    p.down_by_units = p.folded && !mdl->w4 && gemm_down_by_units(d.d_model, d.d_ffn);
-    p.sk_down = p.down_by_units ? gemm_resid_slots(gemm_pack_tiles(n_o, 1), d.d_ffn)
-                : p.folded ? (mdl->w4 && gemm_down_by_units(d.d_model, d.d_ffn) ? gemm_w4_slots(d.d_ffn, n_o, 1, true) : 1) : proj_splits(mdl, M, d.d_ffn, n_o, 1, false, true);
     p.half_copies = d.dtype == PSD_BF16 && (M > kStreamMaxRows || (mdl->w4 && p.folded));
     auto need = [&](int sk, int N) { const size_t b = (size_t)sk * M * N * 4; if (b > p.partial_bytes) p.partial_bytes = b; };
     need(p.sk_qkv, p.width_qkv);
@@ -354,7 +358,7 @@ void plan_layout(const psd_model *mdl, int batch, int n_new, int len_bound, bool
     p.off_pml = take(p.attn_splits > 1 ? (size_t)M * d.n_q_heads * p.attn_splits * 2 * 4 : 0);
     p.off_sumsq = take(p.folded ? (size_t)(d.d_model / 16) * M * 4 : 0);
     p.off_rope = take(d.dtype == PSD_BF16 ? (size_t)M * (d.d_head / 2) * sizeof(float2) : 0);
-    p.off_tilectr = take(p.down_by_units || (p.folded && mdl->w4) ? (size_t)gemm_pack_tiles(n_o, 1) * 4 : 0);       // arrival counters
+    p.off_tilectr = take(p.o_by_units || p.down_by_units ? (size_t)gemm_pack_tiles(n_o, 1) * 4 : 0);       // arrival counters
     p.off_tree = take(p.fused_rope ? (size_t)kTreeMaxNodes * 4 : 0);      // ancestor masks of a tree pass
     p.total = off;
 }
@@ -459,7 +463,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     (void)hipGetLastError();
     auto norm_gain = [&](int l) { return l < d.n_layers ? m->layer(l, W_ATTN_NORM) : m->final_norm(); };
     const bool op_folded = M <= kOpFoldRows;
-    const bool arrivals = p.folded && (m->w4 || p.down_by_units);        // some tiles are finished by the last block to arrive
+    const bool arrivals = p.o_by_units || p.down_by_units;               // some tiles are finished by the last block to arrive
     unsigned *tile_ctr = arrivals ? (unsigned *)(ws + p.off_tilectr) : nullptr;
     RowScale rs{nullptr, 0, 1.0f / (float)d.d_model, d.rms_eps};
     // ql, qj: layer and index of the first segment among the layer's 4-bit projections (q k v o gate up down), if any
@@ -499,19 +503,18 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
     const OpRows head_rows{head_op ? xn_op : nullptr, n_new, n_new - n_logit_rows, B * n_logit_rows <= kOpFoldRows};
     const float *act = xn;     // what QKV / gate|up / lm_head read: rmsnorm(x) * gain, or x * gain when folded
     auto resid_gemm = [&](const float *xin, int K, const void *w, int sk, const void *wpack, const void *next_gain,
-                          bool by_units, int ql, int qj, bool last = false) {
+                          bool by_units, int ql, int qj, bool last = false) {        // by_units: partial slots + arrival epilogue, else one block per 16 columns
         if (p.folded) {
             GemmArgs g{};
             g.wpack = wpack; g.x = xin; g.x_rows_per_group = M; g.w[0] = w; g.n[0] = d.d_model; g.nseg = 1;
-            const bool slots = m->w4 ? gemm_down_by_units(d.d_model, K) : by_units;         // partial slots + arrival epilogue, else one block per 16 columns
-            g.M = M; g.K = K; g.N = d.d_model; g.splitk = slots ? sk : 1; g.pack_tiles = gemm_pack_tiles(g.n, 1);
+            g.M = M; g.K = K; g.N = d.d_model; g.splitk = sk; g.pack_tiles = gemm_pack_tiles(g.n, 1);
             g.x_op = (const uint16_t *)xin; g.op_folded = op_folded;
             g.xg_op = m->w4 && !last ? nullptr : xn_op;   // 4-bit projections read xn16, the head xn
             g.bands = kUnitBands; g.x_resid = x; g.xg16_out = xn16; g.gain = next_gain; g.sumsq_out = sumsq; g.w4 = m->w4;
             g.x16 = xin == attn ? attn16 : (xin == h ? h16 : nullptr);
-            if (slots) { g.tile_counter = tile_ctr; g.partial = partial; }
+            if (by_units) { g.tile_counter = tile_ctr; g.partial = partial; }
             launch_gemm(d.dtype, g, st);
-            rs.tiles = slots ? g.pack_tiles : col_tiles;
+            rs.tiles = by_units ? g.pack_tiles : col_tiles;
         } else {
             gemm(xin, M, K, w, d.d_model, nullptr, 0, nullptr, 0, sk, partial, nullptr, ql, qj);       // (packed strip-major: for the column kernel alone)
             const bool to_head = last && head_op;
@@ -552,7 +555,7 @@ static psd_status forward_once(psd_model *m, const int32_t *tokens_dev, int32_t 
         a.splits = p.attn_splits;
         launch_attention(d.dtype, a, st);
 
-        resid_gemm(attn, hd, m->layer(l, W_O), p.sk_o, m->pack(l, P_O), m->layer(l, W_FFN_NORM), false, l, 3);
+        resid_gemm(attn, hd, m->layer(l, W_O), p.sk_o, m->pack(l, P_O), m->layer(l, W_FFN_NORM), p.o_by_units, l, 3);
         gemm(act, M, d.d_model, m->layer(l, W_GATE), d.d_ffn, m->layer(l, W_UP), d.d_ffn, nullptr, 0, p.sk_gu,
              p.gated ? nullptr : partial, m->pack(l, P_GU), l, 4);
         if (!p.gated)

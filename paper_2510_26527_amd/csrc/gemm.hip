@@ -1015,7 +1015,8 @@ __global__ __launch_bounds__(512) void gemm_w4_gate_kernel(GemmArgs g) {
     const int q = wave & 3, up = wave >> 2;
     const int i = lane & 15, gq = lane >> 4;
     const int K = g.K, ns = K / kSkinnyStepK, nq = w4_quads(K), tiles = gridDim.x;
-    // the rows' sums of squares, requested ahead of the first weights: 32 threads a row, the first eight strips or tiles each
+    // the rows' sums of squares, requested ahead of the first weights: 32 threads a row, up to eight strips or tiles each (O leaves a sum per
+    // strip up to a width of 4096, per tile of 64 columns above: 256 at most)
     __shared__ float s_scale[16];
     const int sm = threadIdx.x >> 5, sl = threadIdx.x & 31;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(g.scale.sumsq), 0, g.scale.tiles * g.M * 4, 0x00020000);
@@ -1051,8 +1052,6 @@ __global__ __launch_bounds__(512) void gemm_w4_gate_kernel(GemmArgs g) {
         float v = 0.f;
 #pragma unroll
         for (int t = 0; t < 8; ++t) v += __uint_as_float(ssq[t]);
-        for (int t = 256 + sl; t < g.scale.tiles; t += 32)
-            v += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, sm < g.M ? (uint32_t)(t * g.M + sm) * 4 : 0x80000000u, 0, 0));
 #pragma unroll
         for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
         if (sl == 0) s_scale[sm] = 1.0f / sqrtf(v * g.scale.inv_d + g.scale.eps);
