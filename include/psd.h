@@ -110,10 +110,10 @@ psd_status psd_model_create_w4(const psd_model_desc *desc, const void *const *we
 /* Optional streaming copy of the projection weights for verify steps and batches of up to 128 rows
  * (batch * n_new <= 128), where the forward pass is bound by reading the weights once from HBM.
  * psd_model_pack rewrites every projection matrix into caller memory in the order the
- * wavefronts of the streaming GEMMs load it (64-row x 128-column units of 16 KB, each stored
- * as the 64 lanes' 16-byte operands, units of one projection contiguous; for the O and most models' down
- * projections 16 rows x all columns in one piece), so that each
- * wavefront reads one contiguous byte range.  packed_mem: device, 256-byte aligned, at least
+ * wavefronts of the streaming GEMMs load it (strips of 16 rows x 128 columns, each stored as the 64 lanes' 16-byte
+ * operands, and these in the order of the kernel that streams the projection: all of K of a few strips, or of one, in one
+ * piece, or units of four strips), so that each block reads contiguous byte ranges.  The layout follows from the model's sizes
+ * and is the library's own.  packed_mem: device, 256-byte aligned, at least
  * psd_model_packed_bytes() bytes (about the size of the weights), kept alive with the model;
  * the row-major weights stay in use for larger steps and must stay alive too.  After a
  * successful call, forwards with batch * n_new <= 16 read the packed copy, and those of up to 128 rows

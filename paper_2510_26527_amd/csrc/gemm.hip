@@ -14,9 +14,9 @@
 //                            K quarters of every unit, and writes one partial per tile it touches.
 //                            With RESID (the down projection of wide models and very long ones) the block that arrives
 //                            last at a tile adds the tile's partials and runs the residual epilogue below.
-//   gemm_bf16_band_kernel    M <= 16: QKV (wide ones) and gate|up, one block per band of 16-row strips over the whole K range; gate|up with
-//                            the row scale and SwiGLU in its epilogue.
-//   gemm_bf16_rows_kernel    17 to 128 rows on the same units: the weights stream into MFMA operands as above, the
+//   gemm_bf16_band_kernel    M <= 16: QKV (wide ones) and gate|up, one block per band of 16-row strips over the whole K range, the row
+//                            scale in its epilogue, gate|up with SwiGLU.
+//   gemm_bf16_rows_kernel    17 to 128 rows on the same units and bands: the weights stream into MFMA operands as above, the
 //                            activations (fp16) go through LDS; whole tiles where they fill the chip.
 //   gemm_bf16_column_kernel  M <= 16, the projections that write the residual stream (O, most models' down): one
 //                            block per 16 output columns over the whole K range; the residual add, the
@@ -1275,10 +1275,12 @@ __device__ __forceinline__ u32x4 w4x8_to_f16x8(uint32_t raw, uint32_t sz) {
 // bf16 high + low pair.  Activations beyond +-65504 would overflow; none of the decoder's normalised or gated
 // activations come near.  Rows are padded to 72 elements (144 B): conflict-free 16-byte reads.  LDS is dynamic.
 //
-// What bounds it.  With many rows: the power the chip allows, i.e. its clock: 2001 x 11008 x 4096 takes 185 us on normal operands and
-// 129 (1.39 PFLOP/s) on all-zero ones, 2001 x 4096 x 22016 396 and 281 (at 2048 x 8192 x 8192 the MFMAs and the barrier alone
-// run at 1.57 PFLOP/s, with the LDS reads and stores 1.31, with the global loads too 1.12; reading both operands from L2
-// only gains nothing).  The loads alone are not it: tiles enter a CU at 80 to 99 B/ns while the blocks of an XCD are in step.  So the K loop is one straight line without a branch: every load is a buffer load whose range says
+// What bounds it.  With many rows: not one thing.  At 2048 x 8192 x 8192 the MFMAs and the barrier alone run at 1.57 PFLOP/s, with the LDS
+// reads and stores 1.31, with the global loads too 1.12 (reading both operands from L2 only gains nothing; tiles alone enter a CU at 80
+// to 99 B/ns while the blocks of an XCD are in step): about 30 % go outside the MFMAs.  The clock, which falls with what the operands make
+// the chip spend, is another part: 2001 x 11008 x 4096 takes 185 us on normal operands and 129 (1.39 PFLOP/s) on all-zero ones,
+// 2001 x 4096 x 22016 396 and 281.  Of 129 to 256 rows, one row of 256-row tiles, a narrow product leaves CUs without a tile (256 x 3584 x 3584:
+// 112 blocks).  So the K loop is one straight line without a branch: every load is a buffer load whose range says
 // what exists (rows past the end and K tiles past the last read nothing), the next tile goes into a second set of LDS
 // tiles spread over three of the four MFMA groups of the current one, its registers are refilled with the tile after
 // it at once, the operands of the next 16 K are read ahead of the MFMAs of the current ones, and there is one barrier
@@ -1770,10 +1772,10 @@ void launch_gemm_pack_w4(const void *const *q, const void *const *scale, const v
     }
 }
 
-// grid and partial slots of a 4-bit projection: the unit kernel's policy with the quad as the unit, except that a
+// grid and partial slots of a 4-bit projection in equal ranges: the unit kernel's policy with the quad as the unit, except that a
 // block gets at least three quads where that still leaves one block per CU (measured on the LLaMA3-8B shape: QKV,
-// 768 quads, 8.0 us on 512 blocks and 7.2 us on 256; gate|up, 3584 quads, 15.3 us on 512 and 17.6 us on 256; the
-// residual projections 15.4 us (down) on 256 blocks, 16.9 us on 512, 18.9 us on 128)
+// 768 quads, 8.0 us on 512 blocks and 7.2 us on 256; a gate|up of 3584 quads 15.3 us on 512 and 17.6 us on 256; a down projection
+// with the arrival epilogue 15.4 us on 256 blocks, 16.9 us on 512, 18.9 us on 128)
 static int gemm_w4_grid(int tiles, int K, bool resid) {
     const long U = (long)tiles * w4_quads(K);
     long cap = kStreamBlocks / 2;

@@ -50,9 +50,6 @@ struct RowScale {
     int tiles;
     float inv_d, eps;
 };
-// What the kernels read first stands first: a block begins by waiting for the 64-byte lines of arguments that it needs, every launch
-// brings them in anew (the implicit ones, the grid's size among them, lie behind this struct).  Tiled launches of 22 rows, us, with
-// M, K, n, the tile count and the grid's size on four lines / on the first: 4608 x 3584 12.3 / 11.9, 3584 x 3584 11.0 / 10.5.
 // How a packed copy groups its strips of 16 rows: `strips` of them a band, the strips of all matrices one behind the other, or, paired
 // (gate|up), each matrix in whole bands.  Bands of four are the 64-row tiles of the unit kernel.
 struct GemmBands {
@@ -62,6 +59,9 @@ struct GemmBands {
     bool owned;                   // up to kStreamMaxRows rows the band kernel runs: one block a band, or a pair of them
 };
 constexpr GemmBands kUnitBands{4, 0, 1u << 30, false};
+// What the kernels read first stands first: a block begins by waiting for the 64-byte lines of arguments that it needs, every launch
+// brings them in anew (the implicit ones, the grid's size among them, lie behind this struct).  Tiled launches of 22 rows, us, with
+// M, K, n, the tile count and the grid's size on four lines / on the first: 4608 x 3584 12.3 / 11.9, 3584 x 3584 11.0 / 10.5.
 struct GemmArgs {
     int M, K, N, nseg;            // N = sum n[i]
     int n[3];
