@@ -574,7 +574,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 2 : 1) void attn_mfma_kernel(AttnA
 // 64-key tiles travel in registers (stage = tile parity) while a third is multiplied, and the next tile is stored
 // into the second set of LDS tiles in the middle of the current one's MFMAs (one barrier per tile).
 // Keys: up to the position of the block's last row, so a prompt's blocks walk half of them on average.  Where no keys are split, the
-// blocks go out by how many they walk (longest_first), heads innermost (2001 rows of the 7B shape: all keys 131 us a
+// blocks go out by how many they walk (attn_longest_first), heads innermost (2001 rows of the 7B shape: all keys 131 us a
 // launch, seen keys 122 in grid order, 78 in this one; first half of the blocks descending and the second ascending 91).
 // OP: the output in operand order (passes of up to 16 rows), a build of its own: with these stores in it the row-major one is
 // 2 200 instructions longer, and slower though it skips them (us a launch, 7B shape, 16 sequences x 20 rows 23.1 / 21.5, 12 x 20 22.0 / 20.6).
@@ -859,12 +859,15 @@ inline int wide_rows(int NQ) { return NQ <= 64 ? 64 : 128; }
 
 // Whether the LDS-staged kernel's blocks go out longest first, heads innermost.  Between a head's chunks the K and V of all others then pass
 // through the 256 MB last-level cache, where a head's chunks side by side read theirs once: with more than that, or, where one chunk of
-// every head fills the chip, so that none of a head's run together, from about 100 MB on, the chunks stay side by side (longest first / side
-// by side, us, two layers, 128-wide heads: 32 x 40 rows on 4000 keys of 8 KV heads, 530 MB, 1124 / 1064; 8 x 200 of 32, 157 MB, 1118 / 1108;
-// 64 x 40 on 1000 of 4, 136 MB, 1067 / 1057; but 2 x 700 on 4000 of 32, 154 MB and 64 heads, 1270 / 1295, and 8 x 500 of 32, 66 MB, 1950 / 1985).
-static bool longest_first(int B, int h_kv, int d_h, int len_bound) {
-    const long heads = (long)B * h_kv, bytes = heads * len_bound * d_h * 4;
-    return bytes <= (heads < 256 ? 256l << 20 : 96l << 20);
+// every head fills the chip, so that none of a head's run together, from about 100 MB on, the chunks stay side by side, unless the step has so
+// many rows that the even end gains more, up to half a MB for each (861 calls).  Longest first / side by side, us, two layers, query / KV heads,
+// sequences x rows on cached keys: 32 / 8, 32 x 40 on 4000 (530 MB) 726 / 681; 32 / 32, 8 x 200 on 1000 (157 MB) 485 / 479; 64 / 16, 32 x 200 on 1000
+// (300 MB) 2103 / 1996; 32 / 8, 32 x 500 on 2000 (312 MB) 3557 / 3549; but 64 / 16, 16 x 1000 (125 MB) 3511 / 4129; 32 / 32, 8 x 500 on 500 (125 MB)
+// 805 / 834; 16 x 1000 on 1000 (500 MB) 3556 / 3733; 32 / 8, 16 x 1000 on 4000 (312 MB, 128 heads) 5281 / 5555.
+bool attn_longest_first(int B, int R, int h_kv, int d_h, int len_bound) {
+    const long heads = (long)B * h_kv, bytes = heads * len_bound * d_h * 4, even = (long)R << 19;
+    const long most = heads < 256 ? 256l << 20 : 96l << 20;
+    return bytes <= (most > even ? most : even);
 }
 
 // The LDS-staged kernel's chunks of `rows` query rows in the order of the keys that they see, most first (equal ones as they come).
@@ -980,7 +983,8 @@ static void launch_mfma(const AttnArgs &a, hipStream_t stream) {
     if (wide) {
         const int rows = wide_rows(NQ);
         const unsigned wchunks = (NQ + rows - 1) / rows, heads = a.B * a.h_kv;
-        const ChunkOrder order = a.splits == 1 && wchunks > 1 && longest_first(a.B, a.h_kv, DH, a.len_bound) ? attn_chunk_order(a.R, a.h_q / a.h_kv, rows) : ChunkOrder{};
+        const bool longest = a.splits == 1 && wchunks > 1 && attn_longest_first(a.B, a.R, a.h_kv, DH, a.len_bound);
+        const ChunkOrder order = longest ? attn_chunk_order(a.R, a.h_q / a.h_kv, rows) : ChunkOrder{};
         const dim3 wgrid = order.heads_inner ? dim3(1, heads, wchunks) : dim3(a.splits, wchunks, heads);
         {
             ScopedProf sp(PSD_KIND_ATTN, stream);

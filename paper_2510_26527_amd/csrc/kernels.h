@@ -182,6 +182,7 @@ struct ChunkOrder {
     __host__ __device__ __forceinline__ int at(unsigned i) const { return (int)(chunk[i / 4] >> 8 * (i % 4) & 255u); }
 };
 ChunkOrder attn_chunk_order(int R, int group, int rows);
+bool attn_longest_first(int B, int R, int h_kv, int d_h, int len_bound);
 // the step's row (0 .. R - 1) whose position bounds what the query rows [c * rows, (c + 1) * rows) of a KV head see; query row i is row i % R
 // of head i / R of the group (a chunk that reaches into the next head's rows: the last one)
 __host__ __device__ inline int chunk_last_row(int c, int rows, int R, int group) {

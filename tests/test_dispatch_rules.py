@@ -43,6 +43,14 @@ def test_attention_chunks_go_out_longest_first(rule, group):
         assert all(seen[a] >= seen[b] for a, b in zip(chunks, chunks[1:])), (R, group, chunks)
 
 
+@pytest.mark.parametrize("B,R,h_kv,d_h,keys,longest", [
+    (16, 1000, 16, 128, 1000, True), (8, 500, 32, 128, 1000, True), (16, 1000, 32, 128, 2000, True), (16, 1000, 8, 128, 5000, True), (2, 700, 32, 128, 4700, True),
+    (32, 40, 8, 128, 4040, False), (8, 200, 32, 128, 1200, False), (32, 200, 16, 128, 1200, False), (32, 500, 8, 128, 2500, False)])
+def test_attention_order_by_the_bytes_between_a_heads_chunks(rule, B, R, h_kv, d_h, keys, longest):
+    """On each side of the line: batches measured to be faster longest first, and with each head's blocks side by side."""
+    assert rule("attn_longest_first", ctypes.c_bool, *[ctypes.c_int] * 5)(B, R, h_kv, d_h, keys) == longest
+
+
 @pytest.mark.parametrize("d_model,d_ffn,by_tiles", [
     (6656, 17920, False), (8192, 16896, False), (6656, 4096, False), (5120, 128, False),
     (3584, 18944, True), (4096, 14336, True), (8192, 28672, True), (5120, 27648, True), (4096, 16896, True)])
