@@ -38,7 +38,7 @@ def stream_kernel_bytes(shape):
 
 
 def measured_traffic_bytes():
-    """HBM bytes per launch of gemm_bf16_band_kernel and gemm_bf16_unit_kernel as measured with rocprofv3 --pmc FETCH_SIZE /
+    """HBM bytes per launch of gemm_bf16_band_kernel and gemm_bf16_unit_kernel together as measured with rocprofv3 --pmc FETCH_SIZE /
     WRITE_SIZE (the committed summary under profiles/ records the commands); None if it is not there."""
     path = os.path.join(ROOT, "profiles", "bench_verify_step_llama2_7b_hbm_traffic.txt")
     try:
@@ -274,16 +274,30 @@ def main():
     psd.psd_profile_enable(0)
     kernels = {k: {"launches_per_step": c / prof_steps, "avg_us": 1e3 * ms / c, "ms_per_step": ms / prof_steps}
                for k, (ms, c) in prof.items() if c}
-    # dominant kernel: gemm_bf16_band_kernel (QKV and gate|up, the latter with SwiGLU in it; with the lm_head on gemm_bf16_unit_kernel 65
-    # launches per step, 70 % of the step's bytes); the O / down projections (column kernel) beside it
+    # dominant kernel: gemm_bf16_band_kernel (QKV and gate|up, the latter with SwiGLU in it); the event kind counts the lm_head on
+    # gemm_bf16_unit_kernel with it (65 launches per step, 70 % of the step's bytes).  Gate|up alone from the first layer: the pass' first
+    # launches up to it, less those before it.  The O / down projections (column kernel) beside it
+    def first_launches_ms(n):
+        psd.psd_profile_enable(n)
+        ms = 0.0
+        for _ in range(prof_steps):
+            step()
+            ms += psd.psd_profile_collect()["gemm_skinny"][0]
+        psd.psd_profile_enable(0)
+        return ms / prof_steps
+
+    before_gate = 4 + (1 if prof["attn_combine"][1] else 0)           # embedding, QKV, attention and combine, O
+    gate_us = 1e3 * (first_launches_ms(before_gate + 1) - first_launches_ms(before_gate))
+    gate_gbs = projection_bytes(shape)["gate|up"] / (gate_us * 1e-6) / 1e9
     sk_ms, sk_n = prof["gemm_skinny"]
     w_bytes = weight_stream_bytes(shape)
     stream_bytes = stream_kernel_bytes(shape)
     achieved = stream_bytes * prof_steps / (sk_ms * 1e-3) / 1e9
-    roofline = {"kernel": "gemm_bf16_band_kernel (lm_head: gemm_bf16_unit_kernel)", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
+    roofline = {"kernel": "gemm_bf16_band_kernel (QKV, gate|up), averaged with the lm_head's gemm_bf16_unit_kernel", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic_bytes(),
                 "bytes_per_launch": stream_bytes * prof_steps / sk_n, "avg_launch_us": 1e3 * sk_ms / sk_n,
                 "launches_per_step": sk_n / prof_steps,
+                "gate_up_alone": {"avg_launch_us": gate_us, "achieved": gate_gbs, "frac": gate_gbs / HBM_PEAK_GBS},
                 "measured_stream_read_GB/s": ceilings["stream_read_GB/s"],
                 "frac_of_measured_stream_read": achieved / ceilings["stream_read_GB/s"]}
     gemm_ms = sk_ms
