@@ -875,10 +875,12 @@ ChunkOrder attn_chunk_order(int R, int group, int rows) {
     ChunkOrder o{};
     o.heads_inner = 1;
     const int C = (group * R + rows - 1) / rows;
+    int last[kMaxGroupRows / 128];
     uint8_t sorted[kMaxGroupRows / 128];
     for (int c = 0; c < C; ++c) {
         int at = c;
-        for (; at > 0 && chunk_last_row(sorted[at - 1], rows, R, group) < chunk_last_row(c, rows, R, group); --at) sorted[at] = sorted[at - 1];
+        last[c] = chunk_last_row(c, rows, R, group);
+        for (; at > 0 && last[sorted[at - 1]] < last[c]; --at) sorted[at] = sorted[at - 1];
         sorted[at] = (uint8_t)c;
     }
     for (int c = 0; c < C; ++c) o.chunk[c / 4] |= (uint32_t)sorted[c] << 8 * (c % 4);
