@@ -1092,8 +1092,9 @@ __global__ __launch_bounds__(512) void gemm_w4_gate_kernel(GemmArgs g) {
 // meet in LDS at the end.
 // LDS: fragment (quarter q, tile mt) of a step is 64 lanes x 16 bytes; lane (i, g) lies at 16 g + (i ^ (4 q + g)): threads write
 // whole rows, 16 bytes to each of 16 fragments, which without the xor were all in one bank (0.65 us a step).
-// GATED is a build of its own: with both epilogues inlined at every ring stage the code of the loop is twice as long, which shows in
-// launches of one round (a head of 32000 x 4096 at 45 rows 44.8 -> 44.5 us, two layers and head of the 7B shape 333 -> 330.5).
+// GATED is a build of its own: with both epilogues inlined at every ring stage the code of the loop is twice as long, which shows little, in
+// launches of one round (a head of 32000 x 4096 at 45 rows 44.8 -> 44.5 us, two layers and head of the 7B shape 333 -> 330.5 on one box;
+// boxes differ by more).
 constexpr int kRowsBlocks = 256, kRowsMax = 128;
 
 template <int NW, int MT, bool GATED>
